@@ -10,9 +10,10 @@
 //               of a half-wave meet in a bank whatever the bytes are; added to the global
 //               histogram at the end;
 //   code        one workgroup: the used symbols are ranked by (count, symbol) in parallel, one
-//               lane runs the two-queue construction over the ranked leaves (at most 255
-//               merges) and walks the tree for the depths; counts are halved and the
-//               construction repeated while a code would exceed 24 bits; canonical codes;
+//               wave runs the two-queue construction over the ranked leaves (at most 255
+//               merges, those that do not depend on each other side by side) and every leaf
+//               walks up the tree for its depth; counts are halved and the construction
+//               repeated while a code would exceed 24 bits; canonical codes;
 //   count       a wave reads four chunks at a time with one 16-byte load per lane and adds the
 //               code lengths up over each chunk's sixteen lanes: the chunk's length in words;
 //   scan        the sums of groups of 256 chunks (a workgroup of the count pass) are scanned by
@@ -146,105 +147,160 @@ __global__ __launch_bounds__(256) void huffman_histogram_kernel(const Batch<Layo
 }
 
 // ---- code lengths and canonical codes ---------------------------------------------------------------
-// One workgroup of 256 threads, thread s = symbol s.
-__global__ __launch_bounds__(256) void huffman_code_kernel(const Batch<Layout> batch)
+// The merges of the two-queue construction, one wave, as many of them at a time as do not depend on each other.
+// Before a merge, let t be the sum of the two lightest nodes.  Every node made from now on weighs t at least and
+// queues behind whatever weighs the same, so the nodes of weight <= t that are there now are taken in their present
+// order, pair by pair, before any node made from now on: floor(k / 2) merges of one round, k being their number.
+// Their order is the two queues merged by weight, a leaf first where weights are equal.  The wave looks at a window
+// of 64 nodes of either queue, one per lane, so a round is limited to the first 64 nodes of that order (whatever
+// comes behind a window cannot precede them).  A node's place in the order is its place in its own queue plus the
+// nodes of the other queue that precede it.  Weights at least double from one round to the round after next, so the rounds are few (19 for the
+// 256 symbols of an index stream, 12 for equal counts) where the merges one by one are up to 255 dependent steps
+// of some 40 instructions each: the kernel took 58 us for an index stream's 250 merges and takes 24.
+constexpr uint32_t kNoNode = ~(uint32_t)0;
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t from) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)from); }
+__device__ __forceinline__ uint32_t smaller(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint32_t add_capped(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+__device__ __forceinline__ uint32_t lane_below(uint32_t v)    // lanes 1..15 of a row: the lane before
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)kNoNode, (int)v, 0x111, 0xf, 0xf, false);
+}
+
+// weight[0 .. m): the leaves in rank order; weight[m .. 2m - 1) and parent[0 .. 2m - 2) are filled.  m >= 2.
+__device__ __forceinline__ void merge_in_rounds(const uint32_t m, uint32_t* weight, uint16_t* parent, uint32_t* flag /* [64] */,
+                                                const uint32_t lane)
+{
+    uint32_t next_leaf = 0, next_internal = m, made = m;      // wave-uniform
+    while (made < 2u * m - 1u) {                              // a round makes a node at least
+        const uint32_t leaf = next_leaf + lane, node = next_internal + lane;
+        const bool is_leaf = leaf < m, is_node = node < made;
+        const uint32_t of_leaf = is_leaf ? weight[leaf] : kNoNode, of_node = is_node ? weight[node] : kNoNode;
+        // the smallest sum of two: leaf 0 + leaf 1 and node 0 + node 1 in lane 1, leaf 0 + node 0 in lane 0; sums with a
+        // node that does not exist stay at kNoNode (two nodes exist, and all weights together are below 2^32)
+        const uint32_t alike = smaller(add_capped(of_leaf, lane_below(of_leaf)), add_capped(of_node, lane_below(of_node)));
+        const uint32_t t = smaller(lane_value(alike, 1), lane_value(add_capped(of_leaf, of_node), 0));
+        const uint32_t leaves = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(is_leaf && of_leaf <= t));
+        const uint32_t nodes = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(is_node && of_node <= t));
+        const uint32_t all = leaves + nodes, taken = (all < 64u ? all : 64u) & ~1u;
+        // Which places of the round's order the nodes of the queue with fewer candidates take: a candidate of the
+        // other queue has its place by one compare and add per candidate of this one, its weight read from its lane.
+        // (Four at a time: the weights behind the candidates are above t and precede no candidate.)
+        const bool by_leaf = leaves < nodes;                  // wave-uniform
+        const uint32_t theirs = by_leaf ? of_node : of_leaf, steps = by_leaf ? leaves : nodes, others = by_leaf ? nodes : leaves;
+        uint32_t place = lane;
+        if (by_leaf) {
+            for (uint32_t k = 0; k < steps; k += 4)
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) place += lane_value(of_leaf, k + j) <= theirs ? 1u : 0u;   // a leaf first
+        } else {
+            for (uint32_t k = 0; k < steps; k += 4)
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) place += lane_value(of_node, k + j) < theirs ? 1u : 0u;
+        }
+        flag[lane] = 0u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); // LDS operations of one wave complete in order
+        if (lane < others && place < 64u) flag[place] = 1u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // lane l is place l of the order from here on
+        const uint64_t marked = __builtin_amdgcn_ballot_w64(flag[lane] != 0u);
+        const bool other = (marked >> lane) & 1u;
+        const uint32_t marked_before = __builtin_amdgcn_mbcnt_hi((uint32_t)(marked >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)marked, 0u));
+        const uint32_t index = other ? marked_before : lane - marked_before;      // in its queue's window
+        const bool is_taken_node = other == by_leaf;
+        const uint32_t at = (is_taken_node ? next_internal : next_leaf) + index;
+        uint32_t w = 0;
+        if (lane < taken) {
+            w = weight[at];
+            parent[at] = (uint16_t)(made + (lane >> 1));
+        }
+        const uint32_t sum = dpp_add<0x111, 0xf>(w);           // with the lane below
+        if (lane < taken && (lane & 1u)) weight[made + (lane >> 1)] = sum;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint32_t gone = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(lane < taken && !is_taken_node));
+        next_leaf += gone;
+        next_internal += taken - gone;
+        made += taken >> 1;
+    }
+}
+
+// One workgroup per stream.  It runs once, alone on its compute unit, and every phase is a chain of dependent steps,
+// so what counts is the length of the chains: the sixteen waves compare a quarter of the counts each for the ranks
+// (four waves on a SIMD hide each other's latencies), threads 0..255 stand for the symbols elsewhere.  58 us before
+// the merges were taken in rounds, the comparisons shared out and the depths doubled (34 us with the rounds alone).
+constexpr int kCodeThreads = 1024;
+__global__ __launch_bounds__(kCodeThreads) void huffman_code_kernel(const Batch<Layout> batch)
 {
     const Layout& lay = batch.item[blockIdx.x];
     // counts and weights are sums of at most 2^32 - 1 symbols: 32 bits hold them
     __shared__ __align__(16) uint32_t count[256];             // this round's counts, by symbol
+    __shared__ uint32_t rank_of[256];
     __shared__ uint32_t weight[511];                          // leaves in rank order, then internal nodes as made
     __shared__ uint16_t parent[511];
-    __shared__ uint8_t  length[256];
-    __shared__ uint32_t code_of[256];
+    __shared__ uint32_t flag[64];                             // merges of a round: places that nodes of the one queue take
+    __shared__ uint32_t up[2][511];
     __shared__ uint32_t in_wave[4][kMaxLen + 2];              // [w][k]: wave w's symbols that are unused (k = 0) / of length k
+    __shared__ uint32_t first_code[64];
+    __shared__ uint32_t bits_in_wave[4][2];
     __shared__ uint32_t deepest;
-    const uint32_t s = threadIdx.x, wave = s >> 6, lane = s & 63u;
+    const uint32_t thread = threadIdx.x, lane = thread & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(thread >> 6));
+    const uint32_t s = thread & 255u, symbols = wave & 3u, quarter = wave >> 2;   // the wave's symbols: 64 symbols + lane
+    const bool symbol = wave < 4u;
     const uint32_t original = lay.hist[s];
-    uint32_t c = original;
+    uint32_t c = original, my_length = 0;
     for (;;) {                                                // workgroup-uniform; counts halve, so it ends
-        count[s] = c;
-        length[s] = 0;
-        {
-            const uint64_t unused = __ballot(c == 0u);
+        if (symbol) {
+            count[s] = c;
+            rank_of[s] = 0u;
+            const uint64_t unused = __builtin_amdgcn_ballot_w64(c == 0u);
             if (lane == 0) in_wave[wave][0] = (uint32_t)__popcll(unused);
+            if (s == 0) deepest = 0u;
         }
         __syncthreads();
-        const int m = 256 - (int)(in_wave[0][0] + in_wave[1][0] + in_wave[2][0] + in_wave[3][0]);   // used symbols
-        // used symbols before this one by (count, symbol): those with a smaller count, the unused ones taken off
-        // again, plus those of the same count and a smaller value
-        uint32_t rank = 0;
-#pragma unroll 4
-        for (int t = 0; t < 256; t += 4) {
-            const u32x4 four = *reinterpret_cast<const u32x4*>(&count[t]);
-            const uint32_t o[4] = {four.x, four.y, four.z, four.w};
+        const uint32_t m = 256u - (in_wave[0][0] + in_wave[1][0] + in_wave[2][0] + in_wave[3][0]);   // used symbols
+        // symbols before this one by (count, symbol), of this thread's quarter.  On equal counts those of a quarter
+        // below precede, those of one above do not: "<=" is "< c + 1", which needs a count below 2^32 - 1, and one
+        // symbol alone can have that many: any count above 0 ranks it last.
+        {
+            const uint32_t key = c < ~0u ? c : c - 1u;
+            const uint32_t bound = quarter < symbols ? key + 1u : key;
+            uint32_t before = 0;
+            u32x4 four[16];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) rank += (o[k] < c ? 1u : 0u) + ((o[k] == c && (uint32_t)(t + k) < s) ? 1u : 0u);
-        }
-        rank -= 256u - (uint32_t)m;
-        if (c != 0) weight[rank] = c;
-        __syncthreads();
-        if (wave == 0) {
-            // The merges are one chain of dependent steps.  The whole first wave runs it with every value the same
-            // in all lanes and made known as such (readfirstlane), so that counters, comparisons and branches are
-            // scalar instructions; the lanes' LDS stores write one value to one address.  (Both queues spread
-            // over the lanes of registers, read with v_readlane and a scalar select, measured slower -- 71 us
-            // against 58 for 250 merges: what a merge costs is its instruction count, not the LDS latency.  So did
-            // a 64-node window of either queue in one register each, 59 us.  Merges that do not depend on each
-            // other done by the lanes at once -- the k leaves no heavier than the front node pair up in
-            // floor(k / 2) leaf-leaf merges, the k nodes lighter than the front leaf likewise -- give the same
-            // depths and take a uniform histogram's 255 merges from 46 to 7 us, but on the index streams of the
-            // predictive form leaves and nodes alternate, few steps find a batch, and the dearer step made the
-            // kernel slower: 64 us.  And a merge without branches -- the next two nodes of both queues read from
-            // register windows by lane index, the two smallest of the four taken by selects -- is some 50
-            // instructions with no wait for LDS, and takes the same time to the microsecond.)
-            if (lane == 0) deepest = 0u;
-            const uint32_t mm = (uint32_t)__builtin_amdgcn_readfirstlane(m);
-            if (mm > 1u) {
-                // The first two nodes of either queue are at hand -- the front as a scalar, the one behind it
-                // requested from LDS when the front was taken -- so that nothing waits for LDS until a further
-                // node has been taken.  kNone stands for a node that does not exist (yet): only the root can
-                // weigh 2^32 - 1, and the root is never compared.  One of the fronts always exists: before a
-                // merge the queues hold two nodes or more.
-                constexpr uint32_t kNone = ~(uint32_t)0;
-                uint32_t next_leaf = 0, next_internal = mm, made = mm;
-                uint32_t leaf0 = (uint32_t)__builtin_amdgcn_readfirstlane(weight[0]);     // leaf next_leaf
-                uint32_t leaf1 = weight[1];                                             // leaf next_leaf + 1, in flight
-                uint32_t node0 = kNone;                                                 // internal node next_internal
-                uint32_t node1 = kNone;                                                 // internal node next_internal + 1
-                while (made < 2u * mm - 1u) {                 // at most 255 merges
-                    uint32_t sum = 0;
+            for (int k = 0; k < 16; ++k) four[k] = *reinterpret_cast<const u32x4*>(&count[64u * quarter + 4u * k]);
+            if (quarter == symbols) {
 #pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        if (leaf0 <= node0) {                 // a leaf is preferred to an internal node of equal weight
-                            sum += leaf0;
-                            parent[next_leaf] = (uint16_t)made;
-                            ++next_leaf;
-                            leaf0 = (uint32_t)__builtin_amdgcn_readfirstlane(leaf1);
-                            leaf1 = next_leaf + 1u < mm ? weight[next_leaf + 1u] : kNone;
-                        } else {
-                            sum += node0;
-                            parent[next_internal] = (uint16_t)made;
-                            ++next_internal;
-                            node0 = (uint32_t)__builtin_amdgcn_readfirstlane(node1);
-                            node1 = next_internal + 1u < made ? weight[next_internal + 1u] : kNone;
-                        }
-                    }
-                    weight[made] = sum;
-                    if (made == next_internal) node0 = sum;           // the new node is the queue's front,
-                    else if (made == next_internal + 1u) node1 = sum; // or the one behind it
-                    ++made;
-                }
+                for (int k = 0; k < 64; ++k) before += four[k >> 2][k & 3] < key + ((uint32_t)k < lane ? 1u : 0u) ? 1u : 0u;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 64; ++k) before += four[k >> 2][k & 3] < bound ? 1u : 0u;
             }
+            atomicAdd(&rank_of[s], before);
         }
         __syncthreads();
-        if (c != 0) {                                         // every leaf walks up to the root: its depth
-            uint32_t d = 1;
-            if (m > 1) {
-                d = 0;
-                for (uint32_t node = rank; node != (uint32_t)(2 * m - 2) && d < 256u; ++d) node = parent[node];
+        const uint32_t rank = rank_of[s] - (256u - m);        // the unused ones come first: taken off again
+        if (symbol && c != 0) weight[rank] = c;
+        __syncthreads();
+        const uint32_t mm = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+        if (wave == 0 && mm > 1u) merge_in_rounds(mm, weight, parent, flag, lane);
+        __syncthreads();
+        // Depths by pointer doubling: up[node] = steps << 16 | the node that many steps above it, doubled five times,
+        // so that a leaf that has not arrived at the root is more than 32 deep and the code is over the limit anyway.
+        const uint32_t root = m ? 2u * m - 2u : 0u;
+        if (thread < 511u) up[0][thread] = thread < root ? 0x10000u | parent[thread] : thread;
+        __syncthreads();
+#pragma unroll
+        for (int step = 0; step < 5; ++step) {
+            if (thread < 511u) {
+                const uint32_t here = up[step & 1][thread];
+                up[~step & 1][thread] = (here & 0xffff0000u) + up[step & 1][here & 0xffffu];
             }
-            length[s] = (uint8_t)(d < 255u ? d : 255u);
-            atomicMax(&deepest, d);
+            __syncthreads();
+        }
+        if (symbol && c != 0) {
+            const uint32_t mine = up[1][rank];
+            my_length = m == 1u ? 1u : (mine & 0xffffu) == root ? mine >> 16 : 255u;
+            atomicMax(&deepest, my_length);
         }
         __syncthreads();
         if (deepest <= (uint32_t)kMaxLen) break;
@@ -252,41 +308,41 @@ __global__ __launch_bounds__(256) void huffman_code_kernel(const Batch<Layout> b
         __syncthreads();                                      // everyone has read `deepest` before it is written again
     }
     // canonical codes: by increasing (length, symbol); a symbol's place among those of its length from lane masks
-    // inside the wave plus the counts of the waves below
-    __shared__ uint32_t first_code[kMaxLen + 2];
-    const uint32_t my_length = length[s];
+    // inside the wave plus the counts of the waves below.  Payload bits: every symbol's count times its length (the
+    // counts as they were), the counts' halves apart so that a wave's sums fit 32 bits.
     uint32_t before = 0;
+    if (symbol) {
 #pragma unroll
-    for (int k = 1; k <= kMaxLen; ++k) {
-        const uint64_t same = __ballot(my_length == (uint32_t)k);
-        if (my_length == (uint32_t)k) before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-        if (lane == 0) in_wave[wave][k] = (uint32_t)__popcll(same);
+        for (int k = 1; k <= kMaxLen; ++k) {
+            const uint64_t same = __builtin_amdgcn_ballot_w64(my_length == (uint32_t)k);
+            if (my_length == (uint32_t)k) before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+            if (lane == 0) in_wave[wave][k] = (uint32_t)__popcll(same);
+        }
+        const uint32_t low = wave_inclusive_scan((original & 0xffffu) * my_length), high = wave_inclusive_scan((original >> 16) * my_length);
+        if (lane == 63u) { bits_in_wave[wave][0] = low; bits_in_wave[wave][1] = high; }
     }
     __syncthreads();
-    if (s == 0) {
-        uint32_t code = 0;
-        first_code[0] = first_code[1] = 0u;
-#pragma unroll
-        for (int l = 2; l <= kMaxLen; ++l) {
-            code = (code + in_wave[0][l - 1] + in_wave[1][l - 1] + in_wave[2][l - 1] + in_wave[3][l - 1]) << 1;
-            first_code[l] = code;
+    if (wave == 0) {
+        // first code of length k = sum over the shorter lengths j of their symbols << (k - j); scaled by 2^(24 - k) that
+        // is a prefix sum (at most 2^24, Kraft's sum being at most 1)
+        const bool a_length = lane >= 1u && lane <= (uint32_t)kMaxLen;
+        const uint32_t of_length = a_length ? in_wave[0][lane] + in_wave[1][lane] + in_wave[2][lane] + in_wave[3][lane] : 0u;
+        const uint32_t scaled = a_length ? of_length << ((uint32_t)kMaxLen - lane) : 0u;
+        const uint32_t shorter = wave_inclusive_scan(scaled) - scaled;
+        first_code[lane] = a_length ? shorter >> ((uint32_t)kMaxLen - lane) : 0u;
+        if (lane == 0) {
+            uint64_t bits = 0;
+            for (int w = 0; w < 4; ++w) bits += bits_in_wave[w][0] + ((uint64_t)bits_in_wave[w][1] << 16);
+            lay.totals[1] = bits;
         }
     }
     __syncthreads();
-    if (my_length) for (uint32_t w = 0; w < wave; ++w) before += in_wave[w][my_length];
-    code_of[s] = my_length ? first_code[my_length] + before : 0u;
-    __syncthreads();
-    lay.len[s] = length[s];
-    lay.table[s] = (code_of[s] << 8) | length[s];
-    // payload bits: every symbol's count times its length (the counts as they were)
-    __shared__ uint64_t bit_sum[256];
-    bit_sum[s] = (uint64_t)original * length[s];
-    __syncthreads();
-    for (int step = 128; step >= 1; step >>= 1) {
-        if (s < (uint32_t)step) bit_sum[s] += bit_sum[s + step];
-        __syncthreads();
+    if (symbol) {
+        if (my_length) for (uint32_t w = 0; w < wave; ++w) before += in_wave[w][my_length];
+        const uint32_t code = my_length ? first_code[my_length] + before : 0u;
+        lay.len[s] = (uint8_t)my_length;
+        lay.table[s] = (code << 8) | my_length;
     }
-    if (s == 0) lay.totals[1] = bit_sum[0];
 }
 
 // the symbols of a chunk, 16 at a time; `valid` of them exist
@@ -981,9 +1037,9 @@ fh_status check_decode(const fh_huffman_decode_item& it)
 }
 
 template <typename Kernel, typename Item>
-void launch(Kernel kernel, const Batch<Item>& b, uint32_t grid, hipStream_t s)
+void launch(Kernel kernel, const Batch<Item>& b, uint32_t grid, hipStream_t s, int threads = kThreads)
 {
-    if (grid > 0) hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, s, b);
+    if (grid > 0) hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, b);
 }
 
 
@@ -1035,7 +1091,7 @@ fh_status fh_huffman_encode_batch(const fh_huffman_encode_item* items, int32_t c
         seal(each); seal(hist); seal(grouped);
         launch(huffman_clear_kernel, each, (uint32_t)each.count, s);
         launch(huffman_histogram_kernel, hist, hist.block_start[hist.count], s);
-        launch(huffman_code_kernel, each, (uint32_t)each.count, s);
+        launch(huffman_code_kernel, each, (uint32_t)each.count, s, kCodeThreads);
         launch(huffman_count_kernel, grouped, grouped.block_start[grouped.count], s);
         launch(huffman_scan_kernel, each, (uint32_t)each.count, s);
         launch(huffman_write_kernel, grouped, grouped.block_start[grouped.count], s);

@@ -82,6 +82,20 @@ def test_distributions(api, kind):
     _check(api, data, kind)
 
 
+@pytest.mark.parametrize("used", [2, 3, 4, 63, 64, 65, 66, 127, 128, 129, 191, 255, 256])
+@pytest.mark.parametrize("kind", ["equal", "pairs", "doubling", "alternating", "random"])
+def test_code_construction_in_rounds(api, used, kind):
+    """Histograms around the 64 nodes of either queue that a round of merges looks at: all counts equal (full windows,
+    odd numbers of candidates), equal pairs, groups that double (leaves tie with nodes made of them), leaves that
+    alternate with the nodes, and counts that rarely tie."""
+    rng = np.random.default_rng(used)
+    i = np.arange(used)
+    counts = {"equal": np.full(used, 7), "pairs": 3 + i // 2, "doubling": 1 << (i * 12 // used),
+              "alternating": 1 + i + (i % 3) * used // 2, "random": rng.integers(1, 4000, used)}[kind]
+    symbols = rng.permutation(256)[:used].astype(np.uint8)
+    _check(api, rng.permutation(np.repeat(symbols, counts)), f"{kind} counts of {used} symbols")
+
+
 def test_codes_that_would_exceed_24_bits(api):
     fib = [1, 1]
     while len(fib) < 28:
