@@ -41,7 +41,8 @@ constexpr int kThreads = 256;                      // chunks per workgroup: a gr
 constexpr int kMaxLen = 24;
 constexpr int kChunkWordsMax = kChunk * kMaxLen / 32;
 constexpr int kHistCopies = 32;                     // one per LDS bank
-constexpr int kHistBlocksMax = 640;                // histogram workgroups per stream: 2.5 per compute unit
+constexpr int kHistThreads = 1024;
+constexpr int kHistBlocksMax = 512;                // histogram workgroups per stream: two per compute unit
 constexpr int kFastBits = 12;
 constexpr int kBurst = 8;                          // decode: 16-byte output vectors held back and stored together
 // decode: chunks per workgroup.  The payload slice in LDS is what limits the chunks in flight on a compute unit,
@@ -108,7 +109,10 @@ struct DecodeJob {
 __global__ __launch_bounds__(256) void huffman_clear_kernel(const Batch<Layout> batch) { batch.item[blockIdx.x].hist[threadIdx.x] = 0u; }
 
 // ---- histogram ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void huffman_histogram_kernel(const Batch<Layout> batch)
+// A workgroup clears, adds up and sends off 32 KiB of counters whatever it counts; the atomics of all workgroups meet
+// on the stream's 256 counters.  So the workgroup has the most threads there are: at 51 MB in five streams 29 us
+// with 256 threads (1340 workgroups), 18 us with 1024.
+__global__ __launch_bounds__(kHistThreads) void huffman_histogram_kernel(const Batch<Layout> batch)
 {
     uint32_t block;
     const Layout lay = resolved(batch.item[batch_item(batch, blockIdx.x, block)]);
@@ -119,12 +123,12 @@ __global__ __launch_bounds__(256) void huffman_histogram_kernel(const Batch<Layo
     // lane l counts in copy l mod 32, and whatever the bytes are no two lanes of a half-wave meet in a bank
     // (bytes clustered around one value would otherwise serialise on the few bins they share).
     __shared__ uint32_t local[256][kHistCopies];
-    for (int i = threadIdx.x; i < kHistCopies * 256; i += 256) (&local[0][0])[i] = 0u;
+    for (int i = threadIdx.x; i < kHistCopies * 256; i += kHistThreads) (&local[0][0])[i] = 0u;
     __syncthreads();
     uint32_t* mine = &local[0][threadIdx.x & (kHistCopies - 1)];
     const uint64_t vectors = n >> 4;                          // `in` is 16-byte aligned
-    const uint64_t stride = (uint64_t)lay.hist_blocks * 256;
-    uint64_t v = (uint64_t)block * 256 + threadIdx.x;
+    const uint64_t stride = (uint64_t)lay.hist_blocks * kHistThreads;
+    uint64_t v = (uint64_t)block * kHistThreads + threadIdx.x;
     u32x4 ahead = v < vectors ? reinterpret_cast<const u32x4*>(in)[v] : u32x4{0u, 0u, 0u, 0u};
     for (; v < vectors; v += stride) {
         const u32x4 w = ahead;
@@ -140,10 +144,15 @@ __global__ __launch_bounds__(256) void huffman_histogram_kernel(const Batch<Layo
         if (threadIdx.x < 16 && i < n) atomicAdd(&mine[(uint32_t)in[i] * kHistCopies], 1u);
     }
     __syncthreads();
+    // four neighbouring threads per bin, eight copies each; the fourth then has the bin's total
+    static_assert(kHistThreads == 4 * 256 && kHistCopies == 32, "a thread adds up eight copies of a bin");
+    const uint32_t bin = threadIdx.x >> 2, first = (threadIdx.x & 3u) * 8u;
     uint32_t total = 0;
 #pragma unroll
-    for (int c = 0; c < kHistCopies; ++c) total += local[threadIdx.x][(c + threadIdx.x) & (kHistCopies - 1)];   // a bank per lane
-    if (total) atomicAdd(&hist[threadIdx.x], total);
+    for (uint32_t c = 0; c < 8u; ++c) total += local[bin][first + ((c + bin) & 7u)];
+    total = dpp_add<0x111, 0xf>(total);                       // row_shr:1, then 2: over the lane and the three below it
+    total = dpp_add<0x112, 0xf>(total);
+    if ((threadIdx.x & 3u) == 3u && total) atomicAdd(&hist[bin], total);
 }
 
 // ---- code lengths and canonical codes ---------------------------------------------------------------
@@ -1077,7 +1086,7 @@ fh_status fh_huffman_encode_batch(const fh_huffman_encode_item* items, int32_t c
             lay.n_dev = static_cast<const uint64_t*>(it.n_device);
             // about eight vectors per thread, more in long streams: a workgroup clears and adds up 32 KiB of
             // counters and sends 256 atomics to the stream's histogram whatever it counts
-            const uint64_t want = it.n == 0 ? 0 : (it.n / 16 + 255) / 256 / 8 + 1;
+            const uint64_t want = it.n == 0 ? 0 : (it.n / 16 + kHistThreads - 1) / kHistThreads / 8 + 1;
             lay.hist_blocks = (uint32_t)(want < (uint64_t)kHistBlocksMax ? want : (uint64_t)kHistBlocksMax);
             if ((uint64_t)grouped.block_start[grouped.count] + lay.groups > (uint64_t)INT_MAX) {
                 if (each.count == 0) return FH_ERR_BAD_NUMEL;
@@ -1090,7 +1099,7 @@ fh_status fh_huffman_encode_batch(const fh_huffman_encode_item* items, int32_t c
         }
         seal(each); seal(hist); seal(grouped);
         launch(huffman_clear_kernel, each, (uint32_t)each.count, s);
-        launch(huffman_histogram_kernel, hist, hist.block_start[hist.count], s);
+        launch(huffman_histogram_kernel, hist, hist.block_start[hist.count], s, kHistThreads);
         launch(huffman_code_kernel, each, (uint32_t)each.count, s, kCodeThreads);
         launch(huffman_count_kernel, grouped, grouped.block_start[grouped.count], s);
         launch(huffman_scan_kernel, each, (uint32_t)each.count, s);
