@@ -24,8 +24,8 @@
 //               contiguous piece -- with consecutive lanes on consecutive words.
 // Decoding needs no pass but one: the offsets are part of the stream.  A workgroup rebuilds the
 // canonical tables from the 256 lengths (a 12-bit lookup table for the short codes, first-code /
-// count comparisons for the longer ones), stages the payload slice of 768 chunks in LDS (150 of
-// the compute unit's 160 KiB: one workgroup of twelve waves each), and a thread decodes its chunk
+// count comparisons for the longer ones), stages the payload slice of up to 1024 chunks in LDS (150
+// of the compute unit's 160 KiB: one workgroup of sixteen waves each), and a thread decodes its chunk
 // from there; the tables serve several such groups in long streams.
 // Everything here is integer work; results do not depend on launch geometry.
 #include "../../include/fedhybrid.h"
@@ -45,15 +45,18 @@ constexpr int kHistThreads = 1024;
 constexpr int kHistBlocksMax = 512;                // histogram workgroups per stream: two per compute unit
 constexpr int kFastBits = 12;
 constexpr int kBurst = 8;                          // decode: 16-byte output vectors held back and stored together
-// decode: chunks per workgroup.  The payload slice in LDS is what limits the chunks in flight on a compute unit,
+// decode: threads per workgroup.  The payload slice in LDS is what limits the chunks in flight on a compute unit,
 // and the decode waits on dependent instructions, not on a unit: one workgroup with the whole LDS holds 768
 // chunks (twelve waves) where workgroups of 256 with their own tables held 512.
-constexpr int kDecodeThreads = 768;
-constexpr int kDecodeThreadsSmall = 256;           // ... of a launch that would leave compute units idle with 768
+// The stage then holds 768 chunks at 46 words (5.75 bits per symbol) and 880 at 40 words, so the workgroup has as many
+// threads as there are: where a stream's chunks come to slightly more than 768 per compute unit (51 MB of index
+// streams: 788) they take one pass and not two.
+constexpr int kDecodeThreads = 1024;
+constexpr int kDecodeThreadsSmall = 256;           // ... of a launch whose chunks fit the device this way
 // decode: LDS for a workgroup's payload slice, in words per chunk: 48 (6 bits per symbol) is what fits beside the
-// tables when one workgroup of 768 takes the whole LDS; two workgroups of 256 per unit have room for 64 (8 bits per
+// tables for 768 chunks when one workgroup takes the whole LDS; two workgroups of 256 per unit have room for 64 (8 bits per
 // symbol: any slice fits on average, and streams of 7-8 bits per symbol no longer fall back to the rings)
-template <int THREADS> struct StageWords { static constexpr int kPerChunk = THREADS >= 768 ? 46 : 64; };
+template <int THREADS> struct StageWords { static constexpr int kAll = THREADS >= 768 ? 768 * 46 : THREADS * 64; };
 constexpr int kSecondEntries = 2048;               // decode: entries of the table behind the fast one
 constexpr int kComputeUnits = 256;                 // MI355X
 
@@ -102,7 +105,7 @@ struct DecodeJob {
     const uint64_t* n_dev;                                    // device: the symbol count; or null
     uint64_t        stream_bytes;                             // the valid prefix of the stream
     uint32_t        payload_words, chunks;
-    uint32_t        chunks_per_block;                         // chunks that a workgroup decodes with one set of tables
+    uint32_t        blocks;                                   // workgroups of this stream
 };
 
 // Every pass serves up to kBatch streams (fh_batch.hpp); the per-stream passes take a workgroup per stream.
@@ -790,7 +793,7 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
 template <int kDecodeThreads>
 __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Batch<DecodeJob> batch)
 {
-    constexpr int kStageWords = kDecodeThreads * StageWords<kDecodeThreads>::kPerChunk;
+    constexpr int kStageWords = StageWords<kDecodeThreads>::kAll;
     uint32_t block;
     const DecodeJob& job = batch.item[batch_item(batch, blockIdx.x, block)];
     const uint8_t* len_in = job.len;
@@ -899,13 +902,14 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
     }
     __syncthreads();
 
-    // These tables serve `chunks_per_block` chunks, in passes of as many chunks as there are threads at most.  The payload words of consecutive chunks are one contiguous slice.  A pass takes the chunks whose
+    // These tables serve an equal share of the stream's chunks (a wave's worth at least), in passes of as many chunks as there are threads at most.  The payload words of consecutive chunks are one contiguous slice.  A pass takes the chunks whose
     // slice fits the stage -- all of them up to 46 (64) words per chunk on average, fewer on streams that hardly
     // compress, where the threads beyond sit the pass out -- brings the slice into LDS with contiguous loads, and
     // the threads read their words from there (a thread walking its chunk in memory would fetch a cache line per
     // word).  A pass that could seat few of its chunks, and offsets that do not describe a slice (no encoder wrote
     // them), go through per-thread rings instead.
-    const uint64_t share = job.chunks_per_block;
+    const uint32_t even = (chunks + job.blocks - 1u) / job.blocks;
+    const uint64_t share = even < 64u ? 64u : even;
     const uint32_t chunk_stop = (uint32_t)((block + 1u) * share < chunks ? (block + 1u) * share : chunks);
     for (uint32_t chunk0 = (uint32_t)(block * share < chunks ? block * share : chunks); chunk0 < chunk_stop;) {
         const uint32_t want = chunk_stop - chunk0 < (uint32_t)kDecodeThreads ? chunk_stop - chunk0 : (uint32_t)kDecodeThreads;
@@ -922,9 +926,9 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
         }
         __syncthreads();
         const uint32_t fitting = local.fitting;
-        // (workgroup-uniform) Below three quarters of the threads the rings do better: at eight bits per symbol every
+        // (workgroup-uniform) Below three quarters of twelve waves the rings do better: at eight bits per symbol every
         // chunk is 64 words long, the threads' words lie 64 apart in the stage and all in one LDS bank.
-        const bool staged = fitting > 0u && 4u * fitting >= 3u * want;
+        const bool staged = fitting > 0u && 4u * fitting >= 3u * (want < 768u ? want : 768u);
         const uint32_t take = staged ? fitting : want;        // chunks of this pass
         const uint32_t slice_end = staged ? offsets[chunk0 + fitting] : slice_at;
         const uint32_t chunk = chunk0 + threadIdx.x;
@@ -1118,14 +1122,14 @@ fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t c
         if (st != FH_OK) return st;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // A workgroup of 768 threads (the whole LDS of a compute unit: one per unit) decodes 768 chunks at a time.
-    // A call whose streams together give fewer such groups than the device has compute units would leave
-    // units idle for the whole launch; it is cut into groups of 256 chunks instead (workgroups of 256 threads,
-    // two per unit): three times as many units at work, each building the tables for a third of the chunks.
-    uint64_t wide = 0;
-    for (int32_t i = 0; i < count; ++i) wide += (chunks_of(items[i].n) + kDecodeThreads - 1) / kDecodeThreads;
-    const bool small = wide < (uint64_t)kComputeUnits;
-    const uint64_t per_group = small ? kDecodeThreadsSmall : kDecodeThreads;
+    // A workgroup of 1024 threads takes the whole LDS of a compute unit: one per unit.  A call whose chunks fit the
+    // device as workgroups of 256, two per unit, takes those: more units at work, each stream's tables built side by
+    // side, and one pass.  Beyond that they would take two passes, where the wide ones seat up to twice as many chunks
+    // in one; those get at least 512 chunks each, so that every unit has one.
+    uint64_t narrow = 0;
+    for (int32_t i = 0; i < count; ++i) narrow += (chunks_of(items[i].n) + kDecodeThreadsSmall - 1) / kDecodeThreadsSmall;
+    const bool small = narrow <= 2u * (uint64_t)kComputeUnits;
+    const uint64_t per_group = small ? kDecodeThreadsSmall : 512u;
     const uint64_t slots = small ? 2u * kComputeUnits : kComputeUnits;         // workgroups the device holds at once
     bool launched = false;
     for (int32_t i = 0; i < count;) {
@@ -1162,9 +1166,8 @@ fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t c
             uint64_t blocks = total <= slots ? groups[k] : groups[k] * slots / total;
             if (blocks < 1u) blocks = 1u;
             const uint64_t chunks = job[k].chunks;
-            job[k].chunks_per_block = (uint32_t)((chunks + blocks - 1u) / blocks);
-            if (!push(b, job[k], (int64_t)((chunks + job[k].chunks_per_block - 1u) / job[k].chunks_per_block)))
-                return FH_ERR_BAD_NUMEL;                      // cannot happen: a stream has at most 2^16 groups
+            job[k].blocks = (uint32_t)(blocks < chunks ? blocks : chunks);
+            if (!push(b, job[k], (int64_t)job[k].blocks)) return FH_ERR_BAD_NUMEL;   // cannot happen: a stream has at most 2^16 groups
         }
         seal(b);
         if (b.count > 0) {
