@@ -152,12 +152,16 @@ int32_t   fh_batch_capacity(void);
  *
  * x: device, 16-byte aligned, outer*channels*inner elements of x_dtype.
  * workspace: device, 16-byte aligned, >= fh_classify_workspace_bytes(numel) bytes,
- *   scratch for the partial sums (contents undefined afterwards).
+ *   scratch for the partial sums (contents undefined afterwards).  With
+ *   fh_classify_workspace_bytes_ranges(numel) bytes (32 more per 1024 elements) there is also
+ *   room for the range of the values of every 128 elements, and the second pass over the
+ *   tensor reads only the pieces whose range reaches beyond the threshold; results are the same.
  * stats: device, 8-byte aligned, 4 doubles {mean, variance, threshold, numel}.
  * counts: device, uint32[channels].  mask: device, uint8[channels].
  * 1 <= channels <= 16384, inner >= 1, outer >= 0.  outer == 0 zeroes the outputs.
  * Everything is enqueued on `stream`; nothing is allocated or synchronised. */
 size_t    fh_classify_workspace_bytes(int64_t numel);
+size_t    fh_classify_workspace_bytes_ranges(int64_t numel);
 fh_status fh_classify_channels(const void *x, fh_dtype x_dtype, int64_t outer, int64_t channels, int64_t inner,
                                double k_sigma, int64_t min_outliers,
                                void *workspace, size_t workspace_cap,

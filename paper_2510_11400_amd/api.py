@@ -30,7 +30,7 @@ FH_ROUND_NEAREST, FH_ROUND_STOCHASTIC = 0, 1
 
 EXPORTS = ("fh_packed_bytes", "fh_meta_bytes", "fh_compress", "fh_decompress", "fh_roundtrip",
            "fh_compress_batch", "fh_decompress_batch", "fh_roundtrip_batch", "fh_batch_capacity",
-           "fh_classify_workspace_bytes", "fh_classify_channels", "fh_classify_channels_batch",
+           "fh_classify_workspace_bytes", "fh_classify_workspace_bytes_ranges", "fh_classify_channels", "fh_classify_channels_batch",
            "fh_classify_batch_capacity", "fh_classify_static_scratch_bytes", "fh_classify_channels_static",
            "fh_raw_bytes", "fh_channel_slots", "fh_channel_slots_used", "fh_channel_slots_batch", "fh_compress_mixed", "fh_decompress_mixed",
            "fh_compress_mixed_batch", "fh_decompress_mixed_batch", "fh_mixed_batch_capacity",
@@ -119,8 +119,9 @@ _lib.fh_roundtrip.restype = ctypes.c_int
 for _name in ("fh_compress_batch", "fh_decompress_batch", "fh_roundtrip_batch"):
     getattr(_lib, _name).argtypes = [_P(fh_item), ctypes.c_int32, ctypes.c_void_p]
     getattr(_lib, _name).restype = ctypes.c_int
-_lib.fh_classify_workspace_bytes.argtypes = [ctypes.c_int64]
-_lib.fh_classify_workspace_bytes.restype = ctypes.c_size_t
+for _name in ("fh_classify_workspace_bytes", "fh_classify_workspace_bytes_ranges"):
+    getattr(_lib, _name).argtypes = [ctypes.c_int64]
+    getattr(_lib, _name).restype = ctypes.c_size_t
 _lib.fh_classify_channels.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64,
                                       ctypes.c_double, ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t,
                                       ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
@@ -451,6 +452,11 @@ def classify_workspace_bytes(numel: int) -> int:
     return int(_lib.fh_classify_workspace_bytes(numel))
 
 
+def classify_workspace_bytes_ranges(numel: int) -> int:
+    """Workspace with room for the value ranges that spare the second pass most of the tensor."""
+    return int(_lib.fh_classify_workspace_bytes_ranges(numel))
+
+
 def fh_classify_channels(x: torch.Tensor, outer: int, channels: int, inner: int, k_sigma: float = 3.0,
                          min_outliers: int = 1, workspace: Optional[torch.Tensor] = None,
                          stats: Optional[torch.Tensor] = None, counts: Optional[torch.Tensor] = None,
@@ -463,7 +469,7 @@ def fh_classify_channels(x: torch.Tensor, outer: int, channels: int, inner: int,
         raise ValueError("x.numel() != outer * channels * inner")
     dev = x.device
     if workspace is None:
-        workspace = _scratch(classify_workspace_bytes(x.numel()), dev, stream)
+        workspace = _scratch(classify_workspace_bytes_ranges(x.numel()), dev, stream)
     if stats is None:
         stats = torch.empty(4, dtype=torch.float64, device=dev)
     if counts is None:
@@ -833,7 +839,7 @@ class ClassifyBatch:
             dev = e.x.device
             self.device = self.device or dev
             if e.workspace is None:
-                e.workspace = torch.empty(classify_workspace_bytes(e.x.numel()), dtype=torch.uint8, device=dev)
+                e.workspace = torch.empty(classify_workspace_bytes_ranges(e.x.numel()), dtype=torch.uint8, device=dev)
             if e.stats is None:
                 e.stats = torch.empty(4, dtype=torch.float64, device=dev)
             if e.counts is None:

@@ -17,6 +17,7 @@
 #include "../../include/fedhybrid.h"
 
 #include "fh_batch.hpp"
+#include "fh_classify.hpp"
 
 #include <vector>
 
@@ -213,7 +214,10 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
     fh_status st;
 
     // 1. three-sigma statistics, outlier counts, salient mask
+    //    (the ranges that spare the count pass most of the tensor lie where the codes will be: the quantiser writes the
+    //    whole of that part later)
     std::vector<fh_classify_item> cls((size_t)count);
+    std::vector<uint32_t*> ranges((size_t)count);
     for (int32_t i = 0; i < count; ++i) {
         const fh_mix_item& it = items[i];
         fh_classify_item& c = cls[i];
@@ -224,8 +228,10 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
         c.workspace = at(it.workspace, reg[i].classify_ws); c.workspace_cap = reg[i].classify_ws_bytes;
         c.stats = at(it.workspace, reg[i].stats); c.counts = at(it.workspace, reg[i].counts);
         c.mask = at(it.workspace, reg[i].mask);
+        ranges[i] = reg[i].packed_bytes >= range_bytes(numel[i])
+                        ? reinterpret_cast<uint32_t*>(at(it.store, reg[i].packed)) : nullptr;
     }
-    if ((st = fh_classify_channels_batch(cls.data(), count, stream)) != FH_OK) return st;
+    if ((st = classify_with_ranges(cls.data(), ranges.data(), count, s)) != FH_OK) return st;
 
     // 2. slots from the masks; headers and raw stores cleared
     for (int32_t i = 0; i < count;) {

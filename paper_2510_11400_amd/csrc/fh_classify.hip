@@ -16,11 +16,14 @@
 //      each lane keeps a bit mask of its 16 elements and only set bits pay for the
 //      channel index (division by invariant integers through multiply-high) and an LDS
 //      histogram increment; the histogram is flushed with one global atomic per
-//      non-zero bin and workgroup.
+//      non-zero bin and workgroup.  Where the workspace has room, the first pass leaves the
+//      range of the values of every 128 elements behind, and this one reads only the pieces
+//      whose range reaches beyond the threshold.
 #include "../../include/fedhybrid.h"
 
 #include "fh_batch.hpp"
 #include "fh_channels.hpp"
+#include "fh_classify.hpp"
 #include "fh_device.hpp"
 
 #include <limits.h>
@@ -79,64 +82,50 @@ __device__ __forceinline__ double add_across_halves(double v)
 }
 
 // ---- the span tree ---------------------------------------------------------------------
-// In: for each of ROWS rows, the lane's own subtree sums a[r] (of x) and b[r] (of x*x);
-// a row is 64 lanes in element order.  Out (all lanes): the span's two sums.
+// In: for each of four rows, the lane's own subtree sums a[r] (of x) and b[r] (of x*x); a row is 64 lanes in element
+// order.  The rows are those of one span, or rows 0 and 1 of one and 2 and 3 of the next (SPANS == 2).  Out: in lane
+// 2 * k + 4 * m (k < SPANS; also elsewhere) moment m of span k.
 // Exchange levels, in the tree's order:
-//   xor 1   keep the rows whose low bit equals the lane's bit 0        (ROWS == 4 only)
-//   xor 2   keep the row whose high bit equals the lane's bit 1 (ROWS == 4), or the row
-//           whose index equals bit 0 moved here (ROWS == 2: done at xor 1)
-//   next    keep one of the two moments
+//   xor 1   keep the rows whose low bit equals the lane's bit 0
+//   xor 2   keep the row whose high bit equals the lane's bit 1
+//   xor 4   keep one of the two moments
 //   rest    plain butterflies
-// followed by the levels that join the rows.
-template <int ROWS>
-__device__ __forceinline__ void span_tree(const double (&a)[ROWS], const double (&b)[ROWS], uint32_t lane,
-                                          double& s1, double& s2)
+// followed by the levels that join a span's rows.
+template <int SPANS>
+__device__ __forceinline__ double span_tree(const double (&a)[4], const double (&b)[4], uint32_t lane)
 {
-    static_assert(ROWS == 2 || ROWS == 4, "rows per span");
+    static_assert(SPANS == 1 || SPANS == 2, "spans in four rows");
     const bool b0 = lane & 1u, b1 = lane & 2u, b2 = lane & 4u;
-    double t;          // after the scatter levels: one (row, moment) total per lane
-    if constexpr (ROWS == 4) {
-        // xor 1: rows {b0, b0 + 2} of both moments stay
-        double ka[2], kb[2];
+    // xor 1: rows {b0, b0 + 2} of both moments stay
+    double ka[2], kb[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            ka[j] = (b0 ? a[2 * j + 1] : a[2 * j]) + from_lane_xor<1>(b0 ? a[2 * j] : a[2 * j + 1]);
-            kb[j] = (b0 ? b[2 * j + 1] : b[2 * j]) + from_lane_xor<1>(b0 ? b[2 * j] : b[2 * j + 1]);
-        }
-        // xor 2: row 2 * b1 + b0 stays
-        const double ma = (b1 ? ka[1] : ka[0]) + from_lane_xor<2>(b1 ? ka[0] : ka[1]);
-        const double mb = (b1 ? kb[1] : kb[0]) + from_lane_xor<2>(b1 ? kb[0] : kb[1]);
-        // xor 4: moment b2 stays
-        t = (b2 ? mb : ma) + from_lane_xor<4>(b2 ? ma : mb);
-        t = t + from_lane_xor<8>(t);
-        t = t + from_lane_xor<16>(t);
-        t = add_across_halves(t);
-        // rows: (0 + 1), (2 + 3), then their sum; the row index sits in lane bits 0 and 1
-        t = t + from_lane_xor<1>(t);
-        t = t + from_lane_xor<2>(t);
-        // lanes with bit 2 clear hold the sum of x, the others the sum of x*x
-        const double other = from_lane_xor<4>(t);
-        s1 = b2 ? other : t;
-        s2 = b2 ? t : other;
-    } else {
-        // xor 1: row b0 of both moments stays
-        const double ma = (b0 ? a[1] : a[0]) + from_lane_xor<1>(b0 ? a[0] : a[1]);
-        const double mb = (b0 ? b[1] : b[0]) + from_lane_xor<1>(b0 ? b[0] : b[1]);
-        // xor 2: moment b1 stays
-        t = (b1 ? mb : ma) + from_lane_xor<2>(b1 ? ma : mb);
-        t = t + from_lane_xor<4>(t);
-        t = t + from_lane_xor<8>(t);
-        t = t + from_lane_xor<16>(t);
-        t = add_across_halves(t);
-        t = t + from_lane_xor<1>(t);                          // row 0 + row 1
-        const double other = from_lane_xor<2>(t);
-        s1 = b1 ? other : t;
-        s2 = b1 ? t : other;
+    for (int j = 0; j < 2; ++j) {
+        ka[j] = (b0 ? a[2 * j + 1] : a[2 * j]) + from_lane_xor<1>(b0 ? a[2 * j] : a[2 * j + 1]);
+        kb[j] = (b0 ? b[2 * j + 1] : b[2 * j]) + from_lane_xor<1>(b0 ? b[2 * j] : b[2 * j + 1]);
     }
+    // xor 2: row 2 * b1 + b0 stays
+    const double ma = (b1 ? ka[1] : ka[0]) + from_lane_xor<2>(b1 ? ka[0] : ka[1]);
+    const double mb = (b1 ? kb[1] : kb[0]) + from_lane_xor<2>(b1 ? kb[0] : kb[1]);
+    // xor 4: moment b2 stays
+    double t = (b2 ? mb : ma) + from_lane_xor<4>(b2 ? ma : mb);      // one (row, moment) total per lane from here on
+    t = t + from_lane_xor<8>(t);
+    t = t + from_lane_xor<16>(t);
+    t = add_across_halves(t);
+    // rows: (0 + 1) and (2 + 3); of one span, their sum too; the row index sits in lane bits 0 and 1
+    t = t + from_lane_xor<1>(t);
+    if constexpr (SPANS == 1) t = t + from_lane_xor<2>(t);
+    return t;
+}
+// The sums of one span as span_tree leaves them, in every lane.
+__device__ __forceinline__ void both_moments(double t, uint32_t lane, double& s1, double& s2)
+{
+    const double other = from_lane_xor<4>(t);                 // lanes with bit 2 clear hold the sum of x, the others that of x*x
+    s1 = (lane & 4u) ? other : t;
+    s2 = (lane & 4u) ? t : other;
 }
 
 // ---- per-kernel descriptors (fh_batch.hpp: up to kBatch tensors per launch) ----------------
-struct MomentsItem { const void* x; int64_t numel; f64x2* partial; };
+struct MomentsItem { const void* x; int64_t numel; f64x2* partial; uint32_t* ranges; };
 struct ReduceItem  { const f64x2* in; int64_t count; f64x2* out; };
 struct FinishItem  {
     const f64x2* in; int64_t count; int64_t numel; double k_sigma;
@@ -188,26 +177,59 @@ __device__ __forceinline__ double local_tree(const double (&v)[N])
     return w[0];
 }
 
+// ---- value ranges ------------------------------------------------------------------------
+// A piece is what eight neighbouring lanes hold of a span: 128 elements, 128 contiguous bytes in each of the span's
+// rows.  Its range is kept as two bf16 numbers, the smallest value rounded down and the largest rounded up, in one
+// word: (largest << 16) | smallest.  8 words per span, 0.8 % (bf16: 1.6 %) of what the pass reads.
+constexpr int kPieces = 8;                       // of a span
+__device__ __forceinline__ uint32_t pack_range(float lowest, float highest)
+{
+    const uint32_t l = __builtin_bit_cast(uint32_t, lowest), h = __builtin_bit_cast(uint32_t, highest);
+    // away from zero: one step up in magnitude unless the low half is empty; towards zero: the low half dropped
+    const uint32_t down = (l >> 31) ? (l + 0xffffu) >> 16 : l >> 16, up = (h >> 31) ? h >> 16 : (h + 0xffffu) >> 16;
+    return (up << 16) | (down & 0xffffu);
+}
+// Can a piece hold an outlier?  x -> (x - mean)^2 in binary64 rises on either side of the mean, rounding included, so
+// its largest values over a range are at the range's ends.  (Ends that compare as NaN -- infinities or NaNs among the
+// statistics -- count as "yes".)
+__device__ __forceinline__ bool may_hold_outliers(uint32_t range, double mean, double threshold)
+{
+    const double low = (double)bf16_lo(range) - mean, high = (double)bf16_hi(range) - mean;
+    return !(low * low <= threshold && high * high <= threshold);
+}
+
+// A wave reads 4 KiB: one span of fp32, two of bf16.  The reads are the time (6.7 TB/s of 7.1 that nothing but reads
+// reaches); the few bytes written beside them cost as much as their lines travel: with a launch's workgroups dealt to
+// the XCDs one by one, as the hardware does, lines of partial sums and ranges are written from two L2s, and the pass
+// over the 557 MiB set takes 95 us; with each XCD on a contiguous eighth of the launch's tiles, 87 us.
+constexpr int kXcds = 8;
+__device__ __forceinline__ uint32_t tile_of_block()
+{
+    const uint32_t each = gridDim.x / kXcds;                  // the last gridDim.x mod 8 stay where they are
+    return blockIdx.x < each * kXcds ? (blockIdx.x % kXcds) * each + blockIdx.x / kXcds : blockIdx.x;
+}
 template <typename InT>
 __global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsItem> args)
 {
-    constexpr int ROWS = Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
+    constexpr int ROWS = 4, EPL = Span<InT>::EPL, ROW = kWave * EPL, SPANS = ROWS / Span<InT>::ROWS;
     uint32_t block;
-    const MomentsItem& it = args.item[batch_item(args, blockIdx.x, block)];
+    const MomentsItem& it = args.item[batch_item(args, tile_of_block(), block)];
     const InT* x = static_cast<const InT*>(it.x);
     const int64_t numel = it.numel;
-    f64x2* partial = it.partial;
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t span = (int64_t)block * kWavesPerBlock + wave;
+    const int64_t span = ((int64_t)block * kWavesPerBlock + wave) * SPANS;
     const int64_t base = span * kSpan;
     if (base >= numel) return;                                // wave-uniform
     const InT* xs = x + base;
     double a[ROWS], b[ROWS];
-    const bool interior = base + kSpan <= numel;
+    float lowest[SPANS], highest[SPANS];
+#pragma unroll
+    for (int k = 0; k < SPANS; ++k) { lowest[k] = __builtin_inff(); highest[k] = -__builtin_inff(); }
+    const bool interior = base + SPANS * kSpan <= numel;
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-        float v[EPL];
+        float v[EPL];                                         // (elements past the end count as 0, in the range too)
         const uint32_t e0 = r * ROW + lane * EPL;
         if (interior) {
             Span<InT>::load(xs + e0, v);
@@ -215,15 +237,34 @@ __global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsIt
 #pragma unroll
             for (int j = 0; j < EPL; ++j) v[j] = (base + e0 + j < numel) ? Span<InT>::one(xs + e0 + j) : 0.0f;
         }
-        double d[EPL], q[EPL];
+        // the squares are exact, so the fused multiply-add rounds the sum of two of them just as an addition would
+        double d[EPL], q[EPL / 2];
 #pragma unroll
-        for (int j = 0; j < EPL; ++j) { d[j] = (double)v[j]; q[j] = d[j] * d[j]; }   // the square is exact
+        for (int j = 0; j < EPL; ++j) d[j] = (double)v[j];
+#pragma unroll
+        for (int j = 0; j < EPL; j += 2) q[j / 2] = __builtin_fma(d[j], d[j], d[j + 1] * d[j + 1]);
         a[r] = local_tree<EPL>(d);
-        b[r] = local_tree<EPL>(q);
+        b[r] = local_tree<EPL / 2>(q);
+        const int k = r / Span<InT>::ROWS;
+#pragma unroll
+        for (int j = 0; j < EPL; j += 2) {
+            asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lowest[k]) : "v"(v[j]), "v"(v[j + 1]));
+            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(highest[k]) : "v"(v[j]), "v"(v[j + 1]));
+        }
     }
-    double s1, s2;
-    span_tree<ROWS>(a, b, lane, s1, s2);
-    if (lane == 0) partial[span] = f64x2{s1, s2};
+    const double t = span_tree<SPANS>(a, b, lane);
+    const int64_t here = (numel - base + kSpan - 1) / kSpan;  // spans from this one to the tensor's last
+    const uint32_t k = (lane >> 1) & 1u;
+    if (lane < 8u && (lane & 1u) == 0u && k < (uint32_t)SPANS && (int64_t)k < here)
+        reinterpret_cast<double*>(it.partial + span + k)[lane >> 2] = t;
+    if (it.ranges) {                                          // wave-uniform
+        uint32_t* ranges = it.ranges + span * kPieces;
+#pragma unroll
+        for (int s = 0; s < SPANS; ++s) {
+            row_minmax<8>(lowest[s], highest[s]);
+            if ((lane & 7u) == 0u && (int64_t)s < here) ranges[s * kPieces + (lane >> 3)] = pack_range(lowest[s], highest[s]);
+        }
+    }
 }
 
 // ---- pass 1b: spans of partial sums (4 rows of 256 pairs, 4 consecutive pairs per lane) --
@@ -254,7 +295,7 @@ __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const Batch<R
         b[r] = local_tree<EPL>(q);
     }
     double s1, s2;
-    span_tree<ROWS>(a, b, lane, s1, s2);
+    both_moments(span_tree<1>(a, b, lane), lane, s1, s2);
     if (lane == 0) out[span] = f64x2{s1, s2};
 }
 
@@ -289,7 +330,7 @@ __global__ __launch_bounds__(kThreads) void finish_moments_kernel(const FinishBa
         b[r] = local_tree<EPL>(q);
     }
     double s1, s2;
-    span_tree<ROWS>(a, b, lane, s1, s2);
+    both_moments(span_tree<1>(a, b, lane), lane, s1, s2);
     if (lane == 0) {
         double mean = 0.0, variance = 0.0;
         if (numel > 0) {
@@ -308,7 +349,7 @@ __global__ __launch_bounds__(kThreads) void finish_moments_kernel(const FinishBa
 
 // ---- pass 2: outliers per channel ----------------------------------------------------------
 // Channel of an outlier: division by `inner` and `channels` through the small-dividend
-// divider of fh_channels.hpp (dividends stay below divisor + 2 * 1024 here).
+// divider of fh_channels.hpp (dividends stay below divisor + 8 * 1024 here).
 struct CountArgs {
     const void* x;
     int64_t numel;
@@ -316,6 +357,7 @@ struct CountArgs {
     uint32_t* counts;
     SmallDiv inner, channels;
     int32_t spans_per_wave;                                   // consecutive spans one wave walks
+    const uint32_t* ranges;                                   // of the tensor's pieces (count_marked_kernel)
 };
 
 // AHEAD: a launch in which some wave walks more than one span.
@@ -434,6 +476,103 @@ __global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Batch<Co
     }
 }
 
+// The same where the first pass left ranges behind.  A wave looks at the ranges of eight spans at once, a lane per
+// piece, lists the pieces that may hold an outlier, and reads those: eight lanes to a piece, a lane's elements the
+// ones it would have in a span walked whole.  Four rounds of eight pieces are requested together.  What bounds the
+// pass is what the data leave to read: nothing but the salient channels' share on feature maps with outliers
+// clustered in channels (557 MiB set: 15 us, the kernel above 95), a quarter to a third of the lines of
+// [tokens][hidden] tensors (Gaussian tails alone put an outlier in 3 of 10 pieces; 480 MiB of bf16: 44 us against 96).
+// With an outlier in every piece it reads the tensor whole, as the kernel above does.
+constexpr int kLook = 8;                          // spans whose ranges a wave looks at together: 64 pieces
+constexpr int kRounds = 4;                        // rounds of eight pieces requested together
+template <typename InT>
+__global__ __launch_bounds__(kThreads) void count_marked_kernel(const Batch<CountArgs> batch)
+{
+    constexpr int ROWS = Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
+    extern __shared__ uint32_t hist[];
+    uint32_t block;
+    const CountArgs& args = batch.item[batch_item(batch, blockIdx.x, block)];
+    const uint32_t C = args.channels.d;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const InT* x = static_cast<const InT*>(args.x);
+    const int64_t numel = args.numel, all_spans = (numel + kSpan - 1) / kSpan;
+    const int64_t first = ((int64_t)block * kWavesPerBlock + wave) * args.spans_per_wave;
+    const int64_t stop = first + args.spans_per_wave < all_spans ? first + args.spans_per_wave : all_spans;
+    const auto range_of = [&](int64_t span) { return span + (lane >> 3) < stop ? args.ranges[span * kPieces + lane] : 0u; };
+    uint32_t range = range_of(first);                         // in flight while the counters are cleared
+    for (uint32_t c = threadIdx.x; c < C; c += kThreads) hist[c] = 0u;
+    const double mean = args.stats[0], threshold = args.stats[2];
+    __syncthreads();
+    for (int64_t span0 = first; span0 < stop; span0 += kLook) {          // wave-uniform
+        const bool mark = span0 + (lane >> 3) < stop && may_hold_outliers(range, mean, threshold);
+        const uint64_t marks = __ballot(mark);
+        if (span0 + kLook < stop) range = range_of(span0 + kLook);
+        const uint32_t pieces = (uint32_t)__popcll(marks);
+        if (pieces == 0u) continue;
+        // lane k of `list`: the k-th marked piece (the unmarked ones behind them, so that every lane sends and receives)
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(marks >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)marks, 0u));
+        const int list = __builtin_amdgcn_ds_permute((int)((mark ? before : pieces + lane - before) << 2), (int)lane);
+        // position of the first span's first element: rem = index inside the channel run, chan = channel
+        const int64_t base = span0 * kSpan;
+        const uint64_t run = (uint64_t)base / args.inner.d;
+        const uint32_t rem = (uint32_t)((uint64_t)base - run * args.inner.d), chan = (uint32_t)(run % C);
+        const int64_t whole = (numel - base) / kSpan;         // spans from here on that are whole
+        for (uint32_t p0 = 0; p0 < pieces; p0 += 8u * kRounds) {
+            uint32_t at[kRounds];                             // the lane's first element, from the first span's; ~0: no piece
+            bool inside[kRounds];                             // all of the piece's span exists
+            u32x4 w[kRounds][ROWS];
+#pragma unroll
+            for (int k = 0; k < kRounds; ++k) {
+                const uint32_t p = p0 + 8u * k + (lane >> 3);            // at most 63
+                const uint32_t piece = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(p << 2), list);
+                inside[k] = p < pieces && (int64_t)(piece >> 3) < whole;
+                at[k] = p < pieces ? (piece >> 3) * (uint32_t)kSpan + ((piece & 7u) * 8u + (lane & 7u)) * EPL : ~0u;
+                if (inside[k]) {
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r) w[k][r] = stream_load(reinterpret_cast<const u32x4*>(x + base + at[k] + r * ROW));
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kRounds; ++k) {
+                if (p0 + 8u * k >= pieces) break;             // wave-uniform
+                if (at[k] == ~0u) continue;
+                uint32_t bits = 0u;                           // bit r * EPL + j: that element is an outlier
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) {
+                    float v[EPL];
+                    if (inside[k]) {
+                        Span<InT>::widen(w[k][r], v);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < EPL; ++j) {
+                            const int64_t i = base + at[k] + r * ROW + j;
+                            v[j] = i < numel ? Span<InT>::one(x + i) : __builtin_bit_cast(float, 0x7fc00000u);
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < EPL; ++j) {
+                        const double d = (double)v[j] - mean;
+                        if (d * d > threshold) bits |= 1u << (r * EPL + j);          // false for the NaN filler
+                    }
+                }
+                while (bits) {
+                    const uint32_t k2 = (uint32_t)__builtin_ctz(bits);
+                    bits &= bits - 1u;
+                    const uint32_t off = at[k] + (k2 / EPL) * ROW + (k2 % EPL);       // below 8 * 1024
+                    const uint32_t cc = chan + div_small(rem + off, args.inner);      // channel runs crossed from `chan`
+                    atomicAdd(&hist[cc - div_small(cc, args.channels) * C], 1u);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    for (uint32_t c = threadIdx.x; c < C; c += kThreads) {
+        const uint32_t v = hist[c];
+        if (v) atomicAdd(&args.counts[c], v);
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void mask_kernel(const Batch<MaskItem> args)
 {
     uint32_t block;
@@ -461,6 +600,11 @@ size_t fh_classify_workspace_bytes(int64_t numel)
         m = fh::ceil_div(m, fh::kSpan);
     }
     return pairs * 16;
+}
+
+size_t fh_classify_workspace_bytes_ranges(int64_t numel)
+{
+    return fh_classify_workspace_bytes(numel) + fh::range_bytes(numel);
 }
 
 }  // extern "C"
@@ -518,20 +662,23 @@ fh_status check_item(const fh_classify_item& it, int64_t* numel_out)
     return FH_OK;
 }
 
-// One run of up to kBatch tensors of one dtype: five kinds of launches, each covering all of them.
-fh_status run_classify(const fh_classify_item* items, const int64_t* numels, int n, hipStream_t s)
+// One run of up to kBatch tensors of one dtype: five kinds of launches, each covering all of them.  The tensors either
+// all have a place for their ranges or all have none.
+fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, const int64_t* numels, int n, hipStream_t s)
 {
+    const bool marked = ranges[0] != nullptr;
     const dim3 block(kThreads);
     const int dtype = items[0].x_dtype;
     f64x2* level[kBatch];
     int64_t m[kBatch];
+    const int64_t per_block = kWavesPerBlock * (dtype == FH_F32 ? 1 : 2);    // spans of a workgroup of the first pass
 
     Batch<MomentsItem> mb;
     reset(mb);
     for (int i = 0; i < n; ++i) {
         level[i] = static_cast<f64x2*>(items[i].workspace);
         m[i] = numels[i] > 0 ? ceil_div(numels[i], kSpan) : 0;
-        if (numels[i] > 0 && !push(mb, MomentsItem{items[i].x, numels[i], level[i]}, ceil_div(m[i], kWavesPerBlock)))
+        if (numels[i] > 0 && !push(mb, MomentsItem{items[i].x, numels[i], level[i], ranges[i]}, ceil_div(m[i], per_block)))
             return FH_ERR_BAD_NUMEL;
     }
     if (mb.count > 0) {
@@ -582,7 +729,10 @@ fh_status run_classify(const fh_classify_item* items, const int64_t* numels, int
         // that cheap, but no more (short workgroups measured faster on feature maps; 128 elements per bin and
         // wave on [tokens][hidden] tensors, where the outliers of ordinary activations touch most bins)
         const int64_t ch = items[i].channels;
-        a.spans_per_wave = (int32_t)(ch <= 512 ? 1 : ch / 128 < 16 ? ch / 128 : 16);
+        // With ranges a wave looks at eight spans together, whatever the shape, and has little to count in them; the
+        // wide tensors get twice that.
+        a.spans_per_wave = marked ? (ch <= 1024 ? kLook : 2 * kLook) : (int32_t)(ch <= 512 ? 1 : ch / 128 < 16 ? ch / 128 : 16);
+        a.ranges = ranges[i];
         const int64_t per_block = (int64_t)a.spans_per_wave * kWavesPerBlock * kSpan;
         if (!push(cb, a, ceil_div(numels[i], per_block))) return FH_ERR_BAD_NUMEL;
         push(kb, MaskItem{a.counts, static_cast<uint8_t*>(items[i].mask), items[i].min_outliers, (int32_t)ch},
@@ -595,7 +745,10 @@ fh_status run_classify(const fh_classify_item* items, const int64_t* numels, int
         const dim3 grid(cb.block_start[cb.count]);
         bool ahead = false;
         for (int k = 0; k < cb.count; ++k) ahead = ahead || cb.item[k].spans_per_wave > 1;
-        if (dtype == FH_F32) {
+        if (marked) {
+            if (dtype == FH_F32) hipLaunchKernelGGL(count_marked_kernel<float>, grid, block, lds, s, cb);
+            else hipLaunchKernelGGL(count_marked_kernel<uint16_t>, grid, block, lds, s, cb);
+        } else if (dtype == FH_F32) {
             if (ahead) hipLaunchKernelGGL((count_outliers_kernel<float, true>), grid, block, lds, s, cb);
             else hipLaunchKernelGGL((count_outliers_kernel<float, false>), grid, block, lds, s, cb);
         } else {
@@ -607,7 +760,35 @@ fh_status run_classify(const fh_classify_item* items, const int64_t* numels, int
     return hipGetLastError() == hipSuccess ? FH_OK : FH_ERR_LAUNCH;
 }
 
+// All tensors (checked): runs of one dtype that have ranges or have none, at most kBatch long.
+// range_of(i, numel): where the ranges of tensor i go, or null.
+template <typename RangeOf>
+fh_status run_all(const fh_classify_item* items, int32_t count, hipStream_t s, RangeOf range_of)
+{
+    const auto numel_of = [items](int32_t i) { return items[i].outer * items[i].channels * items[i].inner; };
+    int32_t i = 0;
+    while (i < count) {
+        int64_t numels[kBatch];
+        uint32_t* ranges[kBatch];
+        int n = 0;
+        for (; i + n < count && n < kBatch && items[i + n].x_dtype == items[i].x_dtype; ++n) {
+            numels[n] = numel_of(i + n);
+            ranges[n] = range_of(i + n, numels[n]);
+            if (!ranges[n] != !ranges[0]) break;
+        }
+        const fh_status st = run_classify(items + i, ranges, numels, n, s);
+        if (st != FH_OK) return st;
+        i += n;
+    }
+    return FH_OK;
+}
+
 }  // namespace
+
+fh_status fh::classify_with_ranges(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, hipStream_t s)
+{
+    return run_all(items, count, s, [ranges](int32_t i, int64_t) { return ranges[i]; });
+}
 
 extern "C" {
 
@@ -623,20 +804,12 @@ fh_status fh_classify_channels_batch(const fh_classify_item* items, int32_t coun
         const fh_status st = check_item(items[i], &numel);
         if (st != FH_OK) return st;
     }
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    int32_t i = 0;
-    while (i < count) {                                       // runs of one dtype, at most kBatch long
-        int64_t numels[fh::kBatch];
-        int n = 0;
-        while (i + n < count && n < fh::kBatch && items[i + n].x_dtype == items[i].x_dtype) {
-            check_item(items[i + n], &numels[n]);
-            ++n;
-        }
-        const fh_status st = run_classify(items + i, numels, n, s);
-        if (st != FH_OK) return st;
-        i += n;
-    }
-    return FH_OK;
+    // the ranges lie behind the partial sums, where there is room for them
+    return run_all(items, count, static_cast<hipStream_t>(stream), [items](int32_t i, int64_t numel) -> uint32_t* {
+        const size_t pairs = fh_classify_workspace_bytes(numel);
+        if (items[i].workspace_cap < pairs + range_bytes(numel)) return nullptr;
+        return reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(items[i].workspace) + pairs);
+    });
 }
 
 fh_status fh_classify_channels(const void* x, fh_dtype x_dtype, int64_t outer, int64_t channels, int64_t inner,

@@ -99,6 +99,37 @@ def test_workspace_and_outputs_can_be_reused_between_calls(api):
         assert np.array_equal(mask.cpu().numpy(), want[2])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 1023, 1025, 8191, 8192, 8193, 9216, 32768, 32769, 262144 + 1337])
+def test_pieces_without_outliers_are_skipped_and_no_others(api, n, dtype):
+    """With room for value ranges the count pass reads only the pieces whose range reaches beyond the threshold: the
+    same statistics, counts and mask as without (and as the oracle), where outliers are rare, everywhere, at a piece's
+    last element, just beyond and just within a threshold that the rounding of a range straddles, and absent."""
+    C = 3 if n % 3 == 0 else 1
+    rng = np.random.default_rng(n)
+    z = rng.standard_normal(n).astype(f32)
+    cases = {"rare": z.copy(), "none": np.where(z > 0, f32(1), f32(-1)), "all negative": -np.abs(z) - f32(5)}
+    last = z * f32(0.01)
+    last[127::128] = 40.0
+    cases["last of a piece"] = last
+    edge = np.where(rng.random(n) < 0.5, f32(1), f32(-1)).astype(f32)
+    edge[rng.integers(0, n, max(1, n // 500))] = f32(3.0078125)           # between two bf16 values around three sigma
+    cases["edge"] = edge
+    for name, x in cases.items():
+        if dtype == "bf16":
+            x = (x.view(np.uint32) >> 16).astype(np.uint16)
+        for k in (0.5, 3.0):
+            _check(api, x, n // C, C, 1, k, 1, dtype=dtype, name=name)                        # workspace with ranges
+            xd = _device(x, dtype)
+            ws = torch.empty(api.classify_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+            wide = torch.empty(api.classify_workspace_bytes_ranges(n), dtype=torch.uint8, device="cuda")
+            plain = api.fh_classify_channels(xd, 1, 1, n, k, 1, workspace=ws)
+            marked = api.fh_classify_channels(xd, 1, 1, n, k, 1, workspace=wide)
+            torch.cuda.synchronize()
+            for a, b in zip(plain, marked):
+                assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
 @pytest.mark.timeout(600)
 def test_paper_sized_activation_set(api):
     # the five per-sample shapes of the paper's local-engine ablation, at batch 64
