@@ -218,7 +218,7 @@ fh_status fh_channel_slots(const void *mask, int64_t channels, int64_t raw_chann
 /* The same, and *used (device uint64, 8-byte aligned) = raw-store rows in use = min(salient channels, raw_channels). */
 fh_status fh_channel_slots_used(const void *mask, int64_t channels, int64_t raw_channels, void *slots, void *used,
                                 void *stream);
-/* The same for several tensors with one launch per fh_mixed_batch_capacity() of them (used may be NULL). */
+/* The same for several tensors with one launch per fh_mixed_batch_capacity() of them or more (used may be NULL). */
 typedef struct fh_slots_item {
     const void *mask;       int64_t channels, raw_channels;
     void       *slots;      void *used;
@@ -234,7 +234,7 @@ fh_status fh_decompress_mixed(const void *packed, const void *meta, const void *
                               fh_dtype out_dtype, void *out, size_t out_cap, void *stream);
 
 /* The same two calls for several tensors (one launch per run of up to fh_mixed_batch_capacity()
- * items that share dtype and group size; items with no element are skipped, items with
+ * items, or more, that share dtype and group size; items with no element are skipped, items with
  * raw_channels == 0 are served by the plain quantiser's kernels; everything is checked before
  * the first launch; results identical to the single calls).  Compression uses
  * x, x_dtype, the shape, slots, raw_channels, packed, meta, raw (whose dtype is x_dtype) and
@@ -312,8 +312,8 @@ fh_status fh_sparse_decode(const void *info, const void *values, size_t values_b
                            void *out, size_t out_cap, void *workspace, size_t workspace_cap, void *stream);
 
 /* The same for several tensors, as a plan classifies every compressible activation of a model:
- * each kind of kernel is launched once per run of up to fh_classify_batch_capacity() items of
- * one dtype, so small tensors do not each pay five launches.  All items are checked before the
+ * each kind of kernel is launched once per run of up to fh_classify_batch_capacity() items (a launch
+ * may take more) of one dtype, so small tensors do not each pay five launches.  All items are checked before the
  * first launch; results are identical to calling fh_classify_channels item by item.  The
  * items' outputs and workspaces must not overlap. */
 typedef struct fh_classify_item {
@@ -327,7 +327,7 @@ fh_status fh_classify_channels_batch(const fh_classify_item *items, int32_t coun
 int32_t   fh_classify_batch_capacity(void);
 
 /* The same for several sets of maps (the kept channels of every layer of a model): each pass is
- * launched once per run of up to fh_sparse_batch_capacity() items that share dtype and window.
+ * launched once per run of up to fh_sparse_batch_capacity() items, or more, that share dtype and window.
  * All items are checked before the first launch; results are identical to the single calls.
  * The items' buffers must not overlap. */
 typedef struct fh_sparse_encode_item {
@@ -387,7 +387,7 @@ fh_status fh_huffman_decode(const void *stream_in, size_t stream_bytes, uint64_t
                             void *stream);
 
 /* The same two calls for several byte buffers: every pass is launched once per run of up to
- * fh_huffman_batch_capacity() items (the code construction, a single workgroup's work per
+ * fh_huffman_batch_capacity() items or more (the code construction, a single workgroup's work per
  * buffer, then runs for all of them side by side).  Everything is checked before the first
  * launch; results identical to the single calls.
  *

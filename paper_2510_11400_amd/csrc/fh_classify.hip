@@ -792,7 +792,7 @@ fh_status fh::classify_with_ranges(const fh_classify_item* items, uint32_t* cons
 
 extern "C" {
 
-int32_t fh_classify_batch_capacity(void) { return fh::kBatch; }
+int32_t fh_classify_batch_capacity(void) { return fh::kBatchStated; }
 
 fh_status fh_classify_channels_batch(const fh_classify_item* items, int32_t count, void* stream)
 {

@@ -1017,7 +1017,7 @@ size_t fh_huffman_workspace_bytes(uint64_t n)
     return (size_t)(4u * (256u + 256u + (fh::groups_of(n) > 0 ? fh::groups_of(n) : 1u)));
 }
 
-int32_t fh_huffman_batch_capacity(void) { return fh::kBatch; }
+int32_t fh_huffman_batch_capacity(void) { return fh::kBatchStated; }
 
 }  // extern "C"
 

@@ -205,7 +205,7 @@ fh_status check_decompress(const fh_mixed_item& it, int64_t* numel)
 
 extern "C" {
 
-int32_t fh_mixed_batch_capacity(void) { return fh::kBatch; }
+int32_t fh_mixed_batch_capacity(void) { return fh::kBatchStated; }
 
 fh_status fh_compress_mixed_batch(const fh_mixed_item* items, int32_t count, void* stream)
 {

@@ -934,7 +934,7 @@ void add_job(Run& run, Job job, int64_t tiles)
 
 extern "C" {
 
-int32_t fh_sparse_batch_capacity(void) { return fh::kBatch; }
+int32_t fh_sparse_batch_capacity(void) { return fh::kBatchStated; }
 
 fh_status fh_sparse_encode_batch(const fh_sparse_encode_item* items, int32_t count, void* stream)
 {

@@ -104,6 +104,21 @@ def _input(case, seed):
     return x
 
 
+@pytest.mark.parametrize("count", [24, 25, 50])
+def test_batches_at_the_number_of_tensors_that_a_launch_holds(api, count):
+    """A launch of each stage holds 24 tensors: a batch of just that many, one more, and more than two launches."""
+    picked = [(1 + i % 3,) + CASES[0][1:] if i % 2 else (40 + i,) + CASES[6][1:4] + (8,) + CASES[6][5:12] + ("f32", 3)
+              for i in range(count)]
+    xs = [_input(case, 500 + i) for i, case in enumerate(picked)]
+    batch = api.MixBatch([_entry(api, _device(x, case[12]), case, "f32") for x, case in zip(xs, picked)])
+    print(f"[chain] batch of {count}", flush=True)
+    api.fh_mix_compress_batch(batch)
+    api.fh_mix_decompress_batch(batch)
+    torch.cuda.synchronize()
+    for i, (x, case) in enumerate(zip(xs, picked)):
+        _compare(api, batch, i, x, case, "f32")
+
+
 @pytest.mark.parametrize("k", range(len(CASES)))
 @pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
 def test_single_tensor_chain_matches_the_oracle_chain(api, k, out_dtype):
