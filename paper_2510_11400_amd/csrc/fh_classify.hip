@@ -23,7 +23,7 @@
 
 #include "fh_batch.hpp"
 #include "fh_channels.hpp"
-#include "fh_classify.hpp"
+#include "fh_stages.hpp"
 #include "fh_device.hpp"
 
 #include <limits.h>
@@ -662,9 +662,10 @@ fh_status check_item(const fh_classify_item& it, int64_t* numel_out)
     return FH_OK;
 }
 
-// One run of up to kBatch tensors of one dtype: five kinds of launches, each covering all of them.  The tensors either
-// all have a place for their ranges or all have none.
-fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, const int64_t* numels, int n, hipStream_t s)
+// One run of up to kBatch tensors of one dtype: five kinds of launches, each covering all of them (four without the
+// masks).  The tensors either all have a place for their ranges or all have none.
+fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, const int64_t* numels, int n, bool masks,
+                       hipStream_t s)
 {
     const bool marked = ranges[0] != nullptr;
     const dim3 block(kThreads);
@@ -755,7 +756,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
             if (ahead) hipLaunchKernelGGL((count_outliers_kernel<uint16_t, true>), grid, block, lds, s, cb);
             else hipLaunchKernelGGL((count_outliers_kernel<uint16_t, false>), grid, block, lds, s, cb);
         }
-        hipLaunchKernelGGL(mask_kernel, dim3(kb.block_start[kb.count]), block, 0, s, kb);
+        if (masks) hipLaunchKernelGGL(mask_kernel, dim3(kb.block_start[kb.count]), block, 0, s, kb);
     }
     return hipGetLastError() == hipSuccess ? FH_OK : FH_ERR_LAUNCH;
 }
@@ -763,7 +764,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
 // All tensors (checked): runs of one dtype that have ranges or have none, at most kBatch long.
 // range_of(i, numel): where the ranges of tensor i go, or null.
 template <typename RangeOf>
-fh_status run_all(const fh_classify_item* items, int32_t count, hipStream_t s, RangeOf range_of)
+fh_status run_all(const fh_classify_item* items, int32_t count, bool masks, hipStream_t s, RangeOf range_of)
 {
     const auto numel_of = [items](int32_t i) { return items[i].outer * items[i].channels * items[i].inner; };
     int32_t i = 0;
@@ -776,7 +777,7 @@ fh_status run_all(const fh_classify_item* items, int32_t count, hipStream_t s, R
             ranges[n] = range_of(i + n, numels[n]);
             if (!ranges[n] != !ranges[0]) break;
         }
-        const fh_status st = run_classify(items + i, ranges, numels, n, s);
+        const fh_status st = run_classify(items + i, ranges, numels, n, masks, s);
         if (st != FH_OK) return st;
         i += n;
     }
@@ -785,9 +786,9 @@ fh_status run_all(const fh_classify_item* items, int32_t count, hipStream_t s, R
 
 }  // namespace
 
-fh_status fh::classify_with_ranges(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, hipStream_t s)
+fh_status fh::classify_counts(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, hipStream_t s)
 {
-    return run_all(items, count, s, [ranges](int32_t i, int64_t) { return ranges[i]; });
+    return run_all(items, count, false, s, [ranges](int32_t i, int64_t) { return ranges[i]; });
 }
 
 extern "C" {
@@ -805,7 +806,7 @@ fh_status fh_classify_channels_batch(const fh_classify_item* items, int32_t coun
         if (st != FH_OK) return st;
     }
     // the ranges lie behind the partial sums, where there is room for them
-    return run_all(items, count, static_cast<hipStream_t>(stream), [items](int32_t i, int64_t numel) -> uint32_t* {
+    return run_all(items, count, true, static_cast<hipStream_t>(stream), [items](int32_t i, int64_t numel) -> uint32_t* {
         const size_t pairs = fh_classify_workspace_bytes(numel);
         if (items[i].workspace_cap < pairs + range_bytes(numel)) return nullptr;
         return reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(items[i].workspace) + pairs);

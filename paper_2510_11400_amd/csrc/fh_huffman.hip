@@ -32,6 +32,7 @@
 
 #include "fh_batch.hpp"
 #include "fh_scan.hpp"
+#include "fh_stages.hpp"
 
 namespace fh {
 namespace {
@@ -75,6 +76,7 @@ struct Layout {                                    // where things are in the st
     const uint64_t* n_dev;                         // device: the symbol count, known only on the stream; or null
     uint32_t  chunks, groups;
     uint32_t  hist_blocks;                         // workgroups of the histogram pass
+    StoredForm stored;                             // header: null outside the whole chain
 };
 
 __device__ __forceinline__ uint64_t chunks_for(uint64_t n) { return (n + 255u) >> 8; }
@@ -494,8 +496,11 @@ __global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Batch<Layo
         carry += total;
     }
     if (threadIdx.x == 0) {
+        const uint64_t bytes = 256u + 4ull * (lay.chunks + 1ull) + 4ull * carry;
         lay.offsets[lay.chunks] = carry;
-        lay.totals[0] = 256u + 4ull * (lay.chunks + 1ull) + 4ull * carry;
+        lay.totals[0] = bytes;
+        const StoredForm& f = lay.stored;
+        if (f.header) f.header[6] = f.fixed_bytes + f.header[0] * f.value_size + bytes;
     }
 }
 
@@ -1056,19 +1061,9 @@ void launch(Kernel kernel, const Batch<Item>& b, uint32_t grid, hipStream_t s, i
 }
 
 
-}  // namespace
-
-extern "C" {
-
-fh_status fh_huffman_encode_batch(const fh_huffman_encode_item* items, int32_t count, void* stream)
+// The encoder's launches; `stored` null: the histograms are to be cleared, and there is no header to write to.
+fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stored, int32_t count, hipStream_t s)
 {
-    if (count < 0) return FH_ERR_BAD_COUNT;
-    if (count > 0 && !items) return FH_ERR_NULL;
-    for (int32_t i = 0; i < count; ++i) {                     // everything is checked before the first launch
-        const fh_status st = check_encode(items[i]);
-        if (st != FH_OK) return st;
-    }
-    hipStream_t s = static_cast<hipStream_t>(stream);
     for (int32_t i = 0; i < count;) {
         // the same streams three times: a workgroup each | by histogram workgroups | by groups of chunks
         Batch<Layout> each, hist, grouped;
@@ -1088,6 +1083,7 @@ fh_status fh_huffman_encode_batch(const fh_huffman_encode_item* items, int32_t c
             lay.in = static_cast<const uint8_t*>(it.bytes);
             lay.n = it.n;
             lay.n_dev = static_cast<const uint64_t*>(it.n_device);
+            lay.stored = stored ? stored[i] : StoredForm{nullptr, 0, 0};
             // about eight vectors per thread, more in long streams: a workgroup clears and adds up 32 KiB of
             // counters and sends 256 atomics to the stream's histogram whatever it counts
             const uint64_t want = it.n == 0 ? 0 : (it.n / 16 + kHistThreads - 1) / kHistThreads / 8 + 1;
@@ -1102,7 +1098,7 @@ fh_status fh_huffman_encode_batch(const fh_huffman_encode_item* items, int32_t c
             ++i;
         }
         seal(each); seal(hist); seal(grouped);
-        launch(huffman_clear_kernel, each, (uint32_t)each.count, s);
+        if (!stored) launch(huffman_clear_kernel, each, (uint32_t)each.count, s);
         launch(huffman_histogram_kernel, hist, hist.block_start[hist.count], s, kHistThreads);
         launch(huffman_code_kernel, each, (uint32_t)each.count, s, kCodeThreads);
         launch(huffman_count_kernel, grouped, grouped.block_start[grouped.count], s);
@@ -1111,6 +1107,26 @@ fh_status fh_huffman_encode_batch(const fh_huffman_encode_item* items, int32_t c
     }
     if (count == 0) return FH_OK;
     return hipGetLastError() == hipSuccess ? FH_OK : FH_ERR_LAUNCH;
+}
+
+}  // namespace
+
+fh_status fh::huffman_encode_stored(const fh_huffman_encode_item* items, const StoredForm* stored, int32_t count, hipStream_t s)
+{
+    return encode_all(items, stored, count, s);
+}
+
+extern "C" {
+
+fh_status fh_huffman_encode_batch(const fh_huffman_encode_item* items, int32_t count, void* stream)
+{
+    if (count < 0) return FH_ERR_BAD_COUNT;
+    if (count > 0 && !items) return FH_ERR_NULL;
+    for (int32_t i = 0; i < count; ++i) {                     // everything is checked before the first launch
+        const fh_status st = check_encode(items[i]);
+        if (st != FH_OK) return st;
+    }
+    return encode_all(items, nullptr, count, static_cast<hipStream_t>(stream));
 }
 
 fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t count, void* stream)

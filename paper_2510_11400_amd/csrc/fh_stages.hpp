@@ -1,0 +1,28 @@
+// What the whole-chain call needs of the stages beyond their public entry points: the same calls with small pieces of
+// work left out that a kernel of the chain does on its way, and with scratch given separately.  The items of all
+// calls have been checked.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include <hip/hip_runtime.h>
+
+#include "../../include/fedhybrid.h"
+
+namespace fh {
+
+// Bytes of a tensor's value ranges: one word per 128 elements of its 1024-element spans.
+inline size_t range_bytes(int64_t numel) { return numel > 0 ? (size_t)((numel + 1023) / 1024) * 32u : 0u; }
+
+// fh_classify_channels_batch without the masks (which follow from the counts), and with ranges[i] (16-byte aligned,
+// range_bytes() of item i, or null: the count pass then reads the whole tensor).
+fh_status classify_counts(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, hipStream_t s);
+
+// fh_huffman_encode_batch for histograms (the first 256 words of the items' workspaces) that have been cleared, and
+// with the bytes that the stored form of the tensor occupies written to header[6] on the way:
+// fixed_bytes + header[0] * value_size + the stream's bytes.
+struct StoredForm { uint64_t* header; uint64_t fixed_bytes; uint32_t value_size; };
+fh_status huffman_encode_stored(const fh_huffman_encode_item* items, const StoredForm* stored, int32_t count, hipStream_t s);
+
+}  // namespace fh
