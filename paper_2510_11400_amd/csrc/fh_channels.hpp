@@ -180,6 +180,19 @@ __device__ __forceinline__ void kept_runs(const ChannelMap& cm, const ElemPos& w
     }
 }
 
+// Is any of the `count` elements (>= 1) from element `index` on of a kept channel?
+__device__ __forceinline__ bool any_kept(const ChannelMap& cm, uint32_t index, uint32_t count)
+{
+    const ElemPos p = locate_base(cm, index);
+    const uint32_t runs = div_small(p.pos + count - 1u, cm.inner) + 1u;
+    bool any = false;
+    for (uint32_t k = 0; k < runs; ++k) {
+        const uint32_t cc = p.c + k;
+        any = any || kept(cm, cm.slots[cc - div_small(cc, cm.channels) * cm.channels.d]);
+    }
+    return any;
+}
+
 // ---- one channel per element: the kept elements of a span, listed by raw-store row -----------
 // With inner == 1 a raw-store row holds one element per sample, and the kept elements of a
 // wave's span are few and scattered (a few per cent of the channels).  Instead of every lane
@@ -297,6 +310,19 @@ __device__ __forceinline__ void first_pairs(const ChannelMap& cm, PairWalk& p, c
         off[k] = pair_offset(p, rows);
         pair_advance(cm, p);
     }
+}
+
+// Are all N elements of the run kept, as elements of one channel?  (The common case on feature maps.)  Then they are
+// N consecutive elements of the raw store, from raw_first on.
+template <int N>
+__device__ __forceinline__ bool kept_whole(const ChannelMap& cm, const KeptRun<N>& run)
+{
+    return run.mask == (1u << N) - 1u && run.p.pos + N <= cm.inner.d;
+}
+template <int N>
+__device__ __forceinline__ uint64_t raw_first(const ChannelMap& cm, const KeptRun<N>& run)
+{
+    return ((uint64_t)run.p.o * cm.raw_channels + (run.slotw[0] & 0xffffu)) * cm.inner.d + run.p.pos;
 }
 
 // index into the raw store of element j of the run (whose bit in run.mask must be set)

@@ -25,6 +25,7 @@
 #include "fh_channels.hpp"
 #include "fh_stages.hpp"
 #include "fh_device.hpp"
+#include "fh_moments.hpp"
 
 #include <limits.h>
 
@@ -33,96 +34,9 @@
 namespace fh {
 namespace {
 
-constexpr int kSpan = 1024;              // elements (or partial sums) per wave
 constexpr int kThreads = 256;
 constexpr int kWavesPerBlock = kThreads / kWave;
 constexpr int kMaxChannels = 16384;
-
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-
-// ---- lane exchanges of a double ------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v)
-{
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-// ds_swizzle in bit-mask mode: lane l reads lane (l & 0x1f) ^ XOR inside its half
-template <int XOR>
-__device__ __forceinline__ double swizzle_f64(double v)
-{
-    constexpr int pattern = (XOR << 10) | 0x1F;
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_swizzle((int)(uint32_t)u, pattern);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_swizzle((int)(uint32_t)(u >> 32), pattern);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-template <int XOR>
-__device__ __forceinline__ double from_lane_xor(double v)
-{
-    if constexpr (XOR == 1) return dpp_f64<0xB1>(v);        // quad_perm [1,0,3,2]
-    else if constexpr (XOR == 2) return dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
-    else return swizzle_f64<XOR>(v);                          // 4, 8, 16
-}
-// v[l] + v[l ^ 32]: permlane32_swap of two copies returns {lo half, lo half} and
-// {hi half, hi half}; their sum is the same in both halves.
-__device__ __forceinline__ double add_across_halves(double v)
-{
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    uint32_t a0 = (uint32_t)u, a1 = (uint32_t)(u >> 32), b0 = a0, b1 = a1;
-    asm volatile("" : "+v"(b0), "+v"(b1));
-    const u32x2 r0 = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
-    const u32x2 r1 = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-    const uint32_t f0 = r0.x, s0 = r0.y, f1 = r1.x, s1 = r1.y;
-    const double first = __builtin_bit_cast(double, ((uint64_t)f1 << 32) | f0);
-    const double second = __builtin_bit_cast(double, ((uint64_t)s1 << 32) | s0);
-    return first + second;
-}
-
-// ---- the span tree ---------------------------------------------------------------------
-// In: for each of four rows, the lane's own subtree sums a[r] (of x) and b[r] (of x*x); a row is 64 lanes in element
-// order.  The rows are those of one span, or rows 0 and 1 of one and 2 and 3 of the next (SPANS == 2).  Out: in lane
-// 2 * k + 4 * m (k < SPANS; also elsewhere) moment m of span k.
-// Exchange levels, in the tree's order:
-//   xor 1   keep the rows whose low bit equals the lane's bit 0
-//   xor 2   keep the row whose high bit equals the lane's bit 1
-//   xor 4   keep one of the two moments
-//   rest    plain butterflies
-// followed by the levels that join a span's rows.
-template <int SPANS>
-__device__ __forceinline__ double span_tree(const double (&a)[4], const double (&b)[4], uint32_t lane)
-{
-    static_assert(SPANS == 1 || SPANS == 2, "spans in four rows");
-    const bool b0 = lane & 1u, b1 = lane & 2u, b2 = lane & 4u;
-    // xor 1: rows {b0, b0 + 2} of both moments stay
-    double ka[2], kb[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        ka[j] = (b0 ? a[2 * j + 1] : a[2 * j]) + from_lane_xor<1>(b0 ? a[2 * j] : a[2 * j + 1]);
-        kb[j] = (b0 ? b[2 * j + 1] : b[2 * j]) + from_lane_xor<1>(b0 ? b[2 * j] : b[2 * j + 1]);
-    }
-    // xor 2: row 2 * b1 + b0 stays
-    const double ma = (b1 ? ka[1] : ka[0]) + from_lane_xor<2>(b1 ? ka[0] : ka[1]);
-    const double mb = (b1 ? kb[1] : kb[0]) + from_lane_xor<2>(b1 ? kb[0] : kb[1]);
-    // xor 4: moment b2 stays
-    double t = (b2 ? mb : ma) + from_lane_xor<4>(b2 ? ma : mb);      // one (row, moment) total per lane from here on
-    t = t + from_lane_xor<8>(t);
-    t = t + from_lane_xor<16>(t);
-    t = add_across_halves(t);
-    // rows: (0 + 1) and (2 + 3); of one span, their sum too; the row index sits in lane bits 0 and 1
-    t = t + from_lane_xor<1>(t);
-    if constexpr (SPANS == 1) t = t + from_lane_xor<2>(t);
-    return t;
-}
-// The sums of one span as span_tree leaves them, in every lane.
-__device__ __forceinline__ void both_moments(double t, uint32_t lane, double& s1, double& s2)
-{
-    const double other = from_lane_xor<4>(t);                 // lanes with bit 2 clear hold the sum of x, the others that of x*x
-    s1 = (lane & 4u) ? other : t;
-    s2 = (lane & 4u) ? t : other;
-}
 
 // ---- per-kernel descriptors (fh_batch.hpp: up to kBatch tensors per launch) ----------------
 struct MomentsItem { const void* x; int64_t numel; f64x2* partial; uint32_t* ranges; };
@@ -163,32 +77,7 @@ template <> struct Span<uint16_t> {         // 2 rows of 512, 8 consecutive elem
     }
 };
 
-// balanced tree over N consecutive values (N a power of two)
-template <int N>
-__device__ __forceinline__ double local_tree(const double (&v)[N])
-{
-    double w[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) w[i] = v[i];
-#pragma unroll
-    for (int n = N; n > 1; n /= 2)
-#pragma unroll
-        for (int i = 0; i < n / 2; ++i) w[i] = w[2 * i] + w[2 * i + 1];
-    return w[0];
-}
-
 // ---- value ranges ------------------------------------------------------------------------
-// A piece is what eight neighbouring lanes hold of a span: 128 elements, 128 contiguous bytes in each of the span's
-// rows.  Its range is kept as two bf16 numbers, the smallest value rounded down and the largest rounded up, in one
-// word: (largest << 16) | smallest.  8 words per span, 0.8 % (bf16: 1.6 %) of what the pass reads.
-constexpr int kPieces = 8;                       // of a span
-__device__ __forceinline__ uint32_t pack_range(float lowest, float highest)
-{
-    const uint32_t l = __builtin_bit_cast(uint32_t, lowest), h = __builtin_bit_cast(uint32_t, highest);
-    // away from zero: one step up in magnitude unless the low half is empty; towards zero: the low half dropped
-    const uint32_t down = (l >> 31) ? (l + 0xffffu) >> 16 : l >> 16, up = (h >> 31) ? h >> 16 : (h + 0xffffu) >> 16;
-    return (up << 16) | (down & 0xffffu);
-}
 // Can a piece hold an outlier?  x -> (x - mean)^2 in binary64 rises on either side of the mean, rounding included, so
 // its largest values over a range are at the range's ends.  (Ends that compare as NaN -- infinities or NaNs among the
 // statistics -- count as "yes".)
@@ -222,49 +111,20 @@ __global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsIt
     const int64_t base = span * kSpan;
     if (base >= numel) return;                                // wave-uniform
     const InT* xs = x + base;
-    double a[ROWS], b[ROWS];
-    float lowest[SPANS], highest[SPANS];
-#pragma unroll
-    for (int k = 0; k < SPANS; ++k) { lowest[k] = __builtin_inff(); highest[k] = -__builtin_inff(); }
+    float v[ROWS][EPL];
     const bool interior = base + SPANS * kSpan <= numel;
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-        float v[EPL];                                         // (elements past the end count as 0, in the range too)
         const uint32_t e0 = r * ROW + lane * EPL;
         if (interior) {
-            Span<InT>::load(xs + e0, v);
+            Span<InT>::load(xs + e0, v[r]);
         } else {
 #pragma unroll
-            for (int j = 0; j < EPL; ++j) v[j] = (base + e0 + j < numel) ? Span<InT>::one(xs + e0 + j) : 0.0f;
-        }
-        // the squares are exact, so the fused multiply-add rounds the sum of two of them just as an addition would
-        double d[EPL], q[EPL / 2];
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) d[j] = (double)v[j];
-#pragma unroll
-        for (int j = 0; j < EPL; j += 2) q[j / 2] = __builtin_fma(d[j], d[j], d[j + 1] * d[j + 1]);
-        a[r] = local_tree<EPL>(d);
-        b[r] = local_tree<EPL / 2>(q);
-        const int k = r / Span<InT>::ROWS;
-#pragma unroll
-        for (int j = 0; j < EPL; j += 2) {
-            asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lowest[k]) : "v"(v[j]), "v"(v[j + 1]));
-            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(highest[k]) : "v"(v[j]), "v"(v[j + 1]));
+            for (int j = 0; j < EPL; ++j) v[r][j] = (base + e0 + j < numel) ? Span<InT>::one(xs + e0 + j) : 0.0f;
         }
     }
-    const double t = span_tree<SPANS>(a, b, lane);
-    const int64_t here = (numel - base + kSpan - 1) / kSpan;  // spans from this one to the tensor's last
-    const uint32_t k = (lane >> 1) & 1u;
-    if (lane < 8u && (lane & 1u) == 0u && k < (uint32_t)SPANS && (int64_t)k < here)
-        reinterpret_cast<double*>(it.partial + span + k)[lane >> 2] = t;
-    if (it.ranges) {                                          // wave-uniform
-        uint32_t* ranges = it.ranges + span * kPieces;
-#pragma unroll
-        for (int s = 0; s < SPANS; ++s) {
-            row_minmax<8>(lowest[s], highest[s]);
-            if ((lane & 7u) == 0u && (int64_t)s < here) ranges[s * kPieces + (lane >> 3)] = pack_range(lowest[s], highest[s]);
-        }
-    }
+    leave_moments<SPANS, EPL>(v, it.partial + span, it.ranges ? it.ranges + span * kPieces : nullptr,
+                              (numel - base + kSpan - 1) / kSpan, lane);
 }
 
 // ---- pass 1b: spans of partial sums (4 rows of 256 pairs, 4 consecutive pairs per lane) --
@@ -665,7 +525,7 @@ fh_status check_item(const fh_classify_item& it, int64_t* numel_out)
 // One run of up to kBatch tensors of one dtype: five kinds of launches, each covering all of them (four without the
 // masks).  The tensors either all have a place for their ranges or all have none.
 fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, const int64_t* numels, int n, bool masks,
-                       hipStream_t s)
+                       bool first_pass_done, hipStream_t s)
 {
     const bool marked = ranges[0] != nullptr;
     const dim3 block(kThreads);
@@ -679,7 +539,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
     for (int i = 0; i < n; ++i) {
         level[i] = static_cast<f64x2*>(items[i].workspace);
         m[i] = numels[i] > 0 ? ceil_div(numels[i], kSpan) : 0;
-        if (numels[i] > 0 && !push(mb, MomentsItem{items[i].x, numels[i], level[i], ranges[i]}, ceil_div(m[i], per_block)))
+        if (numels[i] > 0 && !first_pass_done && !push(mb, MomentsItem{items[i].x, numels[i], level[i], ranges[i]}, ceil_div(m[i], per_block)))
             return FH_ERR_BAD_NUMEL;
     }
     if (mb.count > 0) {
@@ -764,7 +624,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
 // All tensors (checked): runs of one dtype that have ranges or have none, at most kBatch long.
 // range_of(i, numel): where the ranges of tensor i go, or null.
 template <typename RangeOf>
-fh_status run_all(const fh_classify_item* items, int32_t count, bool masks, hipStream_t s, RangeOf range_of)
+fh_status run_all(const fh_classify_item* items, int32_t count, bool masks, bool first_pass_done, hipStream_t s, RangeOf range_of)
 {
     const auto numel_of = [items](int32_t i) { return items[i].outer * items[i].channels * items[i].inner; };
     int32_t i = 0;
@@ -777,7 +637,7 @@ fh_status run_all(const fh_classify_item* items, int32_t count, bool masks, hipS
             ranges[n] = range_of(i + n, numels[n]);
             if (!ranges[n] != !ranges[0]) break;
         }
-        const fh_status st = run_classify(items + i, ranges, numels, n, masks, s);
+        const fh_status st = run_classify(items + i, ranges, numels, n, masks, first_pass_done, s);
         if (st != FH_OK) return st;
         i += n;
     }
@@ -786,9 +646,10 @@ fh_status run_all(const fh_classify_item* items, int32_t count, bool masks, hipS
 
 }  // namespace
 
-fh_status fh::classify_counts(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, hipStream_t s)
+fh_status fh::classify_counts(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, bool first_pass_done,
+                              hipStream_t s)
 {
-    return run_all(items, count, false, s, [ranges](int32_t i, int64_t) { return ranges[i]; });
+    return run_all(items, count, false, first_pass_done, s, [ranges](int32_t i, int64_t) { return ranges[i]; });
 }
 
 extern "C" {
@@ -806,7 +667,7 @@ fh_status fh_classify_channels_batch(const fh_classify_item* items, int32_t coun
         if (st != FH_OK) return st;
     }
     // the ranges lie behind the partial sums, where there is room for them
-    return run_all(items, count, true, static_cast<hipStream_t>(stream), [items](int32_t i, int64_t numel) -> uint32_t* {
+    return run_all(items, count, true, false, static_cast<hipStream_t>(stream), [items](int32_t i, int64_t numel) -> uint32_t* {
         const size_t pairs = fh_classify_workspace_bytes(numel);
         if (items[i].workspace_cap < pairs + range_bytes(numel)) return nullptr;
         return reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(items[i].workspace) + pairs);

@@ -24,6 +24,7 @@
 #include "fh_channels.hpp"
 #include "fh_device.hpp"
 #include "fh_kernels.hpp"
+#include "fh_moments.hpp"
 
 namespace fh {
 
@@ -294,10 +295,33 @@ template <> struct RawElem<float> {
     __device__ static __forceinline__ void put(void* raw, uint64_t i, float v) {
         static_cast<uint32_t*>(raw)[i] = __builtin_bit_cast(uint32_t, v);
     }
+    // N consecutive elements, 16 bytes at a time where they lie on 16 bytes (maps of a multiple of four elements)
+    template <int N> __device__ static __forceinline__ void put_run(void* raw, uint64_t i, const float (&v)[N]) {
+        if ((i & 3u) == 0u) {
+#pragma unroll
+            for (int j = 0; j < N; j += 4)
+                *reinterpret_cast<f32x4*>(static_cast<float*>(raw) + i + j) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
+        } else {
+#pragma unroll
+            for (int j = 0; j < N; ++j) put(raw, i + j, v[j]);
+        }
+    }
 };
 template <> struct RawElem<uint16_t> {
     __device__ static __forceinline__ void put(void* raw, uint64_t i, float v) {
         static_cast<uint16_t*>(raw)[i] = (uint16_t)(__builtin_bit_cast(uint32_t, v) >> 16);   // the original bits
+    }
+    template <int N> __device__ static __forceinline__ void put_run(void* raw, uint64_t i, const float (&v)[N]) {
+        static_assert(N == 8, "eight bf16 elements are 16 bytes");
+        if ((i & 7u) == 0u) {
+            const auto two = [&](int j) {
+                return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, v[j + 1]), __builtin_bit_cast(uint32_t, v[j]), 0x07060302u);
+            };
+            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(raw) + i) = u32x4{two(0), two(2), two(4), two(6)};
+        } else {
+#pragma unroll
+            for (int j = 0; j < N; ++j) put(raw, i + j, v[j]);
+        }
     }
 };
 
@@ -307,6 +331,12 @@ template <> struct RawElem<uint16_t> {
 template <typename InT, int N>
 __device__ __forceinline__ void divert_kept(const ChannelMap& cm, const KeptRun<N>& run, float (&x)[N])
 {
+    if (kept_whole<N>(cm, run)) {
+        RawElem<InT>::template put_run<N>(cm.raw, raw_first<N>(cm, run), x);
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = __builtin_bit_cast(float, 0x7fc00000u);
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < N; ++j) {
         if (run.mask & (1u << j)) {
@@ -375,12 +405,12 @@ __device__ __forceinline__ void divert_listed(const ChannelMap& cm, const ElemPo
 //   * fp32 (4 elements per lane and row): a Philox block (8 elements) spans a lane pair;
 //     the even lane computes the blocks of rows 0 and 2, the odd lane those of rows 1
 //     and 3, and they trade the halves.  bf16 (8 per lane and row): a block per lane and row.
-template <typename InT, int G, int B, bool STOCH, bool MIXED>
+template <typename InT, int G, int B, bool STOCH, bool MIXED, bool FIRST>
 __device__ __forceinline__ void compress_span(const CompressItem& it, int64_t wave_base, const InT* xw,
                                               uint8_t* pw, float* mw, uint32_t lane,
                                               uint8_t* stage_codes, float* stage_meta,
                                               const ChannelMap* cm, const ElemPos& wave_pos, const uint16_t* rows,
-                                              u32x4 (&w)[4])
+                                              u32x4 (&w)[4], const FirstCompressJob* first)
 {
     using L = Layout<InT>;
     constexpr int ROWS = 4, EPL = L::EPL, ROW = L::ROW;
@@ -407,6 +437,11 @@ __device__ __forceinline__ void compress_span(const CompressItem& it, int64_t wa
             for (int r = 0; r < ROWS; ++r)
                 if (run[r].mask) divert_kept<InT, EPL>(*cm, run[r], x[r]);
         }
+    }
+    if constexpr (FIRST) {
+        constexpr int SPANS = L::SPAN / kSpan;
+        const int64_t span = wave_base / kSpan;
+        leave_moments<SPANS, EPL>(x, reinterpret_cast<f64x2*>(first->partial) + span, first->ranges + span * kPieces, SPANS, lane);
     }
 
     float mn[ROWS], mx[ROWS];
@@ -641,10 +676,12 @@ __device__ __forceinline__ void compress_edge(const CompressItem& it, int64_t wa
 
 // `listed` (MIXED only): LDS for the list of raw-store rows, built here -- by every thread of the workgroup, which
 // all call this with the same arguments -- when the tensor has one channel per element.
-template <typename InT, int G, int B, bool STOCH, bool MIXED = false>
+// `first` (FIRST only): where the classification's first pass goes.
+template <typename InT, int G, int B, bool STOCH, bool MIXED = false, bool FIRST = false>
 __device__ __forceinline__ void compress_tile(const CompressItem& it, uint32_t tile, uint32_t* stage,
                                               const ChannelMap* cm = nullptr, uint16_t* listed = nullptr,
-                                              uint32_t stage_dwords = kStageDwords)
+                                              uint32_t stage_dwords = kStageDwords,
+                                              const FirstCompressJob* first = nullptr)
 {
     using L = Layout<InT>;
     const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -686,8 +723,25 @@ __device__ __forceinline__ void compress_tile(const CompressItem& it, uint32_t t
     if (interior) {
         uint8_t* stage_codes = reinterpret_cast<uint8_t*>(stage + wave * stage_dwords);
         float* stage_meta = reinterpret_cast<float*>(stage_codes + kStageCodeBytes);
-        compress_span<InT, G, B, STOCH, MIXED>(it, wave_base, xw, pw, mw, lane, stage_codes, stage_meta, cm, wave_pos, rows, w);
+        compress_span<InT, G, B, STOCH, MIXED, FIRST>(it, wave_base, xw, pw, mw, lane, stage_codes, stage_meta, cm, wave_pos,
+                                                      rows, w, first);
     } else {
+        if constexpr (FIRST) {
+            if (wave_base < numel) {                          // wave-uniform
+                constexpr int SPANS = L::SPAN / kSpan;
+                const int64_t span = wave_base / kSpan;
+                float x[4][L::EPL];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int j = 0; j < L::EPL; ++j) {
+                        const uint32_t e = r * L::ROW + lane * L::EPL + j;
+                        x[r][j] = wave_base + e < numel ? Loader<InT>::one(xw, e) : 0.0f;
+                    }
+                leave_moments<SPANS, L::EPL>(x, reinterpret_cast<f64x2*>(first->partial) + span, first->ranges + span * kPieces,
+                                             (numel - wave_base + kSpan - 1) / kSpan, lane);
+            }
+        }
         compress_edge<InT, G, B, STOCH, MIXED>(it, wave_base, extent, xw, pw, mw, lane, cm, wave_pos);
     }
 }
@@ -753,7 +807,97 @@ __global__ __launch_bounds__(kCBlock) void compress_mixed_kernel(const Batch<Mix
     }
 }
 
+// The plain quantiser and the classification's first pass over the same elements: one read of the tensor where two
+// kernels would make two.  The reads bound it: the 557 MiB set (fp32, G128, 4-bit nearest) takes 112 us, the quantiser
+// alone 105 and the first pass alone 87; some 400 vector instructions per span hide behind 4 KiB read and 0.7 KiB written.
+template <typename InT, int G>
+__global__ __launch_bounds__(kCBlock) void compress_first_kernel(const Batch<FirstCompressJob> batch)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kStageDwords];
+    uint32_t tile;
+    const FirstCompressJob& job = batch.item[batch_item(batch, blockIdx.x, tile)];
+    const CompressItem& it = job.it;
+    switch (it.bits * 2 + it.stochastic) {
+        case 4:  compress_tile<InT, G, 2, false, false, true>(it, tile, stage, nullptr, nullptr, kStageDwords, &job); break;
+        case 5:  compress_tile<InT, G, 2, true , false, true>(it, tile, stage, nullptr, nullptr, kStageDwords, &job); break;
+        case 8:  compress_tile<InT, G, 4, false, false, true>(it, tile, stage, nullptr, nullptr, kStageDwords, &job); break;
+        case 9:  compress_tile<InT, G, 4, true , false, true>(it, tile, stage, nullptr, nullptr, kStageDwords, &job); break;
+        case 16: compress_tile<InT, G, 8, false, false, true>(it, tile, stage, nullptr, nullptr, kStageDwords, &job); break;
+        case 17: compress_tile<InT, G, 8, true , false, true>(it, tile, stage, nullptr, nullptr, kStageDwords, &job); break;
+        default: break;
+    }
+}
+
+// What compress_first_kernel could not know: the spans with kept elements are quantised again without those, which go
+// to the raw store.  A wave tests kStrip spans, a lane per span, and walks those that hold kept elements; its spans lie
+// far apart, since a kept channel of a feature map makes a dozen neighbours such spans.  (A wave per span, nearly all
+// of which find nothing to do, took 56 us on the 557 MiB set; this takes 24, with 4 or 16 spans per wave 26 and 45.)
+constexpr int kStrip = 8;
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t from) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)from); }
+template <typename InT, int G, int B, bool STOCH>
+__device__ __forceinline__ void compress_kept_spans(const CompressItem& it, const ChannelMap& cm, uint32_t strip, uint32_t strips,
+                                                    uint32_t* stage)
+{
+    using L = Layout<InT>;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t numel = (uint32_t)it.numel, spans = (numel + L::SPAN - 1u) / L::SPAN;      // at most 2^31 elements
+    // the lane-th of every `strips` spans, each time another one: with equal steps, a step that is a multiple of a
+    // sample's spans would give a wave the same channel in every sample
+    const uint32_t skew = (uint32_t)(strips * 0.618f) | 1u;
+    const uint32_t mine = lane * strips + (strip + lane * skew) % strips;          // at most 2^25
+    bool any = false;
+    if (lane < (uint32_t)kStrip && mine < spans) {
+        const uint32_t left = numel - mine * L::SPAN;
+        any = any_kept(cm, mine * L::SPAN, left < (uint32_t)L::SPAN ? left : (uint32_t)L::SPAN);
+    }
+    uint8_t* stage_codes = reinterpret_cast<uint8_t*>(stage);
+    float* stage_meta = reinterpret_cast<float*>(stage_codes + kStageCodeBytes);
+    const int64_t padded_elems = (int64_t)(it.packed_padded * 8u / (unsigned)B);
+    const int64_t extent = it.numel > padded_elems ? it.numel : padded_elems;
+    for (uint64_t todo = __builtin_amdgcn_ballot_w64(any); todo; todo &= todo - 1u) {         // wave-uniform
+        const uint32_t span = lane_value(mine, (uint32_t)__builtin_ctzll(todo));
+        const int64_t wave_base = (int64_t)span * L::SPAN;
+        const InT* xw = static_cast<const InT*>(it.x) + wave_base;
+        uint8_t* pw = it.packed + ((uint64_t)wave_base * B >> 3);
+        float* mw = it.meta + 2 * (wave_base >> Log2<G>::v);
+        const ElemPos wave_pos = locate_base(cm, (uint32_t)wave_base);
+        if (wave_base + L::SPAN <= it.numel) {
+            u32x4 unused[4] = {};
+            compress_span<InT, G, B, STOCH, true, false>(it, wave_base, xw, pw, mw, lane, stage_codes, stage_meta, &cm, wave_pos,
+                                                         nullptr, unused, nullptr);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");         // the staging area is the next span's
+        } else {
+            compress_edge<InT, G, B, STOCH, true>(it, wave_base, extent, xw, pw, mw, lane, &cm, wave_pos);
+        }
+    }
+}
+
+template <typename InT, int G>
+__global__ __launch_bounds__(kCBlock) void compress_kept_kernel(const Batch<MixedCompressJob> batch)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kStageDwords];
+    uint32_t block;
+    const int k = batch_item(batch, blockIdx.x, block);
+    const MixedCompressJob& job = batch.item[k];
+    const CompressItem& it = job.it;
+    if (nothing_kept(job.cm)) return;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t strip = block * kWaves + wave, strips = (batch.block_start[k + 1] - batch.block_start[k]) * kWaves;
+    uint32_t* mine = stage + wave * kStageDwords;
+    switch (it.bits * 2 + it.stochastic) {
+        case 4:  compress_kept_spans<InT, G, 2, false>(it, job.cm, strip, strips, mine); break;
+        case 5:  compress_kept_spans<InT, G, 2, true >(it, job.cm, strip, strips, mine); break;
+        case 8:  compress_kept_spans<InT, G, 4, false>(it, job.cm, strip, strips, mine); break;
+        case 9:  compress_kept_spans<InT, G, 4, true >(it, job.cm, strip, strips, mine); break;
+        case 16: compress_kept_spans<InT, G, 8, false>(it, job.cm, strip, strips, mine); break;
+        case 17: compress_kept_spans<InT, G, 8, true >(it, job.cm, strip, strips, mine); break;
+        default: break;
+    }
+}
+
 }  // namespace
+
+int compress_kept_block_elems(int dtype) { return compress_tile_elems(dtype, 0) * kStrip; }
 
 int compress_tile_elems(int dtype, int) { return dtype == 0 ? Layout<float>::TILE : Layout<uint16_t>::TILE; }
 
@@ -763,6 +907,44 @@ hipError_t launch_compress(const CompressBatch& b, int dtype, int group_size, hi
     if (tiles == 0) return hipSuccess;
     const dim3 grid(tiles), block(kCBlock);
 #define FH_LAUNCH(T, GS) hipLaunchKernelGGL((compress_kernel<T, GS>), grid, block, 0, s, b)
+    if (dtype == 0) {
+        if (group_size == 64) FH_LAUNCH(float, 64);
+        else if (group_size == 128) FH_LAUNCH(float, 128);
+        else FH_LAUNCH(float, 256);
+    } else {
+        if (group_size == 64) FH_LAUNCH(uint16_t, 64);
+        else if (group_size == 128) FH_LAUNCH(uint16_t, 128);
+        else FH_LAUNCH(uint16_t, 256);
+    }
+#undef FH_LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t launch_compress_first(const Batch<FirstCompressJob>& b, int dtype, int group_size, hipStream_t s)
+{
+    const uint32_t tiles = b.block_start[b.count];
+    if (tiles == 0) return hipSuccess;
+    const dim3 grid(tiles), block(kCBlock);
+#define FH_LAUNCH(T, GS) hipLaunchKernelGGL((compress_first_kernel<T, GS>), grid, block, 0, s, b)
+    if (dtype == 0) {
+        if (group_size == 64) FH_LAUNCH(float, 64);
+        else if (group_size == 128) FH_LAUNCH(float, 128);
+        else FH_LAUNCH(float, 256);
+    } else {
+        if (group_size == 64) FH_LAUNCH(uint16_t, 64);
+        else if (group_size == 128) FH_LAUNCH(uint16_t, 128);
+        else FH_LAUNCH(uint16_t, 256);
+    }
+#undef FH_LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t launch_compress_kept(const Batch<MixedCompressJob>& b, int dtype, int group_size, hipStream_t s)
+{
+    const uint32_t tiles = b.block_start[b.count];
+    if (tiles == 0) return hipSuccess;
+    const dim3 grid(tiles), block(kCBlock);
+#define FH_LAUNCH(T, GS) hipLaunchKernelGGL((compress_kept_kernel<T, GS>), grid, block, 0, s, b)
     if (dtype == 0) {
         if (group_size == 64) FH_LAUNCH(float, 64);
         else if (group_size == 128) FH_LAUNCH(float, 128);

@@ -109,6 +109,23 @@ __device__ __forceinline__ void fetch_kept(const ChannelMap& cm, int raw_dtype, 
 template <int N>
 __device__ __forceinline__ void request_kept(const ChannelMap& cm, int raw_dtype, const KeptRun<N>& run, uint32_t (&bits)[N])
 {
+    if (kept_whole<N>(cm, run)) {
+        const uint64_t first = raw_first<N>(cm, run);
+        if (raw_dtype == 0 && (first & 3u) == 0u) {
+#pragma unroll
+            for (int j = 0; j < N; j += 4) {
+                const u32x4 w = *reinterpret_cast<const u32x4*>(static_cast<const uint32_t*>(cm.raw) + first + j);
+                bits[j] = w.x; bits[j + 1] = w.y; bits[j + 2] = w.z; bits[j + 3] = w.w;
+            }
+        } else if (raw_dtype == 0) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) bits[j] = static_cast<const uint32_t*>(cm.raw)[first + j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < N; ++j) bits[j] = (uint32_t) static_cast<const uint16_t*>(cm.raw)[first + j] << 16;
+        }
+        return;
+    }
     if (raw_dtype == 0) {
 #pragma unroll
         for (int j = 0; j < N; ++j)

@@ -89,6 +89,17 @@ struct MixedDecompressJob {
     int32_t        raw_dtype;
     int32_t        pad;
 };
+// The plain quantiser that leaves the classification's first pass behind on its way (fh_moments.hpp): for tensors that
+// are quantised before it is known which of their channels are kept.
+struct FirstCompressJob {
+    CompressItem it;
+    double*      partial;              // {sum x, sum x * x} per 1024 elements
+    uint32_t*    ranges;
+};
+// Tensors that have been: the spans with kept elements again, those elements to the raw store.  inner > 1.
+int compress_kept_block_elems(int dtype);          // elements whose spans one workgroup looks at
+hipError_t launch_compress_kept(const Batch<MixedCompressJob>& b, int dtype, int group_size, hipStream_t s);
+hipError_t launch_compress_first(const Batch<FirstCompressJob>& b, int dtype, int group_size, hipStream_t s);
 hipError_t launch_compress_mixed(const Batch<MixedCompressJob>& b, int dtype, int group_size, hipStream_t s);
 hipError_t launch_decompress_mixed(const Batch<MixedDecompressJob>& b, int out_dtype, int group_size, hipStream_t s);
 

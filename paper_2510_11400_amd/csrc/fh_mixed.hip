@@ -7,6 +7,7 @@
 
 #include "fh_channels.hpp"
 #include "fh_kernels.hpp"
+#include "fh_stages.hpp"
 
 namespace fh {
 namespace {
@@ -201,7 +202,75 @@ fh_status check_decompress(const fh_mixed_item& it, int64_t* numel)
     return FH_OK;
 }
 
+CompressItem quantiser_item(const fh_mixed_item& it, int64_t numel)
+{
+    CompressItem q;
+    q.x = it.x;
+    q.packed = static_cast<uint8_t*>(it.packed);
+    q.meta = static_cast<float*>(it.meta);
+    q.numel = numel;
+    q.packed_padded = fh_packed_bytes(numel, it.params.bits);
+    q.seed = it.params.seed;
+    q.tensor_id = it.params.tensor_id;
+    q.bits = it.params.bits;
+    q.stochastic = it.params.rounding == FH_ROUND_STOCHASTIC ? 1 : 0;
+    return q;
+}
+
+// the tensors (checked) with room in the raw store; `kept_only`: those that compress_first has quantised
+fh_status run_compress(const fh_mixed_item* items, int32_t count, bool kept_only, hipStream_t s)
+{
+    int32_t i = 0;
+    while (i < count) {                                       // runs of one dtype and group size
+        Batch<MixedCompressJob> b;
+        reset(b);
+        const int dtype = items[i].x_dtype, G = items[i].params.group_size;
+        const int tile = kept_only ? compress_kept_block_elems(dtype) : compress_tile_elems(dtype, G);
+        while (i < count && items[i].x_dtype == dtype && items[i].params.group_size == G) {
+            const fh_mixed_item& it = items[i];
+            int64_t numel;
+            check_compress(it, &numel);
+            if (numel == 0 || it.raw_channels == 0) { ++i; continue; }
+            MixedCompressJob job;
+            job.it = quantiser_item(it, numel);
+            job.cm = make_map(it.slots, it.raw, it.channels, it.inner, it.raw_channels, it.rows_in_use);
+            if (!push(b, job, (numel + tile - 1) / tile)) break;      // launch what is there, go on with this item
+            ++i;
+        }
+        if (b.count == 0) continue;
+        seal(b);
+        if ((kept_only ? launch_compress_kept(b, dtype, G, s) : launch_compress_mixed(b, dtype, G, s)) != hipSuccess) return FH_ERR_LAUNCH;
+    }
+    return FH_OK;
+}
+
 }  // namespace
+
+fh_status fh::compress_first(const fh_mixed_item* items, const fh_classify_item* classify, uint32_t* const* ranges, int32_t count,
+                             hipStream_t s)
+{
+    int32_t i = 0;
+    while (i < count) {                                       // runs of one dtype and group size
+        Batch<FirstCompressJob> b;
+        reset(b);
+        const int dtype = items[i].x_dtype, G = items[i].params.group_size;
+        const int tile = compress_tile_elems(dtype, G);
+        while (i < count && items[i].x_dtype == dtype && items[i].params.group_size == G) {
+            const fh_mixed_item& it = items[i];
+            const int64_t numel = it.outer * it.channels * it.inner;
+            if (numel == 0) { ++i; continue; }
+            const FirstCompressJob job = {quantiser_item(it, numel), static_cast<double*>(classify[i].workspace), ranges[i]};
+            if (!push(b, job, (numel + tile - 1) / tile)) break;
+            ++i;
+        }
+        if (b.count == 0) continue;
+        seal(b);
+        if (launch_compress_first(b, dtype, G, s) != hipSuccess) return FH_ERR_LAUNCH;
+    }
+    return FH_OK;
+}
+
+fh_status fh::compress_kept(const fh_mixed_item* items, int32_t count, hipStream_t s) { return run_compress(items, count, true, s); }
 
 extern "C" {
 
@@ -236,37 +305,7 @@ fh_status fh_compress_mixed_batch(const fh_mixed_item* items, int32_t count, voi
             plain_count = 0;
         }
     }
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    int32_t i = 0;
-    while (i < count) {                                       // runs of one dtype and group size
-        Batch<MixedCompressJob> b;
-        reset(b);
-        const int dtype = items[i].x_dtype, G = items[i].params.group_size;
-        const int tile = compress_tile_elems(dtype, G);
-        while (i < count && items[i].x_dtype == dtype && items[i].params.group_size == G) {
-            const fh_mixed_item& it = items[i];
-            int64_t numel;
-            check_compress(it, &numel);
-            if (numel == 0 || it.raw_channels == 0) { ++i; continue; }
-            MixedCompressJob job;
-            job.it.x = it.x;
-            job.it.packed = static_cast<uint8_t*>(it.packed);
-            job.it.meta = static_cast<float*>(it.meta);
-            job.it.numel = numel;
-            job.it.packed_padded = fh_packed_bytes(numel, it.params.bits);
-            job.it.seed = it.params.seed;
-            job.it.tensor_id = it.params.tensor_id;
-            job.it.bits = it.params.bits;
-            job.it.stochastic = it.params.rounding == FH_ROUND_STOCHASTIC ? 1 : 0;
-            job.cm = make_map(it.slots, it.raw, it.channels, it.inner, it.raw_channels, it.rows_in_use);
-            if (!push(b, job, (numel + tile - 1) / tile)) break;      // launch what is there, go on with this item
-            ++i;
-        }
-        if (b.count == 0) continue;
-        seal(b);
-        if (launch_compress_mixed(b, dtype, G, s) != hipSuccess) return FH_ERR_LAUNCH;
-    }
-    return FH_OK;
+    return run_compress(items, count, false, static_cast<hipStream_t>(stream));
 }
 
 fh_status fh_decompress_mixed_batch(const fh_mixed_item* items, int32_t count, void* stream)

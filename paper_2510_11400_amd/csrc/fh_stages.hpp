@@ -16,8 +16,19 @@ namespace fh {
 inline size_t range_bytes(int64_t numel) { return numel > 0 ? (size_t)((numel + 1023) / 1024) * 32u : 0u; }
 
 // fh_classify_channels_batch without the masks (which follow from the counts), and with ranges[i] (16-byte aligned,
-// range_bytes() of item i, or null: the count pass then reads the whole tensor).
-fh_status classify_counts(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, hipStream_t s);
+// range_bytes() of item i, or null: the count pass then reads the whole tensor).  `first_pass_done`: the partial sums
+// and the ranges (all given) are there.
+fh_status classify_counts(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, bool first_pass_done,
+                          hipStream_t s);
+
+// The forward side in two steps, for tensors of which few elements are kept: compress_first quantises the tensors as if
+// nothing were kept and makes the classification's first pass on the way (partial sums at classify[i].workspace, ranges
+// at ranges[i]); compress_kept, once the slots are known, does fh_compress_mixed_batch's work for the spans of the
+// tensors that hold kept elements.  Together they leave what fh_compress_mixed_batch leaves.
+fh_status compress_first(const fh_mixed_item* items, const fh_classify_item* classify, uint32_t* const* ranges, int32_t count,
+                         hipStream_t s);
+fh_status compress_kept(const fh_mixed_item* items, int32_t count, hipStream_t s);
+constexpr int64_t kFirstSpan = 2048;               // elements of such a span at most
 
 // fh_huffman_encode_batch for histograms (the first 256 words of the items' workspaces) that have been cleared, and
 // with the bytes that the stored form of the tensor occupies written to header[6] on the way:

@@ -104,6 +104,39 @@ def _input(case, seed):
     return x
 
 
+#               outer C   inner (h, w)    raw G    B  rounding      dtype  min_out
+QUANTISED_FIRST = [
+    (3, 24, 2345, (35, 67), 1, 128, 4, "nearest",    "f32",  30),       # spans that straddle channels, a ragged end
+    (3, 24, 2345, (35, 67), 1, 64,  2, "stochastic", "bf16", 30),
+    (1, 33, 4096, (64, 64), 1, 256, 8, "stochastic", "f32",  30),       # channels that end where spans do
+    (2, 40, 2052, (54, 38), 1, 256, 4, "stochastic", "bf16", 20),
+    (5, 24, 3136, (56, 56), 1, 64,  8, "nearest",    "f32",  10**6),    # nothing salient
+    (4, 64, 3136, (56, 56), 4, 128, 4, "nearest",    "bf16", 1),        # every row in use, more channels salient than rows
+    (2, 20, 6001, (6001, 1), 1, 64, 2, "nearest",    "f32",  60),
+]
+
+
+@pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
+def test_tensors_quantised_before_their_kept_channels_are_known(api, out_dtype):
+    """Feature maps of which few spans can hold kept elements are quantised while the classification's first pass
+    reads them, and those spans again once the channels are known: the stored form is the oracle chain's, tensor by
+    tensor and as one batch of both dtypes and all group sizes."""
+    picked = [c[:8] + (4, 0.5, 0.02, 1) + c[8:] for c in QUANTISED_FIRST]
+    for outer, C, inner, _, raw in (c[:5] for c in picked):
+        assert inner > 1 and 4 * outer * raw * (inner + 4096) <= outer * C * inner      # the rule of the call
+    xs = [_input(case, 900 + i) for i, case in enumerate(picked)]
+    for one_by_one in (True, False):
+        groups = [[i] for i in range(len(picked))] if one_by_one else [list(range(len(picked)))]
+        for group in groups:
+            batch = api.MixBatch([_entry(api, _device(xs[i], picked[i][12]), picked[i], out_dtype) for i in group])
+            print(f"[chain] quantised first: {group}", flush=True)
+            api.fh_mix_compress_batch(batch)
+            api.fh_mix_decompress_batch(batch)
+            torch.cuda.synchronize()
+            for k, i in enumerate(group):
+                _compare(api, batch, k, xs[i], picked[i], out_dtype)
+
+
 @pytest.mark.parametrize("count", [24, 25, 50])
 def test_batches_at_the_number_of_tensors_that_a_launch_holds(api, count):
     """A launch of each stage holds 24 tensors: a batch of just that many, one more, and more than two launches."""
