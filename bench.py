@@ -148,7 +148,7 @@ def bench_classify(args, api, W, dev) -> dict:
         x, _ = W.outlier_channel_tensor(outer, C, inner, seed=i, dist="relu")
         host.append(x)
         xd = torch.from_numpy(x).to(dev)
-        ws = torch.empty(api.classify_workspace_bytes(x.size), dtype=torch.uint8, device=dev)
+        ws = torch.empty(api.classify_workspace_bytes_ranges(x.size), dtype=torch.uint8, device=dev)
         stats = torch.empty(4, dtype=torch.float64, device=dev)
         counts = torch.empty(C, dtype=torch.int32, device=dev)
         mask = torch.empty(C, dtype=torch.uint8, device=dev)
