@@ -51,10 +51,6 @@ struct MaskItem    { const uint32_t* counts; uint8_t* mask; int64_t min_outliers
 template <typename InT> struct Span;
 template <> struct Span<float> {            // 4 rows of 256, 4 consecutive elements per lane
     static constexpr int ROWS = 4, EPL = 4;
-    __device__ static __forceinline__ void load(const float* p, float (&x)[EPL]) {
-        const f32x4 v = stream_load(reinterpret_cast<const f32x4*>(p));
-        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    }
     __device__ static __forceinline__ void widen(const u32x4& w, float (&x)[EPL]) {
         const f32x4 v = __builtin_bit_cast(f32x4, w);
         x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
@@ -63,11 +59,6 @@ template <> struct Span<float> {            // 4 rows of 256, 4 consecutive elem
 };
 template <> struct Span<uint16_t> {         // 2 rows of 512, 8 consecutive elements per lane
     static constexpr int ROWS = 2, EPL = 8;
-    __device__ static __forceinline__ void load(const uint16_t* p, float (&x)[EPL]) {
-        const u32x4 v = stream_load(reinterpret_cast<const u32x4*>(p));
-        x[0] = bf16_lo(v.x); x[1] = bf16_hi(v.x); x[2] = bf16_lo(v.y); x[3] = bf16_hi(v.y);
-        x[4] = bf16_lo(v.z); x[5] = bf16_hi(v.z); x[6] = bf16_lo(v.w); x[7] = bf16_hi(v.w);
-    }
     __device__ static __forceinline__ void widen(const u32x4& v, float (&x)[EPL]) {
         x[0] = bf16_lo(v.x); x[1] = bf16_hi(v.x); x[2] = bf16_lo(v.y); x[3] = bf16_hi(v.y);
         x[4] = bf16_lo(v.z); x[5] = bf16_hi(v.z); x[6] = bf16_lo(v.w); x[7] = bf16_hi(v.w);
@@ -87,22 +78,25 @@ __device__ __forceinline__ bool may_hold_outliers(uint32_t range, double mean, d
     return !(low * low <= threshold && high * high <= threshold);
 }
 
-// A wave reads 4 KiB: one span of fp32, two of bf16.  The reads are the time (6.7 TB/s of 7.1 that nothing but reads
-// reaches); the few bytes written beside them cost as much as their lines travel: with a launch's workgroups dealt to
-// the XCDs one by one, as the hardware does, lines of partial sums and ranges are written from two L2s, and the pass
-// over the 557 MiB set takes 95 us; with each XCD on a contiguous eighth of the launch's tiles, 87 us.
+// The reads are the time.  Two forms: up to kLargeLaunch bytes a wave takes one span and the tiles go to the workgroups
+// in order.  A LARGE launch gives a wave 4 KiB (one span of fp32, two of bf16) and each XCD a contiguous eighth of the
+// tiles: dealt out one by one, as the hardware does, the lines of partial sums and ranges are written from two L2s, and
+// when the tensors come from HBM those few bytes cost as much as their lines travel.  First pass of a launch, one span in
+// order against LARGE, us:  bf16 8 MB 4.0 / 4.9, 50 MB 11.1 / 11.3, 100 MB 20.4 / 20.0, 180 MB 35.1 / 31.8,
+// 750 MB 137 / 121; fp32 40 MB 9.5 / 10.1, 134 MB 22.5 / 22.6, 557 MB 91 / 87.
 constexpr int kXcds = 8;
+constexpr int64_t kLargeLaunch = (int64_t)96 << 20;
 __device__ __forceinline__ uint32_t tile_of_block()
 {
     const uint32_t each = gridDim.x / kXcds;                  // the last gridDim.x mod 8 stay where they are
     return blockIdx.x < each * kXcds ? (blockIdx.x % kXcds) * each + blockIdx.x / kXcds : blockIdx.x;
 }
-template <typename InT>
+template <typename InT, bool LARGE>
 __global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsItem> args)
 {
-    constexpr int ROWS = 4, EPL = Span<InT>::EPL, ROW = kWave * EPL, SPANS = ROWS / Span<InT>::ROWS;
+    constexpr int SPANS = LARGE ? 4 / Span<InT>::ROWS : 1, ROWS = SPANS * Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
     uint32_t block;
-    const MomentsItem& it = args.item[batch_item(args, tile_of_block(), block)];
+    const MomentsItem& it = args.item[batch_item(args, LARGE ? tile_of_block() : blockIdx.x, block)];
     const InT* x = static_cast<const InT*>(it.x);
     const int64_t numel = it.numel;
     const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -110,21 +104,23 @@ __global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsIt
     const int64_t span = ((int64_t)block * kWavesPerBlock + wave) * SPANS;
     const int64_t base = span * kSpan;
     if (base >= numel) return;                                // wave-uniform
-    const InT* xs = x + base;
+    const InT* xs = x + base + lane * EPL;
     float v[ROWS][EPL];
-    const bool interior = base + SPANS * kSpan <= numel;
+    if (base + SPANS * kSpan <= numel) {                      // one branch around all rows: none waits for another
+        u32x4 w[ROWS];
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        const uint32_t e0 = r * ROW + lane * EPL;
-        if (interior) {
-            Span<InT>::load(xs + e0, v[r]);
-        } else {
+        for (int r = 0; r < ROWS; ++r) w[r] = stream_load(reinterpret_cast<const u32x4*>(xs + r * ROW));
 #pragma unroll
-            for (int j = 0; j < EPL; ++j) v[r][j] = (base + e0 + j < numel) ? Span<InT>::one(xs + e0 + j) : 0.0f;
-        }
+        for (int r = 0; r < ROWS; ++r) Span<InT>::widen(w[r], v[r]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int j = 0; j < EPL; ++j)
+                v[r][j] = base + r * ROW + lane * EPL + j < numel ? Span<InT>::one(xs + r * ROW + j) : 0.0f;
     }
-    leave_moments<SPANS, EPL>(v, it.partial + span, it.ranges ? it.ranges + span * kPieces : nullptr,
-                              (numel - base + kSpan - 1) / kSpan, lane);
+    leave_moments<SPANS>(v, it.partial + span, it.ranges ? it.ranges + span * kPieces : nullptr,
+                         (numel - base + kSpan - 1) / kSpan, lane);
 }
 
 // ---- pass 1b: spans of partial sums (4 rows of 256 pairs, 4 consecutive pairs per lane) --
@@ -530,9 +526,12 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
     const bool marked = ranges[0] != nullptr;
     const dim3 block(kThreads);
     const int dtype = items[0].x_dtype;
+    int64_t elements = 0;
+    for (int i = 0; i < n; ++i) elements += numels[i];
+    const bool large = elements * (dtype == FH_F32 ? 4 : 2) > kLargeLaunch;
     f64x2* level[kBatch];
     int64_t m[kBatch];
-    const int64_t per_block = kWavesPerBlock * (dtype == FH_F32 ? 1 : 2);    // spans of a workgroup of the first pass
+    const int64_t per_block = kWavesPerBlock * (dtype == FH_F32 || !large ? 1 : 2);      // spans of a workgroup of the first pass
 
     Batch<MomentsItem> mb;
     reset(mb);
@@ -545,8 +544,13 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
     if (mb.count > 0) {
         seal(mb);
         const dim3 grid(mb.block_start[mb.count]);
-        if (dtype == FH_F32) hipLaunchKernelGGL(moments_kernel<float>, grid, block, 0, s, mb);
-        else hipLaunchKernelGGL(moments_kernel<uint16_t>, grid, block, 0, s, mb);
+        if (dtype == FH_F32) {
+            if (large) hipLaunchKernelGGL((moments_kernel<float, true>), grid, block, 0, s, mb);
+            else hipLaunchKernelGGL((moments_kernel<float, false>), grid, block, 0, s, mb);
+        } else {
+            if (large) hipLaunchKernelGGL((moments_kernel<uint16_t, true>), grid, block, 0, s, mb);
+            else hipLaunchKernelGGL((moments_kernel<uint16_t, false>), grid, block, 0, s, mb);
+        }
     }
     for (;;) {                                                // tree levels above the first, where needed
         Batch<ReduceItem> rb;

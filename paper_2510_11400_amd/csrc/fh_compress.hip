@@ -441,7 +441,7 @@ __device__ __forceinline__ void compress_span(const CompressItem& it, int64_t wa
     if constexpr (FIRST) {
         constexpr int SPANS = L::SPAN / kSpan;
         const int64_t span = wave_base / kSpan;
-        leave_moments<SPANS, EPL>(x, reinterpret_cast<f64x2*>(first->partial) + span, first->ranges + span * kPieces, SPANS, lane);
+        leave_moments<SPANS>(x, reinterpret_cast<f64x2*>(first->partial) + span, first->ranges + span * kPieces, SPANS, lane);
     }
 
     float mn[ROWS], mx[ROWS];
@@ -738,7 +738,7 @@ __device__ __forceinline__ void compress_tile(const CompressItem& it, uint32_t t
                         const uint32_t e = r * L::ROW + lane * L::EPL + j;
                         x[r][j] = wave_base + e < numel ? Loader<InT>::one(xw, e) : 0.0f;
                     }
-                leave_moments<SPANS, L::EPL>(x, reinterpret_cast<f64x2*>(first->partial) + span, first->ranges + span * kPieces,
+                leave_moments<SPANS>(x, reinterpret_cast<f64x2*>(first->partial) + span, first->ranges + span * kPieces,
                                              (numel - wave_base + kSpan - 1) / kSpan, lane);
             }
         }

@@ -56,41 +56,46 @@ __device__ __forceinline__ double add_across_halves(double v)
 }
 
 // ---- the span tree ---------------------------------------------------------------------
-// In: for each of four rows, the lane's own subtree sums a[r] (of x) and b[r] (of x*x); a row is 64 lanes in element
-// order.  The rows are those of one span, or rows 0 and 1 of one and 2 and 3 of the next (SPANS == 2).  Out: in lane
-// 2 * k + 4 * m (k < SPANS; also elsewhere) moment m of span k.
+// In: for each of ROWS rows, the lane's own subtree sums a[r] (of x) and b[r] (of x*x); a row is 64 lanes in element
+// order.  Four rows are those of one span, or rows 0 and 1 of one and 2 and 3 of the next (SPANS == 2); two rows are one
+// span's.  Out: moment m of span k in lane 2 * k + 4 * m of four rows, in lane 2 * m of two (also elsewhere).
 // Exchange levels, in the tree's order:
 //   xor 1   keep the rows whose low bit equals the lane's bit 0
-//   xor 2   keep the row whose high bit equals the lane's bit 1
-//   xor 4   keep one of the two moments
+//   next    four rows: keep the row whose high bit equals the lane's bit 1
+//   next    keep one of the two moments
 //   rest    plain butterflies
 // followed by the levels that join a span's rows.
-template <int SPANS>
-__device__ __forceinline__ double span_tree(const double (&a)[4], const double (&b)[4], uint32_t lane)
+template <int SPANS, int ROWS>
+__device__ __forceinline__ double span_tree(const double (&a)[ROWS], const double (&b)[ROWS], uint32_t lane)
 {
-    static_assert(SPANS == 1 || SPANS == 2, "spans in four rows");
+    static_assert((ROWS == 4 && (SPANS == 1 || SPANS == 2)) || (ROWS == 2 && SPANS == 1), "one span or two in four rows, one in two");
     const bool b0 = lane & 1u, b1 = lane & 2u, b2 = lane & 4u;
     // xor 1: rows {b0, b0 + 2} of both moments stay
-    double ka[2], kb[2];
+    double ka[ROWS / 2], kb[ROWS / 2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < ROWS / 2; ++j) {
         ka[j] = (b0 ? a[2 * j + 1] : a[2 * j]) + from_lane_xor<1>(b0 ? a[2 * j] : a[2 * j + 1]);
         kb[j] = (b0 ? b[2 * j + 1] : b[2 * j]) + from_lane_xor<1>(b0 ? b[2 * j] : b[2 * j + 1]);
     }
-    // xor 2: row 2 * b1 + b0 stays
-    const double ma = (b1 ? ka[1] : ka[0]) + from_lane_xor<2>(b1 ? ka[0] : ka[1]);
-    const double mb = (b1 ? kb[1] : kb[0]) + from_lane_xor<2>(b1 ? kb[0] : kb[1]);
-    // xor 4: moment b2 stays
-    double t = (b2 ? mb : ma) + from_lane_xor<4>(b2 ? ma : mb);      // one (row, moment) total per lane from here on
+    double t;                                                 // one (row, moment) total per lane
+    if constexpr (ROWS == 4) {
+        // xor 2: row 2 * b1 + b0 stays
+        const double ma = (b1 ? ka[1] : ka[0]) + from_lane_xor<2>(b1 ? ka[0] : ka[1]);
+        const double mb = (b1 ? kb[1] : kb[0]) + from_lane_xor<2>(b1 ? kb[0] : kb[1]);
+        t = (b2 ? mb : ma) + from_lane_xor<4>(b2 ? ma : mb);  // xor 4: moment b2 stays
+    } else {
+        t = (b1 ? kb[0] : ka[0]) + from_lane_xor<2>(b1 ? ka[0] : kb[0]);      // xor 2: moment b1 stays
+        t = t + from_lane_xor<4>(t);
+    }
     t = t + from_lane_xor<8>(t);
     t = t + from_lane_xor<16>(t);
     t = add_across_halves(t);
-    // rows: (0 + 1) and (2 + 3); of one span, their sum too; the row index sits in lane bits 0 and 1
+    // rows: (0 + 1) and (2 + 3); of one span in four, their sum too; the row index sits in the lowest lane bits
     t = t + from_lane_xor<1>(t);
-    if constexpr (SPANS == 1) t = t + from_lane_xor<2>(t);
+    if constexpr (ROWS == 4 && SPANS == 1) t = t + from_lane_xor<2>(t);
     return t;
 }
-// The sums of one span as span_tree leaves them, in every lane.
+// The sums of one span of four rows as span_tree leaves them, in every lane.
 __device__ __forceinline__ void both_moments(double t, uint32_t lane, double& s1, double& s2)
 {
     const double other = from_lane_xor<4>(t);                 // lanes with bit 2 clear hold the sum of x, the others that of x*x
@@ -127,16 +132,13 @@ __device__ __forceinline__ uint32_t pack_range(float lowest, float highest)
 // The wave's elements v (row r, 64 lanes with EPL consecutive elements each; what lies past the tensor's end is 0, in
 // the range too) are SPANS spans: their sums to partial[0 .. SPANS) and, unless null, their ranges to ranges[], of
 // which `here` (or more) exist.  All 64 lanes.
-template <int SPANS, int EPL>
-__device__ __forceinline__ void leave_moments(const float (&v)[4][EPL], f64x2* partial, uint32_t* ranges, int64_t here,
+template <int SPANS, int ROWS, int EPL>
+__device__ __forceinline__ void leave_moments(const float (&v)[ROWS][EPL], f64x2* partial, uint32_t* ranges, int64_t here,
                                               uint32_t lane)
 {
-    double a[4], b[4];
-    float lowest[SPANS], highest[SPANS];
+    double a[ROWS], b[ROWS];
 #pragma unroll
-    for (int k = 0; k < SPANS; ++k) { lowest[k] = __builtin_inff(); highest[k] = -__builtin_inff(); }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         // the squares are exact, so the fused multiply-add rounds the sum of two of them just as an addition would
         double d[EPL], q[EPL / 2];
 #pragma unroll
@@ -145,22 +147,24 @@ __device__ __forceinline__ void leave_moments(const float (&v)[4][EPL], f64x2* p
         for (int j = 0; j < EPL; j += 2) q[j / 2] = __builtin_fma(d[j], d[j], d[j + 1] * d[j + 1]);
         a[r] = local_tree<EPL>(d);
         b[r] = local_tree<EPL / 2>(q);
-        const int k = r * SPANS / 4;
-#pragma unroll
-        for (int j = 0; j < EPL; j += 2) {
-            asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lowest[k]) : "v"(v[r][j]), "v"(v[r][j + 1]));
-            asm("v_max3_f32 %0, %1, %2, %0" : "+v"(highest[k]) : "v"(v[r][j]), "v"(v[r][j + 1]));
-        }
     }
     const double t = span_tree<SPANS>(a, b, lane);
-    const uint32_t k = (lane >> 1) & 1u;
-    if (lane < 8u && (lane & 1u) == 0u && k < (uint32_t)SPANS && (int64_t)k < here)
-        reinterpret_cast<double*>(partial + k)[lane >> 2] = t;
+    const uint32_t k = ROWS == 4 ? (lane >> 1) & 1u : 0u, moment = lane / ROWS;
+    if (moment < 2u && (lane & 1u) == 0u && k < (uint32_t)SPANS && (int64_t)k < here)
+        reinterpret_cast<double*>(partial + k)[moment] = t;
     if (ranges) {                                             // wave-uniform
 #pragma unroll
         for (int s = 0; s < SPANS; ++s) {
-            row_minmax<8>(lowest[s], highest[s]);
-            if ((lane & 7u) == 0u && (int64_t)s < here) ranges[s * kPieces + (lane >> 3)] = pack_range(lowest[s], highest[s]);
+            float lowest = __builtin_inff(), highest = -__builtin_inff();
+#pragma unroll
+            for (int r = s * ROWS / SPANS; r < (s + 1) * ROWS / SPANS; ++r)
+#pragma unroll
+                for (int j = 0; j < EPL; j += 2) {
+                    asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lowest) : "v"(v[r][j]), "v"(v[r][j + 1]));
+                    asm("v_max3_f32 %0, %1, %2, %0" : "+v"(highest) : "v"(v[r][j]), "v"(v[r][j + 1]));
+                }
+            row_minmax<8>(lowest, highest);
+            if ((lane & 7u) == 0u && (int64_t)s < here) ranges[s * kPieces + (lane >> 3)] = pack_range(lowest, highest);
         }
     }
 }

@@ -1,0 +1,66 @@
+"""What the compiler made of the kernels, read from the code objects inside the built library: properties that cost
+time and not correctness when they are lost, and that no result shows."""
+from __future__ import annotations
+
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2510_11400_amd", "libfedhybrid.so")
+LLVM = "/opt/rocm/lib/llvm/bin"
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    """Paths of the device code objects of the library: one bundle per source file."""
+    if not os.path.exists(os.path.join(LLVM, "llvm-objdump")):
+        pytest.skip("no llvm-objdump")
+    out = tmp_path_factory.mktemp("code")
+    data = open(LIB, "rb").read()
+    magic, paths = b"__CLANG_OFFLOAD_BUNDLE__", []
+    for m in re.finditer(magic, data):
+        at = m.start() + len(magic)
+        (entries,) = struct.unpack_from("<Q", data, at)
+        at += 8
+        for _ in range(entries):
+            offset, size, length = struct.unpack_from("<QQQ", data, at)
+            name = data[at + 24:at + 24 + length]
+            at += 24 + length
+            if b"gfx950" in name and size:
+                paths.append(str(out / f"{len(paths)}.o"))
+                with open(paths[-1], "wb") as f:
+                    f.write(data[m.start() + offset:m.start() + offset + size])
+    assert len(paths) >= 6, "the library's code objects were not found"
+    return paths
+
+
+def _disassembly(paths, function):
+    """{demangled name: [instructions]} of the functions whose name contains `function`."""
+    found = {}
+    for p in paths:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--demangle", "--no-show-raw-insn", p], check=True,
+                              capture_output=True, text=True).stdout
+        name = None
+        for line in text.splitlines():
+            head = re.match(r"[0-9a-f]+ <(.*)>:$", line)
+            if head:
+                name = head.group(1) if function in head.group(1) else None
+            elif name and line.strip():
+                found.setdefault(name, []).append(line.split("//")[0].strip())
+    return found
+
+
+def test_the_rows_of_a_wave_are_requested_together(code_objects):
+    """The classification's first pass: a wave's whole rows are read by non-temporal 16-byte loads with no wait for
+    one of them before the last is on its way (a test around each row's load makes the compiler wait for the first)."""
+    kernels = _disassembly(code_objects, "moments_kernel<")
+    assert len(kernels) >= 2
+    for name, code in kernels.items():
+        rows = [i for i, op in enumerate(code) if op.startswith("global_load_dwordx4") and op.endswith(" nt")]
+        assert len(rows) in (2, 4), f"{name}: {len(rows)} row loads"
+        waits = [op for op in code[rows[0]:rows[-1]] if op.startswith("s_waitcnt") and "vmcnt" in op]
+        assert not waits, f"{name}: {waits} between the row loads"

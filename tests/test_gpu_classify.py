@@ -131,6 +131,19 @@ def test_pieces_without_outliers_are_skipped_and_no_others(api, n, dtype):
 
 
 @pytest.mark.timeout(600)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_first_pass_on_both_sides_of_a_large_launch(api, dtype):
+    """Beyond 96 MiB the first pass gives a wave 4 KiB and each XCD a contiguous part of the tiles: the last size of
+    the one form, the first of the other, and ends inside a wave's first and second span."""
+    edge = (96 << 20) // (4 if dtype == "f32" else 2)
+    x = np.random.default_rng(edge).standard_normal(edge + 8192 + 1500, dtype=f32)
+    if dtype == "bf16":
+        x = (x.view(np.uint32) >> 16).astype(np.uint16)
+    for n in (edge, edge + 1, edge + 1024, edge + 1025, edge + 8192 + 1500):
+        _check(api, x[:n], 1, 1, n, 3.0, 1, dtype=dtype, name="large launch")
+
+
+@pytest.mark.timeout(600)
 def test_paper_sized_activation_set(api):
     # the five per-sample shapes of the paper's local-engine ablation, at batch 64
     for i, (C, h, w) in enumerate(W.ABLATION_SHAPES):
