@@ -26,6 +26,7 @@
 #include "fh_stages.hpp"
 #include "fh_device.hpp"
 #include "fh_moments.hpp"
+#include "fh_rules.hpp"
 
 #include <limits.h>
 
@@ -334,16 +335,19 @@ __global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Batch<Co
 
 // The same where the first pass left ranges behind.  A wave looks at the ranges of eight spans at once, a lane per
 // piece, lists the pieces that may hold an outlier, and reads those: eight lanes to a piece, a lane's elements the
-// ones it would have in a span walked whole.  Four rounds of eight pieces are requested together.  What bounds the
+// ones it would have in a span walked whole.  Two rounds of eight pieces are requested together: with four the kernel
+// takes 112 vector registers in fp32 and four waves fit a SIMD, with two 82 (64 in bf16).  What bounds the
 // pass is what the data leave to read: nothing but the salient channels' share on feature maps with outliers
 // clustered in channels (557 MiB set: 15 us, the kernel above 95), a quarter to a third of the lines of
-// [tokens][hidden] tensors (Gaussian tails alone put an outlier in 3 of 10 pieces; 480 MiB of bf16: 44 us against 96).
-// With an outlier in every piece it reads the tensor whole, as the kernel above does.
+// [tokens][hidden] tensors (Gaussian tails alone put an outlier in 3 of 10 pieces; 720 MiB of bf16: 114 us against 160,
+// with clustered outliers 53 against 154).  With an outlier in most pieces it reads nearly all of the tensor, in as many
+// waves as the rules of fh_rules.hpp give the launch: 23 us for 100 MB of fp32 with 3072 channels, the kernel above 25.
 constexpr int kLook = 8;                          // spans whose ranges a wave looks at together: 64 pieces
-constexpr int kRounds = 4;                        // rounds of eight pieces requested together
-template <typename InT>
-__global__ __launch_bounds__(kThreads) void count_marked_kernel(const Batch<CountArgs> batch)
+constexpr int kRounds = 2;                        // rounds of eight pieces requested together
+template <typename InT, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Batch<CountArgs> batch)
 {
+    constexpr int kThreads = WAVES * kWave;
     constexpr int ROWS = Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
     extern __shared__ uint32_t hist[];
     uint32_t block;
@@ -353,7 +357,7 @@ __global__ __launch_bounds__(kThreads) void count_marked_kernel(const Batch<Coun
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const InT* x = static_cast<const InT*>(args.x);
     const int64_t numel = args.numel, all_spans = (numel + kSpan - 1) / kSpan;
-    const int64_t first = ((int64_t)block * kWavesPerBlock + wave) * args.spans_per_wave;
+    const int64_t first = ((int64_t)block * WAVES + wave) * args.spans_per_wave;
     const int64_t stop = first + args.spans_per_wave < all_spans ? first + args.spans_per_wave : all_spans;
     const auto range_of = [&](int64_t span) { return span + (lane >> 3) < stop ? args.ranges[span * kPieces + lane] : 0u; };
     uint32_t range = range_of(first);                         // in flight while the counters are cleared
@@ -526,8 +530,11 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
     const bool marked = ranges[0] != nullptr;
     const dim3 block(kThreads);
     const int dtype = items[0].x_dtype;
-    int64_t elements = 0;
-    for (int i = 0; i < n; ++i) elements += numels[i];
+    int64_t elements = 0, spans = 0;                          // of the launch
+    for (int i = 0; i < n; ++i) {
+        elements += numels[i];
+        spans += ceil_div(numels[i], kSpan);
+    }
     const bool large = elements * (dtype == FH_F32 ? 4 : 2) > kLargeLaunch;
     f64x2* level[kBatch];
     int64_t m[kBatch];
@@ -579,7 +586,11 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
     Batch<MaskItem> kb;
     reset(cb);
     reset(kb);
-    size_t lds = 0;
+    int64_t widest = 0;
+    for (int i = 0; i < n; ++i)
+        if (numels[i] > 0 && items[i].channels > widest) widest = items[i].channels;
+    const size_t lds = (size_t)widest * sizeof(uint32_t);
+    const int waves = marked ? marked_waves_per_workgroup(widest) : kWavesPerBlock;
     for (int i = 0; i < n; ++i) {
         if (numels[i] == 0) continue;                         // no outliers: the cleared mask stands
         CountArgs a;
@@ -594,15 +605,13 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
         // that cheap, but no more (short workgroups measured faster on feature maps; 128 elements per bin and
         // wave on [tokens][hidden] tensors, where the outliers of ordinary activations touch most bins)
         const int64_t ch = items[i].channels;
-        // With ranges a wave looks at eight spans together, whatever the shape, and has little to count in them; the
-        // wide tensors get twice that.
-        a.spans_per_wave = marked ? (ch <= 1024 ? kLook : 2 * kLook) : (int32_t)(ch <= 512 ? 1 : ch / 128 < 16 ? ch / 128 : 16);
+        a.spans_per_wave = marked ? marked_spans_per_wave(spans, ceil_div(numels[i], kSpan), ch, widest)
+                                  : (int32_t)(ch <= 512 ? 1 : ch / 128 < 16 ? ch / 128 : 16);
         a.ranges = ranges[i];
-        const int64_t per_block = (int64_t)a.spans_per_wave * kWavesPerBlock * kSpan;
+        const int64_t per_block = (int64_t)a.spans_per_wave * waves * kSpan;
         if (!push(cb, a, ceil_div(numels[i], per_block))) return FH_ERR_BAD_NUMEL;
         push(kb, MaskItem{a.counts, static_cast<uint8_t*>(items[i].mask), items[i].min_outliers, (int32_t)ch},
              ceil_div(ch, kThreads));
-        if ((size_t)ch * sizeof(uint32_t) > lds) lds = (size_t)ch * sizeof(uint32_t);
     }
     if (cb.count > 0) {
         seal(cb);
@@ -611,8 +620,14 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
         bool ahead = false;
         for (int k = 0; k < cb.count; ++k) ahead = ahead || cb.item[k].spans_per_wave > 1;
         if (marked) {
-            if (dtype == FH_F32) hipLaunchKernelGGL(count_marked_kernel<float>, grid, block, lds, s, cb);
-            else hipLaunchKernelGGL(count_marked_kernel<uint16_t>, grid, block, lds, s, cb);
+            const dim3 threads(waves * kWave);
+            if (dtype == FH_F32) {
+                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<float, 4>), grid, threads, lds, s, cb);
+                else hipLaunchKernelGGL((count_marked_kernel<float, 8>), grid, threads, lds, s, cb);
+            } else {
+                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<uint16_t, 4>), grid, threads, lds, s, cb);
+                else hipLaunchKernelGGL((count_marked_kernel<uint16_t, 8>), grid, threads, lds, s, cb);
+            }
         } else if (dtype == FH_F32) {
             if (ahead) hipLaunchKernelGGL((count_outliers_kernel<float, true>), grid, block, lds, s, cb);
             else hipLaunchKernelGGL((count_outliers_kernel<float, false>), grid, block, lds, s, cb);

@@ -1,0 +1,30 @@
+// Rules by which the host chooses the shape of a launch, apart from the launches so that they can be looked at on any
+// machine: plain C++, no HIP.
+#pragma once
+
+#include <stdint.h>
+
+namespace fh {
+
+// The classification's count pass where it has value ranges.
+// A workgroup sends a histogram of `channels` counters to the tensor's own, and on wide tensors those atomics are what
+// the pass takes, so a launch with such a tensor has workgroups of eight waves that share one.  With four, 100 MB of
+// 3072 channels take 26.4 us (fp32) and 33.6 us (bf16), with eight 23.0 and 28.6, 768 channels 28.7 and 42.1, then 22.9
+// and 28.3; narrow tensors are better off with four (16 MB to 557 MB of feature maps: up to 4 us of 27).
+inline int marked_waves_per_workgroup(int64_t widest) { return widest > 512 ? 8 : 4; }
+
+// Spans of 1024 elements per wave, of a tensor of `tensor_spans` with `channels` channels in a launch of `launch_spans`
+// altogether and `widest` channels at most.  A wave reads its pieces one batch after the other, so a launch is cut into 4096 waves (four per SIMD) before a wave
+// gets a second span: with eight spans a wave whatever the size, 4 MB took 9.9 us and 64 MB 14.0 us where most pieces hold
+// an outlier; this way 4.4 and 12.7 (where few do, 4.3 and 6.7, now 3.7 and 6.0).  A wide tensor is cut into 256 workgroups at most
+// until a wave has its fill (25 MB of 768 channels in workgroups of four waves: 13.3 us with six spans, 15.2 with three,
+// 25.5 with one).  Eight spans are as many as a wave looks at together.
+inline int32_t marked_spans_per_wave(int64_t launch_spans, int64_t tensor_spans, int64_t channels, int64_t widest)
+{
+    int64_t spans = launch_spans / 4096;
+    const int64_t least = tensor_spans / (256 * marked_waves_per_workgroup(widest));
+    if (channels > 512 && least > spans) spans = least;
+    return (int32_t)(spans < 1 ? 1 : spans > 8 ? 8 : spans);
+}
+
+}  // namespace fh

@@ -144,6 +144,23 @@ def test_first_pass_on_both_sides_of_a_large_launch(api, dtype):
 
 
 @pytest.mark.timeout(600)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("channels", [500, 513, 3072])
+def test_waves_of_the_count_pass_walk_one_span_or_several(api, channels, dtype):
+    """Beyond 4096 spans in the launch (2048 in a wide tensor) a wave of the count pass gets two spans, three beyond
+    three times as many, ...: sizes on both sides of these lines and with a last wave that has less to do."""
+    rng = np.random.default_rng(channels)
+    for spans in (4095, 8192, 8192 + 4, 3 * 4096 + 1000):
+        outer = (spans * 1024 + 500) // channels
+        x = rng.standard_normal(outer * channels, dtype=f32)
+        x[rng.integers(0, x.size, x.size // 3000)] *= f32(50)
+        if dtype == "bf16":
+            x = (x.view(np.uint32) >> 16).astype(np.uint16)
+        for k in (1.0, 3.0):
+            _check(api, x, outer, channels, 1, k, 1, dtype=dtype, name="spans per wave")
+
+
+@pytest.mark.timeout(600)
 def test_paper_sized_activation_set(api):
     # the five per-sample shapes of the paper's local-engine ablation, at batch 64
     for i, (C, h, w) in enumerate(W.ABLATION_SHAPES):

@@ -1,0 +1,55 @@
+"""The rules by which the host shapes its launches (paper_2510_11400_amd/csrc/fh_rules.hpp), looked at without a GPU."""
+from __future__ import annotations
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2510_11400_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    """rules(name, rows of integers) -> the rule's value for every row."""
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if not cxx:
+        pytest.skip("no C++ compiler")
+    out = tmp_path_factory.mktemp("rules")
+    src, exe = str(out / "rules.cpp"), str(out / "rules")
+    with open(src, "w") as f:
+        f.write('''#include "fh_rules.hpp"
+#include <cstdio>
+#include <cstring>
+int main(int, char** argv)
+{
+    long long a, b, c, d;
+    while (std::scanf("%lld %lld %lld %lld", &a, &b, &c, &d) == 4)
+        if (!std::strcmp(argv[1], "marked_spans_per_wave")) std::printf("%lld\\n", (long long)fh::marked_spans_per_wave(a, b, c, d));
+}
+''')
+    subprocess.run([cxx, "-std=c++17", "-I", CSRC, src, "-o", exe], check=True)
+
+    def run(name, rows):
+        text = "".join(" ".join(str(v) for v in r) + "\n" for r in rows)
+        return [int(v) for v in subprocess.run([exe, name], input=text, text=True, check=True, capture_output=True).stdout.split()]
+
+    return run
+
+
+def test_count_pass_fills_the_device_before_a_wave_gets_a_second_span(rules):
+    """Tensors of 1 to 4096 spans and beyond, one or several in a launch, beside wider ones or not: a narrow tensor's
+    launch has a wave per span or at least 4096 waves' worth; a wide one's is not cut finer than 256 workgroups (of eight
+    waves in its launch) ask for."""
+    rows = [(n * count, n, channels, max(channels, widest)) for n in (1, 7, 255, 1024, 4095, 4096, 4097, 9000, 16384, 40000, 1 << 20)
+            for count in (1, 3, 24) for channels in (1, 64, 512, 513, 768, 1024, 1025, 3072, 16384) for widest in (0, 768)]
+    for (launch, tensor, channels, _), spans in zip(rows, rules("marked_spans_per_wave", rows)):
+        assert 1 <= spans <= 8, (launch, tensor, channels, spans)
+        if channels <= 512:
+            assert spans == 1 or launch // spans >= 4096, (launch, tensor, channels, spans)
+        else:
+            assert spans == 1 or launch // spans >= 4096 or tensor // spans >= 2048, (launch, tensor, channels, spans)
+            assert spans == 8 or tensor < 2048 * (spans + 1), (launch, tensor, channels, spans)
+        assert spans == 8 or launch < 4096 * (spans + 1), (launch, tensor, channels, spans)
