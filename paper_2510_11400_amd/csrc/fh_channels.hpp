@@ -205,7 +205,7 @@ __device__ __forceinline__ bool any_kept(const ChannelMap& cm, uint32_t index, u
 constexpr uint32_t kListedRows = 2048;                        // raw-store rows the list has room for
 constexpr uint32_t kNoChannel = 0xffffu;                      // channels are below 2^14
 
-__device__ __forceinline__ bool rows_listed(const ChannelMap& cm)
+__host__ __device__ __forceinline__ bool rows_listed(const ChannelMap& cm)
 {
     return cm.inner.d == 1u && cm.raw_channels - 1u < kListedRows;
 }

@@ -405,7 +405,7 @@ __device__ __forceinline__ void divert_listed(const ChannelMap& cm, const ElemPo
 //   * fp32 (4 elements per lane and row): a Philox block (8 elements) spans a lane pair;
 //     the even lane computes the blocks of rows 0 and 2, the odd lane those of rows 1
 //     and 3, and they trade the halves.  bf16 (8 per lane and row): a block per lane and row.
-template <typename InT, int G, int B, bool STOCH, bool MIXED, bool FIRST>
+template <typename InT, int G, int B, bool STOCH, bool MIXED, bool FIRST, bool LISTED>
 __device__ __forceinline__ void compress_span(const CompressItem& it, int64_t wave_base, const InT* xw,
                                               uint8_t* pw, float* mw, uint32_t lane,
                                               uint8_t* stage_codes, float* stage_meta,
@@ -423,7 +423,7 @@ __device__ __forceinline__ void compress_span(const CompressItem& it, int64_t wa
     const bool b0 = lane & 1u, b1 = lane & 2u;
 
     float x[ROWS][EPL];
-    if (MIXED && rows != nullptr) {                           // wave-uniform: one channel per element; `w` holds the span
+    if (MIXED && (LISTED || rows != nullptr)) {               // wave-uniform: one channel per element; `w` holds the span
         divert_listed<InT, ROWS>(*cm, wave_pos, rows, stage_codes, lane, w);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) Loader<InT>::widen(w[r], x[r]);
@@ -677,7 +677,8 @@ __device__ __forceinline__ void compress_edge(const CompressItem& it, int64_t wa
 // `listed` (MIXED only): LDS for the list of raw-store rows, built here -- by every thread of the workgroup, which
 // all call this with the same arguments -- when the tensor has one channel per element.
 // `first` (FIRST only): where the classification's first pass goes.
-template <typename InT, int G, int B, bool STOCH, bool MIXED = false, bool FIRST = false>
+// LISTED: the tensor is known to have its rows listed.
+template <typename InT, int G, int B, bool STOCH, bool MIXED = false, bool FIRST = false, bool LISTED = false>
 __device__ __forceinline__ void compress_tile(const CompressItem& it, uint32_t tile, uint32_t* stage,
                                               const ChannelMap* cm = nullptr, uint16_t* listed = nullptr,
                                               uint32_t stage_dwords = kStageDwords,
@@ -697,7 +698,7 @@ __device__ __forceinline__ void compress_tile(const CompressItem& it, uint32_t t
     const uint16_t* rows = nullptr;
     u32x4 w[4] = {};
     if constexpr (MIXED) {
-        if (rows_listed(*cm)) {
+        if (LISTED || rows_listed(*cm)) {
             // the table entries first, then the span (so that waiting for the former does not wait for the latter),
             // and the list is filed while the span is on its way
             SlotWords words;
@@ -723,8 +724,8 @@ __device__ __forceinline__ void compress_tile(const CompressItem& it, uint32_t t
     if (interior) {
         uint8_t* stage_codes = reinterpret_cast<uint8_t*>(stage + wave * stage_dwords);
         float* stage_meta = reinterpret_cast<float*>(stage_codes + kStageCodeBytes);
-        compress_span<InT, G, B, STOCH, MIXED, FIRST>(it, wave_base, xw, pw, mw, lane, stage_codes, stage_meta, cm, wave_pos,
-                                                      rows, w, first);
+        compress_span<InT, G, B, STOCH, MIXED, FIRST, LISTED>(it, wave_base, xw, pw, mw, lane, stage_codes, stage_meta, cm,
+                                                              wave_pos, rows, w, first);
     } else {
         if constexpr (FIRST) {
             if (wave_base < numel) {                          // wave-uniform
@@ -775,10 +776,13 @@ constexpr int kMixedStageDwords = 1024;
 static_assert(kMixedStageDwords >= kStageDwords && kMixedStageDwords * 4 == Layout<float>::SPAN * 4 &&
               kMixedStageDwords * 4 == Layout<uint16_t>::SPAN * 2, "a span of either dtype is 4 KiB");
 
-// (Eight waves per SIMD, which asks for 64 vector registers: with the 74 that the compiler takes by itself six fit, and
-// the 720 MiB encoder set takes 228 us instead of 216.)
-template <typename InT, int G>
-__global__ __launch_bounds__(kCBlock, 8) void compress_mixed_kernel(const Batch<MixedCompressJob> batch)
+// LISTED: every tensor of the launch has its rows listed.  What a wave waits for bounds the kernel, so registers count: with
+// the walk over kept runs left out it takes 64 in bf16 and eight waves fit a SIMD, beside it 74 and six.  (Held to 64 the
+// common form fitted eight as well, with 28 bytes per lane of scratch memory, which feature maps paid for: 205 MB of bf16
+// 64.1 us at 8 bits, 58.4 without.)  The 720 MiB encoder set takes 241 us at 2 bits stochastic and 179 at 4 bits nearest,
+// 259 and 192 in the common form; 100 MB of fp32 with 3072 channels 22.3, and 24.5.
+template <typename InT, int G, bool LISTED>
+__global__ __launch_bounds__(kCBlock) void compress_mixed_kernel(const Batch<MixedCompressJob> batch)
 {
     __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kMixedStageDwords];
     __shared__ uint16_t listed[kListedRows];
@@ -799,12 +803,12 @@ __global__ __launch_bounds__(kCBlock, 8) void compress_mixed_kernel(const Batch<
         return;
     }
     switch (it.bits * 2 + it.stochastic) {
-        case 4:  compress_tile<InT, G, 2, false, true>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
-        case 5:  compress_tile<InT, G, 2, true , true>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
-        case 8:  compress_tile<InT, G, 4, false, true>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
-        case 9:  compress_tile<InT, G, 4, true , true>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
-        case 16: compress_tile<InT, G, 8, false, true>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
-        case 17: compress_tile<InT, G, 8, true , true>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
+        case 4:  compress_tile<InT, G, 2, false, true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
+        case 5:  compress_tile<InT, G, 2, true , true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
+        case 8:  compress_tile<InT, G, 4, false, true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
+        case 9:  compress_tile<InT, G, 4, true , true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
+        case 16: compress_tile<InT, G, 8, false, true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
+        case 17: compress_tile<InT, G, 8, true , true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
         default: break;
     }
 }
@@ -865,7 +869,7 @@ __device__ __forceinline__ void compress_kept_spans(const CompressItem& it, cons
         const ElemPos wave_pos = locate_base(cm, (uint32_t)wave_base);
         if (wave_base + L::SPAN <= it.numel) {
             u32x4 unused[4] = {};
-            compress_span<InT, G, B, STOCH, true, false>(it, wave_base, xw, pw, mw, lane, stage_codes, stage_meta, &cm, wave_pos,
+            compress_span<InT, G, B, STOCH, true, false, false>(it, wave_base, xw, pw, mw, lane, stage_codes, stage_meta, &cm, wave_pos,
                                                          nullptr, unused, nullptr);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");         // the staging area is the next span's
         } else {
@@ -965,7 +969,13 @@ hipError_t launch_compress_mixed(const Batch<MixedCompressJob>& b, int dtype, in
     const uint32_t tiles = b.block_start[b.count];
     if (tiles == 0) return hipSuccess;
     const dim3 grid(tiles), block(kCBlock);
-#define FH_LAUNCH(T, GS) hipLaunchKernelGGL((compress_mixed_kernel<T, GS>), grid, block, 0, s, b)
+    bool listed = true;
+    for (int k = 0; k < b.count; ++k) listed = listed && rows_listed(b.item[k].cm);
+#define FH_LAUNCH(T, GS) \
+    do { \
+        if (listed) hipLaunchKernelGGL((compress_mixed_kernel<T, GS, true>), grid, block, 0, s, b); \
+        else hipLaunchKernelGGL((compress_mixed_kernel<T, GS, false>), grid, block, 0, s, b); \
+    } while (0)
     if (dtype == 0) {
         if (group_size == 64) FH_LAUNCH(float, 64);
         else if (group_size == 128) FH_LAUNCH(float, 128);

@@ -159,7 +159,8 @@ __device__ __forceinline__ OutT raw_as(const void* raw, uint64_t i, int raw_dtyp
     }
 }
 
-template <typename OutT, int G, int B, bool MIXED = false>
+// LISTED: the tensor is known to have its rows listed.
+template <typename OutT, int G, int B, bool MIXED = false, bool LISTED = false>
 __device__ __forceinline__ void decompress_tile(const DecompressItem& it, uint32_t tile,
                                                 const ChannelMap* cm = nullptr, int raw_dtype = 0,
                                                 uint16_t* listed = nullptr, uint8_t* park = nullptr)
@@ -188,7 +189,7 @@ __device__ __forceinline__ void decompress_tile(const DecompressItem& it, uint32
     using RawBits = typename std::conditional<sizeof(OutT) == 4, uint32_t, uint16_t>::type;
     RawBits ahead[kPairsAhead] = {};                          // MIXED: a lane's first raw-store entries, in the output's dtype
     if constexpr (MIXED) {
-        if (rows_listed(*cm)) {                               // the same for every thread of the workgroup, which all get here
+        if (LISTED || rows_listed(*cm)) {                     // the same for every thread of the workgroup, which all get here
             // the table entries first, then the span's codes (so that waiting for the former does not wait for the
             // latter), and the list is filed while the codes are on their way
             SlotWords words;
@@ -221,9 +222,9 @@ __device__ __forceinline__ void decompress_tile(const DecompressItem& it, uint32
 
     if (interior) {
         // ---- interior: all loads first, then one 128-bit store per lane and row ----
-        if (!(MIXED && rows != nullptr)) load_span();
+        if (!(MIXED && (LISTED || rows != nullptr))) load_span();
         if constexpr (MIXED) {
-            if (rows != nullptr) {                            // wave-uniform: one channel per element
+            if (LISTED || rows != nullptr) {                  // wave-uniform: one channel per element
                 using Bits = typename std::conditional<sizeof(OutT) == 4, uint32_t, uint16_t>::type;
                 typedef Bits __attribute__((may_alias)) Parked;
                 const uint64_t raw0 = (uint64_t)wave_pos.o * cm->raw_channels;
@@ -350,10 +351,12 @@ __global__ __launch_bounds__(kDBlock) void decompress_kernel(const DecompressBat
     }
 }
 
-// Tensors whose kept channels come from the raw store.  (Eight waves per SIMD, as in the forward kernel: 206 us on the
-// encoder set restored to bf16 where six took 220, and 192 with the conversion of pack_bf16x8.)
-template <typename OutT, int G>
-__global__ __launch_bounds__(kDBlock, 8) void decompress_mixed_kernel(const Batch<MixedDecompressJob> batch)
+// Tensors whose kept channels come from the raw store.  LISTED: every one of the launch has its rows listed.  Restoring
+// bf16, the kernel then takes 54 vector registers and eight waves fit a SIMD; with the values of kept runs beside it, 74
+// and six.  (Held to 64 the common form spilled 68 bytes per lane: 205 MB of feature maps 74.4 us at 8 bits and 58.1 at 2,
+// 51.1 and 39.7 without.)  The 720 MiB encoder set takes 185 us from 2-bit codes, 195 in the common form.
+template <typename OutT, int G, bool LISTED>
+__global__ __launch_bounds__(kDBlock) void decompress_mixed_kernel(const Batch<MixedDecompressJob> batch)
 {
     uint32_t tile;
     const MixedDecompressJob& job = batch.item[batch_item(batch, gridDim.x - 1u - blockIdx.x, tile)];
@@ -372,9 +375,9 @@ __global__ __launch_bounds__(kDBlock, 8) void decompress_mixed_kernel(const Batc
         return;
     }
     switch (it.bits) {
-        case 2: decompress_tile<OutT, G, 2, true>(it, tile, &cm, raw_dtype, listed, park); break;
-        case 4: decompress_tile<OutT, G, 4, true>(it, tile, &cm, raw_dtype, listed, park); break;
-        case 8: decompress_tile<OutT, G, 8, true>(it, tile, &cm, raw_dtype, listed, park); break;
+        case 2: decompress_tile<OutT, G, 2, true, LISTED>(it, tile, &cm, raw_dtype, listed, park); break;
+        case 4: decompress_tile<OutT, G, 4, true, LISTED>(it, tile, &cm, raw_dtype, listed, park); break;
+        case 8: decompress_tile<OutT, G, 8, true, LISTED>(it, tile, &cm, raw_dtype, listed, park); break;
         default: break;
     }
 }
@@ -410,7 +413,13 @@ hipError_t launch_decompress_mixed(const Batch<MixedDecompressJob>& b, int out_d
     const uint32_t tiles = b.block_start[b.count];
     if (tiles == 0) return hipSuccess;
     const dim3 grid(tiles), block(kDBlock);
-#define FH_LAUNCH(T, GS) hipLaunchKernelGGL((decompress_mixed_kernel<T, GS>), grid, block, 0, s, b)
+    bool listed = true;
+    for (int k = 0; k < b.count; ++k) listed = listed && rows_listed(b.item[k].cm);
+#define FH_LAUNCH(T, GS) \
+    do { \
+        if (listed) hipLaunchKernelGGL((decompress_mixed_kernel<T, GS, true>), grid, block, 0, s, b); \
+        else hipLaunchKernelGGL((decompress_mixed_kernel<T, GS, false>), grid, block, 0, s, b); \
+    } while (0)
     if (out_dtype == 0) {
         if (group_size == 64) FH_LAUNCH(float, 64);
         else if (group_size == 128) FH_LAUNCH(float, 128);

@@ -54,6 +54,25 @@ def _disassembly(paths, function):
     return found
 
 
+def _resources(paths):
+    """{mangled name: its entry in the code objects' notes}"""
+    found = {}
+    for p in paths:
+        text = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", p], check=True, capture_output=True, text=True).stdout
+        for entry in text.split("  - .agpr_count:")[1:]:
+            values = dict(re.findall(r"^    \.(\w+):\s+(\S+)$", entry, re.M))
+            found[values["symbol"].strip("'").removesuffix(".kd")] = {k: int(v) for k, v in values.items() if v.isdigit()}
+    return found
+
+
+def test_no_routed_kernel_needs_scratch_memory(code_objects):
+    """A register bound that the compiler meets by spilling costs more than the waves it buys."""
+    kernels = {n: r for n, r in _resources(code_objects).items() if "compress_mixed_kernel" in n}
+    assert len(kernels) >= 12
+    for name, r in kernels.items():
+        assert r["vgpr_spill_count"] == 0 and r["private_segment_fixed_size"] == 0, f"{name}: {r}"
+
+
 def test_the_rows_of_a_wave_are_requested_together(code_objects):
     """The classification's first pass: a wave's whole rows are read by non-temporal 16-byte loads with no wait for
     one of them before the last is on its way (a test around each row's load makes the compiler wait for the first)."""
