@@ -65,10 +65,10 @@ def _resources(paths):
     return found
 
 
-def test_no_routed_kernel_needs_scratch_memory(code_objects):
-    """A register bound that the compiler meets by spilling costs more than the waves it buys."""
-    kernels = {n: r for n, r in _resources(code_objects).items() if "compress_mixed_kernel" in n}
-    assert len(kernels) >= 12
+def test_no_kernel_needs_scratch_memory(code_objects):
+    """A register bound that the compiler meets by spilling costs more than the waves or the loads in flight it buys."""
+    kernels = _resources(code_objects)
+    assert len(kernels) >= 80
     for name, r in kernels.items():
         assert r["vgpr_spill_count"] == 0 and r["private_segment_fixed_size"] == 0, f"{name}: {r}"
 
