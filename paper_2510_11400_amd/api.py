@@ -542,7 +542,7 @@ def fh_channel_slots(mask: torch.Tensor, raw_channels: int, slots: Optional[torc
 
 
 def fh_channel_slots_batch(masks: Sequence[torch.Tensor], raw_channels: Sequence[int], stream=None):
-    """Slot numbering for several tensors with one launch per 16 of them; returns (slots, used): lists
+    """Slot numbering for several tensors with one launch per 16 of them or more; returns (slots, used): lists
     of device tensors int16[channels] and int64[1] (raw-store rows in use)."""
     if not masks:
         return [], []

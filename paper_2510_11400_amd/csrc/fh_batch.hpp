@@ -10,9 +10,10 @@
 namespace fh {
 
 // Tensors per launch: as many as the largest descriptor (the routed quantiser's, 152 bytes) lets into 4 KiB of kernel
-// arguments.  A stage's serial kernels (the Huffman tables and codes, the finishing kernels) take as long for 24 tensors
-// as for one, so a set of 24 activations pays for them once: the whole chain on it 1047 -> 871 us against 16 per launch.
-constexpr int kBatch = 24;
+// arguments (fh_kernels.hpp holds it to that).  A stage's serial kernels (the Huffman tables and codes, the finishing
+// kernels) take as long for a full launch as for one tensor: the whole chain on 24 activations takes 871 us in one launch
+// per stage, 1047 in launches of 16.  Launches of one tensor pay for the longer argument segment with some 0.1 us each.
+constexpr int kBatch = 26;
 constexpr int kBatchStated = 16;                   // what the *_batch_capacity() calls promise
 
 template <typename Item> struct Batch {

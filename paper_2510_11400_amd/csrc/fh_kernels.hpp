@@ -89,6 +89,7 @@ struct MixedDecompressJob {
     int32_t        raw_dtype;
     int32_t        pad;
 };
+static_assert(sizeof(Batch<MixedCompressJob>) + sizeof(MixedCompressJob) + sizeof(uint32_t) > 4096, "a launch holds as many as fit");
 // The plain quantiser that leaves the classification's first pass behind on its way (fh_moments.hpp): for tensors that
 // are quantised before it is known which of their channels are kept.
 struct FirstCompressJob {
