@@ -24,6 +24,16 @@ def test_bench_refuses_a_multi_rank_launch():
     assert res.returncode == 2 and "ONE GPU" in res.stderr
 
 
+def test_bytes_a_classification_and_a_chain_are_priced_at():
+    """Each input read once, each output written once: a fraction of the peak on them cannot exceed 1 because a call
+    moves less than a second and third read of the tensors."""
+    sys.path.insert(0, ROOT)
+    import bench
+
+    assert bench.classify_bytes(1000) == 1000
+    assert bench.chain_bytes(1000, 130) == (1130, 1130)
+
+
 def test_channel_wise_hooks_view_a_tensor_as_outer_channels_inner():
     torch = pytest.importorskip("torch")
     from paper_2510_11400_amd import hooks
