@@ -38,9 +38,9 @@ __device__ __forceinline__ uint32_t div_exact(uint32_t n, const ExactDiv& v)
     return (t + ((n - t) >> v.sh1)) >> v.sh2;
 }
 
-// floor(n / d) for small dividends: n < d + 4096 and n < 2^17.  magic = floor(2^32 / d) + 1
-// is exact while n * d < 2^32, which covers every d below 2^15; larger divisors can only
-// give 0 or 1.
+// floor(n / d) for small dividends: n < d + 8192 (the count pass of the classification comes
+// closest).  magic = floor(2^32 / d) + 1 is exact while n * d < 2^32, which covers every d below
+// 2^15 (40960 * 32768 < 2^31); larger divisors can only give 0 or 1.
 struct SmallDiv {
     uint32_t d, magic;
 };

@@ -80,8 +80,7 @@ __device__ __forceinline__ void restore(uint32_t c0, uint32_t c1, f32x2 m, float
 
 __device__ __forceinline__ u32x4 pack_bf16x8(const float (&v)[8])
 {
-    // gfx950's conversion of two values at once: the bits of bf16_bits() for every one of the 2^32 inputs (compared on
-    // the device, NaNs included), in one instruction instead of a dozen
+    // gfx950's conversion of two values at once rounds as bf16_bits() does, in one instruction instead of a dozen
     const auto two = [&](int j) {
         uint32_t r;
         asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(v[j]), "v"(v[j + 1]));

@@ -47,15 +47,15 @@ constexpr int kHistBlocksMax = 512;                // histogram workgroups per s
 constexpr int kFastBits = 12;
 constexpr int kBurst = 8;                          // decode: 16-byte output vectors held back and stored together
 // decode: threads per workgroup.  The payload slice in LDS is what limits the chunks in flight on a compute unit,
-// and the decode waits on dependent instructions, not on a unit: one workgroup with the whole LDS holds 768
-// chunks (twelve waves) where workgroups of 256 with their own tables held 512.
-// The stage then holds 768 chunks at 46 words (5.75 bits per symbol) and 880 at 40 words, so the workgroup has as many
-// threads as there are: where a stream's chunks come to slightly more than 768 per compute unit (51 MB of index
+// and the decode waits on dependent instructions, not on a unit: one workgroup with the whole LDS holds more chunks than
+// the two workgroups of 256, each with tables of its own, that fit a unit.
+// The stage then holds 768 chunks at 46 words (5.75 bits per symbol) and 1024 at 34, so the workgroup has as many
+// threads as there can be: where a stream's chunks come to slightly more than 768 per compute unit (51 MB of index
 // streams: 788) they take one pass and not two.
 constexpr int kDecodeThreads = 1024;
 constexpr int kDecodeThreadsSmall = 256;           // ... of a launch whose chunks fit the device this way
-// decode: LDS for a workgroup's payload slice, in words per chunk: 48 (6 bits per symbol) is what fits beside the
-// tables for 768 chunks when one workgroup takes the whole LDS; two workgroups of 256 per unit have room for 64 (8 bits per
+// decode: LDS for a workgroup's payload slice, in words: what fits beside the tables when one workgroup takes the whole
+// LDS is 46 words per chunk (5.75 bits per symbol) for 768 chunks; two workgroups of 256 per unit have room for 64 (8 bits per
 // symbol: any slice fits on average, and streams of 7-8 bits per symbol no longer fall back to the rings)
 template <int THREADS> struct StageWords { static constexpr int kAll = THREADS >= 768 ? 768 * 46 : THREADS * 64; };
 constexpr int kSecondEntries = 2048;               // decode: entries of the table behind the fast one
@@ -1178,7 +1178,7 @@ fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t c
             total += groups[jobs];
             ++jobs;
         }
-        // A workgroup builds a stream's tables once and then decodes `chunks_per_block` chunks.  With more groups
+        // A workgroup builds a stream's tables once and then decodes its share of the chunks.  With more groups
         // in the launch than workgroups fit on the device at once, every stream gets its share of that many
         // workgroups, and its chunks are dealt out evenly among them: all of them are resident from the start and
         // finish together (their last pass seats fewer chunks), whereas a launch of 1.4 times as many would run a

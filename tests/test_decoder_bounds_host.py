@@ -165,12 +165,12 @@ def test_huffman_foreign_streams_stay_in_bounds(decoders):
 
 
 def test_huffman_large_launch_uses_the_wide_workgroups(decoders):
-    """More than 256 groups of 768 chunks: the launch with workgroups of 768 work-items and 46 staged words per
-    chunk; one valid stream -- its second half too wide for a pass to seat 768 chunks -- and the same stream with
-    its offsets and payload replaced by noise."""
+    """More than 256 * 1024 chunks: the launch with workgroups of 1024 work-items, each of which takes a pass of as many
+    chunks and a second one; one valid stream -- its last part too wide for a pass to seat that many -- and the same
+    stream with its offsets and payload replaced by noise."""
     rng = np.random.default_rng(7)
-    n = 256 * 768 * 256 + 77
-    data = np.concatenate([_clustered(rng, n // 2, 6.0), _clustered(rng, n - n // 2, 20.0)])
+    n = 256 * (1024 * 256 + 300) + 77
+    data = np.concatenate([_clustered(rng, n - n // 8, 2.5), _clustered(rng, n // 8, 20.0)])
     stream, _ = oracle.huffman_encode(data)
     head = 256 + 4 * ((n + 255) // 256 + 1)
     noisy = stream.copy()

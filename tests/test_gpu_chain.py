@@ -137,14 +137,25 @@ def test_tensors_quantised_before_their_kept_channels_are_known(api, out_dtype):
                 _compare(api, batch, k, xs[i], picked[i], out_dtype)
 
 
-@pytest.mark.parametrize("count", [24, 25, 50])
-def test_batches_at_the_number_of_tensors_that_a_launch_holds(api, count):
-    """A launch of each stage holds 24 tensors: a batch of just that many, one more, and more than two launches."""
-    picked = [(1 + i % 3,) + CASES[0][1:] if i % 2 else (40 + i,) + CASES[6][1:4] + (8,) + CASES[6][5:12] + ("f32", 3)
-              for i in range(count)]
+@pytest.mark.parametrize("more", [0, 1, 2])
+@pytest.mark.parametrize("kind", ["quantised first", "maps", "tokens"])
+def test_batches_at_the_number_of_tensors_that_a_launch_holds(api, per_launch, kind, more):
+    """Tensors of one dtype and one group size, so that every stage takes as many per launch as it holds: a batch of
+    just that many, one more, and one more than two launches, for each way the chain quantises."""
+    count = (per_launch, per_launch + 1, 2 * per_launch + 1)[more]
+    picked = []
+    for i in range(count):
+        if kind == "quantised first":                # few spans can hold kept elements
+            c = (2 + i % 3, 20 + i % 5, 2100 + i, (2100 + i, 1), 1) + QUANTISED_FIRST[0][5:8]
+            picked.append(c + (4, 0.5, 0.02, 1, "f32", 20))
+            assert 4 * c[0] * c[4] * (c[2] + 4096) <= c[0] * c[1] * c[2]        # the rule of the call
+        elif kind == "maps":
+            picked.append((1 + i % 3,) + CASES[0][1:])
+        else:
+            picked.append((40 + i,) + CASES[6][1:4] + (8,) + CASES[6][5:12] + ("f32", 3))
     xs = [_input(case, 500 + i) for i, case in enumerate(picked)]
     batch = api.MixBatch([_entry(api, _device(x, case[12]), case, "f32") for x, case in zip(xs, picked)])
-    print(f"[chain] batch of {count}", flush=True)
+    print(f"[chain] {kind}, batch of {count}", flush=True)
     api.fh_mix_compress_batch(batch)
     api.fh_mix_decompress_batch(batch)
     torch.cuda.synchronize()

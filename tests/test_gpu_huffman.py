@@ -52,13 +52,14 @@ def test_sizes_around_vectors_chunks_and_groups(api, n):
 
 @pytest.mark.parametrize("spread", [2.5, 14.0, 20.0, -1.0, 0.0])
 def test_streams_long_enough_that_a_workgroup_decodes_several_groups(api, spread):
-    # The decoder takes 768 chunks per workgroup and one workgroup per compute unit: 300 such groups and a ragged
-    # tail are more than the device holds at once, so a workgroup takes two and the last one the ragged one.
-    # spread 14: codes longer than the decoder's fast table occur; 20: more words per chunk than the decoder's LDS
-    # stage holds for 768 chunks, so its passes seat fewer; -1: a clustered first half and noise behind it, passes of
+    # Beyond 131072 chunks the decoder has a workgroup of 1024 threads per compute unit and deals the chunks out evenly: 1026
+    # each here, so a workgroup takes a pass with every thread at work (34 words per chunk fit the LDS stage then; spread
+    # 2.5 gives 27) and another of two chunks, the last one fewer and a ragged chunk.
+    # spread 14: codes longer than the decoder's fast table occur; 14 and 20: more words per chunk than the stage
+    # holds for 1024 (and for 768) chunks, so its passes seat fewer; -1: a clustered first half and noise behind it, passes of
     # every kind in one launch; 0: uniform bytes, whose 64 words per chunk do not fit the LDS stage of either side
     # (the direct payload stores and the per-thread rings)
-    n = 256 * 768 * 300 + 77
+    n = 256 * (256 * 1024 + 300) + 77
     rng = np.random.default_rng(int(abs(spread) * 10))
     if spread > 0:
         data = np.clip(np.rint(rng.normal(128, spread, n)), 0, 255)
@@ -67,6 +68,16 @@ def test_streams_long_enough_that_a_workgroup_decodes_several_groups(api, spread
     else:
         data = rng.integers(0, 256, n)
     _check(api, data.astype(np.uint8), f"spread {spread}")
+
+
+@pytest.mark.parametrize("spread", [2.5, 14.0])
+@pytest.mark.parametrize("groups", [512, 513])
+def test_decoder_on_both_sides_of_the_wide_workgroups(api, groups, spread):
+    """Up to 512 groups of 256 chunks go to workgroups of 256 threads, two per compute unit; one chunk more and the
+    launch has workgroups of 1024, which are given half of them each."""
+    n = 256 * 256 * 512 + (0 if groups == 512 else 1)
+    rng = np.random.default_rng(groups)
+    _check(api, np.clip(np.rint(rng.normal(128, spread, n)), 0, 255).astype(np.uint8), f"{groups} groups, spread {spread}")
 
 
 @pytest.mark.parametrize("kind", ["uniform", "one", "two", "geometric", "all-once", "ties"])
@@ -171,15 +182,14 @@ def test_buffers_can_be_reused_and_errors_reach_the_caller(api):
         api.fh_huffman_encode(torch.from_numpy(a).cuda()[1:], stream_out=out, totals=tot, workspace=ws)   # misaligned
 
 
-def test_batched_calls_match_the_oracle_for_every_stream(api):
+def test_batched_calls_match_the_oracle_for_every_stream(api, per_launch):
     """More streams than one launch holds, an empty one among them, sizes from one symbol to a few groups."""
     rng = np.random.default_rng(9)
-    sizes = [1, 0, 300, 65536, 200001, 77] + [1000 + 4099 * i for i in range(14)]
+    sizes = [1, 0, 300, 65536, 200001, 77] + [1000 + 4099 * (i % 14) + i for i in range(2 * per_launch + 1)]
     datas = []
     for i, n in enumerate(sizes):
         spread = 1.0 + (i % 5) * 3.0
         datas.append(np.clip(np.rint(rng.normal(128, spread, n)), 0, 255).astype(np.uint8))
-    assert len(datas) > api.huffman_batch_capacity()
     dev = [torch.from_numpy(d).cuda() if d.size else torch.empty(0, dtype=torch.uint8, device="cuda") for d in datas]
     batch = api.HuffmanBatch(dev)
     api.fh_huffman_encode_batch(batch)

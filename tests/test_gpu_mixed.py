@@ -229,12 +229,12 @@ def test_argument_errors_reach_the_caller(api):
 
 # ---- the batched calls ---------------------------------------------------------------------------
 
-def test_batched_calls_match_the_oracle_for_every_tensor(api):
+def test_batched_calls_match_the_oracle_for_every_tensor(api, per_launch):
     """More tensors than one launch holds, both dtypes and several group sizes (several runs),
     an empty tensor, capacities below and above the salient count."""
     specs = [(8, 32, 196, "f32", 128, 4, "nearest"), (64, 768, 1, "bf16", 64, 2, "stochastic"), (0, 12, 9, "f32", 128, 4, "nearest"),
              (3, 16, 4097, "f32", 256, 8, "stochastic"), (5, 100, 1, "bf16", 64, 4, "nearest"), (2, 10, 7, "f32", 64, 8, "nearest")]
-    specs += [(2 + i % 3, 8 + i, 50 + 13 * i, "f32", 128, 4, "stochastic") for i in range(16)]
+    specs += [(2 + i % 3, 8 + i, 50 + 13 * i, "f32", 128, 4, "stochastic") for i in range(2 * per_launch + 1)]      # one run: three launches
     entries, host = [], []
     for i, (outer, C, inner, dtype, G, B, rounding) in enumerate(specs):
         x, _ = W.outlier_channel_tensor(max(outer, 1), C, inner, seed=70 + i, salient_fraction=0.1, dtype=dtype)
@@ -250,7 +250,6 @@ def test_batched_calls_match_the_oracle_for_every_tensor(api):
         xd = _device(x, dtype) if x.size else torch.empty(0, dtype=tdt, device="cuda")
         entries.append(api.MixedEntry(outer, C, inner, torch.from_numpy(slots).cuda(), cap, G, B, rounding, 3, 100 + i,
                                       x=xd, out=torch.empty(x.size, dtype=torch.float32, device="cuda")))
-    assert len(entries) > api.mixed_batch_capacity()
     batch = api.MixedBatch(entries)
     print(f"[mixed] batch of {len(entries)} tensors", flush=True)
     api.fh_compress_mixed_batch(batch)
@@ -266,6 +265,49 @@ def test_batched_calls_match_the_oracle_for_every_tensor(api):
         # restore with the oracle's raw store where unused rows are zero: kept rows are what matter
         want = oracle.decompress_mixed(p, m, raw, outer, C, inner, slots, cap, G, B, raw_dtype=dtype, out_dtype="f32")
         assert np.array_equal(e.out.cpu().numpy().view(np.uint32), want.view(np.uint32)), f"tensor {i}: restored"
+
+
+@pytest.mark.parametrize("layout", ["maps", "tokens", "both"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_full_launches_of_either_layout(api, per_launch, dtype, layout):
+    """One run of one more than twice what a launch holds: launches whose tensors all have one channel per element have
+    a kernel of their own, and launches with both layouts (the last one here has a single tensor) the common one; both
+    restored dtypes."""
+    entries, host = [], []
+    for i in range(2 * per_launch + 1):
+        tokens = layout == "tokens" or (layout == "both" and i % 3 == 1)
+        outer, C, inner = (90 + 7 * i, 96 + 8 * (i % 3), 1) if tokens else (3 + i % 4, 20 + i, 60 + 17 * i)
+        x, _ = W.outlier_channel_tensor(outer, C, inner, seed=900 + i, salient_fraction=0.1, dtype=dtype)
+        mask = _mask(C, 0.15, i)
+        mask[i % C] = 1
+        cap = max(1, int(mask.sum()) - (i % 2))
+        slots, used = oracle.channel_slots(mask, cap)
+        host.append((x, outer, C, inner, slots, cap))
+        entries.append(api.MixedEntry(outer, C, inner, torch.from_numpy(slots).cuda(), cap, 64, (2, 4, 8)[i % 3], "stochastic", 3, i,
+                                      x=_device(x, dtype), out=torch.empty(x.size, dtype=_tdtype(dtype), device="cuda")))
+    batch = api.MixedBatch(entries)
+    print(f"[mixed] {len(entries)} tensors, {layout} {dtype}", flush=True)
+    api.fh_compress_mixed_batch(batch)
+    api.fh_decompress_mixed_batch(batch)
+    torch.cuda.synchronize()
+    for i, ((x, outer, C, inner, slots, cap), e) in enumerate(zip(host, entries)):
+        p, m, raw = oracle.compress_mixed(x, outer, C, inner, slots, cap, 64, (2, 4, 8)[i % 3], "stochastic", 3, i, dtype=dtype)
+        used = int((slots >= 0).sum())
+        assert np.array_equal(e.packed.cpu().numpy(), p), f"tensor {i}: codes"
+        assert np.array_equal(e.meta.cpu().numpy().view(np.uint32), m.view(np.uint32)), f"tensor {i}: meta"
+        assert np.array_equal(_bits(_host(e.raw, dtype).reshape(outer, cap, inner)[:, :used]),
+                              _bits(raw.reshape(outer, cap, inner)[:, :used])), f"tensor {i}: raw"
+        want = oracle.decompress_mixed(p, m, raw, outer, C, inner, slots, cap, 64, (2, 4, 8)[i % 3], raw_dtype=dtype, out_dtype=dtype)
+        assert np.array_equal(_bits(_host(e.out, dtype)), _bits(want)), f"tensor {i}: restored"
+
+
+def test_slots_of_more_tensors_than_a_launch_holds(api, per_launch):
+    masks = [_mask(5 + 3 * i, 0.3, i) for i in range(2 * per_launch + 1)]
+    slots, used = api.fh_channel_slots_batch([torch.from_numpy(m).cuda() for m in masks], [1 + i % 4 for i in range(len(masks))])
+    torch.cuda.synchronize()
+    for i, m in enumerate(masks):
+        want, n = oracle.channel_slots(m, 1 + i % 4)
+        assert np.array_equal(slots[i].cpu().numpy(), want) and int(used[i].item()) == n, f"tensor {i}"
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

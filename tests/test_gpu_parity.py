@@ -275,6 +275,27 @@ def test_full_configuration_bit_exact(api, idx):
     _full_config_check(api, idx)
 
 
+def test_restored_values_of_every_bf16_neighbourhood_round_as_the_oracle_does(api):
+    """Restoring bf16 rounds with the hardware's conversion.  A group whose codes and scale are 0 restores its zero
+    point: every upper half of a binary32 with the lower halves around the ties and the ends, subnormals, infinities and
+    NaN (whose payload is not compared) among them."""
+    high = np.arange(1 << 16, dtype=np.uint32) << 16
+    low = np.array([0, 1, 0x7fff, 0x8000, 0x8001, 0xffff], dtype=np.uint32)
+    zero = (high[:, None] | low[None, :]).reshape(-1).view(f32)
+    meta = np.zeros((zero.size, 2), dtype=f32)
+    meta[:, 1] = zero
+    n = zero.size * 64
+    packed = np.zeros(n // 4, dtype=np.uint8)
+    print("[parity] bf16 rounding of restored values", flush=True)
+    got = api.fh_decompress(torch.from_numpy(packed).cuda(), torch.from_numpy(meta).cuda(), n, 64, 2, torch.bfloat16)
+    torch.cuda.synchronize()
+    got = _host(got)
+    want = oracle.decompress(packed, meta, n, 64, 2, "bf16")
+    nan = np.repeat(np.isnan(zero), 64)
+    assert np.array_equal(got[~nan], want[~nan])
+    assert np.all((got[nan] & 0x7fff) > 0x7f80)
+
+
 @pytest.mark.timeout(600)
 def test_full_configuration_4_transformer_bf16(api):
     _full_config_check(api, 4)
