@@ -19,8 +19,12 @@ def code_objects(tmp_path_factory):
     """Paths of the device code objects of the library: one bundle per source file."""
     if not os.path.exists(os.path.join(LLVM, "llvm-objdump")):
         pytest.skip("no llvm-objdump")
+    if not os.path.exists(LIB):
+        import __graft_entry__
+        __graft_entry__.build()
     out = tmp_path_factory.mktemp("code")
-    data = open(LIB, "rb").read()
+    with open(LIB, "rb") as f:
+        data = f.read()
     magic, paths = b"__CLANG_OFFLOAD_BUNDLE__", []
     for m in re.finditer(magic, data):
         at = m.start() + len(magic)
