@@ -22,11 +22,10 @@
 //               then codes four chunks at a time, every lane placing the bits of its sixteen
 //               symbols in an LDS area by OR, and stores the four chunks' words -- one
 //               contiguous piece -- with consecutive lanes on consecutive words.
-// Decoding needs no pass but one: the offsets are part of the stream.  A workgroup rebuilds the
-// canonical tables from the 256 lengths (a 12-bit lookup table for the short codes, first-code /
-// count comparisons for the longer ones), stages the payload slice of up to 1024 chunks in LDS (150
-// of the compute unit's 160 KiB: one workgroup of sixteen waves each), and a thread decodes its chunk
-// from there; the tables serve several such groups in long streams.
+// Decoding needs no pass but one: the offsets are part of the stream.  A workgroup has the whole LDS of a compute unit.
+// While the payload slice of up to 1024 chunks is on its way there it rebuilds the canonical tables from the 256 lengths
+// (a lookup table for the short codes, a second one for the longer, comparisons for the longest), and a thread decodes
+// its chunk from LDS; the tables serve several such groups in long streams.
 // Everything here is integer work; results do not depend on launch geometry.
 #include "../../include/fedhybrid.h"
 
@@ -44,20 +43,24 @@ constexpr int kChunkWordsMax = kChunk * kMaxLen / 32;
 constexpr int kHistCopies = 32;                     // one per LDS bank
 constexpr int kHistThreads = 1024;
 constexpr int kHistBlocksMax = 512;                // histogram workgroups per stream: two per compute unit
-constexpr int kFastBits = 12;
-constexpr int kBurst = 8;                          // decode: 16-byte output vectors held back and stored together
-// decode: threads per workgroup.  The payload slice in LDS is what limits the chunks in flight on a compute unit,
-// and the decode waits on dependent instructions, not on a unit: one workgroup with the whole LDS holds more chunks than
-// the two workgroups of 256, each with tables of its own, that fit a unit.
-// The stage then holds 768 chunks at 46 words (5.75 bits per symbol) and 1024 at 34, so the workgroup has as many
-// threads as there can be: where a stream's chunks come to slightly more than 768 per compute unit (51 MB of index
-// streams: 788) they take one pass and not two.
+// decode: 16-byte output vectors held back and stored together; at 51 MB one at a time 67 us, 2 51, 4 49, with 8 the code no
+// longer fits the instruction cache and takes 53 (the rings' fits either way)
+constexpr int kBurst = 4, kRingBurst = 8;
+// decode: threads per workgroup, one workgroup per compute unit.  The payload slice in LDS is what limits the chunks in
+// flight on a unit.  With 1024 threads the stage holds 768 chunks at 46 words (5.75 bits per symbol) and 1024 at 34: a
+// stream whose chunks come to slightly more than 768 per unit (51 MB of index streams: 788) takes one pass and not two;
+// four waves per SIMD then keep the LDS busy (54 us before four symbols shared a window of the stream, 49 now).
+// A launch of fewer chunks has 512 threads and two waves per SIMD, and there a symbol's chain of dependent steps is the
+// time: 158 cycles for a code that the first table has, some 400 more for the whole wave when a lane's is longer.  So the
+// LDS that the chunks leave goes to that table: 14 bits, where 12 had some lane of the wave in the second table at two
+// symbols in five.  Index streams of 25 MB: 46.8 us as two workgroups of 256 with 12 bits each, 35.5 now.
 constexpr int kDecodeThreads = 1024;
-constexpr int kDecodeThreadsSmall = 256;           // ... of a launch whose chunks fit the device this way
-// decode: LDS for a workgroup's payload slice, in words: what fits beside the tables when one workgroup takes the whole
-// LDS is 46 words per chunk (5.75 bits per symbol) for 768 chunks; two workgroups of 256 per unit have room for 64 (8 bits per
-// symbol: any slice fits on average, and streams of 7-8 bits per symbol no longer fall back to the rings)
-template <int THREADS> struct StageWords { static constexpr int kAll = THREADS >= 768 ? 768 * 46 : THREADS * 64; };
+constexpr int kDecodeThreadsSmall = 512;
+template <int THREADS> struct FastBits { static constexpr int kAll = THREADS >= 768 ? 12 : 14; };
+// LDS for the payload slice, in words: what fits beside the tables
+constexpr int kSmallWords = 61;
+template <int THREADS> struct StageWords { static constexpr int kAll = THREADS >= 768 ? 768 * 46 : THREADS * kSmallWords; };
+constexpr uint64_t kSmallSeats = kSmallWords * kDecodeThreadsSmall / 64;    // chunks of 8 bits per symbol that fit it: in practice, any
 constexpr int kSecondEntries = 2048;               // decode: entries of the table behind the fast one
 constexpr int kComputeUnits = 256;                 // MI355X
 
@@ -605,22 +608,40 @@ struct LongCodes {
     uint8_t  sorted[256];                                     // symbols by (length, symbol)
 };
 
-// The symbol whose code, longer than kFastBits, is on top of the stream, as symbol | length << 8 like an entry of the
-// fast table.
+// An entry of the decoder's tables: symbol << 8 | 32 - length; 0 where there is none.  With what the code leaves of a
+// word at the bottom, the entry as it is read is the shift amount that moves the stream up (drop_code).
+__device__ __forceinline__ uint32_t entry_of(uint32_t symbol, uint32_t length) { return (symbol << 8) | (32u - length); }
+__device__ __forceinline__ uint32_t symbol_in(uint32_t entry) { return entry >> 8; }
+__device__ __forceinline__ uint32_t length_in(uint32_t entry) { return 32u - (entry & 0xffu); }     // 32 where there is none
+
+// The next 64 bits of the stream, the next one on top.  Two words and 32-bit shifts: a 64-bit shift whose amount the
+// compiler put into the last register of a wave's 128 was seen to shift by register 0 instead, on some waves.
+struct Ahead {
+    uint32_t high, low;
+};
+// low word of high:low >> by; by mod 32 counts
+__device__ __forceinline__ uint32_t align_right(uint32_t high, uint32_t low, uint32_t by) { return __builtin_amdgcn_alignbit(high, low, by); }
+__device__ __forceinline__ Ahead drop_code(const Ahead& a, uint32_t entry)                         // an entry that exists
+{
+    return Ahead{align_right(a.high, a.low, entry), a.low << ((0u - entry) & 31u)};
+}
+
+// The entry of the symbol whose code, longer than SHORT bits, is on top of the stream.
 // Canonical codes grow with their length, so the 32-bit windows that start with a code of length <= k are those up
 // to last[k]: the length of the code on top is one more than the number of those bounds that the window exceeds -- a
 // compare and an add per length, the bounds (the same for the whole workgroup) in scalar registers -- and its place
 // among the symbols sorted by (length, symbol) is its value less `first - start` of its length.  `top`: the next
 // 32 bits of the stream.
-struct LongRegs {
-    uint32_t last[kMaxLen - kFastBits - 1];        // [i]: the largest window that starts with a code of length <= kFastBits + 1 + i
+template <int SHORT> struct LongRegs {
+    uint32_t last[kMaxLen - SHORT - 1];            // [i]: the largest window that starts with a code of length <= SHORT + 1 + i
 };
-__device__ __forceinline__ LongRegs long_regs(const LongCodes* t)
+template <int SHORT>
+__device__ __forceinline__ LongRegs<SHORT> long_regs(const LongCodes* t)
 {
-    LongRegs r;
+    LongRegs<SHORT> r;
 #pragma unroll
-    for (int i = 0; i < kMaxLen - kFastBits - 1; ++i) {
-        const int k = kFastBits + 1 + i;
+    for (int i = 0; i < kMaxLen - SHORT - 1; ++i) {
+        const int k = SHORT + 1 + i;
         // left-justified: one past the windows of length <= k (lengths no encoder wrote can claim more than there is)
         const uint64_t end = ((uint64_t)t->first[k] + t->per_length[k]) << (32 - k);
         const uint32_t last = end > 0xffffffffull ? 0xffffffffu : end ? (uint32_t)end - 1u : 0u;
@@ -628,13 +649,14 @@ __device__ __forceinline__ LongRegs long_regs(const LongCodes* t)
     }
     return r;
 }
-// symbol | length << 8 like an entry of the fast table; the length is kFastBits + 1 at least, whatever the tables say
-__device__ __forceinline__ uint32_t decode_long(uint32_t top, const LongRegs& r, const LongCodes* t)
+// its entry; the length is SHORT + 1 at least, whatever the tables say
+template <int SHORT>
+__device__ __forceinline__ uint32_t decode_long(uint32_t top, const LongRegs<SHORT>& r, const LongCodes* t)
 {
-    uint32_t length = kFastBits + 1;
+    uint32_t length = SHORT + 1;
 #pragma unroll
-    for (int i = 0; i < kMaxLen - kFastBits - 1; ++i) length += top > r.last[i] ? 1u : 0u;
-    return t->sorted[((top >> (32u - length)) + t->start[length] - t->first[length]) & 0xffu] | (length << 8);
+    for (int i = 0; i < kMaxLen - SHORT - 1; ++i) length += top > r.last[i] ? 1u : 0u;
+    return entry_of(t->sorted[((top >> (32u - length)) + t->start[length] - t->first[length]) & 0xffu], length);
 }
 
 // A long code is rare per symbol, but a wave pays for one whenever ANY of its 64 lanes meets one -- one step in six
@@ -645,23 +667,24 @@ __device__ __forceinline__ uint32_t decode_long(uint32_t top, const LongRegs& r,
 // as large as kSecondEntries allow, the longest code at most; with no long codes, or more long prefixes than
 // entries, there is no second table.
 struct Second {
-    uint32_t extra;                                // bits beyond kFastBits that index the table; 0: no table
-    uint32_t from;                                 // the first index (of kFastBits + extra bits) it covers
+    uint32_t extra;                                // bits beyond FAST that index the table; 0: no table
+    uint32_t from;                                 // the first index (of FAST + extra bits) it covers
     uint32_t entries;
 };
+template <int FAST>
 __device__ __forceinline__ Second second_of(const LongCodes* t)
 {
     Second s{0u, 0u, 0u};
     uint32_t longest = 0;
 #pragma unroll
-    for (int k = kFastBits + 1; k <= kMaxLen; ++k)
+    for (int k = FAST + 1; k <= kMaxLen; ++k)
         if (__builtin_amdgcn_readfirstlane((int)t->per_length[k])) longest = (uint32_t)k;
-    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)t->first[kFastBits + 1]) >> 1;   // as kFastBits bits
-    if (longest == 0u || first >= (1u << kFastBits)) return s;
-    const uint32_t prefixes = (1u << kFastBits) - first;
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)t->first[FAST + 1]) >> 1;   // as FAST bits
+    if (longest == 0u || first >= (1u << FAST)) return s;
+    const uint32_t prefixes = (1u << FAST) - first;
     if (prefixes > (uint32_t)kSecondEntries / 2u) return s;
     uint32_t extra = 1;
-    while (extra < longest - kFastBits && (prefixes << (extra + 1u)) <= (uint32_t)kSecondEntries) ++extra;
+    while (extra < longest - FAST && (prefixes << (extra + 1u)) <= (uint32_t)kSecondEntries) ++extra;
     s.extra = extra;
     s.from = first << extra;
     s.entries = prefixes << extra;
@@ -675,37 +698,44 @@ struct Lookup {
     const LongCodes* tables;
     Second           behind;
 };
-// What the next symbol's code decodes to, as symbol | length << 8, from the stream's next 32 bits.
-__device__ __forceinline__ uint32_t decode_symbol(const uint16_t* fast, const uint16_t* second, const Second& behind,
-                                                  const LongRegs& longer, const LongCodes* tables, uint32_t top)
+// The entry of the next symbol's code, from the stream's next 32 bits; behind_fast: of a code that the fast table
+// does not have.
+template <int FAST>
+__device__ __forceinline__ uint32_t behind_fast(const uint16_t* second, const Second& behind, const LongRegs<FAST>& longer,
+                                                const LongCodes* tables, uint32_t top)
 {
-    uint32_t e = fast[top >> (32 - kFastBits)];
-    if (!e) {
-        if (behind.extra) {                                   // workgroup-uniform
-            // below `from` only in a stream that no encoder wrote: any entry will do
-            const uint32_t i = (top >> (32u - kFastBits - behind.extra)) - behind.from;
-            e = second[i < behind.entries ? i : behind.entries - 1u];
-        }
-        if (!e) e = decode_long(top, longer, tables);
+    uint32_t e = 0;
+    if (behind.extra) {                                       // workgroup-uniform
+        // below `from` only in a stream that no encoder wrote: any entry will do
+        const uint32_t i = (top >> (32u - FAST - behind.extra)) - behind.from;
+        e = second[i < behind.entries ? i : behind.entries - 1u];
     }
+    if (!e) e = decode_long<FAST>(top, longer, tables);
     return e;
 }
+template <int FAST>
+__device__ __forceinline__ uint32_t decode_symbol(const uint16_t* fast, const uint16_t* second, const Second& behind,
+                                                  const LongRegs<FAST>& longer, const LongCodes* tables, uint32_t top)
+{
+    const uint32_t e = fast[top >> (32 - FAST)];
+    return e ? e : behind_fast<FAST>(second, behind, longer, tables, top);
+}
 
-template <typename NextWord>
+template <int FAST, typename NextWord>
 __device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const Lookup table, NextWord next_word)
 {
-    const LongRegs longer = long_regs(table.tables);
+    const LongRegs<FAST> longer = long_regs<FAST>(table.tables);
     const Second behind = table.behind;
     const uint16_t* fast = table.fast;
     const uint16_t* second = table.second;
     const LongCodes* tables = table.tables;
-    uint32_t taken = 0;                                       // words moved into `buf`
-    uint64_t buf = 0;                                         // pending bits, the next one on top
-    uint32_t have = 0;
-    for (uint32_t half = 0; half < valid; half += 16 * kBurst) {
-        u32x4 piece[kBurst];
+    uint32_t taken = 0;                                       // words moved into `next`
+    Ahead next = {0u, 0u};
+    uint32_t have = 0;                                        // bits of it that are there
+    for (uint32_t half = 0; half < valid; half += 16 * kRingBurst) {
+        u32x4 piece[kRingBurst];
 #pragma unroll
-        for (int v = 0; v < kBurst; ++v) {
+        for (int v = 0; v < kRingBurst; ++v) {
             uint32_t sixteen[4];
             if (half + 16u * v >= valid) { piece[v] = u32x4{0u, 0u, 0u, 0u}; continue; }
 #pragma unroll
@@ -716,14 +746,14 @@ __device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const
                     if (have <= 32u) {
                         const uint32_t w = next_word(taken);
                         ++taken;
-                        buf |= (uint64_t)w << (32u - have);
+                        next.high |= have < 32u ? w >> have : 0u;
+                        next.low = have == 32u ? w : have ? w << (32u - have) : 0u;
                         have += 32u;
                     }
-                    const uint32_t e = decode_symbol(fast, second, behind, longer, tables, (uint32_t)(buf >> 32));
-                    const uint32_t symbol = e & 0xffu, used_bits = e >> 8;
-                    buf <<= used_bits;
-                    have -= used_bits;
-                    four |= symbol << (8 * b);
+                    const uint32_t e = decode_symbol<FAST>(fast, second, behind, longer, tables, next.high);
+                    next = drop_code(next, e);
+                    have -= length_in(e);
+                    four |= symbol_in(e) << (8 * b);
                 }
                 sixteen[q] = four;
             }
@@ -731,7 +761,7 @@ __device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const
         }
         // a whole cache line's worth of stores back to back: the line is complete in the L2 before it can be evicted
 #pragma unroll
-        for (int v = 0; v < kBurst; ++v) {
+        for (int v = 0; v < kRingBurst; ++v) {
             const uint32_t i = half + 16u * v;
             if (i + 16 <= valid) {
                 *reinterpret_cast<u32x4*>(dst + i) = piece[v];
@@ -743,22 +773,32 @@ __device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const
     }
 }
 
-// The same from words in LDS: no bit buffer to refill (lanes would diverge on when) -- every
-// symbol reads the two words its bits start in and shifts them into place, so a step is two
-// dependent LDS reads and nothing data-dependent in the control flow.
+// The same from words in LDS.  What a symbol costs is the chain from one table read to the next, so four symbols come
+// from one 64-bit window of the stream, kept in registers: a table read, a shift by what it says.  Four codes of the
+// fast table fit it; around a longer one (rare, and then the wave steps aside anyway) there may be too few bits left, and
+// a new window is taken.  The words of the next window are requested before the fourth symbol's table read: its code moves the
+// window's first word by one at most, so four words hold it either way.
+// A window at bit `pos` starts in word (pos - 1) / 32, rounded down, so that its shift is 0 .. 31: at the chunk's first
+// bit that is words[-1], shifted out whole.
+struct Window {
+    uint32_t w0, w1, w2;
+};
+__device__ __forceinline__ int32_t window_word(uint32_t pos) { return (int32_t)(pos - 1u) >> 5; }
+__device__ __forceinline__ Ahead window_bits(const Window& w, uint32_t pos)
+{
+    return Ahead{align_right(w.w0, w.w1, 0u - pos), align_right(w.w1, w.w2, 0u - pos)};
+}
+template <int FAST>
 __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst, const Lookup table, const uint32_t* words)
 {
-    const LongRegs longer = long_regs(table.tables);
+    const LongRegs<FAST> longer = long_regs<FAST>(table.tables);
     const Second behind = table.behind;
     const uint16_t* fast = table.fast;
     const uint16_t* second = table.second;
     const LongCodes* tables = table.tables;
-    // Three words of the chunk stay in registers: w0 holds bit `pos`, w1 follows, w2 is the word after that.  A
-    // symbol advances by at most 24 bits, one word, so after it the registers move up by one at most, and w2 is
-    // read again for the new position: that read is needed one symbol later, so that a symbol waits for one LDS
-    // access in a row (the table) rather than two (words, then table).
-    uint32_t pos = 0, at = 0;                                 // bits of the chunk consumed; at = pos / 32
-    uint32_t w0 = words[0], w1 = words[1], w2 = words[2];
+    uint32_t pos = 0;                                         // bits of the chunk consumed
+    Window w = {0u, words[0], words[1]};
+#pragma unroll 1
     for (uint32_t half = 0; half < valid; half += 16 * kBurst) {
         u32x4 piece[kBurst];
 #pragma unroll
@@ -767,20 +807,40 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
             if (half + 16u * v >= valid) { piece[v] = u32x4{0u, 0u, 0u, 0u}; continue; }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                uint32_t four = 0;
+                Ahead next = window_bits(w, pos);
+                uint32_t window_end = pos + 64u;
+                const auto new_window = [&] {
+                    const uint32_t* from = words + window_word(pos);
+                    window_end = pos + 64u;
+                    return window_bits(Window{from[0], from[1], from[2]}, pos);
+                };
+                uint32_t e[4];
+                int32_t at = 0;                               // where the fourth symbol's window starts
+                uint32_t ahead[4];
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    const uint32_t top = (uint32_t)(((((uint64_t)w0 << 32) | w1) << (pos & 31u)) >> 32);   // the next 32 bits
-                    const uint32_t e = decode_symbol(fast, second, behind, longer, tables, top);
-                    four |= (e & 0xffu) << (8 * b);
-                    pos += e >> 8;
-                    const bool crossed = (pos >> 5) != at;
-                    w0 = crossed ? w1 : w0;
-                    w1 = crossed ? w2 : w1;
-                    at = pos >> 5;
-                    w2 = words[at + 2];
+                    if (b == 3) {
+                        at = window_word(pos);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) ahead[k] = words[at + k];
+                    }
+                    Ahead here = next;
+                    e[b] = fast[here.high >> (32 - FAST)];
+                    next = drop_code(here, e[b]);             // (put right below where there is no entry)
+                    pos += length_in(e[b]);
+                    if (__builtin_expect(e[b] == 0u, 0)) {
+                        pos -= 32u;
+                        // it may need more bits than the window has left, or leave fewer than the codes behind it may need
+                        if ((int32_t)(window_end - pos) < kMaxLen) here = new_window();
+                        e[b] = behind_fast<FAST>(second, behind, longer, tables, here.high);
+                        next = drop_code(here, e[b]);
+                        pos += length_in(e[b]);
+                        if (b < 3 && (int32_t)(window_end - pos) < FAST * (3 - b)) next = new_window();
+                    }
                 }
-                sixteen[q] = four;
+                const bool crossed = window_word(pos) != at;  // a code has at most 24 bits
+                w = Window{crossed ? ahead[1] : ahead[0], crossed ? ahead[2] : ahead[1], crossed ? ahead[3] : ahead[2]};
+                sixteen[q] = (e[0] >> 8) | (e[1] & 0xff00u) | ((e[2] & 0xff00u) << 8) | ((e[3] & 0xff00u) << 16);
             }
             piece[v] = u32x4{sixteen[0], sixteen[1], sixteen[2], sixteen[3]};
         }
@@ -805,7 +865,7 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
 template <int kDecodeThreads>
 __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Batch<DecodeJob> batch)
 {
-    constexpr int kStageWords = StageWords<kDecodeThreads>::kAll;
+    constexpr int kStageWords = StageWords<kDecodeThreads>::kAll, kFastBits = FastBits<kDecodeThreads>::kAll;
     uint32_t block;
     const DecodeJob& job = batch.item[batch_item(batch, blockIdx.x, block)];
     const uint8_t* len_in = job.len;
@@ -826,12 +886,14 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
     // One object, so that the order is the one written here: the tables that every symbol is looked up in come first,
     // at addresses small enough for the offset field of an LDS instruction (one addition less per symbol).
     struct Local {
-        uint16_t  fast[1 << kFastBits];                       // next kFastBits bits -> symbol | length << 8; 0: longer code
+        uint16_t  fast[1 << kFastBits];                       // next kFastBits bits -> entry; 0: longer code
         uint16_t  second[kSecondEntries];                     // the same for the long codes' first kFastBits + extra bits
         LongCodes tables;
         uint32_t  in_wave[kThreads / 64][kMaxLen + 2];        // [w][k]: symbols of length k among wave w's 64
+        uint32_t  all_eight[4];                               // [w]: the codes of wave w's 64 symbols are eight bits long
         uint32_t  fitting;                                    // chunks of a pass whose slice fits the stage
-        __align__(16) uint32_t stage[kStageWords + kChunkWordsMax + 8];   // the workgroup's slice of the payload, or the rings
+        // the workgroup's slice of the payload, or the rings; four words lead in (a chunk's first window reads the one before it)
+        __align__(16) uint32_t slice[4 + kStageWords + kChunkWordsMax + 8];
     };
     __shared__ Local local;
     LongCodes& tables = local.tables;
@@ -840,89 +902,120 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
     uint32_t (&in_wave)[kThreads / 64][kMaxLen + 2] = local.in_wave;
     uint16_t (&fast)[1 << kFastBits] = local.fast;
     uint16_t (&second)[kSecondEntries] = local.second;
-    uint32_t (&stage)[kStageWords + kChunkWordsMax + 8] = local.stage;
-    // threads 0..255 stand for the 256 symbols while the tables are built; the others only fill and wait
+    uint32_t* const stage = local.slice + 4;
     const uint32_t s = threadIdx.x, wave = s >> 6, lane = s & 63u;
-    const bool symbol = s < 256u;
-    uint32_t l = symbol ? len_in[s] : 0u;
+    uint32_t l = s < 256u ? len_in[s] : 0u;
     if (l > (uint32_t)kMaxLen) l = 0u;
-    // thread s is symbol s: its rank among the symbols of its length, by lane masks inside the wave ...
-    uint32_t before = 0;
-#pragma unroll
-    for (int k = 1; k <= kMaxLen; ++k) {
-        const uint64_t same = __ballot(l == (uint32_t)k);
-        if (l == (uint32_t)k) before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-        if (lane == 0 && symbol) in_wave[wave][k] = (uint32_t)__popcll(same);
+    if (wave < 4u) {                                          // wave-uniform
+        const uint64_t eight = __ballot(l == 8u);
+        if (lane == 0) local.all_eight[wave] = eight == ~(uint64_t)0 ? 1u : 0u;
     }
     __syncthreads();
-    if (s < (uint32_t)kMaxLen + 2u) {
-        uint32_t total = 0;
-        if (s >= 1u && s <= (uint32_t)kMaxLen)
-            for (int w = 0; w < kThreads / 64; ++w) total += in_wave[w][s];
-        per_length[s] = total;
-    }
-    __syncthreads();
-    if (s == 0) {
-        uint32_t count[kMaxLen + 1];
+    const bool flat = (local.all_eight[0] & local.all_eight[1] & local.all_eight[2] & local.all_eight[3]) != 0u;
+    Second behind = {0u, 0u, 0u};
+    // Threads 0..255 stand for the 256 symbols while the tables are built; the others only fill and wait.
+    const auto build_tables = [&] {
+        // thread s is symbol s: its rank among the symbols of its length, by lane masks inside the wave ...
+        uint32_t before = 0;
+        if (wave < 4u) {                                      // wave-uniform
 #pragma unroll
-        for (int k = 1; k <= kMaxLen; ++k) count[k] = per_length[k];
-        uint32_t code = 0, at = 0;
-        first[0] = first[1] = 0u;
-        start[0] = start[1] = 0u;
-#pragma unroll
-        for (int k = 2; k <= kMaxLen; ++k) {
-            code = (code + count[k - 1]) << 1;
-            at += count[k - 1];
-            first[k] = code;
-            start[k] = at;
-        }
-    }
-    __syncthreads();
-    if (l) {                                                  // ... plus those in the waves below
-        for (uint32_t w = 0; w < wave; ++w) before += in_wave[w][l];
-        sorted[(start[l] + before) & 0xffu] = (uint8_t)s;
-    }
-    __syncthreads();
-    {
-        // the short lengths' tables in registers (the same in every thread)
-        uint32_t count_of[kFastBits + 1], first_of[kFastBits + 1], start_of[kFastBits + 1];
-#pragma unroll
-        for (int k = 1; k <= kFastBits; ++k) { count_of[k] = per_length[k]; first_of[k] = first[k]; start_of[k] = start[k]; }
-        for (uint32_t i = s; i < (1u << kFastBits); i += kDecodeThreads) {  // the short codes: what the next kFastBits bits decode to
-            uint32_t at = 0, length = 0;
-#pragma unroll
-            for (int k = kFastBits; k >= 1; --k) {                   // at most one length matches a prefix code
-                const uint32_t code = i >> (kFastBits - k);
-                if (count_of[k] && code >= first_of[k] && code - first_of[k] < count_of[k]) {
-                    at = start_of[k] + code - first_of[k];
-                    length = (uint32_t)k;
-                }
+            for (int k = 1; k <= kMaxLen; ++k) {
+                const uint64_t same = __ballot(l == (uint32_t)k);
+                if (l == (uint32_t)k) before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+                if (lane == 0) in_wave[wave][k] = (uint32_t)__popcll(same);
             }
-            fast[i] = length ? (uint16_t)(sorted[at & 0xffu] | (length << 8)) : (uint16_t)0;
         }
-    }
-    Lookup table;
-    table.fast = fast;
-    table.second = second;
-    table.tables = &tables;
-    table.behind = second_of(&tables);
-    const LongRegs longer = long_regs(&tables);
-    for (uint32_t i = s; i < table.behind.entries; i += kDecodeThreads) {
-        const uint32_t width = (uint32_t)kFastBits + table.behind.extra;
-        const uint32_t e = decode_long((table.behind.from + i) << (32u - width), longer, &tables);
-        second[i] = (e >> 8) <= width ? (uint16_t)e : (uint16_t)0;
-    }
-    __syncthreads();
+        __syncthreads();
+        if (s < (uint32_t)kMaxLen + 2u) {
+            uint32_t total = 0;
+            if (s >= 1u && s <= (uint32_t)kMaxLen)
+                for (int w = 0; w < kThreads / 64; ++w) total += in_wave[w][s];
+            per_length[s] = total;
+        }
+        __syncthreads();
+        if (s == 0) {
+            uint32_t count[kMaxLen + 1];
+#pragma unroll
+            for (int k = 1; k <= kMaxLen; ++k) count[k] = per_length[k];
+            uint32_t code = 0, at = 0;
+            first[0] = first[1] = 0u;
+            start[0] = start[1] = 0u;
+#pragma unroll
+            for (int k = 2; k <= kMaxLen; ++k) {
+                code = (code + count[k - 1]) << 1;
+                at += count[k - 1];
+                first[k] = code;
+                start[k] = at;
+            }
+        }
+        __syncthreads();
+        if (l) {                                              // ... plus those in the waves below
+            for (uint32_t w = 0; w < wave; ++w) before += in_wave[w][l];
+            sorted[(start[l] + before) & 0xffu] = (uint8_t)s;
+        }
+        __syncthreads();
+        // The first kSure bits settle most entries, kEach of the table at a time; those that they do not settle, the
+        // prefixes of longer codes at the upper end, one by one.
+        constexpr int kSure = 12, kEach = 1 << (kFastBits - kSure);
+        const LongRegs<0> any = long_regs<0>(&tables);
+        for (uint32_t i = s; i < (1u << kSure); i += kDecodeThreads) {
+            const uint32_t top = (i << (32 - kSure)) | 1u;    // (above the bound 0 of lengths that have no codes below them)
+            uint32_t length = 1;
+#pragma unroll
+            for (int k = 0; k < kSure; ++k) length += top > any.last[k] ? 1u : 0u;
+            const uint32_t symbol_at = (i >> ((uint32_t)kSure - (length < (uint32_t)kSure ? length : (uint32_t)kSure))) + start[length] - first[length];
+            const bool there = length <= (uint32_t)kSure && symbol_at - start[length] < per_length[length];
+            const uint16_t e = there ? (uint16_t)entry_of(sorted[symbol_at & 0xffu], length) : (uint16_t)0;
+#pragma unroll
+            for (int j = 0; j < kEach; ++j) fast[i * kEach + j] = e;
+        }
+        if constexpr (kEach > 1) {
+            __syncthreads();
+            const LongRegs<kSure> longer = long_regs<kSure>(&tables);
+            const uint32_t from = (uint32_t)__builtin_amdgcn_readfirstlane((int)first[kSure + 1]) >> 1;   // of kSure bits: the first that is none
+            for (uint32_t i = from * kEach + s; i < (1u << kFastBits); i += kDecodeThreads) {
+                if (fast[i]) continue;                        // only where the lengths are no encoder's
+                const uint32_t e = decode_long<kSure>(i << (32 - kFastBits), longer, &tables);
+                fast[i] = length_in(e) <= (uint32_t)kFastBits ? (uint16_t)e : (uint16_t)0;
+            }
+        }
+        behind = second_of<kFastBits>(&tables);
+        const LongRegs<kFastBits> longer = long_regs<kFastBits>(&tables);
+        for (uint32_t i = s; i < behind.entries; i += kDecodeThreads) {
+            const uint32_t width = (uint32_t)kFastBits + behind.extra;
+            const uint32_t e = decode_long<kFastBits>((behind.from + i) << (32u - width), longer, &tables);
+            second[i] = length_in(e) <= width ? (uint16_t)e : (uint16_t)0;
+        }
+        __syncthreads();
+    };
 
-    // These tables serve an equal share of the stream's chunks (a wave's worth at least), in passes of as many chunks as there are threads at most.  The payload words of consecutive chunks are one contiguous slice.  A pass takes the chunks whose
-    // slice fits the stage -- all of them up to 46 (64) words per chunk on average, fewer on streams that hardly
-    // compress, where the threads beyond sit the pass out -- brings the slice into LDS with contiguous loads, and
+    // The tables serve an equal share of the stream's chunks (a wave's worth at least), in passes of as many chunks as
+    // there are threads at most.  The payload words of consecutive chunks are one contiguous slice.  A pass takes the
+    // chunks whose slice fits the stage -- all of them up to 46 (61) words per chunk on average, fewer on streams that
+    // hardly compress, where the threads beyond sit the pass out -- brings the slice into LDS with contiguous loads, and
     // the threads read their words from there (a thread walking its chunk in memory would fetch a cache line per
     // word).  A pass that could seat few of its chunks, and offsets that do not describe a slice (no encoder wrote
     // them), go through per-thread rings instead.
+    // Bytes that do not compress at all have codes of eight bits each, their own values: a copy with the bytes of each
+    // word turned round.  (Decoded symbol by symbol, the chunks of 64 words each meet in one LDS bank.)
+    if (flat) {                                       // workgroup-uniform
+        const uint32_t each = (chunks + job.blocks - 1u) / job.blocks;
+        const uint64_t stop = ((uint64_t)block + 1u) * each < chunks ? ((uint64_t)block + 1u) * each : chunks;
+        for (uint64_t q = (uint64_t)block * each * 64u + threadIdx.x; q < stop * 64u; q += kDecodeThreads) {
+            const uint32_t at = offsets[q >> 6] + (uint32_t)(q & 63u);
+            const uint32_t word = at < payload_words ? payload[at] : 0u;
+            if (4u * q + 4u <= n) {
+                reinterpret_cast<uint32_t*>(out)[q] = __builtin_bswap32(word);
+            } else {
+                for (uint32_t k = 0; 4u * q + k < n; ++k) out[4u * q + k] = (uint8_t)(word >> (24u - 8u * k));
+            }
+        }
+        return;
+    }
     const uint32_t even = (chunks + job.blocks - 1u) / job.blocks;
     const uint64_t share = even < 64u ? 64u : even;
     const uint32_t chunk_stop = (uint32_t)((block + 1u) * share < chunks ? (block + 1u) * share : chunks);
+    bool built = false;                                       // the tables: while the first slice is on its way
     for (uint32_t chunk0 = (uint32_t)(block * share < chunks ? block * share : chunks); chunk0 < chunk_stop;) {
         const uint32_t want = chunk_stop - chunk0 < (uint32_t)kDecodeThreads ? chunk_stop - chunk0 : (uint32_t)kDecodeThreads;
         const uint32_t slice_at = offsets[chunk0];
@@ -949,37 +1042,42 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
         const uint32_t valid = !live ? 0u : n - base < (uint64_t)kChunk ? (uint32_t)(n - base) : (uint32_t)kChunk;
         const uint32_t first_word = live ? offsets[chunk] : 0u;
         uint8_t* dst = out + base;
-        if (staged) {                                         // workgroup-uniform
-            // 16 bytes per load, twelve loads of a thread in flight: one at a time, a slice of ~50 words per thread
-            // would cost as many memory latencies.  The stage starts at the 16-byte boundary at or below the
-            // slice's first word (`phase` words earlier); what the vectors cover beyond the payload's ends is
-            // read as zero.
-            const uint32_t slice_words = slice_end - slice_at;
-            const uint32_t phase = (uint32_t)(reinterpret_cast<uintptr_t>(payload + slice_at) >> 2) & 3u;
-            const uint32_t vectors = (slice_words + phase + 3u) / 4u;
-            for (uint32_t v0 = 0; v0 < vectors; v0 += 12u * kDecodeThreads) {
-                u32x4 got[12];
+        // 16 bytes per load, twelve loads of a thread in flight: one at a time, a slice of ~50 words per thread
+        // would cost as many memory latencies.  The stage starts at the 16-byte boundary at or below the
+        // slice's first word (`phase` words earlier); what the vectors cover beyond the payload's ends is
+        // read as zero.
+        const uint32_t slice_words = slice_end - slice_at;    // none where the pass is not staged
+        const uint32_t phase = (uint32_t)(reinterpret_cast<uintptr_t>(payload + slice_at) >> 2) & 3u;
+        const uint32_t vectors = staged ? (slice_words + phase + 3u) / 4u : 0u;
+        constexpr int kVectors = kDecodeThreads > 512 ? 9 : 12;
+        uint32_t v0 = 0;
+        do {                                                  // workgroup-uniform
+            u32x4 got[kVectors];
 #pragma unroll
-                for (int k = 0; k < 12; ++k) {
-                    const uint32_t v = v0 + k * kDecodeThreads + threadIdx.x;
-                    const int64_t w = (int64_t)slice_at + 4 * (int64_t)v - phase;  // below zero in the first vector at most
-                    const auto word_at = [&](int64_t g) { return g >= 0 && g < (int64_t)payload_words ? payload[g] : 0u; };
-                    got[k] = u32x4{0u, 0u, 0u, 0u};
-                    if (v < vectors) {
-                        if (w >= 0 && w + 3 < (int64_t)payload_words) got[k] = *reinterpret_cast<const u32x4*>(payload + w);
-                        else got[k] = u32x4{word_at(w), word_at(w + 1), word_at(w + 2), word_at(w + 3)};
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < 12; ++k) {
-                    const uint32_t v = v0 + k * kDecodeThreads + threadIdx.x;
-                    if (v < vectors) *reinterpret_cast<u32x4*>(stage + 4u * v) = got[k];
+            for (int k = 0; k < kVectors; ++k) {
+                const uint32_t v = v0 + k * kDecodeThreads + threadIdx.x;
+                const int64_t w = (int64_t)slice_at + 4 * (int64_t)v - phase;  // below zero in the first vector at most
+                const auto word_at = [&](int64_t g) { return g >= 0 && g < (int64_t)payload_words ? payload[g] : 0u; };
+                got[k] = u32x4{0u, 0u, 0u, 0u};
+                if (v < vectors) {
+                    if (w >= 0 && w + 3 < (int64_t)payload_words) got[k] = *reinterpret_cast<const u32x4*>(payload + w);
+                    else got[k] = u32x4{word_at(w), word_at(w + 1), word_at(w + 2), word_at(w + 3)};
                 }
             }
+            if (!built) build_tables();
+            built = true;
+#pragma unroll
+            for (int k = 0; k < kVectors; ++k) {
+                const uint32_t v = v0 + k * kDecodeThreads + threadIdx.x;
+                if (v < vectors) *reinterpret_cast<u32x4*>(stage + 4u * v) = got[k];
+            }
+            v0 += (uint32_t)(kVectors * kDecodeThreads);
+        } while (v0 < vectors);
+        if (staged) {                                         // workgroup-uniform
             __syncthreads();
             // anything at all for a foreign stream: clamped, the reads stay inside the array (a chunk is at most 192 words)
             const uint32_t at = first_word - slice_at < slice_words ? first_word - slice_at : slice_words;
-            decode_chunk_staged(valid, dst, table, stage + phase + at);
+            decode_chunk_staged<kFastBits>(valid, dst, Lookup{fast, second, &tables, behind}, stage + phase + at);
         } else if (live) {
             // a ring of eight words per thread: when four have been consumed, the four loaded at the
             // previous refill take their place and the next four are requested, so a load has the time
@@ -990,7 +1088,7 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
             for (int k = 0; k < 8; ++k) mine[k * kDecodeThreads] = first_word + k < payload_words ? payload[first_word + k] : 0u;
 #pragma unroll
             for (int k = 0; k < 4; ++k) pending[k] = first_word + 8 + k < payload_words ? payload[first_word + 8 + k] : 0u;
-            decode_chunk(valid, dst, table, [&](uint32_t taken) {
+            decode_chunk<kFastBits>(valid, dst, Lookup{fast, second, &tables, behind}, [&](uint32_t taken) {
                 if ((taken & 3u) == 0u && taken != 0u) {      // a block of four used up: refill the half of the ring just freed
                     const uint32_t slot = (taken + 4u) & 7u;
 #pragma unroll
@@ -1145,15 +1243,19 @@ fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t c
         if (st != FH_OK) return st;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // A workgroup of 1024 threads takes the whole LDS of a compute unit: one per unit.  A call whose chunks fit the
-    // device as workgroups of 256, two per unit, takes those: more units at work, each stream's tables built side by
-    // side, and one pass.  Beyond that they would take two passes, where the wide ones seat up to twice as many chunks
-    // in one; those get at least 512 chunks each, so that every unit has one.
+    // One workgroup per compute unit, each with an equal share of its stream's chunks.  A call whose chunks fit the
+    // device in workgroups of 512 takes those, a wave per SIMD first (256 chunks); beyond that they would take two
+    // passes, where the wide ones seat up to twice as many in one, and those get at least 512 chunks each, so that
+    // every unit has one.  (A count that is on the device is an upper bound here: the index streams of the whole chain
+    // come to some two thirds of it.  Where the count is exact, a workgroup's share is to fit its stage in one pass.)
     uint64_t narrow = 0;
-    for (int32_t i = 0; i < count; ++i) narrow += (chunks_of(items[i].n) + kDecodeThreadsSmall - 1) / kDecodeThreadsSmall;
-    const bool small = narrow <= 2u * (uint64_t)kComputeUnits;
-    const uint64_t per_group = small ? kDecodeThreadsSmall : 512u;
-    const uint64_t slots = small ? 2u * kComputeUnits : kComputeUnits;         // workgroups the device holds at once
+    for (int32_t i = 0; i < count; ++i) {
+        const uint64_t seats = items[i].n_device ? (uint64_t)kDecodeThreadsSmall : kSmallSeats;
+        narrow += (chunks_of(items[i].n) + seats - 1) / seats;
+    }
+    const bool small = narrow <= (uint64_t)kComputeUnits;
+    const uint64_t per_group = small ? 256u : 512u;
+    const uint64_t slots = kComputeUnits;                     // workgroups the device holds at once
     bool launched = false;
     for (int32_t i = 0; i < count;) {
         DecodeJob job[kBatch];

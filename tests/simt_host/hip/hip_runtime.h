@@ -184,6 +184,7 @@ template <typename T> inline T atomic_min(T* p, T v)
 #define __popc(x) (__builtin_popcount(x))
 #define __umulhi(a, b) ((uint32_t)(((uint64_t)(uint32_t)(a) * (uint64_t)(uint32_t)(b)) >> 32))
 #define __builtin_amdgcn_readfirstlane(v) (v)
+#define __builtin_amdgcn_alignbit(high, low, by) ((uint32_t)((((uint64_t)(uint32_t)(high) << 32) | (uint32_t)(low)) >> ((by) & 31u)))
 #define __builtin_amdgcn_readlane(v, k) (simt::readlane((v), (k)))
 #define __builtin_amdgcn_update_dpp(old, src, ctrl, rm, bm, bc) (simt::update_dpp((old), (src), (ctrl), (rm), (bm), (bc)))
 #define __builtin_amdgcn_mbcnt_lo(m, a) (simt::mbcnt_lo((m), (a)))

@@ -70,6 +70,24 @@ def test_streams_long_enough_that_a_workgroup_decodes_several_groups(api, spread
     _check(api, data.astype(np.uint8), f"spread {spread}")
 
 
+@pytest.mark.parametrize("kind", ["deep", "flat", "nearly flat"])
+@pytest.mark.parametrize("n", [5, 16411, 256 * 488 * 256, 256 * 488 * 256 + 3])
+def test_decoder_forms(api, n, kind):
+    # 488 chunks per compute unit are the most that workgroups of 512 threads take.  deep: code lengths up to the limit of
+    # 24 and long codes side by side, so that a window of the stream runs out between four symbols; flat: eight bits each, which are copied
+    # (the last word a part of one); nearly flat: lengths 7 to 9, 64 words per chunk and all of them decoded.
+    rng = np.random.default_rng(n % 1000)
+    if kind == "deep":
+        data = np.minimum(rng.geometric(0.5, n) - 1, 255)
+        for at in range(0, min(n, 3000) - 40, 97):            # symbols that occur a few times, side by side
+            data[at:at + 33] = 40 + rng.permutation(33)
+    else:
+        data = np.arange(n) % 256
+        if kind == "nearly flat":
+            data = np.where(rng.random(n) < 0.01, 7, data)
+    _check(api, data.astype(np.uint8), f"{kind}")
+
+
 @pytest.mark.parametrize("spread", [2.5, 14.0])
 @pytest.mark.parametrize("groups", [512, 513])
 def test_decoder_on_both_sides_of_the_wide_workgroups(api, groups, spread):
