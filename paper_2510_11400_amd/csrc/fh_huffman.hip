@@ -17,7 +17,8 @@
 //   count       a wave reads four chunks at a time with one 16-byte load per lane and adds the
 //               code lengths up over each chunk's sixteen lanes: the chunk's length in words;
 //   scan        the sums of groups of 256 chunks (a workgroup of the count pass) are scanned by
-//               one workgroup;
+//               one workgroup, in long streams; in others every workgroup of the write pass
+//               adds up the sums before its own;
 //   write       word counts become offsets (group base + a scan over the workgroup); a wave
 //               then codes four chunks at a time, every lane placing the bits of its sixteen
 //               symbols in an LDS area by OR, and stores the four chunks' words -- one
@@ -37,7 +38,7 @@ namespace fh {
 namespace {
 
 constexpr int kChunk = 256;                        // symbols per chunk (= per thread)
-constexpr int kThreads = 256;                      // chunks per workgroup: a group
+constexpr int kThreads = 256;                      // of the passes that have a thread per symbol or per group
 constexpr int kMaxLen = 24;
 constexpr int kChunkWordsMax = kChunk * kMaxLen / 32;
 constexpr int kHistCopies = 32;                     // one per LDS bank
@@ -63,6 +64,19 @@ template <int THREADS> struct StageWords { static constexpr int kAll = THREADS >
 constexpr uint64_t kSmallSeats = kSmallWords * kDecodeThreadsSmall / 64;    // chunks of 8 bits per symbol that fit it: in practice, any
 constexpr int kSecondEntries = 2048;               // decode: entries of the table behind the fast one
 constexpr int kComputeUnits = 256;                 // MI355X
+// encode: a group of the count and write passes has sixteen waves, four rounds of four chunks each.  With four waves of
+// sixteen rounds a launch of fewer groups than the device holds at once waits for every round's loads in turn.  Count and
+// write of 8 MB index streams (187 groups) 13.0 and 21.8 us, now 6.9 and 11.5; of 20 MB 12.7 and 27.5, now 8.5 and 19.7; of
+// 51 MB 17.4 and 37.0, now 15.0 and 32.7 (eight waves: 9.6 and 22.3 at 20 MB, 16.8 and 32.8 at 51 MB).
+constexpr int kGroup = 256;                        // chunks of a group
+constexpr int kGroupThreads = 1024;
+constexpr int kWaves = kGroupThreads / 64;
+constexpr int kRounds = kGroup / kWaves / 4;
+// Streams of up to this many groups have no scan of the group sums between the two passes: a workgroup of the write pass
+// adds up the sums before its own, two to four per thread, which takes no longer than reading the scanned one (32.7
+// against 32.6 us at 51 MB, the longest stream 335 groups) and saves a launch of 4.8 us.  The sums read grow with the square of the
+// groups: at this limit 34 MB from the L2, which is less than that launch takes still.
+constexpr uint32_t kUnscannedGroups = 4096;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -407,7 +421,7 @@ __device__ __forceinline__ uint32_t workgroup_exclusive_scan(uint32_t mine, uint
 
 // ---- count: words per chunk, sums per group -------------------------------------------------------
 // Sixteen lanes share a chunk: a wave reads four consecutive chunks, 1 KiB, with one 16-byte load per lane --
-// whole cache lines, each fetched once -- and does so for its 64 chunks in sixteen rounds.  (A thread per chunk,
+// whole cache lines, each fetched once -- and does so for its 16 chunks in four rounds, all in flight at once.  (A thread per chunk,
 // walking its 256 bytes alone, asks for 16 bytes of every line its wave touches in a round and finds the rest
 // gone from the cache when it comes back: measured, that read 1.2 times the input here and 2.9 times in the
 // write pass.)
@@ -416,19 +430,18 @@ struct PieceOfChunk {                              // what a lane reads in one r
     uint32_t have;                                 // symbols of its 16 that exist: 0 .. 16
     uint64_t first;                                // index of the first of them
 };
-__device__ __forceinline__ PieceOfChunk piece_of(const Layout& lay, uint32_t group, uint32_t wave, uint32_t round, uint32_t lane)
+__device__ __forceinline__ PieceOfChunk piece_of(const Layout& lay, uint32_t chunk0, uint32_t lane)     // the round's first chunk
 {
     PieceOfChunk p;
-    p.chunk = group * kThreads + wave * 64u + round * 4u + (lane >> 4);
+    p.chunk = chunk0 + (lane >> 4);
     p.first = (uint64_t)p.chunk * kChunk + (lane & 15u) * 16u;
     p.have = p.first >= lay.n ? 0u : lay.n - p.first < 16u ? (uint32_t)(lay.n - p.first) : 16u;
     return p;
 }
 // does every lane of the wave have all its 16 symbols in this round?  (wave-uniform, from scalar values)
-__device__ __forceinline__ bool round_is_whole(const Layout& lay, uint32_t group, uint32_t wave, uint32_t round)
+__device__ __forceinline__ bool round_is_whole(const Layout& lay, uint32_t chunk0)
 {
-    const uint64_t end = ((uint64_t)group * kThreads + wave * 64u + round * 4u + 4u) * kChunk;
-    return end <= lay.n;
+    return ((uint64_t)chunk0 + 4u) * kChunk <= lay.n;
 }
 // sum over the 16 lanes that share a chunk, in the last of them (row shifts: a row of the wave is those 16 lanes)
 __device__ __forceinline__ uint32_t sum_to_lane_15_of_row(uint32_t v)
@@ -440,58 +453,72 @@ __device__ __forceinline__ uint32_t sum_to_lane_15_of_row(uint32_t v)
     return v;                                                 // inclusive prefix inside the row
 }
 
-__global__ __launch_bounds__(kThreads) void huffman_count_kernel(const Batch<Layout> batch)
+__global__ __launch_bounds__(kGroupThreads) void huffman_count_kernel(const Batch<Layout> batch)
 {
     uint32_t group;
     const Layout lay = resolved(batch.item[batch_item(batch, blockIdx.x, group)]);
     if (group >= lay.groups) return;                          // workgroup-uniform: past the real extent
     __shared__ uint8_t len[256];
-    __shared__ uint32_t lds[4];
-    len[threadIdx.x] = (uint8_t)(lay.table[threadIdx.x] & 0xffu);
-    __syncthreads();
+    __shared__ uint32_t lds[kWaves];
+    if (threadIdx.x < 256u) len[threadIdx.x] = (uint8_t)(lay.table[threadIdx.x] & 0xffu);
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wave_chunk = group * kGroup + wave * (4u * kRounds);
     uint32_t closed = 0;                                      // words of the chunks this lane closed (lanes 15, 31, 47, 63)
-    constexpr int kRoundsInFlight = 8;
-    for (uint32_t round0 = 0; round0 < 16u; round0 += kRoundsInFlight) {
-        uint32_t word[kRoundsInFlight][4];
+    uint32_t word[kRounds][4];
 #pragma unroll
-        for (int k = 0; k < kRoundsInFlight; ++k) {
-            const PieceOfChunk p = piece_of(lay, group, wave, round0 + k, lane);
-            if (round_is_whole(lay, group, wave, round0 + k)) {
-                const u32x4 w = *reinterpret_cast<const u32x4*>(lay.in + p.first);
-                word[k][0] = w.x; word[k][1] = w.y; word[k][2] = w.z; word[k][3] = w.w;
-            } else {
-                word[k][0] = word[k][1] = word[k][2] = word[k][3] = 0u;
-                if (p.have) load_symbols(lay.in, p.first, p.have, word[k]);
-            }
+    for (int k = 0; k < kRounds; ++k) {
+        const uint32_t chunk0 = wave_chunk + 4u * k;
+        const PieceOfChunk p = piece_of(lay, chunk0, lane);
+        if (round_is_whole(lay, chunk0)) {
+            const u32x4 w = *reinterpret_cast<const u32x4*>(lay.in + p.first);
+            word[k][0] = w.x; word[k][1] = w.y; word[k][2] = w.z; word[k][3] = w.w;
+        } else {
+            word[k][0] = word[k][1] = word[k][2] = word[k][3] = 0u;
+            if (p.have) load_symbols(lay.in, p.first, p.have, word[k]);
         }
+    }
+    __syncthreads();                                          // `len`, once the symbols have been asked for
 #pragma unroll
-        for (int k = 0; k < kRoundsInFlight; ++k) {
-            const PieceOfChunk p = piece_of(lay, group, wave, round0 + k, lane);
-            uint32_t bits = 0;
-            if (round_is_whole(lay, group, wave, round0 + k)) {
+    for (int k = 0; k < kRounds; ++k) {
+        const uint32_t chunk0 = wave_chunk + 4u * k;
+        const PieceOfChunk p = piece_of(lay, chunk0, lane);
+        uint32_t bits = 0;
+        if (round_is_whole(lay, chunk0)) {
 #pragma unroll
-                for (int j = 0; j < 16; ++j) bits += len[(word[k][j >> 2] >> (8 * (j & 3))) & 0xffu];
-            } else {
+            for (int j = 0; j < 16; ++j) bits += len[(word[k][j >> 2] >> (8 * (j & 3))) & 0xffu];
+        } else {
 #pragma unroll
-                for (int j = 0; j < 16; ++j)
-                    if ((uint32_t)j < p.have) bits += len[(word[k][j >> 2] >> (8 * (j & 3))) & 0xffu];
-            }
-            const uint32_t of_chunk = sum_to_lane_15_of_row(bits);
-            if ((lane & 15u) == 15u && p.chunk < lay.chunks) {
-                const uint32_t words = (of_chunk + 31u) >> 5;
-                lay.offsets[p.chunk] = words;                 // becomes the chunk's offset in the write pass
-                closed += words;
-            }
+            for (int j = 0; j < 16; ++j)
+                if ((uint32_t)j < p.have) bits += len[(word[k][j >> 2] >> (8 * (j & 3))) & 0xffu];
+        }
+        const uint32_t of_chunk = sum_to_lane_15_of_row(bits);
+        if ((lane & 15u) == 15u && p.chunk < lay.chunks) {
+            const uint32_t words = (of_chunk + 31u) >> 5;
+            lay.offsets[p.chunk] = words;                     // becomes the chunk's offset in the write pass
+            closed += words;
         }
     }
     const uint32_t of_wave = wave_inclusive_scan(closed);
     if (lane == 63u) lds[wave] = of_wave;
     __syncthreads();
-    if (threadIdx.x == 0) lay.group_sums[group] = lds[0] + lds[1] + lds[2] + lds[3];
+    if (threadIdx.x == 0) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum += lds[w];
+        lay.group_sums[group] = sum;
+    }
 }
 
-// ---- scan of the group sums (in place, exclusive); the stream's size --------------------------------
+// ---- scan of the group sums (in place, exclusive) of long streams; the stream's size ------------------
+// `words`: of the stream's payload; one thread
+__device__ __forceinline__ void leave_size(const Layout& lay, uint32_t words)
+{
+    const uint64_t bytes = 256u + 4ull * (lay.chunks + 1ull) + 4ull * words;
+    lay.offsets[lay.chunks] = words;
+    lay.totals[0] = bytes;
+    const StoredForm& f = lay.stored;
+    if (f.header) f.header[6] = f.fixed_bytes + f.header[0] * f.value_size + bytes;
+}
 __global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Batch<Layout> batch)
 {
     const Layout lay = resolved(batch.item[blockIdx.x]);
@@ -505,13 +532,7 @@ __global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Batch<Layo
         if (i < lay.groups) lay.group_sums[i] = carry + before;
         carry += total;
     }
-    if (threadIdx.x == 0) {
-        const uint64_t bytes = 256u + 4ull * (lay.chunks + 1ull) + 4ull * carry;
-        lay.offsets[lay.chunks] = carry;
-        lay.totals[0] = bytes;
-        const StoredForm& f = lay.stored;
-        if (f.header) f.header[6] = f.fixed_bytes + f.header[0] * f.value_size + bytes;
-    }
+    if (threadIdx.x == 0) leave_size(lay, carry);
 }
 
 // ---- write: offsets and payload -------------------------------------------------------------------
@@ -524,39 +545,63 @@ __global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Batch<Layo
 // (24 bits per symbol), so the area fits whatever the stream holds.
 constexpr int kRoundWordsMax = 4 * kChunkWordsMax;          // 768 words per wave
 
-__global__ __launch_bounds__(kThreads) void huffman_write_kernel(const Batch<Layout> batch)
+template <bool SCANNED>
+__global__ __launch_bounds__(kGroupThreads) void huffman_write_kernel(const Batch<Layout> batch)
 {
     uint32_t group;
     const Layout lay = resolved(batch.item[batch_item(batch, blockIdx.x, group)]);
-    if (group >= lay.groups) return;                          // workgroup-uniform: past the real extent
-    __shared__ uint32_t table[256];
-    __shared__ uint32_t lds[4];
-    __shared__ uint32_t chunk_at[kThreads + 4];               // word offset of every chunk inside the group's slice; [256..]: the total
-    __shared__ uint32_t area[kThreads / 64][kRoundWordsMax + 4];
-    table[threadIdx.x] = lay.table[threadIdx.x];
-    {
-        const uint32_t chunk = group * kThreads + threadIdx.x;
-        const bool live = chunk < lay.chunks;
-        const uint32_t words = live ? lay.offsets[chunk] : 0u;
-        uint32_t total;
-        const uint32_t before = workgroup_exclusive_scan(words, lds, &total);   // also the barrier for `table`
-        if (live) lay.offsets[chunk] = lay.group_sums[group] + before;
-        chunk_at[threadIdx.x] = before;
-        if (threadIdx.x < 4u) chunk_at[kThreads + threadIdx.x] = total;
+    if (group >= lay.groups) {                                // workgroup-uniform: past the real extent
+        if (!SCANNED && lay.groups == 0u && group == 0u && threadIdx.x == 0) leave_size(lay, 0u);
+        return;
     }
+    __shared__ uint32_t table[256];
+    __shared__ uint32_t lds[4], below[kWaves];
+    __shared__ uint32_t chunk_at[kGroup + 4];                 // word offset of every chunk inside the group's slice; [256..]: the total
+    __shared__ uint32_t area[kWaves][kRoundWordsMax + 4];
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the first four waves have a thread per chunk of the group, and per symbol
+    const uint32_t chunk = group * kGroup + threadIdx.x;
+    const bool live = threadIdx.x < (uint32_t)kGroup && chunk < lay.chunks;
+    const uint32_t words = live ? lay.offsets[chunk] : 0u;
+    uint32_t before_group = 0;
+    if constexpr (!SCANNED) {
+        for (uint32_t g = threadIdx.x; g < group; g += kGroupThreads) before_group += lay.group_sums[g];
+    }
+    if (threadIdx.x < 256u) table[threadIdx.x] = lay.table[threadIdx.x];
+    const uint32_t upto = wave_inclusive_scan(words);
+    if (wave < 4u && lane == 63u) lds[wave] = upto;
+    if constexpr (!SCANNED) {
+        const uint32_t of_wave = wave_inclusive_scan(before_group);
+        if (lane == 63u) below[wave] = of_wave;
+    }
     uint32_t* mine = area[wave];
     for (uint32_t w = lane; w < (uint32_t)kRoundWordsMax + 4u; w += 64u) mine[w] = 0u;
     __syncthreads();
-    uint32_t* slice = lay.payload + lay.group_sums[group];
-    for (uint32_t round = 0; round < 16u; ++round) {
-        const PieceOfChunk p = piece_of(lay, group, wave, round, lane);
-        const uint32_t chunk0 = wave * 64u + round * 4u;      // of the group: the first of this round's four
+    uint32_t base = 0;                                        // words of the groups before this one
+    if constexpr (SCANNED) base = lay.group_sums[group];
+    else {
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) base += below[w];
+    }
+    if (wave < 4u) {
+        uint32_t before = upto - words;
+        for (uint32_t w = 0; w < wave; ++w) before += lds[w];
+        if (live) lay.offsets[chunk] = base + before;
+        chunk_at[threadIdx.x] = before;
+        if (threadIdx.x < 4u) chunk_at[kGroup + threadIdx.x] = lds[0] + lds[1] + lds[2] + lds[3];
+    }
+    if (!SCANNED && group + 1u == lay.groups && threadIdx.x == 0) leave_size(lay, base + lds[0] + lds[1] + lds[2] + lds[3]);
+    __syncthreads();
+    uint32_t* slice = lay.payload + base;
+    for (uint32_t round = 0; round < (uint32_t)kRounds; ++round) {
+        const uint32_t chunk0 = wave * (4u * kRounds) + round * 4u;              // of the group: the first of this round's four
+        const PieceOfChunk p = piece_of(lay, group * kGroup + chunk0, lane);
+        const bool whole = round_is_whole(lay, group * kGroup + chunk0);
         const uint32_t run_at = chunk_at[chunk0], run = chunk_at[chunk0 + 4u] - run_at;   // wave-uniform
         if (run == 0u) break;                                 // nothing from here on (the stream has ended)
         // the lane's codes
         uint32_t word[4] = {0u, 0u, 0u, 0u};
-        if (round_is_whole(lay, group, wave, round)) {
+        if (whole) {
             const u32x4 w = *reinterpret_cast<const u32x4*>(lay.in + p.first);
             word[0] = w.x; word[1] = w.y; word[2] = w.z; word[3] = w.w;
         } else if (p.have) {
@@ -564,7 +609,7 @@ __global__ __launch_bounds__(kThreads) void huffman_write_kernel(const Batch<Lay
         }
         uint32_t e[16];                                       // code << 8 | length; a symbol that does not exist: length 0
         uint32_t bits = 0;
-        if (round_is_whole(lay, group, wave, round)) {
+        if (whole) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) e[j] = table[(word[j >> 2] >> (8 * (j & 3))) & 0xffu];
         } else {
@@ -1107,7 +1152,7 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
 
 bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 uint64_t chunks_of(uint64_t n) { return (n + kChunk - 1) / kChunk; }
-uint64_t groups_of(uint64_t n) { return (chunks_of(n) + kThreads - 1) / kThreads; }
+uint64_t groups_of(uint64_t n) { return (chunks_of(n) + kGroup - 1) / kGroup; }
 constexpr uint64_t kMaxSymbols = ((uint64_t)1 << 32) - 1;
 
 }  // namespace
@@ -1173,6 +1218,7 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
         // the same streams three times: a workgroup each | by histogram workgroups | by groups of chunks
         Batch<Layout> each, hist, grouped;
         reset(each); reset(hist); reset(grouped);
+        uint32_t most = 0;                                    // groups of a stream
         while (i < count && each.count < kBatch) {
             const fh_huffman_encode_item& it = items[i];
             Layout lay;
@@ -1199,16 +1245,22 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
             }
             push(each, lay, 1);
             push(hist, lay, lay.hist_blocks);
-            push(grouped, lay, lay.groups);
+            push(grouped, lay, lay.groups > 0 ? lay.groups : 1);       // one writes an empty stream's size
+            if (lay.groups > most) most = lay.groups;
             ++i;
         }
         seal(each); seal(hist); seal(grouped);
         if (!stored) launch(huffman_clear_kernel, each, (uint32_t)each.count, s);
         launch(huffman_histogram_kernel, hist, hist.block_start[hist.count], s, kHistThreads);
         launch(huffman_code_kernel, each, (uint32_t)each.count, s, kCodeThreads);
-        launch(huffman_count_kernel, grouped, grouped.block_start[grouped.count], s);
-        launch(huffman_scan_kernel, each, (uint32_t)each.count, s);
-        launch(huffman_write_kernel, grouped, grouped.block_start[grouped.count], s);
+        const uint32_t all = grouped.block_start[grouped.count];
+        launch(huffman_count_kernel, grouped, all, s, kGroupThreads);
+        if (most > kUnscannedGroups) {
+            launch(huffman_scan_kernel, each, (uint32_t)each.count, s);
+            launch(huffman_write_kernel<true>, grouped, all, s, kGroupThreads);
+        } else {
+            launch(huffman_write_kernel<false>, grouped, all, s, kGroupThreads);
+        }
     }
     if (count == 0) return FH_OK;
     return hipGetLastError() == hipSuccess ? FH_OK : FH_ERR_LAUNCH;

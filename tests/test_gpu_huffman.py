@@ -70,6 +70,16 @@ def test_streams_long_enough_that_a_workgroup_decodes_several_groups(api, spread
     _check(api, data.astype(np.uint8), f"spread {spread}")
 
 
+@pytest.mark.parametrize("more", [0, 1])
+def test_streams_on_both_sides_of_the_scan(api, more):
+    # up to 4096 groups of 65536 symbols every workgroup of the write pass adds up the group sums before its own, beyond
+    # that a scan kernel does; the stream's groups differ in size, so a sum left out or taken twice moves the payload
+    rng = np.random.default_rng(7)
+    piece = np.clip(np.rint(rng.normal(128, 3.0, 99991)), 0, 255).astype(np.uint8)
+    data = np.resize(piece, 4096 * 65536 + more)
+    _check(api, data, f"{data.size} symbols")
+
+
 @pytest.mark.parametrize("kind", ["deep", "flat", "nearly flat"])
 @pytest.mark.parametrize("n", [5, 16411, 256 * 488 * 256, 256 * 488 * 256 + 3])
 def test_decoder_forms(api, n, kind):
