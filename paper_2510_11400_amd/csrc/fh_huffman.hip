@@ -85,7 +85,7 @@ struct Layout {                                    // where things are in the st
     uint32_t* offsets;                             // [chunks + 1]
     uint32_t* payload;
     uint32_t* hist;                                // workspace: [256]
-    uint32_t* table;                               // workspace: [256], code << 8 | length
+    uint32_t* table;                               // workspace: [256], the code from the top bit down | its length
     uint32_t* group_sums;                          // workspace: [groups]
     uint64_t* totals;                              // {stream bytes used, payload bits}
     const uint8_t* in;
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kCodeThreads) void huffman_code_kernel(const Batch<
         if (my_length) for (uint32_t w = 0; w < wave; ++w) before += in_wave[w][my_length];
         const uint32_t code = my_length ? first_code[my_length] + before : 0u;
         lay.len[s] = (uint8_t)my_length;
-        lay.table[s] = (code << 8) | my_length;
+        lay.table[s] = my_length ? (code << (32u - my_length)) | my_length : 0u;
     }
 }
 
@@ -543,7 +543,10 @@ __global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Batch<Layo
 // chunks are one contiguous piece of the payload (each starts on a word); the wave copies it out with consecutive
 // lanes on consecutive words and leaves the area cleared for the next round.  A chunk is at most 192 words
 // (24 bits per symbol), so the area fits whatever the stream holds.
+// What bounds the pass is the vector instructions of a lane's chain: with two symbols a step, a half of the steps, 51 MB
+// of index streams take 27.9 us, 32.4 with one; 20 and 8 MB 17.0 and 10.0, with one 20.0 and 11.4.
 constexpr int kRoundWordsMax = 4 * kChunkWordsMax;          // 768 words per wave
+constexpr uint32_t kCodeMask = ~(uint32_t)0xffu;            // of an entry of the table: codes have 24 bits at most
 
 template <bool SCANNED>
 __global__ __launch_bounds__(kGroupThreads) void huffman_write_kernel(const Batch<Layout> batch)
@@ -593,22 +596,29 @@ __global__ __launch_bounds__(kGroupThreads) void huffman_write_kernel(const Batc
     if (!SCANNED && group + 1u == lay.groups && threadIdx.x == 0) leave_size(lay, base + lds[0] + lds[1] + lds[2] + lds[3]);
     __syncthreads();
     uint32_t* slice = lay.payload + base;
+    const auto ask = [&](uint32_t round, uint32_t (&to)[4]) {
+        const uint32_t first = group * kGroup + wave * (4u * kRounds) + round * 4u;
+        const PieceOfChunk p = piece_of(lay, first, lane);
+        if (round_is_whole(lay, first)) {
+            const u32x4 w = *reinterpret_cast<const u32x4*>(lay.in + p.first);
+            to[0] = w.x; to[1] = w.y; to[2] = w.z; to[3] = w.w;
+        } else {
+            to[0] = to[1] = to[2] = to[3] = 0u;
+            if (p.have) load_symbols(lay.in, p.first, p.have, to);
+        }
+    };
+    uint32_t ahead[4];
+    ask(0, ahead);
     for (uint32_t round = 0; round < (uint32_t)kRounds; ++round) {
         const uint32_t chunk0 = wave * (4u * kRounds) + round * 4u;              // of the group: the first of this round's four
         const PieceOfChunk p = piece_of(lay, group * kGroup + chunk0, lane);
         const bool whole = round_is_whole(lay, group * kGroup + chunk0);
         const uint32_t run_at = chunk_at[chunk0], run = chunk_at[chunk0 + 4u] - run_at;   // wave-uniform
         if (run == 0u) break;                                 // nothing from here on (the stream has ended)
-        // the lane's codes
-        uint32_t word[4] = {0u, 0u, 0u, 0u};
-        if (whole) {
-            const u32x4 w = *reinterpret_cast<const u32x4*>(lay.in + p.first);
-            word[0] = w.x; word[1] = w.y; word[2] = w.z; word[3] = w.w;
-        } else if (p.have) {
-            load_symbols(lay.in, p.first, p.have, word);
-        }
-        uint32_t e[16];                                       // code << 8 | length; a symbol that does not exist: length 0
-        uint32_t bits = 0;
+        // the lane's codes; those of the next round are asked for before these are coded
+        const uint32_t word[4] = {ahead[0], ahead[1], ahead[2], ahead[3]};
+        if (round + 1u < (uint32_t)kRounds) ask(round + 1u, ahead);
+        uint32_t e[16];                                       // a symbol that does not exist: 0
         if (whole) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) e[j] = table[(word[j >> 2] >> (8 * (j & 3))) & 0xffu];
@@ -616,25 +626,39 @@ __global__ __launch_bounds__(kGroupThreads) void huffman_write_kernel(const Batc
 #pragma unroll
             for (int j = 0; j < 16; ++j) e[j] = (uint32_t)j < p.have ? table[(word[j >> 2] >> (8 * (j & 3))) & 0xffu] : 0u;
         }
+        // two symbols as one code of up to 32 bits, from the top bit down: half the steps of the chain below
+        uint32_t code[8], length[8], bits = 0, longest = 0;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) bits += e[j] & 0xffu;
+        for (int j = 0; j < 8; ++j) {
+            length[j] = (e[2 * j] + e[2 * j + 1]) & 0xffu;
+            code[j] = (e[2 * j] & kCodeMask) | ((e[2 * j + 1] & kCodeMask) >> (e[2 * j] & 31u));
+            bits += length[j];
+            longest = longest > length[j] ? longest : length[j];
+        }
         // where the lane's bits start: its chunk's word offset inside the round, then the lanes before it in the chunk
         const uint32_t start = ((chunk_at[chunk0 + (lane >> 4)] - run_at) << 5) + (sum_to_lane_15_of_row(bits) - bits);
-        uint32_t at = start >> 5;                             // the word being filled
-        uint32_t filled = start & 31u;                        // bits of it that precede this lane's (left as zeros here)
-        uint64_t acc = 0;                                     // the low `filled` bits are pending, oldest on top
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const uint32_t l = e[j] & 0xffu;
-            acc = (acc << l) | (e[j] >> 8);
+        uint32_t* at = mine + (start >> 5);                   // the word being filled
+        uint32_t filled = start & 31u;                        // bits of it that are taken
+        uint32_t now = 0;                                     // it, as far as it is this lane's
+        const auto put = [&](uint32_t c, uint32_t l) {        // l <= 32
+            now |= c >> filled;
+            const uint32_t rest = __builtin_amdgcn_alignbit(c, 0u, filled);      // c << (32 - filled); 0 when filled is 0
             filled += l;
-            if (filled >= 32u) {                              // filled < 32 + 24 before this
-                filled -= 32u;
-                atomicOr(&mine[at], (uint32_t)(acc >> filled));
+            if (filled >= 32u) {
+                atomicOr(at, now);
                 ++at;
+                now = rest;
+                filled -= 32u;
             }
+        };
+        if (__builtin_amdgcn_ballot_w64(longest > 32u) == 0u) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) put(code[j], length[j]);
+        } else {                                              // some lane's two codes together do not fit a word
+#pragma unroll
+            for (int j = 0; j < 16; ++j) put(e[j] & kCodeMask, e[j] & 0xffu);
         }
-        if (filled) atomicOr(&mine[at], (uint32_t)(acc << (32u - filled)));      // the rest, zero-padded to the word's end
+        if (filled) atomicOr(at, now);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // LDS operations of one wave complete in order
         for (uint32_t w = lane; w < run; w += 64u) {
             slice[run_at + w] = mine[w];
