@@ -26,7 +26,16 @@
 // of its block in registers.
 // Apart from one division and one multiplication per element in that mode, everything here is
 // integer and byte work; results do not depend on launch geometry.
+// All three passes that touch the maps are bound by vector instructions (400, 600 and 830 per wave of 64 4 x 4 tiles with
+// an error bound).  93 MB of fp32 maps, count, write and read: 20.6, 33.1 and 36.5 us with the general division, a
+// byte of LDS at a time and three 64-bit sums per tile, 18.6, 29.7 and 34.0 now; 47 MB of bf16: 21.8, 32.7 and 38.0, now 17.4, 26.5
+// and 34.5.  (The dense tiles dealt to the first threads of the read pass, so that a wave has tiles of one kind, save a
+// third of its instructions and cost more in stores of single tile rows: 36 us.)
 #include "../../include/fedhybrid.h"
+
+#include <float.h>
+
+#include <cmath>
 
 #include "fh_batch.hpp"
 #include "fh_channels.hpp"
@@ -40,7 +49,6 @@ template <int N> struct Group {
     static constexpr int kTiles = N == 8 ? 128 : 256;
     static constexpr int kWaves = kTiles / 64;
 };
-constexpr int kMaxWaves = 4;
 constexpr int kScanThreads = 512;
 constexpr uint64_t kStreamedFrom = (uint64_t)128 << 20;    // bytes of maps in a launch from which the first pass streams
 constexpr uint32_t kSelfScanLimit = 2048;          // up to this many workgroups each adds up the sums before it
@@ -53,13 +61,19 @@ __device__ __forceinline__ Sums operator+(const Sums& a, const Sums& b)
     return Sums{a.values + b.values, a.index_bytes + b.index_bytes, a.sparse_tiles + b.sparse_tiles};
 }
 
+struct Step {
+    float   two_eps;           // 0: no lattice
+    int32_t down;              // two_eps * 2^down is in [1, 2)
+    float   inverse;           // 1 / (two_eps * 2^down), correctly rounded
+};
+
 struct MapShape {
     const void* x;             // [maps][h][w] (encode: input; decode: output)
     uint32_t h, w, n;
     uint32_t tiles;            // maps * BH * BW
     ExactDiv bw, bh;           // tile index -> (map, tile row, tile column)
     uint32_t BW, BH;
-    float two_eps;             // lattice step of the predictive form of dense tiles; 0 = verbatim
+    Step step;                 // lattice step of the predictive form of dense tiles; 0 = verbatim
     uint32_t rows_are_vectors; // w is a multiple of n and the maps are 16-byte aligned: a tile row is one
                                // aligned vector of n elements (every tile is n wide)
 };
@@ -108,6 +122,15 @@ __device__ __forceinline__ Sums tile_sums(uint32_t info, const TilePos& t, bool 
     return Sums{count, t.rows + 1u + count, 1u};
 }
 
+// the same, values and index bytes in one word (place_tiles)
+__device__ __forceinline__ uint32_t tile_packed(uint32_t info, const TilePos& t, bool predictive)
+{
+    const uint32_t claimed = info & 0x7fu, room = t.rows * t.cols;
+    const uint32_t count = claimed < room ? claimed : room;
+    const uint32_t index_bytes = (info & 0x80u) ? (predictive ? room : 0u) : t.rows + 1u + count;
+    return count | (index_bytes << 16);
+}
+
 template <typename T> __device__ __forceinline__ uint32_t bits_of(T v);
 template <> __device__ __forceinline__ uint32_t bits_of<uint32_t>(uint32_t v) { return v; }
 template <> __device__ __forceinline__ uint32_t bits_of<uint16_t>(uint16_t v) { return v; }
@@ -120,19 +143,36 @@ template <typename Bits> __device__ __forceinline__ Bits stored_of(float f);
 template <> __device__ __forceinline__ uint32_t stored_of<uint32_t>(float f) { return __builtin_bit_cast(uint32_t, f); }
 template <> __device__ __forceinline__ uint16_t stored_of<uint16_t>(float f) { return (uint16_t)bf16_bits(f); }
 
-// the lattice point of x (0 when it has none) and whether it has one
-__device__ __forceinline__ int32_t lattice(float x, float two_eps, bool& ok)
+// x / two_eps, correctly rounded where it is 1/4 or more.  x and the step are scaled alike, by a power of two that takes
+// the step into [1, 2).  With y the correctly rounded reciprocal of d, x * y misses x / d by two units in the
+// last place at most; a residual step leaves it within one, and the next one rounds it correctly (Markstein, "Computation
+// of elementary functions on the IBM RISC System/6000 processor", 1990): six instructions where the general
+// division takes eleven.  Below 1/4 a residual or the scaled x may be inexact, but the lattice point is 0 whatever the
+// last places are; above the largest float, and for x that is no number, the steps give infinities and
+// NaN, which have no lattice point either.
+__device__ __forceinline__ float over_step(float x, const Step& s)
 {
-    const float t = x / two_eps;                              // IEEE division
+    const float scaled = __builtin_ldexpf(x, s.down), step = __builtin_ldexpf(__builtin_fminf(s.two_eps, FLT_MAX), s.down);
+    const float rough = scaled * s.inverse;
+    const float near = __builtin_fmaf(__builtin_fmaf(-rough, step, scaled), s.inverse, rough);
+    return __builtin_fmaf(__builtin_fmaf(-near, step, scaled), s.inverse, near);
+}
+// the lattice point of x (0 when it has none) and whether it has one
+__device__ __forceinline__ int32_t lattice(float x, const Step& s, bool& ok)
+{
+    const float t = over_step(x, s);
     ok = __builtin_fabsf(t) < 0x1p22f;                        // false for NaN and infinities
-    return ok ? (int32_t)__builtin_rintf(t) : 0;
+    // Adding 1.5 * 2^23 rounds to an integer with ties to even (the sum lies in [2^23, 2^24)) and leaves it in the
+    // low bits, behind those of 1.5 * 2^23 itself.
+    constexpr float kMagic = 0x1.8p23f;
+    return ok ? __builtin_bit_cast(int32_t, t + kMagic) - __builtin_bit_cast(int32_t, kMagic) : 0;
 }
 
 // Code bytes of a tile (0 = outlier) and the number of outliers; elements outside the tile
 // (zero padding) are never counted.  q(r,c) is predicted by q(r,c-1) + q(r-1,c) - q(r-1,c-1)
-// with zeros outside the tile.
+// with zeros outside the tile.  With d what the prediction misses, a code is d + 128 where that lies in 1 .. 255.
 template <typename Bits, int N>
-__device__ __forceinline__ uint32_t lorenzo_codes(const Bits (&e)[N][N], const TilePos& t, float two_eps,
+__device__ __forceinline__ uint32_t lorenzo_codes(const Bits (&e)[N][N], const TilePos& t, const Step& step,
                                                   uint8_t (&code)[N][N])
 {
     int32_t q[N][N];
@@ -142,12 +182,12 @@ __device__ __forceinline__ uint32_t lorenzo_codes(const Bits (&e)[N][N], const T
 #pragma unroll
         for (int c = 0; c < N; ++c) {
             bool ok;
-            q[r][c] = lattice(value_of<Bits>(e[r][c]), two_eps, ok);
+            q[r][c] = lattice(value_of<Bits>(e[r][c]), step, ok);
             const int32_t left = c > 0 ? q[r][c - 1] : 0, up = r > 0 ? q[r - 1][c] : 0;
             const int32_t diag = (r > 0 && c > 0) ? q[r - 1][c - 1] : 0;
-            const int32_t d = q[r][c] - (left + up - diag);
-            const bool coded = ok && d > -128 && d < 128;
-            code[r][c] = coded ? (uint8_t)(d + 128) : (uint8_t)0;
+            const uint32_t u = (uint32_t)((q[r][c] - left) + (diag - up) + 128);
+            const bool coded = ok && u - 1u < 255u;
+            code[r][c] = coded ? (uint8_t)u : (uint8_t)0;
             if (!coded && r < (int)t.rows && c < (int)t.cols) ++outliers;
         }
     }
@@ -180,42 +220,76 @@ __device__ __forceinline__ Sums wave_total(const Sums32& inclusive)
                 (uint32_t)__builtin_amdgcn_readlane((int)inclusive.sparse_tiles, 63)};
 }
 
-// the waves' totals through LDS: what the waves before this one add up to, and all of them
-template <int WAVES>
-__device__ __forceinline__ Sums across_waves(const Sums& wave_sum, uint64_t* lds /* [3 * WAVES] */, Sums* all)
+// What a workgroup's tiles write fits one word: values in the low half, index bytes in the high one.  One scan serves
+// both, and the sums of the waves are added in scalar registers.  (As three sums of 64 bits the scan and the sums over
+// the waves were a seventh of the vector instructions of the passes that place tiles.)
+template <int N> struct Packed {
+    static_assert(Group<N>::kTiles * (N * N + N + 1) < 65536, "a workgroup's index bytes, and its values, fit 16 bits");
+};
+__device__ __forceinline__ uint32_t values_in(uint32_t packed) { return packed & 0xffffu; }
+__device__ __forceinline__ uint32_t index_bytes_in(uint32_t packed) { return packed >> 16; }
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v)
 {
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    if (lane == 0u) { lds[3 * wave] = wave_sum.values; lds[3 * wave + 1] = wave_sum.index_bytes; lds[3 * wave + 2] = wave_sum.sparse_tiles; }
+    return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
+}
+
+// Where a tile's pieces go: the workgroup's slices of the streams and the tile's place in them.
+struct Place {
+    Sums     base;                                 // of all earlier workgroups (wave-uniform); sparse_tiles only when asked for
+    uint32_t total, before;                        // packed: of the workgroup (wave-uniform), of the tiles before this thread's
+};
+template <int WAVES> struct PlaceLds {
+    uint32_t packed[WAVES];
+    Sums32   part[WAVES];
+};
+// `scanned`: wg[] holds exclusive prefixes (the scan kernel ran); otherwise it holds per-workgroup sums, of at most
+// kSelfScanLimit workgroups, and they are added up here, a workgroup's width at a time: below 2^32 together.
+template <int N, bool SPARSE_TILES>
+__device__ __forceinline__ Place place_tiles(uint32_t mine, const Sums* wg, bool scanned, uint32_t block,
+                                             PlaceLds<Group<N>::kWaves>& lds)
+{
+    constexpr int WAVES = Group<N>::kWaves;
+    static_assert(sizeof(Packed<N>) > 0 && (uint64_t)kSelfScanLimit * 65536u < ((uint64_t)1 << 32), "32 bits hold the sums");
+    const uint32_t lane = threadIdx.x & 63u, wave = uniform(threadIdx.x >> 6);
+    Place p;
+    if (scanned) p.base = wg[block];
+    const uint32_t upto = wave_inclusive_scan(mine);
+    if (lane == 63u) lds.packed[wave] = upto;
+    if (!scanned) {
+        Sums32 part = {0, 0, 0};
+        for (uint32_t i = threadIdx.x; i < block; i += WAVES * 64) {
+            part.values += (uint32_t)wg[i].values;
+            part.index_bytes += (uint32_t)wg[i].index_bytes;
+            if (SPARSE_TILES) part.sparse_tiles += (uint32_t)wg[i].sparse_tiles;
+        }
+        part.values = wave_inclusive_scan(part.values);
+        part.index_bytes = wave_inclusive_scan(part.index_bytes);
+        if (SPARSE_TILES) part.sparse_tiles = wave_inclusive_scan(part.sparse_tiles);
+        if (lane == 63u) lds.part[wave] = part;
+    }
     __syncthreads();
-    Sums before = {0, 0, 0}, total = {0, 0, 0};
+    uint32_t before = 0;
+    p.total = 0;
 #pragma unroll
     for (int v = 0; v < WAVES; ++v) {
-        const Sums w = {lds[3 * v], lds[3 * v + 1], lds[3 * v + 2]};
-        if ((uint32_t)v < wave) before = before + w;
-        total = total + w;
+        const uint32_t w = uniform(lds.packed[v]);
+        if ((uint32_t)v < wave) before += w;
+        p.total += w;
     }
-    __syncthreads();                                          // lds may be reused right away
-    *all = total;
-    return before;
-}
-
-// Workgroup-wide exclusive scan of what each thread's tile writes.
-template <int WAVES>
-__device__ __forceinline__ Sums workgroup_exclusive_scan(Sums mine, uint64_t* lds /* [3 * WAVES] */, Sums* total)
-{
-    const Sums32 own = narrow(mine), inc = wave_inclusive_scans(own);
-    const Sums before = across_waves<WAVES>(wave_total(inc), lds, total);
-    return Sums{before.values + inc.values - own.values, before.index_bytes + inc.index_bytes - own.index_bytes,
-                before.sparse_tiles + inc.sparse_tiles - own.sparse_tiles};
-}
-
-// Workgroup-wide sum; a thread's part is below 2^32 / 64.
-template <int WAVES>
-__device__ __forceinline__ Sums workgroup_sum(Sums part, uint64_t* lds /* [3 * WAVES] */)
-{
-    Sums total;
-    across_waves<WAVES>(wave_total(wave_inclusive_scans(narrow(part))), lds, &total);
-    return total;
+    p.before = before + upto - mine;
+    if (!scanned) {
+        Sums32 sum = {0, 0, 0};
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) {
+            sum.values += lds.part[v].values;
+            sum.index_bytes += lds.part[v].index_bytes;
+            if (SPARSE_TILES) sum.sparse_tiles += lds.part[v].sparse_tiles;
+        }
+        p.base = Sums{sum.values, sum.index_bytes, sum.sparse_tiles};
+    }
+    p.base = Sums{uniform(p.base.values), uniform(p.base.index_bytes), p.base.sparse_tiles};
+    return p;
 }
 
 // The tile's elements, row-major, zeros where the tile has no element.  Every load is
@@ -286,19 +360,6 @@ __device__ __forceinline__ void store_tile(Bits* out, const TilePos& t, uint32_t
 #pragma unroll
         for (int c = 0; c < N; ++c)
             if (r < (int)t.rows && c < (int)t.cols) out[(uint64_t)r * w + c] = e[r][c];
-}
-
-// What the tiles of all earlier workgroups write.  `scanned`: wg[] already holds exclusive
-// prefixes (the scan kernel ran); otherwise it holds per-workgroup sums and they are added up
-// here, a workgroup's width at a time.
-template <int WAVES>
-__device__ __forceinline__ Sums workgroup_base(const Sums* __restrict__ wg, bool scanned, uint32_t block,
-                                               uint64_t* lds)
-{
-    if (scanned) return wg[block];
-    Sums part = {0, 0, 0};
-    for (uint32_t i = threadIdx.x; i < block; i += WAVES * 64) part = part + wg[i];
-    return workgroup_sum<WAVES>(part, lds);
 }
 
 // ---- a workgroup's slice of a stream, staged in LDS --------------------------------------------
@@ -403,11 +464,37 @@ template <typename Bits, int N> struct Stage {
     static constexpr int kIndexBytes = Group<N>::kTiles * (N * N + N + 1) + 32;
 };
 
+// N bytes of a row to or from a stage, at any address: LDS takes words at odd addresses, and a word costs the one
+// instruction that a byte does.
+template <int N> struct RowWords { static constexpr int kBytes = N < 4 ? N : 4, kCount = N / kBytes; };
+template <int N>
+__device__ __forceinline__ void put_row(uint8_t* to, const uint8_t (&byte)[N])
+{
+    constexpr int B = RowWords<N>::kBytes;
+#pragma unroll
+    for (int k = 0; k < RowWords<N>::kCount; ++k) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int j = 0; j < B; ++j) w |= (uint32_t)byte[k * B + j] << (8 * j);
+        __builtin_memcpy(to + k * B, &w, B);
+    }
+}
+template <int N>
+__device__ __forceinline__ void get_row(const uint8_t* from, uint8_t (&byte)[N])
+{
+    constexpr int B = RowWords<N>::kBytes;
+#pragma unroll
+    for (int k = 0; k < RowWords<N>::kCount; ++k) {
+        uint32_t w = 0;
+        __builtin_memcpy(&w, from + k * B, B);
+#pragma unroll
+        for (int j = 0; j < B; ++j) byte[k * B + j] = (uint8_t)(w >> (8 * j));
+    }
+}
+
 // occupancy of a tile, bit r*N + c for element (r, c)
 template <int N> struct TileMask { typedef uint32_t type; };
 template <> struct TileMask<8> { typedef uint64_t type; };
-__device__ __forceinline__ uint32_t popcount(uint32_t m) { return (uint32_t)__builtin_popcount(m); }
-__device__ __forceinline__ uint32_t popcount(uint64_t m) { return (uint32_t)__builtin_popcountll(m); }
 
 // the elements a tile has (edge tiles are smaller than the window)
 template <int N>
@@ -430,6 +517,40 @@ template <int N>
 __device__ __forceinline__ typename TileMask<N>::type csr_mask(const uint8_t* si, const TilePos& t, uint32_t count)
 {
     typedef typename TileMask<N>::type M;
+    if constexpr (N == 4) {
+        // The same by words: a row's four candidate columns are the bytes of one word, and the byte permute turns a column
+        // into its bit by looking it up in {1, 2, 4, 8} as far as the tile has columns.
+        uint32_t rows;
+        __builtin_memcpy(&rows, si, 4);                       // entries 0 .. 3; a tile of four rows has a fifth
+        const uint32_t fifth = si[4];
+        const uint8_t* col = si + t.rows + 1;
+        const uint32_t bit_of = 0x08040201u & (uint32_t)(((uint64_t)1 << (8u * t.cols)) - 1u);
+        const uint32_t closing = t.rows >= 4u ? fifth : (rows >> (8u * t.rows)) & 0xffu;
+        uint32_t m4 = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t here = (rows >> (8 * r)) & 0xffu, next = r < 3 && r + 1 < (int)t.rows ? (rows >> (8 * (r < 3 ? r + 1 : 3))) & 0xffu : closing;
+            const uint32_t start = here < count ? here : count;
+            const uint32_t len = next > here ? next - here : 0u, left = count - start;
+            const uint32_t taken = len < left ? len : left;
+            uint32_t cols;
+            __builtin_memcpy(&cols, col + start, 4);
+            uint32_t bits = 0;                                // byte j: the bit of candidate j
+            if ((cols & 0xfcfcfcfcu) == 0u) bits = __builtin_amdgcn_perm(0u, bit_of, cols);
+            else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {                 // what follows the row's columns, or a foreign stream: bytes that name none
+                    const uint32_t c = (cols >> (8 * j)) & 0xffu;
+                    if (c < t.cols) bits |= (1u << c) << (8 * j);
+                }
+            }
+            bits = taken < 4u ? bits & ((1u << (8u * taken)) - 1u) : bits;
+            bits |= bits >> 16;
+            bits |= bits >> 8;
+            if (r < (int)t.rows) m4 |= (bits & 0xfu) << (4 * r);
+        }
+        return (M)m4;
+    }
     uint32_t rp[N + 1];
 #pragma unroll
     for (int r = 0; r <= N; ++r) rp[r] = si[r <= (int)t.rows ? r : t.rows];
@@ -461,14 +582,15 @@ template <typename Bits, int N, bool STREAM>
 __global__ __launch_bounds__(Group<N>::kTiles) void sparse_count_kernel(const Batch<Job> batch)
 {
     constexpr int T = Group<N>::kTiles, WAVES = Group<N>::kWaves;
-    __shared__ uint64_t lds[3 * kMaxWaves];
+    __shared__ uint32_t of_wave[WAVES], sparse_in_wave[WAVES];
     uint32_t block;
     const Job& job = batch.item[batch_item(batch, blockIdx.x, block)];
     const MapShape& s = job.shape;
     const float tau = job.tau;
     uint8_t* info = job.info;
     const uint32_t b = block * T + threadIdx.x;
-    Sums mine = {0, 0, 0};
+    uint32_t mine = 0;
+    bool sparse = false;
     if (b < s.tiles) {
         const TilePos t = tile_pos(s, b);
         Bits e[N][N];
@@ -481,15 +603,29 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_count_kernel(const Ba
         const uint32_t area = t.rows * t.cols;
         const float density = (float)nnz / (float)area;       // IEEE division: average pooling of the mask
         uint32_t byte = density <= tau ? nnz : (0x80u | area);
-        if ((byte & 0x80u) && s.two_eps > 0.0f) {             // dense, within the error bound: count the outliers
+        if ((byte & 0x80u) && s.step.two_eps > 0.0f) {             // dense, within the error bound: count the outliers
             uint8_t code[N][N];
-            byte = 0x80u | lorenzo_codes<Bits, N>(e, t, s.two_eps, code);
+            byte = 0x80u | lorenzo_codes<Bits, N>(e, t, s.step, code);
         }
         info[b] = (uint8_t)byte;
-        mine = tile_sums(byte, t, s.two_eps > 0.0f);
+        mine = tile_packed(byte, t, s.step.two_eps > 0.0f);
+        sparse = !(byte & 0x80u);
     }
-    const Sums total = workgroup_sum<WAVES>(mine, lds);
-    if (threadIdx.x == 0) job.wg[block] = total;
+    const uint32_t upto = wave_inclusive_scan(mine), sparse_here = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(sparse));
+    if ((threadIdx.x & 63u) == 63u) {
+        of_wave[threadIdx.x >> 6] = upto;
+        sparse_in_wave[threadIdx.x >> 6] = sparse_here;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t all = 0, tiles = 0;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) {
+            all += of_wave[v];
+            tiles += sparse_in_wave[v];
+        }
+        job.wg[block] = Sums{values_in(all), index_bytes_in(all), tiles};
+    }
 }
 
 // decode: the same sums from the info bytes.  A wave owns a group: a lane takes the tiles lane,
@@ -513,7 +649,7 @@ __global__ __launch_bounds__(64 * kGroupsPerWorkgroup) void sparse_sums_kernel(c
 #pragma unroll
     for (int j = 0; j < PER_LANE; ++j) {
         const uint32_t b = group * T + j * 64 + lane;
-        if (b < s.tiles) mine = mine + tile_sums(byte[j], tile_pos(s, b), s.two_eps > 0.0f);
+        if (b < s.tiles) mine = mine + tile_sums(byte[j], tile_pos(s, b), s.step.two_eps > 0.0f);
     }
     const Sums total = wave_total(wave_inclusive_scans(narrow(mine)));
     if (lane == 0u) job.wg[group] = total;
@@ -596,9 +732,9 @@ __global__ __launch_bounds__(kScanThreads) void sparse_scan_kernel(const Batch<J
 template <typename Bits, int N, bool STREAM>
 __global__ __launch_bounds__(Group<N>::kTiles) void sparse_write_kernel(const Batch<Job> batch)
 {
-    constexpr int T = Group<N>::kTiles, WAVES = Group<N>::kWaves;
+    constexpr int T = Group<N>::kTiles;
     typedef typename Alias<Bits>::type StagedBits;
-    __shared__ uint64_t lds[3 * kMaxWaves];
+    __shared__ PlaceLds<Group<N>::kWaves> lds;
     __shared__ __attribute__((aligned(16))) uint8_t stage_v[Stage<Bits, N>::kValueBytes];
     __shared__ __attribute__((aligned(16))) uint8_t stage_i[Stage<Bits, N>::kIndexBytes];
     uint32_t block;
@@ -612,41 +748,53 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_write_kernel(const Ba
     const bool live = b < s.tiles;
     TilePos t = {0, 1, 1};
     uint32_t byte = 0x80u;
-    Sums mine = {0, 0, 0};
+    uint32_t mine = 0;
     Bits e[N][N];
     if (live) {
         t = tile_pos(s, b);
         byte = info[b];
-        mine = tile_sums(byte, t, s.two_eps > 0.0f);
+        mine = tile_packed(byte, t, s.step.two_eps > 0.0f);
         load_tile<Bits, N, STREAM>(static_cast<const Bits*>(s.x) + t.origin, t, s.w, s.rows_are_vectors != 0u, e);
     }
-    const Sums base = workgroup_base<WAVES>(wg, scanned, block, lds);
-    Sums total;
-    const Sums before = workgroup_exclusive_scan<WAVES>(mine, lds, &total);
+    const Place place = place_tiles<N, true>(mine, wg, scanned, block, lds);
+    const Sums& base = place.base;
+    const uint32_t total_values = values_in(place.total), total_index_bytes = index_bytes_in(place.total);
     if (!scanned && totals && block == job.wg_count - 1 && threadIdx.x == 0) {
-        totals[0] = base.values + total.values;
-        totals[1] = base.index_bytes + total.index_bytes;
-        totals[2] = base.sparse_tiles + total.sparse_tiles;
-        totals[3] = (uint64_t)s.tiles - totals[2];
+        const uint64_t sparse_tiles = base.sparse_tiles + wg[block].sparse_tiles;
+        totals[0] = base.values + total_values;
+        totals[1] = base.index_bytes + total_index_bytes;
+        totals[2] = sparse_tiles;
+        totals[3] = (uint64_t)s.tiles - sparse_tiles;
     }
     // this workgroup's slices of the two streams
     Bits* value_slice = static_cast<Bits*>(job.values) + base.values;
     uint8_t* index_slice = job.indices + base.index_bytes;
     if (live) {
-        StagedBits* v = reinterpret_cast<StagedBits*>(stage_v + phase_of(value_slice)) + before.values;
-        uint8_t* idx = stage_i + phase_of(index_slice) + before.index_bytes;
-        if ((byte & 0x80u) && s.two_eps > 0.0f) {             // dense, predictive: code bytes + outliers
+        StagedBits* v = reinterpret_cast<StagedBits*>(stage_v + phase_of(value_slice)) + values_in(place.before);
+        uint8_t* idx = stage_i + phase_of(index_slice) + index_bytes_in(place.before);
+        if ((byte & 0x80u) && s.step.two_eps > 0.0f) {             // dense, predictive: code bytes + outliers
             uint8_t code[N][N];
-            lorenzo_codes<Bits, N>(e, t, s.two_eps, code);
+            lorenzo_codes<Bits, N>(e, t, s.step, code);
             uint32_t k = 0;
+            if (s.rows_are_vectors) {                         // wave-uniform: every tile is N wide, its code bytes are rows of N
 #pragma unroll
-            for (int r = 0; r < N; ++r)
+                for (int r = 0; r < N; ++r)
+                    if (r < (int)t.rows) {
+                        put_row<N>(idx + r * N, code[r]);
 #pragma unroll
-                for (int c = 0; c < N; ++c)
-                    if (r < (int)t.rows && c < (int)t.cols) {
-                        idx[r * t.cols + c] = code[r][c];
-                        if (code[r][c] == 0) v[k++] = e[r][c];
+                        for (int c = 0; c < N; ++c)
+                            if (code[r][c] == 0) v[k++] = e[r][c];
                     }
+            } else {
+#pragma unroll
+                for (int r = 0; r < N; ++r)
+#pragma unroll
+                    for (int c = 0; c < N; ++c)
+                        if (r < (int)t.rows && c < (int)t.cols) {
+                            idx[r * t.cols + c] = code[r][c];
+                            if (code[r][c] == 0) v[k++] = e[r][c];
+                        }
+            }
         } else if (byte & 0x80u) {                            // dense: the tile, row-major
 #pragma unroll
             for (int r = 0; r < N; ++r)
@@ -672,8 +820,8 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_write_kernel(const Ba
         }
     }
     __syncthreads();
-    stage_to_stream<T>(stage_v, reinterpret_cast<uint8_t*>(value_slice), (uint32_t)total.values * (uint32_t)sizeof(Bits));
-    stage_to_stream<T>(stage_i, index_slice, (uint32_t)total.index_bytes);
+    stage_to_stream<T>(stage_v, reinterpret_cast<uint8_t*>(value_slice), total_values * (uint32_t)sizeof(Bits));
+    stage_to_stream<T>(stage_i, index_slice, total_index_bytes);
 }
 
 // ---- pass 3 (decode): tiles back from the streams -------------------------------------------------
@@ -684,10 +832,10 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_write_kernel(const Ba
 template <typename Bits, int N>
 __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Batch<Job> batch)
 {
-    constexpr int T = Group<N>::kTiles, WAVES = Group<N>::kWaves;
+    constexpr int T = Group<N>::kTiles;
     typedef typename Alias<Bits>::type StagedBits;
     typedef typename TileMask<N>::type Mask;
-    __shared__ uint64_t lds[3 * kMaxWaves];
+    __shared__ PlaceLds<Group<N>::kWaves> lds;
     __shared__ __attribute__((aligned(16))) uint8_t stage_v[Stage<Bits, N>::kValueBytes];
     __shared__ __attribute__((aligned(16))) uint8_t stage_i[Stage<Bits, N>::kIndexBytes];
     uint32_t block;
@@ -701,23 +849,23 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Bat
     const bool live = b < s.tiles;
     TilePos t = {0, 1, 1};
     uint32_t byte = 0x80u;
-    Sums mine = {0, 0, 0};
+    uint32_t mine = 0;
     if (live) {
         t = tile_pos(s, b);
         byte = info[b];
-        mine = tile_sums(byte, t, s.two_eps > 0.0f);
+        mine = tile_packed(byte, t, s.step.two_eps > 0.0f);
     }
-    const Sums base = workgroup_base<WAVES>(wg, scanned, block, lds);
-    Sums total;
-    const Sums before = workgroup_exclusive_scan<WAVES>(mine, lds, &total);
+    const Place place = place_tiles<N, false>(mine, wg, scanned, block, lds);
+    const Sums& base = place.base;
+    const uint32_t values_before = values_in(place.before), index_before = index_bytes_in(place.before);
 
     // what the streams hold of this workgroup's slices
     const Bits* value_slice = static_cast<const Bits*>(job.values) + base.values;
     const uint8_t* index_slice = job.indices + base.index_bytes;
     uint64_t have_v = base.values < value_count ? value_count - base.values : 0u;
     uint64_t have_i = base.index_bytes < index_count ? index_count - base.index_bytes : 0u;
-    if (have_v > total.values) have_v = total.values;
-    if (have_i > total.index_bytes) have_i = total.index_bytes;
+    if (have_v > values_in(place.total)) have_v = values_in(place.total);
+    if (have_i > index_bytes_in(place.total)) have_i = index_bytes_in(place.total);
     {
         SliceLoads<4> of_values;
         SliceLoads<2> of_indices;
@@ -727,14 +875,15 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Bat
         slice_commit<T, 4>(of_values, stage_v, reinterpret_cast<const uint8_t*>(value_slice), value_bytes);
         slice_commit<T, 2>(of_indices, stage_i, index_slice, (uint32_t)have_i);
     }
+    const bool any = __builtin_amdgcn_ballot_w64((byte & 0x80u) && values_in(mine) != 0u) != 0u;     // dense tiles with outliers
     __syncthreads();
     if (!live) return;
 
-    const StagedBits* v = reinterpret_cast<const StagedBits*>(stage_v + phase_of(value_slice)) + before.values;
-    const uint8_t* idx = stage_i + phase_of(index_slice) + before.index_bytes;
-    const uint32_t count = mine.values;                       // the byte's count, at most the tile's elements
+    const StagedBits* v = reinterpret_cast<const StagedBits*>(stage_v + phase_of(value_slice)) + values_before;
+    const uint8_t* idx = stage_i + phase_of(index_slice) + index_before;
+    const uint32_t count = values_in(mine);                     // the byte's count, at most the tile's elements
     const uint32_t last = count > 0u ? count - 1u : 0u;       // reads of values are clamped to the tile's piece
-    const bool in_bounds = before.values + mine.values <= have_v && before.index_bytes + mine.index_bytes <= have_i;
+    const bool in_bounds = values_before + count <= (uint32_t)have_v && index_before + index_bytes_in(mine) <= (uint32_t)have_i;
     Bits* out = static_cast<Bits*>(const_cast<void*>(s.x)) + t.origin;
     Bits e[N][N];
 #pragma unroll
@@ -742,37 +891,54 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Bat
 #pragma unroll
         for (int c = 0; c < N; ++c) e[r][c] = (Bits)0;
 
-    if (in_bounds && (byte & 0x80u) && s.two_eps > 0.0f) {    // dense, predictive
+    if (in_bounds && (byte & 0x80u) && s.step.two_eps > 0.0f) {    // dense, predictive
         uint8_t code[N][N];                                   // all code bytes first (clamped addresses)
 #pragma unroll
         for (int r = 0; r < N; ++r)
 #pragma unroll
-            for (int c = 0; c < N; ++c) {
-                const uint32_t rr = r < (int)t.rows ? r : t.rows - 1, cc = c < (int)t.cols ? c : t.cols - 1;
-                code[r][c] = idx[rr * t.cols + cc];
-            }
+            for (int c = 0; c < N; ++c) code[r][c] = 0;
+        if (s.rows_are_vectors) {                             // wave-uniform: as the encoder puts them
+#pragma unroll
+            for (int r = 0; r < N; ++r) get_row<N>(idx + (r < (int)t.rows ? r : t.rows - 1) * N, code[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < N; ++r)
+#pragma unroll
+                for (int c = 0; c < N; ++c) {
+                    const uint32_t rr = r < (int)t.rows ? r : t.rows - 1, cc = c < (int)t.cols ? c : t.cols - 1;
+                    code[r][c] = idx[rr * t.cols + cc];
+                }
+        }
+        // Outliers are read, and put back on the lattice, without a branch for each: of 64 tiles some one nearly always
+        // has an outlier at any given place, and every branch then waited for LDS by itself.  A wave without any leaves
+        // that out.
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+#pragma unroll
+            for (int c = 0; c < N; ++c)
+                if (!(r < (int)t.rows && c < (int)t.cols)) code[r][c] = 128;     // no element there: no outlier, and predicts none
         int32_t q[N][N];
         uint32_t used = 0;
 #pragma unroll
-        for (int r = 0; r < N; ++r) {
+        for (int r = 0; r < N; ++r)
 #pragma unroll
             for (int c = 0; c < N; ++c) {
                 const int32_t left = c > 0 ? q[r][c - 1] : 0, up = r > 0 ? q[r - 1][c] : 0;
                 const int32_t diag = (r > 0 && c > 0) ? q[r - 1][c - 1] : 0;
-                q[r][c] = 0;
-                if (r < (int)t.rows && c < (int)t.cols) {
-                    if (code[r][c] == 0) {                    // an outlier: unchanged, and back on the lattice
-                        e[r][c] = used < count ? (Bits)v[used] : (Bits)0;
-                        ++used;
-                        bool ok;
-                        q[r][c] = lattice(value_of<Bits>(e[r][c]), s.two_eps, ok);
-                    } else {
-                        q[r][c] = left + up - diag + ((int32_t)code[r][c] - 128);
-                        e[r][c] = stored_of<Bits>((float)q[r][c] * s.two_eps);
-                    }
+                q[r][c] = left + (up - diag) + ((int32_t)code[r][c] - 128);
+                e[r][c] = stored_of<Bits>((float)q[r][c] * s.step.two_eps);
+                const bool outlier = code[r][c] == 0;         // unchanged, and back on the lattice
+                Bits kept = 0;
+                int32_t point = 0;
+                if (any) {                                    // wave-uniform
+                    if (used < count) kept = (Bits)v[used];
+                    used += outlier ? 1u : 0u;
+                    bool ok;
+                    point = lattice(value_of<Bits>(kept), s.step, ok);
                 }
+                q[r][c] = outlier ? point : q[r][c];
+                e[r][c] = outlier ? kept : e[r][c];
             }
-        }
     } else if (in_bounds) {
         // verbatim: a dense tile holds every element it has, a sparse one those its CSR structure
         // names; either way the k-th set bit of the occupancy is the k-th value of the piece
@@ -782,13 +948,15 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Bat
         } else if (count > 0u) {
             m = csr_mask<N>(idx, t, count);
         }
+        uint32_t rank = 0;
 #pragma unroll
         for (int r = 0; r < N; ++r)
 #pragma unroll
             for (int c = 0; c < N; ++c) {
-                const int p = r * N + c;
-                const uint32_t rank = popcount((Mask)(m & (((Mask)1 << p) - 1)));
-                if ((m >> p) & 1) e[r][c] = (Bits)v[rank < last ? rank : last];
+                const uint32_t here = (uint32_t)(m >> (r * N + c)) & 1u;
+                const Bits value = (Bits)v[rank < last ? rank : last];
+                e[r][c] = (Bits)(value & (Bits)(0u - here));
+                rank += here;
             }
     }
     store_tile<Bits, N>(out, t, s.w, s.rows_are_vectors != 0u, e);
@@ -816,7 +984,11 @@ MapShape make_shape(const void* x, int64_t h, int64_t w, int n, int64_t tiles, f
 {
     MapShape s;
     s.x = x;
-    s.two_eps = eps > 0.0f ? eps + eps : 0.0f;                // also 0 for NaN
+    s.step.two_eps = eps > 0.0f ? eps + eps : 0.0f;           // also 0 for NaN
+    int up = 0;
+    const float half = s.step.two_eps <= FLT_MAX ? std::frexp(s.step.two_eps, &up) : 0.5f;       // in [1/2, 1), or 0
+    s.step.down = s.step.two_eps <= FLT_MAX ? 1 - up : -1000; // all that is finite is no step at all of an infinite one
+    s.step.inverse = 1.0f / (half + half);
     s.rows_are_vectors = (w % n == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0u) ? 1u : 0u;
     s.h = (uint32_t)h; s.w = (uint32_t)w; s.n = (uint32_t)n;
     s.tiles = (uint32_t)tiles;

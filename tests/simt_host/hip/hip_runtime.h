@@ -74,6 +74,14 @@ inline uint64_t ballot(bool p)
     return m;
 }
 
+// byte k of the result is the byte of high:low that byte k of `select` names (0 .. 7; the kernels use no others)
+inline uint32_t perm(uint32_t high, uint32_t low, uint32_t select)
+{
+    const uint64_t from = ((uint64_t)high << 32) | low;
+    uint32_t r = 0;
+    for (int k = 0; k < 4; ++k) r |= (uint32_t)((from >> (8 * ((select >> (8 * k)) & 7u))) & 0xffu) << (8 * k);
+    return r;
+}
 // __builtin_amdgcn_update_dpp for the controls used here: row_shr:1..15 (0x111..0x11f), row_bcast:15 (0x142),
 // row_bcast:31 (0x143); bank mask 0xf.
 inline int update_dpp(int old, int src, int ctrl, int row_mask, int /*bank_mask*/, bool bound_ctrl)
@@ -184,6 +192,7 @@ template <typename T> inline T atomic_min(T* p, T v)
 #define __popc(x) (__builtin_popcount(x))
 #define __umulhi(a, b) ((uint32_t)(((uint64_t)(uint32_t)(a) * (uint64_t)(uint32_t)(b)) >> 32))
 #define __builtin_amdgcn_readfirstlane(v) (v)
+#define __builtin_amdgcn_perm(high, low, select) (simt::perm((high), (low), (select)))
 #define __builtin_amdgcn_alignbit(high, low, by) ((uint32_t)((((uint64_t)(uint32_t)(high) << 32) | (uint32_t)(low)) >> ((by) & 31u)))
 #define __builtin_amdgcn_readlane(v, k) (simt::readlane((v), (k)))
 #define __builtin_amdgcn_update_dpp(old, src, ctrl, rm, bm, bc) (simt::update_dpp((old), (src), (ctrl), (rm), (bm), (bc)))

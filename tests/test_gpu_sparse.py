@@ -233,6 +233,23 @@ def test_predictive_blocks_with_values_off_the_lattice(api):
         assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("eps", [1e-45, 3e-39, 1e-30, 0.02, 1.0 / 3.0, 7e20, 1.6e38, 2e38])
+def test_lattice_points_beside_the_ties_of_the_division(api, eps):
+    # the kernels divide by the step in scaled residual steps: quotients a unit or two in the last place beside a half, of
+    # every size up to the lattice's end, steps without a normal form or beyond the largest float among them
+    rng = np.random.default_rng(17)
+    maps, h, w = 64, 32, 32
+    step = f32(eps) + f32(eps) if eps < 1.7e38 else f32(np.inf)
+    k = np.floor(2.0 ** rng.uniform(0.0, 22.2, (maps, h // 4, 1, w // 4, 1))) * rng.choice([-1.0, 1.0], (maps, h // 4, 1, w // 4, 1))
+    t = k + rng.integers(-3, 4, (maps, h // 4, 4, w // 4, 4)) + rng.choice([0.0, 0.5, 0.5], (maps, h // 4, 4, w // 4, 4))
+    with np.errstate(over="ignore"):
+        x = np.clip(t * np.float64(step if np.isfinite(step) else 1e38), -3.4e38, 3.4e38).astype(f32).reshape(-1)
+    x = (x.view(np.int32) + rng.integers(-2, 3, x.size).astype(np.int32)).view(f32)
+    x[~np.isfinite(x)] = f32(1.0)
+    for n in (2, 4, 8):
+        _check(api, x, maps, h, w, n, -1.0, name="ties", eps=eps)
+
+
 def test_predictive_full_size_layer_meets_the_bound(api):
     maps, h, w, n, eps = 64 * 4, 112, 112, 8, 0.05
     x = W.salient_feature_maps(maps, h, w, seed=6, zero_level=0.0)
