@@ -8,6 +8,7 @@ no CPU fallback: if the library is missing, importing this module raises.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from dataclasses import dataclass
@@ -303,9 +304,21 @@ def _device_tensor(t: torch.Tensor, what: str) -> torch.Tensor:
     return t
 
 
+_HERE = contextlib.nullcontext()
+
+
+def _on(device: torch.device):
+    """The context in which `device` is the current one.  Entering torch.cuda.device and building a Stream object cost
+    1.4 and 2.9 us a call, a kernel on 1 MiB takes 5: nothing is entered where the device is current already, and the
+    current stream's handle is asked for as such (_stream_ptr)."""
+    return _HERE if getattr(device, "index", None) == torch._C._cuda_getDevice() else torch.cuda.device(device)
+
+
 def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    """The handle of `stream`, or of the current device's current one."""
+    if stream is not None:
+        return int(stream.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _scratch(nbytes: int, device, stream: Optional[torch.cuda.Stream]) -> torch.Tensor:
@@ -339,7 +352,7 @@ def fh_compress(x: torch.Tensor, group_size: int, bits: int, rounding="nearest",
     if packed is None or meta is None:
         packed, meta = alloc_compressed(n, group_size, bits, x.device)
     p = make_params(group_size, bits, rounding, seed, tensor_id)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(_lib.fh_compress(x.data_ptr(), _dtype_code(x), n, ctypes.byref(p),
                                 packed.data_ptr(), packed.numel() * packed.element_size(),
                                 meta.data_ptr(), meta.numel() * meta.element_size(), _stream_ptr(stream)))
@@ -358,7 +371,7 @@ def fh_decompress(packed: torch.Tensor, meta: torch.Tensor, numel: int, group_si
             meta.numel() * meta.element_size() < meta_bytes(numel, group_size):
         raise FedHybridError(7)
     p = make_params(group_size, bits)
-    with torch.cuda.device(packed.device):
+    with _on(packed.device):
         _check(_lib.fh_decompress(packed.data_ptr(), meta.data_ptr(), numel, ctypes.byref(p),
                                   _dtype_code(out), out.data_ptr(), out.numel() * out.element_size(),
                                   _stream_ptr(stream)))
@@ -375,7 +388,7 @@ def fh_roundtrip(x: torch.Tensor, group_size: int, bits: int, rounding="nearest"
     if out is None:
         out = torch.empty(n, dtype=out_dtype, device=x.device)
     p = make_params(group_size, bits, rounding, seed, tensor_id)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(_lib.fh_roundtrip(x.data_ptr(), _dtype_code(x), n, ctypes.byref(p),
                                  packed.data_ptr(), packed.numel() * packed.element_size(),
                                  meta.data_ptr(), meta.numel() * meta.element_size(),
@@ -432,7 +445,7 @@ class Batch:
     def _call(self, fn, stream) -> None:
         if self.count == 0:
             return
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(fn(self.items, self.count, _stream_ptr(stream)))
 
 
@@ -481,7 +494,7 @@ def fh_classify_channels(x: torch.Tensor, outer: int, channels: int, inner: int,
     if stats.numel() * stats.element_size() < 32 or counts.numel() * counts.element_size() < 4 * channels \
             or mask.numel() * mask.element_size() < channels:
         raise FedHybridError(7)
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(_lib.fh_classify_channels(x.data_ptr(), _dtype_code(x), outer, channels, inner, float(k_sigma),
                                          int(min_outliers), workspace.data_ptr(),
                                          workspace.numel() * workspace.element_size(),
@@ -505,7 +518,7 @@ def fh_classify_channels_static(x: torch.Tensor, outer: int, channels: int, inne
         raise ValueError("x.numel() != outer * channels * inner")
     if _nbytes(stats) < 32 or _nbytes(counts) < 4 * channels or _nbytes(mask) < channels:
         raise FedHybridError(7)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(_lib.fh_classify_channels_static(x.data_ptr(), _dtype_code(x), outer, channels, inner,
                                                 float(k_sigma), int(min_outliers), stats.data_ptr(),
                                                 counts.data_ptr(), mask.data_ptr(), _stream_ptr(stream)))
@@ -535,7 +548,7 @@ def fh_channel_slots(mask: torch.Tensor, raw_channels: int, slots: Optional[torc
     _device_tensor(slots, "slots")
     if mask.element_size() != 1 or _nbytes(slots) < 2 * channels or (used is not None and _nbytes(used) < 8):
         raise FedHybridError(7)
-    with torch.cuda.device(mask.device):
+    with _on(mask.device):
         _check(_lib.fh_channel_slots_used(mask.data_ptr(), channels, int(raw_channels), slots.data_ptr(),
                                           None if used is None else used.data_ptr(), _stream_ptr(stream)))
     return slots
@@ -554,7 +567,7 @@ def fh_channel_slots_batch(masks: Sequence[torch.Tensor], raw_channels: Sequence
         s_k = torch.empty(m.numel(), dtype=torch.int16, device=dev)
         slots.append(s_k)
         items[k] = fh_slots_item(m.data_ptr(), m.numel(), int(rc), s_k.data_ptr(), used[k:].data_ptr())
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(_lib.fh_channel_slots_batch(items, len(masks), _stream_ptr(stream)))
     return slots, [used[k:k + 1] for k in range(len(masks))]
 
@@ -580,7 +593,7 @@ def fh_compress_mixed(x: torch.Tensor, outer: int, channels: int, inner: int, sl
     if raw is None:
         raw = torch.empty(max(0, outer * raw_channels * inner), dtype=x.dtype, device=x.device)
     p = make_params(group_size, bits, rounding, seed, tensor_id)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         if rows_in_use is not None:                           # the count travels in the item struct: a batch of one
             _device_tensor(rows_in_use, "rows_in_use")
             it = fh_mixed_item(x.data_ptr(), _dtype_code(x), FH_F32, outer, channels, inner, slots.data_ptr(),
@@ -610,7 +623,7 @@ def fh_decompress_mixed(packed: torch.Tensor, meta: torch.Tensor, raw: torch.Ten
             or _nbytes(slots) < 2 * channels or _nbytes(raw) < raw_bytes(outer, raw_channels, inner, raw.dtype):
         raise FedHybridError(7)
     p = make_params(group_size, bits)
-    with torch.cuda.device(packed.device):
+    with _on(packed.device):
         if rows_in_use is not None:
             _device_tensor(rows_in_use, "rows_in_use")
             it = fh_mixed_item(None, FH_F32, _dtype_code(out), outer, channels, inner, slots.data_ptr(),
@@ -623,6 +636,86 @@ def fh_decompress_mixed(packed: torch.Tensor, meta: torch.Tensor, raw: torch.Ten
                                         outer, channels, inner, ctypes.byref(p), slots.data_ptr(),
                                         int(raw_channels), _dtype_code(out), _ptr(out), _nbytes(out),
                                         _stream_ptr(stream)))
+    return out
+
+
+class ChannelWiseStore:
+    """The stored form of one tensor on the channel-wise path -- codes, meta, slots, rows in use and raw store -- in one
+    device buffer, at `places` of it."""
+    __slots__ = ("data", "places", "numel", "outer", "channels", "inner", "raw_channels", "group_size", "bits", "raw_dtype")
+
+    def __init__(self, x: torch.Tensor, outer: int, channels: int, inner: int, raw_channels: int, group_size: int, bits: int):
+        self.numel, self.outer, self.channels, self.inner = x.numel(), outer, channels, inner
+        self.raw_channels, self.group_size, self.bits, self.raw_dtype = raw_channels, group_size, bits, x.dtype
+        sizes = (packed_bytes(self.numel, bits), meta_bytes(self.numel, group_size), 2 * channels, 8,
+                 outer * raw_channels * inner * x.element_size())
+        places, at = [], 0
+        for n in sizes:
+            places.append((at, n))
+            at += (n + 255) & ~255
+        self.places = places
+        self.data = torch.empty(max(16, at), dtype=torch.uint8, device=x.device)
+
+    @property
+    def nbytes(self) -> int:                       # codes, meta, slots and raw store
+        return sum(n for _, n in self.places) - 8
+
+    def item(self, x: Optional[torch.Tensor], out: Optional[torch.Tensor], params: fh_params) -> fh_mixed_item:
+        base = self.data.data_ptr()
+        (packed, n_packed), (meta, n_meta), (slots, _), (used, _), (raw, n_raw) = self.places
+        return fh_mixed_item(None if x is None else x.data_ptr(), FH_F32 if x is None else _dtype_code(x),
+                             FH_F32 if out is None else _dtype_code(out), self.outer, self.channels, self.inner, base + slots,
+                             self.raw_channels, base + packed, n_packed, base + meta, n_meta, base + raw, n_raw,
+                             _DT[self.raw_dtype], 0, None if out is None else out.data_ptr(),
+                             0 if out is None else _nbytes(out), params, base + used)
+
+
+def compress_channel_wise(xs: Sequence[torch.Tensor], splits, k_sigma: float, outlier_share: float, group_size: int, bits: int,
+                          rounding, seed: int, tensor_ids: Sequence[int]) -> "List[ChannelWiseStore]":
+    """Classification, slot numbering and routed quantisation of several tensors, contiguous and 16-byte
+    aligned, on the current stream; splits: (outer, channels, inner, raw_channels) of each.  The batched entry points on
+    items that are filled in directly: two buffers a tensor are allocated where the batch objects allocate eight, and
+    what only the classification needs is one buffer for all."""
+    count = len(xs)
+    if count == 0:
+        return []
+    dev = xs[0].device
+    for x, (outer, channels, inner, _) in zip(xs, splits):
+        _device_tensor(x, "x")
+        if x.numel() != outer * channels * inner:
+            raise ValueError("x.numel() != outer * channels * inner")
+    sizes = [classify_workspace_bytes_ranges(x.numel()) for x in xs]
+    up = [(n + 255) & ~255 for n in sizes]
+    rooms = [n + 256 + 4 * ((s[1] + 63) & ~63) + ((s[1] + 255) & ~255) for n, s in zip(up, splits)]
+    stores = [ChannelWiseStore(x, *s, group_size, bits) for x, s in zip(xs, splits)]
+    cls, slots, mixed = (fh_classify_item * count)(), (fh_slots_item * count)(), (fh_mixed_item * count)()
+    with _on(dev):
+        scratch = torch.empty(sum(rooms), dtype=torch.uint8, device=dev)
+        at = scratch.data_ptr()
+        for k, (x, (outer, channels, inner, raw_channels), store) in enumerate(zip(xs, splits, stores)):
+            stats = at + up[k]
+            counts = stats + 256
+            mask = counts + 4 * ((channels + 63) & ~63)
+            cls[k] = fh_classify_item(x.data_ptr(), _dtype_code(x), 0, outer, channels, inner, float(k_sigma),
+                                      max(1, int(outer * inner * outlier_share)), at, sizes[k], stats, counts, mask)
+            item = store.item(x, None, make_params(group_size, bits, rounding, seed, tensor_ids[k]))
+            mixed[k] = item
+            slots[k] = fh_slots_item(mask, channels, raw_channels, item.slots, item.rows_in_use)
+            at += rooms[k]
+        stream = _stream_ptr(None)
+        _check(_lib.fh_classify_channels_batch(cls, count, stream))
+        _check(_lib.fh_channel_slots_batch(slots, count, stream))
+        _check(_lib.fh_compress_mixed_batch(mixed, count, stream))
+    return stores
+
+
+def restore_channel_wise(store: ChannelWiseStore, out_dtype) -> torch.Tensor:
+    """Enqueue the restore of one tensor on the current stream; returns it flat."""
+    dev = store.data.device
+    with _on(dev):
+        out = torch.empty(store.numel, dtype=out_dtype, device=dev)
+        item = store.item(None, out, make_params(store.group_size, store.bits))
+        _check(_lib.fh_decompress_mixed_batch(ctypes.byref(item), 1, _stream_ptr(None)))
     return out
 
 
@@ -672,7 +765,7 @@ def fh_sparse_encode(x: torch.Tensor, maps: int, h: int, w: int, n: int, tau: fl
         _device_tensor(t, what)
     if b.values.dtype != x.dtype or _nbytes(b.totals) < 32:
         raise FedHybridError(7)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         _check(_lib.fh_sparse_encode(_ptr(x), _dtype_code(x), maps, h, w, int(n), float(tau), float(eps),
                                      b.info.data_ptr(), _nbytes(b.info), b.values.data_ptr(), _nbytes(b.values),
                                      b.indices.data_ptr(), _nbytes(b.indices), b.totals.data_ptr(),
@@ -695,7 +788,7 @@ def fh_sparse_decode(info: torch.Tensor, values: torch.Tensor, indices: torch.Te
     _device_tensor(workspace, "workspace")
     if _nbytes(info) < sparse_info_bytes(maps, h, w, n) or out.dtype != values.dtype:
         raise FedHybridError(7)
-    with torch.cuda.device(info.device):
+    with _on(info.device):
         _check(_lib.fh_sparse_decode(_ptr(info), _ptr(values), _nbytes(values), _ptr(indices), _nbytes(indices),
                                      _dtype_code(out), maps, h, w, int(n), float(eps), _ptr(out), _nbytes(out),
                                      workspace.data_ptr(), _nbytes(workspace), _stream_ptr(stream)))
@@ -729,7 +822,7 @@ def fh_huffman_encode(data: torch.Tensor, stream_out: Optional[torch.Tensor] = N
         _device_tensor(t, what)
     if _nbytes(totals) < 16:
         raise FedHybridError(7)
-    with torch.cuda.device(data.device):
+    with _on(data.device):
         _check(_lib.fh_huffman_encode(_ptr(data), n, stream_out.data_ptr(), _nbytes(stream_out), totals.data_ptr(),
                                       workspace.data_ptr(), _nbytes(workspace), _stream_ptr(stream)))
     return stream_out, totals
@@ -742,7 +835,7 @@ def fh_huffman_decode(stream_in: torch.Tensor, n: int, out: Optional[torch.Tenso
     if out is None:
         out = torch.empty(n, dtype=torch.uint8, device=stream_in.device)
     _device_tensor(out, "out")
-    with torch.cuda.device(stream_in.device):
+    with _on(stream_in.device):
         _check(_lib.fh_huffman_decode(_ptr(stream_in), _nbytes(stream_in), n, _ptr(out), _nbytes(out),
                                       _stream_ptr(stream)))
     return out
@@ -799,13 +892,13 @@ class HuffmanBatch:
 
 def fh_huffman_encode_batch(batch: HuffmanBatch, stream=None) -> None:
     if batch.count:
-        with torch.cuda.device(batch.device):
+        with _on(batch.device):
             _check(_lib.fh_huffman_encode_batch(batch.enc, batch.count, _stream_ptr(stream)))
 
 
 def fh_huffman_decode_batch(batch: HuffmanBatch, stream=None) -> None:
     if batch.count:
-        with torch.cuda.device(batch.device):
+        with _on(batch.device):
             _check(_lib.fh_huffman_decode_batch(batch.dec, batch.count, _stream_ptr(stream)))
 
 
@@ -866,7 +959,7 @@ def fh_classify_channels_batch(batch: ClassifyBatch, stream=None) -> None:
     stats / counts / mask tensors."""
     if batch.count == 0:
         return
-    with torch.cuda.device(batch.device):
+    with _on(batch.device):
         _check(_lib.fh_classify_channels_batch(batch.items, batch.count, _stream_ptr(stream)))
 
 
@@ -941,13 +1034,13 @@ class SparseBatch:
 
 def fh_sparse_encode_batch(batch: SparseBatch, stream=None) -> None:
     if batch.count:
-        with torch.cuda.device(batch.device):
+        with _on(batch.device):
             _check(_lib.fh_sparse_encode_batch(batch.enc, batch.count, _stream_ptr(stream)))
 
 
 def fh_sparse_decode_batch(batch: SparseBatch, stream=None) -> None:
     if batch.count:
-        with torch.cuda.device(batch.device):
+        with _on(batch.device):
             _check(_lib.fh_sparse_decode_batch(batch.dec, batch.count, _stream_ptr(stream)))
 
 
@@ -1020,13 +1113,13 @@ class MixedBatch:
 
 def fh_compress_mixed_batch(batch: MixedBatch, stream=None) -> None:
     if batch.count:
-        with torch.cuda.device(batch.device):
+        with _on(batch.device):
             _check(_lib.fh_compress_mixed_batch(batch.items, batch.count, _stream_ptr(stream)))
 
 
 def fh_decompress_mixed_batch(batch: MixedBatch, stream=None) -> None:
     if batch.count:
-        with torch.cuda.device(batch.device):
+        with _on(batch.device):
             _check(_lib.fh_decompress_mixed_batch(batch.items, batch.count, _stream_ptr(stream)))
 
 
@@ -1128,7 +1221,7 @@ class MixBatch:
 
     def _call(self, fn, stream) -> None:
         if self.count:
-            with torch.cuda.device(self.device):
+            with _on(self.device):
                 _check(fn(self.items, self.count, _stream_ptr(stream)))
 
 

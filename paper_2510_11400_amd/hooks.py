@@ -72,6 +72,14 @@ class TensorRecord:
         return mps(self.saved_bytes, freed_lifetime, self.purge_cost, self.regain_cost)
 
 
+class _Stored:
+    """The packed form of a tensor of a batch on the channel-wise path."""
+    __slots__ = ("store", "shape", "dtype", "record")
+
+    def __init__(self, store, shape, dtype):
+        self.store, self.shape, self.dtype, self.record = store, shape, dtype, None
+
+
 class _Packed:
     __slots__ = ("packed", "meta", "shape", "dtype", "numel", "record", "mixed")
 
@@ -152,9 +160,9 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
             if self._pending_bytes >= self.batch_bytes:
                 self.flush()
             return d
-        stream = torch.cuda.current_stream(x.device)
-        rec = None
+        stream, rec = None, None                  # the current one
         if self.record:
+            stream = torch.cuda.current_stream(x.device)
             ev = (torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
             ev[0].record(stream)
         mixed, extra = self._split(x), 0
@@ -187,9 +195,9 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
         pending, self._pending, self._pending_bytes = self._pending, [], 0
         if not pending:
             return
-        stream = torch.cuda.current_stream(pending[0].x.device)
-        ev = None
+        stream, ev = None, None                   # the current one
         if self.record:
+            stream = torch.cuda.current_stream(pending[0].x.device)
             ev = (torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
             ev[0].record(stream)
         plain = [d for d in pending if d.split is None]
@@ -206,22 +214,12 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
                 d.handle = _Packed(e.packed, e.meta, d.shape, d.dtype, d.x.numel(), None)
                 stored[id(d)] = e.packed.numel() + e.meta.numel() * e.meta.element_size()
         if routed:
-            cls = api.ClassifyBatch([api.ClassifyEntry(d.x.view(-1), d.split[0], d.split[1], d.split[2], self.k_sigma,
-                                                       max(1, int(d.split[0] * d.split[2] * self.outlier_share)))
-                                     for d in routed])
-            api.fh_classify_channels_batch(cls, stream)
-            slots, used = api.fh_channel_slots_batch([e.mask for e in cls.entries], [d.split[3] for d in routed], stream)
-            mixed = api.MixedBatch([api.MixedEntry(d.split[0], d.split[1], d.split[2], slots[k], d.split[3],
-                                                   self.group_size, self.bits, self.rounding, self.seed, d.tid,
-                                                   x=d.x.view(-1), rows_in_use=used[k])
-                                    for k, d in enumerate(routed)])
-            api.fh_compress_mixed_batch(mixed, stream)
-            for k, (d, e) in enumerate(zip(routed, mixed.entries)):
-                outer, channels, inner, raw_channels = d.split
-                d.handle = _Packed(e.packed, e.meta, d.shape, d.dtype, d.x.numel(), None,
-                                   (outer, channels, inner, slots[k], raw_channels, e.raw, used[k]))
-                stored[id(d)] = (e.packed.numel() + e.meta.numel() * e.meta.element_size()
-                                 + e.raw.numel() * e.raw.element_size() + slots[k].numel() * 2)
+            stores = api.compress_channel_wise([d.x for d in routed], [d.split for d in routed], self.k_sigma,
+                                               self.outlier_share, self.group_size, self.bits, self.rounding, self.seed,
+                                               [d.tid for d in routed])
+            for d, kept in zip(routed, stores):
+                d.handle = _Stored(kept, d.shape, d.dtype)
+                stored[id(d)] = kept.nbytes
         if ev is not None:
             ev[1].record(stream)
             total = float(sum(d.x.numel() * d.x.element_size() for d in pending))
@@ -256,13 +254,16 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
             if h.handle is None:
                 self.flush()                                  # needed back before its batch was full
             h = h.handle
-        if not isinstance(h, _Packed):
+        if not isinstance(h, (_Packed, _Stored)):
             return h
-        stream = torch.cuda.current_stream(h.packed.device)
+        stream = None                                         # the current one
         if h.record is not None:
+            stream = torch.cuda.current_stream(h.store.data.device if isinstance(h, _Stored) else h.packed.device)
             ev = (torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
             ev[0].record(stream)
-        if h.mixed is None:
+        if isinstance(h, _Stored):
+            out = api.restore_channel_wise(h.store, h.dtype)
+        elif h.mixed is None:
             out = api.fh_decompress(h.packed, h.meta, h.numel, self.group_size, self.bits, out_dtype=h.dtype,
                                     stream=stream)
         else:
