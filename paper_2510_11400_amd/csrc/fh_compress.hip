@@ -496,15 +496,15 @@ __device__ __forceinline__ void compress_span(const CompressItem& it, int64_t wa
         if constexpr (EPL == 8) {
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
-                const u32x4 w = philox4x32_10((uint32_t)blk + r * (ROW / 8) + lane, ctr_hi, t_lo, t_hi, k_lo, k_hi);
-                nr[r][0] = ~w.x; nr[r][1] = ~w.y; nr[r][2] = ~w.z; nr[r][3] = ~w.w;
+                const u32x4 w = philox4x32_10_complement((uint32_t)blk + r * (ROW / 8) + lane, ctr_hi, t_lo, t_hi, k_lo, k_hi);
+                nr[r][0] = w.x; nr[r][1] = w.y; nr[r][2] = w.z; nr[r][3] = w.w;
             }
         } else {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const uint32_t ctr_lo = (uint32_t)blk + (2u * j + (b0 ? 1u : 0u)) * (ROW / 8) + (lane >> 1);
-                const u32x4 w = philox4x32_10(ctr_lo, ctr_hi, t_lo, t_hi, k_lo, k_hi);
-                const uint32_t n0 = ~w.x, n1 = ~w.y, n2 = ~w.z, n3 = ~w.w;
+                const u32x4 w = philox4x32_10_complement(ctr_lo, ctr_hi, t_lo, t_hi, k_lo, k_hi);
+                const uint32_t n0 = w.x, n1 = w.y, n2 = w.z, n3 = w.w;
                 // even lane: owns words 0,1 of both rows' blocks; odd lane: words 2,3
                 const uint32_t r0 = from_pair_lane_u32(b0 ? n0 : n2);
                 const uint32_t r1 = from_pair_lane_u32(b0 ? n1 : n3);
@@ -651,10 +651,10 @@ __device__ __forceinline__ void compress_edge(const CompressItem& it, int64_t wa
         uint32_t nr[4] = {0u, 0u, 0u, 0u};
         if constexpr (STOCH) {
             const uint64_t blk = (uint64_t)row_base >> 3;
-            const u32x4 w = philox4x32_10((uint32_t)blk + lane, (uint32_t)(blk >> 32),
+            const u32x4 w = philox4x32_10_complement((uint32_t)blk + lane, (uint32_t)(blk >> 32),
                                           (uint32_t)it.tensor_id, (uint32_t)(it.tensor_id >> 32),
                                           (uint32_t)it.seed, (uint32_t)(it.seed >> 32));
-            nr[0] = ~w.x; nr[1] = ~w.y; nr[2] = ~w.z; nr[3] = ~w.w;
+            nr[0] = w.x; nr[1] = w.y; nr[2] = w.z; nr[3] = w.w;
         }
         uint32_t e[kEPL];
 #pragma unroll
