@@ -28,14 +28,15 @@
 // integer and byte work; results do not depend on launch geometry.
 // All three passes that touch the maps are bound by vector instructions (400, 600 and 830 per wave of 64 4 x 4 tiles with
 // an error bound).  93 MB of fp32 maps, count, write and read: 20.6, 33.1 and 36.5 us with the general division, a
-// byte of LDS at a time and three 64-bit sums per tile, 18.6, 29.7 and 34.0 now; 47 MB of bf16: 21.8, 32.7 and 38.0, now 17.4, 26.5
-// and 34.5.  (The dense tiles dealt to the first threads of the read pass, so that a wave has tiles of one kind, save a
+// byte of LDS at a time and three 64-bit sums per tile, 18.6, 29.7 and 32.4 now; 47 MB of bf16: 21.8, 32.7 and 38.0, now 17.4, 26.5
+// and 35.0.  (The dense tiles dealt to the first threads of the read pass, so that a wave has tiles of one kind, save a
 // third of its instructions and cost more in stores of single tile rows: 36 us.)
 #include "../../include/fedhybrid.h"
 
 #include <float.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "fh_batch.hpp"
 #include "fh_channels.hpp"
@@ -925,28 +926,32 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Bat
 #pragma unroll
             for (int c = 0; c < N; ++c)
                 if (!(r < (int)t.rows && c < (int)t.cols)) code[r][c] = 128;     // no element there: no outlier, and predicts none
-        int32_t q[N][N];
-        uint32_t used = 0;
+        const auto rebuild = [&](auto outliers) {
+            int32_t q[N][N];
+            uint32_t used = 0;
 #pragma unroll
-        for (int r = 0; r < N; ++r)
+            for (int r = 0; r < N; ++r)
 #pragma unroll
-            for (int c = 0; c < N; ++c) {
-                const int32_t left = c > 0 ? q[r][c - 1] : 0, up = r > 0 ? q[r - 1][c] : 0;
-                const int32_t diag = (r > 0 && c > 0) ? q[r - 1][c - 1] : 0;
-                q[r][c] = left + (up - diag) + ((int32_t)code[r][c] - 128);
-                e[r][c] = stored_of<Bits>((float)q[r][c] * s.step.two_eps);
-                const bool outlier = code[r][c] == 0;         // unchanged, and back on the lattice
-                Bits kept = 0;
-                int32_t point = 0;
-                if (any) {                                    // wave-uniform
-                    if (used < count) kept = (Bits)v[used];
-                    used += outlier ? 1u : 0u;
-                    bool ok;
-                    point = lattice(value_of<Bits>(kept), s.step, ok);
+                for (int c = 0; c < N; ++c) {
+                    const int32_t left = c > 0 ? q[r][c - 1] : 0, up = r > 0 ? q[r - 1][c] : 0;
+                    const int32_t diag = (r > 0 && c > 0) ? q[r - 1][c - 1] : 0;
+                    q[r][c] = left + (up - diag) + ((int32_t)code[r][c] - 128);
+                    e[r][c] = stored_of<Bits>((float)q[r][c] * s.step.two_eps);
+                    const bool outlier = code[r][c] == 0;     // unchanged, and back on the lattice
+                    Bits kept = 0;
+                    int32_t point = 0;
+                    if constexpr (outliers.value) {
+                        kept = used < count ? (Bits)v[used] : (Bits)0;
+                        used += outlier ? 1u : 0u;
+                        bool ok;
+                        point = lattice(value_of<Bits>(kept), s.step, ok);
+                    }
+                    q[r][c] = outlier ? point : q[r][c];
+                    e[r][c] = outlier ? kept : e[r][c];
                 }
-                q[r][c] = outlier ? point : q[r][c];
-                e[r][c] = outlier ? kept : e[r][c];
-            }
+        };
+        if (any) rebuild(std::true_type());                   // wave-uniform
+        else rebuild(std::false_type());
     } else if (in_bounds) {
         // verbatim: a dense tile holds every element it has, a sparse one those its CSR structure
         // names; either way the k-th set bit of the occupancy is the k-th value of the piece
