@@ -79,22 +79,35 @@ class _Stored:
     def __init__(self, store, shape, dtype):
         self.store, self.shape, self.dtype, self.record = store, shape, dtype, None
 
+    def buffers(self):
+        return (self.store.data,)
+
 
 class _Packed:
     __slots__ = ("packed", "meta", "shape", "dtype", "numel", "record", "mixed")
 
     def __init__(self, packed, meta, shape, dtype, numel, record, mixed=None):
         self.packed, self.meta, self.shape, self.dtype, self.numel, self.record = packed, meta, shape, dtype, numel, record
-        self.mixed = mixed                 # (outer, channels, inner, slots, raw_channels, raw) on the channel-wise path
+        self.mixed = mixed                 # (outer, channels, inner, slots, raw_channels, raw, used) on the channel-wise path
+
+    def buffers(self):                     # of a tensor of a batch
+        return (self.packed, self.meta)
 
 
 class _Deferred:
     """A tensor handed to the pack hook that waits for its batch: `handle` is the packed form once
     the batch has been compressed, and the tensor itself is let go then."""
-    __slots__ = ("x", "tid", "shape", "dtype", "split", "handle")
+    __slots__ = ("x", "tid", "shape", "dtype", "split", "stream", "handle")
 
-    def __init__(self, x, tid, shape, dtype, split):
+    def __init__(self, x, tid, shape, dtype, split, stream):
         self.x, self.tid, self.shape, self.dtype, self.split, self.handle = x, tid, shape, dtype, split, None
+        self.stream = stream               # the one it was saved on
+
+
+def _is_current(stream: torch.cuda.Stream) -> bool:
+    """Whether `stream` is the current one, of the current device."""
+    index = torch._C._cuda_getDevice()
+    return stream.device_index == index and stream.cuda_stream == torch._C._cuda_getCurrentRawStream(index)
 
 
 class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
@@ -122,7 +135,8 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
     and once `batch_bytes` of them wait (or one of them is needed back, or the context ends) the
     whole batch goes through the batched entry points -- a handful of launches for the batch
     instead of one to seven per tensor, at the price of holding up to `batch_bytes` of
-    activations uncompressed a little longer.  Results are the same bytes either way.
+    activations uncompressed a little longer.  Results are the same bytes either way.  A tensor is
+    compressed on the device and the stream that it was saved on, whichever are current when its batch is.
     """
 
     def __init__(self, group_size: int = 256, bits: int = 4, rounding="nearest", seed: int = 0,
@@ -133,6 +147,7 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
         self.batch_bytes = int(batch_bytes)
         self._pending: List[_Deferred] = []
         self._pending_bytes = 0
+        self._streams = {}                        # of the tensors that wait: (device, handle) -> Stream
         self.min_numel = min_numel
         self.channel_dim, self.k_sigma, self.outlier_share, self.raw_share = channel_dim, k_sigma, outlier_share, raw_share
         self.next_tensor_id = first_tensor_id
@@ -154,7 +169,7 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
         tid = self.next_tensor_id
         self.next_tensor_id += 1
         if self.batch_bytes > 0:
-            d = _Deferred(x, tid, t.shape, t.dtype, self._split(x))
+            d = _Deferred(x, tid, t.shape, t.dtype, self._split(x), self._stream_of(x.device))
             self._pending.append(d)
             self._pending_bytes += x.numel() * x.element_size()
             if self._pending_bytes >= self.batch_bytes:
@@ -190,11 +205,28 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
             self.records.append(rec)
         return _Packed(packed, meta, t.shape, t.dtype, x.numel(), rec, mixed)
 
+    def _stream_of(self, device: torch.device) -> torch.cuda.Stream:
+        """The current stream of `device`; one object per stream and batch, building one costs more than asking for its handle."""
+        key = (device.index, torch._C._cuda_getCurrentRawStream(device.index))
+        stream = self._streams.get(key)
+        if stream is None:
+            stream = self._streams[key] = torch.cuda.current_stream(device)
+        return stream
+
     def flush(self) -> None:
-        """Compress every tensor that waits for its batch (batched entry points, current stream)."""
+        """Compress every tensor that waits for its batch (batched entry points, a batch for each stream they were saved on)."""
         pending, self._pending, self._pending_bytes = self._pending, [], 0
-        if not pending:
-            return
+        streams, self._streams = self._streams, {}
+        for stream in streams.values():
+            batch = [d for d in pending if d.stream is stream]
+            if _is_current(stream):
+                self._compress(batch)
+            else:
+                with torch.cuda.stream(stream):
+                    self._compress(batch)
+
+    def _compress(self, pending: List[_Deferred]) -> None:
+        """Compress `pending` as one batch on the current stream."""
         stream, ev = None, None                   # the current one
         if self.record:
             stream = torch.cuda.current_stream(pending[0].x.device)
@@ -253,6 +285,11 @@ class SavedActivations(torch.autograd.graph.saved_tensors_hooks):
         if isinstance(h, _Deferred):
             if h.handle is None:
                 self.flush()                                  # needed back before its batch was full
+            if not _is_current(h.stream):                     # backward runs a node on its forward stream; others have to wait
+                here = torch.cuda.current_stream(h.stream.device)
+                here.wait_stream(h.stream)
+                for t in h.handle.buffers():
+                    t.record_stream(here)
             h = h.handle
         if not isinstance(h, (_Packed, _Stored)):
             return h

@@ -289,3 +289,54 @@ def test_tensors_compressed_in_batches_give_the_same_bytes(hooks, channel_wise, 
             want = _oracle_roundtrip(h, G, B, rounding, seed, 3 + k, "f32")
         assert torch.equal(seen[k].cpu().view(torch.int32), want.view(torch.int32)), f"tensor {k}"
     assert len(ctx.records) == len(xs) and all(r.purge_cost is not None and r.purge_cost >= 0 for r in ctx.records)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("where", ["current stream", "side stream", "both streams"])
+@pytest.mark.parametrize("batch_bytes", [0, 100_000, 1 << 30])
+def test_channel_wise_tensors_without_records_on_any_stream(hooks, dtype, where, batch_bytes):
+    """As a training program has it: nothing recorded and the stream left to the library, tensor by tensor and in batches.
+    On a side stream, with memory handed out and written on the default stream meanwhile; and with the layers dealt
+    to two streams, a batch being full or the context ending while either is current."""
+    from paper_2510_11400_amd import workloads as W
+    print(f"[hooks] channel-wise {dtype}, {where}, batches of {batch_bytes} bytes", flush=True)
+    shapes = [(6, 40, 10, 10), (50, 96), (12, 24, 7, 7), (64, 128), (3, 16, 33)]
+    G, B, rounding, seed = 64, 4, "stochastic", 22
+    tdt, bits = (torch.float32, torch.int32) if dtype == "f32" else (torch.bfloat16, torch.int16)
+    splits = [(s[0], s[1], int(np.prod(s[2:]))) for s in shapes]
+    hosts = []
+    for k, (shp, split) in enumerate(zip(shapes, splits)):
+        x_np, _ = W.outlier_channel_tensor(*split, seed=k, dist="gauss", salient_fraction=0.1, dtype=dtype)
+        hosts.append((torch.from_numpy(x_np.view(np.int16)).view(tdt) if dtype == "bf16" else torch.from_numpy(x_np)).reshape(shp))
+    here, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    on = {"current stream": [here] * 5, "side stream": [side] * 5, "both streams": [here, side, here, side, side]}[where]
+    xs = [h.cuda() for h in hosts]
+    torch.cuda.synchronize()
+    _Probe.seen.clear()
+    busy = torch.randn(3, 2048, 2048, device="cuda")
+    torch.cuda.synchronize()
+    ctx = hooks.SavedActivations(G, B, rounding, seed=seed, min_numel=1, first_tensor_id=6, channel_dim=1, batch_bytes=batch_bytes)
+    ys = []
+    with ctx:
+        for k, (x, stream) in enumerate(zip(xs, on)):
+            with torch.cuda.stream(stream):
+                for _ in range(4):                            # the layer's input is late on its own stream
+                    work = busy[k % 2] @ busy[2]
+                late = (x + work[0, 0] * 0.0).to(tdt).requires_grad_(True)
+                ys.append(_Probe.apply(late))
+                del late
+            if stream is side:
+                for fill in range(4):
+                    torch.empty(xs[0].numel() * 8, dtype=torch.uint8, device="cuda").fill_(fill)
+    here.wait_stream(side)
+    sum(y.float().sum() for y in ys).backward()
+    torch.cuda.synchronize()
+    assert not ctx.records and not ctx._pending and len(_Probe.seen) == 5
+    for k, (h, split, got) in enumerate(zip(hosts, splits, _in_order(xs, _Probe.seen))):
+        want, _ = _oracle_channel_wise(h, *split, G, B, rounding, seed, 6 + k, dtype, 3.0, 0.01, 1.0 / 16.0)
+        assert got.dtype == tdt and torch.equal(got.cpu().view(bits), want.view(bits)), f"tensor {k}"
+
+
+def _in_order(xs, seen):
+    """What backward saw of each tensor: the shapes differ."""
+    return [next(s for s in seen if s.shape == x.shape) for x in xs]
