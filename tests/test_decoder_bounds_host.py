@@ -15,6 +15,7 @@ import shutil
 import struct
 import subprocess
 
+import huffman_streams as HS
 import numpy as np
 import pytest
 
@@ -91,7 +92,8 @@ def _clustered(rng, n, spread):
 def test_huffman_valid_streams_decode_as_the_oracle_does(decoders):
     rng = np.random.default_rng(5)
     datas = [_clustered(rng, n, s) for n, s in ((1, 3.0), (255, 3.0), (256, 1.0), (257, 6.0), (70_001, 6.0), (300_001, 0.4))]
-    datas.append(rng.integers(0, 256, 200_000, dtype=np.uint8))            # 8 bits per symbol: slices too long to stage
+    datas.append(rng.integers(0, 256, 200_000, dtype=np.uint8))            # codes of eight bits each: copied
+    assert (oracle.huffman_encode(datas[-1])[0][:256] == 8).all()
     skew = np.minimum(rng.geometric(0.5, 150_000) - 1, 255).astype(np.uint8)  # code lengths up to the limit of 24
     datas.append(skew)
     cases = []
@@ -101,6 +103,30 @@ def test_huffman_valid_streams_decode_as_the_oracle_does(decoders):
     for d, (st, got) in zip(datas, decoders(cases)):
         assert st == FH_OK
         assert np.array_equal(got, d), f"n = {d.size}"
+
+
+def test_huffman_rings_decode_as_the_oracle_does(decoders):
+    """Valid streams with slices too long to stage: a workgroup between two that stage theirs, and the last one with a
+    ragged chunk; the same with the payload cut short and with noise in its place."""
+    rng = np.random.default_rng(12)
+    (threads, stage), _ = HS.decoder_shapes()[0].items()
+    n, share = 700 * 256 - 37, 234                            # three workgroups
+    cases, datas = [], []
+    for noise, rings in (([(234, 468)], [False, True, False]), ([(468, 700)], [False, False, True]), ([(0, 700)], [True] * 3)):
+        data, stream = HS.long_codes(rng, n, noise)
+        offsets = HS.offsets_of(stream, n)
+        assert [not HS.passes(offsets, a, min(a + share, 700), threads, stage)[0][1] for a in (0, 234, 468)] == rings
+        assert np.array_equal(oracle.huffman_decode(stream, n), data)
+        cases.append(_huffman_case(stream, n))
+        datas.append(data)
+    cases.append(_huffman_case(stream, n, stream_bytes=stream.size - 8 * 192))
+    junk = stream.copy()
+    junk[256 + 4 * 701:] = rng.integers(0, 256, junk.size - 256 - 4 * 701, dtype=np.uint8)
+    cases.append(_huffman_case(junk, n))
+    results = decoders(cases)
+    assert all(st == FH_OK for st, _ in results)
+    for data, (_, got) in zip(datas, results):
+        assert np.array_equal(got, data)
 
 
 def test_huffman_encoder_on_the_cpu_writes_the_oracles_streams(decoders):

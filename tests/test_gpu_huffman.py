@@ -4,6 +4,7 @@ decoding).  Bar: the stream -- length bytes, chunk offsets, payload words -- and
 bit-exact; decoding restores the input bytes."""
 from __future__ import annotations
 
+import huffman_streams as HS
 import numpy as np
 import pytest
 
@@ -40,7 +41,7 @@ def _check(api, data, name=""):
     back = api.fh_huffman_decode(stream[:used], data.size)
     torch.cuda.synchronize()
     assert np.array_equal(back.cpu().numpy(), data), f"{name}: decoded bytes differ"
-    return used
+    return want
 
 
 @pytest.mark.parametrize("n", [0, 1, 15, 16, 17, 255, 256, 257, 4095, 65535, 65536, 65537, 1 << 20, (1 << 22) + 13])
@@ -52,13 +53,12 @@ def test_sizes_around_vectors_chunks_and_groups(api, n):
 
 @pytest.mark.parametrize("spread", [2.5, 14.0, 20.0, -1.0, 0.0])
 def test_streams_long_enough_that_a_workgroup_decodes_several_groups(api, spread):
-    # Beyond 131072 chunks the decoder has a workgroup of 1024 threads per compute unit and deals the chunks out evenly: 1026
+    # Beyond 256 * 488 chunks the decoder has a workgroup of 1024 threads per compute unit and deals the chunks out evenly: 1026
     # each here, so a workgroup takes a pass with every thread at work (34 words per chunk fit the LDS stage then; spread
     # 2.5 gives 27) and another of two chunks, the last one fewer and a ragged chunk.
     # spread 14: codes longer than the decoder's fast table occur; 14 and 20: more words per chunk than the stage
-    # holds for 1024 (and for 768) chunks, so its passes seat fewer; -1: a clustered first half and noise behind it, passes of
-    # every kind in one launch; 0: uniform bytes, whose 64 words per chunk do not fit the LDS stage of either side
-    # (the direct payload stores and the per-thread rings)
+    # holds for 1024 (and for 768) chunks, so its passes seat fewer; -1: a clustered first half and noise behind it, whose words
+    # go through the per-thread rings; 0: uniform bytes, all codes eight bits long, which are copied
     n = 256 * (256 * 1024 + 300) + 77
     rng = np.random.default_rng(int(abs(spread) * 10))
     if spread > 0:
@@ -67,7 +67,15 @@ def test_streams_long_enough_that_a_workgroup_decodes_several_groups(api, spread
         data = np.concatenate([np.clip(np.rint(rng.normal(128, 3.0, n // 2)), 0, 255), rng.integers(0, 256, n - n // 2)])
     else:
         data = rng.integers(0, 256, n)
-    _check(api, data.astype(np.uint8), f"spread {spread}")
+    want = _check(api, data.astype(np.uint8), f"spread {spread}")
+    (_, (threads, stage)), seats = HS.decoder_shapes()[0].items(), HS.decoder_shapes()[1]
+    chunks = -(-n // 256)
+    share = -(-chunks // 256)
+    assert chunks > 256 * seats and share > threads
+    offsets = HS.offsets_of(want, n)
+    kinds = {staged for b in range(256) for _, staged in HS.passes(offsets, b * share, min((b + 1) * share, chunks), threads, stage)}
+    assert bool((want[:256] == 8).all()) == (spread == 0.0)
+    assert spread == 0.0 or kinds == ({True, False} if spread < 0 else {True})
 
 
 @pytest.mark.parametrize("more", [0, 1])
@@ -98,14 +106,68 @@ def test_decoder_forms(api, n, kind):
     _check(api, data.astype(np.uint8), f"{kind}")
 
 
-@pytest.mark.parametrize("spread", [2.5, 14.0])
-@pytest.mark.parametrize("groups", [512, 513])
-def test_decoder_on_both_sides_of_the_wide_workgroups(api, groups, spread):
-    """Up to 512 groups of 256 chunks go to workgroups of 256 threads, two per compute unit; one chunk more and the
-    launch has workgroups of 1024, which are given half of them each."""
-    n = 256 * 256 * 512 + (0 if groups == 512 else 1)
-    rng = np.random.default_rng(groups)
-    _check(api, np.clip(np.rint(rng.normal(128, spread, n)), 0, 255).astype(np.uint8), f"{groups} groups, spread {spread}")
+@pytest.mark.parametrize("kind", ["2.5", "14", "nearly flat"])
+@pytest.mark.parametrize("counts_on", ["host", "device"])
+def test_decoder_on_both_sides_of_the_wide_workgroups(api, counts_on, kind):
+    """Workgroups of 512 threads take up to 488 chunks per compute unit where the count is the host's, up to 512 where it is
+    on the device and the host knows a bound; one symbol more and the launch has workgroups of 1024.  Counts on the
+    device: the bound itself, and two thirds of it, as the whole chain has them.  Nearly flat: 64 words per chunk, of which
+    the narrow workgroup's stage does not hold 512 chunks, so that its share takes a second pass."""
+    shapes, seats = HS.decoder_shapes()
+    (narrow, stage), _ = shapes.items()
+    limit = 256 * (seats if counts_on == "host" else narrow) * 256
+    rng = np.random.default_rng(limit % 1000)
+    full = rng.integers(0, 256, limit + 1) if kind == "nearly flat" else np.clip(np.rint(rng.normal(128, float(kind), limit + 1)), 0, 255)
+    full = full.astype(np.uint8)
+    if kind == "nearly flat":
+        full[rng.random(full.size) < 0.01] = 7
+    for n in (limit, limit + 1):
+        if counts_on == "host":
+            _check(api, full[:n], f"{n} symbols, {kind}")
+            continue
+        d = torch.from_numpy(full[:n].copy()).cuda()
+        for count in (n, n * 2 // 3 + 5):
+            print(f"[huffman] {count} of {n} symbols, {kind}", flush=True)
+            batch = api.HuffmanBatch([d], n_device=[torch.tensor([count], dtype=torch.int64, device="cuda")])
+            batch.out[0].fill_(0xEE)
+            api.fh_huffman_encode_batch(batch)
+            api.fh_huffman_decode_batch(batch)
+            torch.cuda.synchronize()
+            want, bits = oracle.huffman_encode(full[:count])
+            assert batch.totals.cpu().tolist() == [[want.size, bits]]
+            assert np.array_equal(batch.streams[0].cpu().numpy()[:want.size], want)
+            back = batch.out[0].cpu().numpy()
+            assert np.array_equal(back[:count], full[:count])
+            assert np.all(back[-(-count // 16) * 16:] == 0xEE)
+            if kind == "nearly flat" and count == limit:
+                assert HS.passes(HS.offsets_of(want, count), 0, narrow, narrow, stage)[1:], "one pass is enough"
+
+
+def test_rings_of_the_narrow_workgroups(api):
+    """Symbols that are rare in the stream and stand together have codes of some 16 bits: 128 words per chunk, of which the
+    stage of a workgroup of 512 threads holds a half of its 488 chunks.  Such passes go through the rings: a
+    workgroup in the middle, and the last one with a ragged chunk.  Then codes of 24 bits, the longest there are."""
+    shapes, seats = HS.decoder_shapes()
+    (threads, stage), _ = shapes.items()
+    n = 256 * seats * 256 - 37
+    rng = np.random.default_rng(31)
+    data = np.clip(np.rint(rng.normal(128, 2.5, n)), 0, 255).astype(np.uint8)
+    for b in (100, 255):
+        part = data[b * seats * 256: (b + 1) * seats * 256]
+        part[:] = rng.integers(0, 256, part.size)
+    want = _check(api, data, "noise in two workgroups")
+    offsets = HS.offsets_of(want, n)
+    for b in (0, 99, 100, 255):
+        kinds = {staged for _, staged in HS.passes(offsets, b * seats, (b + 1) * seats, threads, stage)}
+        assert kinds == {b not in (100, 255)}, f"workgroup {b}"
+    n = 700 * 256 - 37                                        # three workgroups of 234 chunks
+    data, stream = HS.long_codes(rng, n, [(234, 700)])
+    offsets = HS.offsets_of(stream, n)
+    assert [HS.passes(offsets, a, min(a + 234, 700), threads, stage)[0][1] for a in (0, 234, 468)] == [True, False, False]
+    print("[huffman] codes of 24 bits", flush=True)
+    back = api.fh_huffman_decode(torch.from_numpy(stream).cuda(), n)
+    torch.cuda.synchronize()
+    assert np.array_equal(back.cpu().numpy(), data)
 
 
 @pytest.mark.parametrize("kind", ["uniform", "one", "two", "geometric", "all-once", "ties"])
@@ -142,8 +204,7 @@ def test_codes_that_would_exceed_24_bits(api):
     data = np.repeat(np.arange(10, 38, dtype=np.uint8), fib)          # a 27-deep comb: counts are halved
     rng = np.random.default_rng(2)
     rng.shuffle(data)
-    used = _check(api, data, "comb")
-    assert used < data.size
+    assert _check(api, data, "comb").size < data.size
 
 
 def test_index_stream_of_the_predictive_form_end_to_end(api):
