@@ -45,8 +45,8 @@ constexpr int kHistCopies = 32;                     // one per LDS bank
 constexpr int kHistThreads = 1024;
 constexpr int kHistBlocksMax = 512;                // histogram workgroups per stream: two per compute unit
 // decode: 16-byte output vectors held back and stored together; at 51 MB one at a time 67 us, 2 51, 4 49, with 8 the code no
-// longer fits the instruction cache and takes 53 (the rings' fits either way)
-constexpr int kBurst = 4, kRingBurst = 8;
+// longer fits the instruction cache and takes 53 (the rings' form likewise: half of 51 MB noise 102 us with 8, 89 with 4)
+constexpr int kBurst = 4;
 // decode: threads per workgroup, one workgroup per compute unit.  The payload slice in LDS is what limits the chunks in
 // flight on a unit.  With 1024 threads the stage holds 768 chunks at 46 words (5.75 bits per symbol) and 1024 at 34: a
 // stream whose chunks come to slightly more than 768 per unit (51 MB of index streams: 788) takes one pass and not two;
@@ -668,7 +668,6 @@ __global__ __launch_bounds__(kGroupThreads) void huffman_write_kernel(const Batc
     }
 }
 
-// One chunk: `valid` symbols from the words next_word(0), next_word(1), ... to dst (16-byte aligned).
 // The per-length tables of a stream, in LDS: what a code longer than the fast table's index is decoded with.
 struct LongCodes {
     uint32_t per_length[kMaxLen + 2];                         // [k]: codes of length k
@@ -680,7 +679,10 @@ struct LongCodes {
 // An entry of the decoder's tables: symbol << 8 | 32 - length; 0 where there is none.  With what the code leaves of a
 // word at the bottom, the entry as it is read is the shift amount that moves the stream up (drop_code).
 __device__ __forceinline__ uint32_t entry_of(uint32_t symbol, uint32_t length) { return (symbol << 8) | (32u - length); }
-__device__ __forceinline__ uint32_t symbol_in(uint32_t entry) { return entry >> 8; }
+__device__ __forceinline__ uint32_t symbols_in(const uint32_t (&e)[4])                              // a byte each
+{
+    return (e[0] >> 8) | (e[1] & 0xff00u) | ((e[2] & 0xff00u) << 8) | ((e[3] & 0xff00u) << 16);
+}
 __device__ __forceinline__ uint32_t length_in(uint32_t entry) { return 32u - (entry & 0xffu); }     // 32 where there is none
 
 // The next 64 bits of the stream, the next one on top.  Two words and 32-bit shifts: a 64-bit shift whose amount the
@@ -786,52 +788,33 @@ template <int FAST>
 __device__ __forceinline__ uint32_t decode_symbol(const uint16_t* fast, const uint16_t* second, const Second& behind,
                                                   const LongRegs<FAST>& longer, const LongCodes* tables, uint32_t top)
 {
-    const uint32_t e = fast[top >> (32 - FAST)];
-    return e ? e : behind_fast<FAST>(second, behind, longer, tables, top);
+    uint32_t e = fast[top >> (32 - FAST)];
+    if (__builtin_expect(e == 0u, 0)) e = behind_fast<FAST>(second, behind, longer, tables, top);
+    return e;
 }
 
-template <int FAST, typename NextWord>
-__device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const Lookup table, NextWord next_word)
-{
-    const LongRegs<FAST> longer = long_regs<FAST>(table.tables);
-    const Second behind = table.behind;
-    const uint16_t* fast = table.fast;
-    const uint16_t* second = table.second;
-    const LongCodes* tables = table.tables;
-    uint32_t taken = 0;                                       // words moved into `next`
-    Ahead next = {0u, 0u};
-    uint32_t have = 0;                                        // bits of it that are there
-    for (uint32_t half = 0; half < valid; half += 16 * kRingBurst) {
-        u32x4 piece[kRingBurst];
+// What a thread has decoded goes out kBurst vectors at a time.  LINES: half of a cache line waits for the other half, and the
+// line's stores go out back to back, so that it is complete in the L2 before it can be evicted.
+template <bool LINES> struct Output {
+    uint8_t* dst;
+    u32x4    first_half[kBurst];
+    __device__ __forceinline__ void store(uint32_t at, uint32_t valid, const u32x4 (&piece)[kBurst])
+    {
+        if constexpr (LINES) {
+            const bool second = (at / (16 * kBurst)) % 2u != 0u;
+            if (!second && at + 16 * kBurst < valid) {
 #pragma unroll
-        for (int v = 0; v < kRingBurst; ++v) {
-            uint32_t sixteen[4];
-            if (half + 16u * v >= valid) { piece[v] = u32x4{0u, 0u, 0u, 0u}; continue; }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t four = 0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    if (have <= 32u) {
-                        const uint32_t w = next_word(taken);
-                        ++taken;
-                        next.high |= have < 32u ? w >> have : 0u;
-                        next.low = have == 32u ? w : have ? w << (32u - have) : 0u;
-                        have += 32u;
-                    }
-                    const uint32_t e = decode_symbol<FAST>(fast, second, behind, longer, tables, next.high);
-                    next = drop_code(next, e);
-                    have -= length_in(e);
-                    four |= symbol_in(e) << (8 * b);
-                }
-                sixteen[q] = four;
+                for (int v = 0; v < kBurst; ++v) first_half[v] = piece[v];
+                return;
             }
-            piece[v] = u32x4{sixteen[0], sixteen[1], sixteen[2], sixteen[3]};
-        }
-        // a whole cache line's worth of stores back to back: the line is complete in the L2 before it can be evicted
+            if (second) {
 #pragma unroll
-        for (int v = 0; v < kRingBurst; ++v) {
-            const uint32_t i = half + 16u * v;
+                for (int v = 0; v < kBurst; ++v) *reinterpret_cast<u32x4*>(dst + at - 16 * (kBurst - v)) = first_half[v];
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < kBurst; ++v) {
+            const uint32_t i = at + 16u * v;
             if (i + 16 <= valid) {
                 *reinterpret_cast<u32x4*>(dst + i) = piece[v];
             } else if (i < valid) {
@@ -839,6 +822,53 @@ __device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const
                 for (uint32_t b = 0; i + b < valid; ++b) dst[i + b] = (uint8_t)(w[b >> 2] >> (8 * (b & 3u)));
             }
         }
+    }
+};
+// One chunk: `valid` symbols from the words first_word, next_word(1), next_word(2), ... to dst (16-byte aligned).
+// A lane in three or four takes a word at any step, so the wave steps aside for it nearly always: the word that it takes then
+// has been read before, and only the table is waited for (51 MB, half of it noise, 107 us with the word read when it is
+// needed, 89 now; with eight vectors held back, the word read ahead alone 102).
+template <int FAST, typename NextWord>
+__device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const Lookup table, uint32_t first_word, NextWord next_word)
+{
+    const LongRegs<FAST> longer = long_regs<FAST>(table.tables);
+    const Second behind = table.behind;
+    const uint16_t* fast = table.fast;
+    const uint16_t* second = table.second;
+    const LongCodes* tables = table.tables;
+    uint32_t word = first_word, taken = 1;                    // the word that comes behind `next`; words taken up to it
+    Ahead next = {0u, 0u};
+    uint32_t have = 0;                                        // bits of it that are there
+    Output<true> out;
+    out.dst = dst;
+#pragma unroll 1
+    for (uint32_t half = 0; half < valid; half += 16 * kBurst) {
+        u32x4 piece[kBurst];
+#pragma unroll
+        for (int v = 0; v < kBurst; ++v) {
+            uint32_t sixteen[4];
+            if (half + 16u * v >= valid) { piece[v] = u32x4{0u, 0u, 0u, 0u}; continue; }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                uint32_t e[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    if (have < 32u) {                         // (the low word is used up: 32 bits are enough for any code)
+                        next.high |= word >> have;
+                        next.low = align_right(word, 0u, have);
+                        have += 32u;
+                        word = next_word(taken);
+                        ++taken;
+                    }
+                    e[b] = decode_symbol<FAST>(fast, second, behind, longer, tables, next.high);
+                    next = Ahead{align_right(next.high, next.low, e[b]), align_right(next.low, 0u, e[b])};
+                    have -= length_in(e[b]);
+                }
+                sixteen[q] = symbols_in(e);
+            }
+            piece[v] = u32x4{sixteen[0], sixteen[1], sixteen[2], sixteen[3]};
+        }
+        out.store(half, valid, piece);
     }
 }
 
@@ -867,6 +897,8 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
     const LongCodes* tables = table.tables;
     uint32_t pos = 0;                                         // bits of the chunk consumed
     Window w = {0u, words[0], words[1]};
+    Output<false> out;
+    out.dst = dst;
 #pragma unroll 1
     for (uint32_t half = 0; half < valid; half += 16 * kBurst) {
         u32x4 piece[kBurst];
@@ -909,21 +941,11 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
                 }
                 const bool crossed = window_word(pos) != at;  // a code has at most 24 bits
                 w = Window{crossed ? ahead[1] : ahead[0], crossed ? ahead[2] : ahead[1], crossed ? ahead[3] : ahead[2]};
-                sixteen[q] = (e[0] >> 8) | (e[1] & 0xff00u) | ((e[2] & 0xff00u) << 8) | ((e[3] & 0xff00u) << 16);
+                sixteen[q] = symbols_in(e);
             }
             piece[v] = u32x4{sixteen[0], sixteen[1], sixteen[2], sixteen[3]};
         }
-        // a whole cache line's worth of stores back to back: the line is complete in the L2 before it can be evicted
-#pragma unroll
-        for (int v = 0; v < kBurst; ++v) {
-            const uint32_t i = half + 16u * v;
-            if (i + 16 <= valid) {
-                *reinterpret_cast<u32x4*>(dst + i) = piece[v];
-            } else if (i < valid) {
-                const uint32_t w[4] = {piece[v].x, piece[v].y, piece[v].z, piece[v].w};
-                for (uint32_t b = 0; i + b < valid; ++b) dst[i + b] = (uint8_t)(w[b >> 2] >> (8 * (b & 3u)));
-            }
-        }
+        out.store(half, valid, piece);
     }
 }
 
@@ -1157,8 +1179,8 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
             for (int k = 0; k < 8; ++k) mine[k * kDecodeThreads] = first_word + k < payload_words ? payload[first_word + k] : 0u;
 #pragma unroll
             for (int k = 0; k < 4; ++k) pending[k] = first_word + 8 + k < payload_words ? payload[first_word + 8 + k] : 0u;
-            decode_chunk<kFastBits>(valid, dst, Lookup{fast, second, &tables, behind}, [&](uint32_t taken) {
-                if ((taken & 3u) == 0u && taken != 0u) {      // a block of four used up: refill the half of the ring just freed
+            decode_chunk<kFastBits>(valid, dst, Lookup{fast, second, &tables, behind}, mine[0], [&](uint32_t taken) {
+                if ((taken & 3u) == 0u) {                     // a block of four used up: refill the half of the ring just freed
                     const uint32_t slot = (taken + 4u) & 7u;
 #pragma unroll
                     for (int k = 0; k < 4; ++k) mine[((slot + k) & 7u) * kDecodeThreads] = pending[k];
