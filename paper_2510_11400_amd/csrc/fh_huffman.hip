@@ -31,6 +31,7 @@
 #include "../../include/fedhybrid.h"
 
 #include "fh_batch.hpp"
+#include "fh_rules.hpp"
 #include "fh_scan.hpp"
 #include "fh_stages.hpp"
 
@@ -887,7 +888,7 @@ __device__ __forceinline__ Ahead window_bits(const Window& w, uint32_t pos)
 {
     return Ahead{align_right(w.w0, w.w1, 0u - pos), align_right(w.w1, w.w2, 0u - pos)};
 }
-template <int FAST>
+template <int FAST, bool LINES>
 __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst, const Lookup table, const uint32_t* words)
 {
     const LongRegs<FAST> longer = long_regs<FAST>(table.tables);
@@ -897,7 +898,7 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
     const LongCodes* tables = table.tables;
     uint32_t pos = 0;                                         // bits of the chunk consumed
     Window w = {0u, words[0], words[1]};
-    Output<false> out;
+    Output<LINES> out;
     out.dst = dst;
 #pragma unroll 1
     for (uint32_t half = 0; half < valid; half += 16 * kBurst) {
@@ -953,7 +954,7 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
 // The stream may be foreign: the tables are built from whatever the 256 length bytes say
 // (lengths above 24 count as unused), reads of payload words are bounded by the stream's size
 // (words outside read as zero), and every loop is bounded by the symbol count.
-template <int kDecodeThreads>
+template <int kDecodeThreads, bool LINES>
 __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Batch<DecodeJob> batch)
 {
     constexpr int kStageWords = StageWords<kDecodeThreads>::kAll, kFastBits = FastBits<kDecodeThreads>::kAll;
@@ -1168,7 +1169,7 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
             __syncthreads();
             // anything at all for a foreign stream: clamped, the reads stay inside the array (a chunk is at most 192 words)
             const uint32_t at = first_word - slice_at < slice_words ? first_word - slice_at : slice_words;
-            decode_chunk_staged<kFastBits>(valid, dst, Lookup{fast, second, &tables, behind}, stage + phase + at);
+            decode_chunk_staged<kFastBits, LINES>(valid, dst, Lookup{fast, second, &tables, behind}, stage + phase + at);
         } else if (live) {
             // a ring of eight words per thread: when four have been consumed, the four loaded at the
             // previous refill take their place and the next four are requested, so a load has the time
@@ -1346,10 +1347,11 @@ fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t c
     // passes, where the wide ones seat up to twice as many in one, and those get at least 512 chunks each, so that
     // every unit has one.  (A count that is on the device is an upper bound here: the index streams of the whole chain
     // come to some two thirds of it.  Where the count is exact, a workgroup's share is to fit its stage in one pass.)
-    uint64_t narrow = 0;
+    uint64_t narrow = 0, symbols = 0;
     for (int32_t i = 0; i < count; ++i) {
         const uint64_t seats = items[i].n_device ? (uint64_t)kDecodeThreadsSmall : kSmallSeats;
         narrow += (chunks_of(items[i].n) + seats - 1) / seats;
+        symbols += items[i].n;
     }
     const bool small = narrow <= (uint64_t)kComputeUnits;
     const uint64_t per_group = small ? 256u : 512u;
@@ -1395,10 +1397,13 @@ fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t c
         seal(b);
         if (b.count > 0) {
             if (small)
-                hipLaunchKernelGGL(huffman_decode_kernel<kDecodeThreadsSmall>, dim3(b.block_start[b.count]),
+                hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreadsSmall, false>), dim3(b.block_start[b.count]),
                                    dim3(kDecodeThreadsSmall), 0, s, b);
+            else if (decode_in_whole_lines(symbols))
+                hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, true>), dim3(b.block_start[b.count]),
+                                   dim3(kDecodeThreads), 0, s, b);
             else
-                hipLaunchKernelGGL(huffman_decode_kernel<kDecodeThreads>, dim3(b.block_start[b.count]),
+                hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, false>), dim3(b.block_start[b.count]),
                                    dim3(kDecodeThreads), 0, s, b);
             launched = true;
         }

@@ -88,6 +88,31 @@ def test_streams_on_both_sides_of_the_scan(api, more):
     _check(api, data, f"{data.size} symbols")
 
 
+@pytest.mark.parametrize("kind", ["2.5", "14", "mixed"])
+def test_outputs_stored_in_whole_cache_lines(api, kind):
+    # a call of 384 MiB and more, as two streams that end inside a line, inside a half of one and inside a vector; 14: passes
+    # that seat fewer chunks; mixed: noise behind the clustered half, whose words go through the rings
+    rng = np.random.default_rng(3)
+    sizes = [(200 << 20) + 256 * 77 + 64 + 48 + 5, (184 << 20) + 70]
+    assert sum(sizes) >= 384 << 20
+    piece = np.clip(np.rint(rng.normal(128, 2.5 if kind == "mixed" else float(kind), 9999991)), 0, 255).astype(np.uint8)
+    datas = []
+    for n in sizes:
+        data = np.resize(piece, n)
+        if kind == "mixed":
+            data[n // 2:] = np.resize(rng.integers(0, 256, 9999973, dtype=np.uint8), n - n // 2)
+        datas.append(data)
+    print(f"[huffman] whole lines, {kind}", flush=True)
+    batch = api.HuffmanBatch([torch.from_numpy(d).cuda() for d in datas])
+    for o in batch.out:
+        o.fill_(0xEE)
+    api.fh_huffman_encode_batch(batch)
+    api.fh_huffman_decode_batch(batch)
+    torch.cuda.synchronize()
+    for d, o in zip(batch.data, batch.out):
+        assert torch.equal(o, d)
+
+
 @pytest.mark.parametrize("kind", ["deep", "flat", "nearly flat"])
 @pytest.mark.parametrize("n", [5, 16411, 256 * 488 * 256, 256 * 488 * 256 + 3])
 def test_decoder_forms(api, n, kind):

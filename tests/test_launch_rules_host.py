@@ -28,6 +28,7 @@ int main(int, char** argv)
     long long a, b, c, d;
     while (std::scanf("%lld %lld %lld %lld", &a, &b, &c, &d) == 4)
         if (!std::strcmp(argv[1], "marked_spans_per_wave")) std::printf("%lld\\n", (long long)fh::marked_spans_per_wave(a, b, c, d));
+        else if (!std::strcmp(argv[1], "decode_in_whole_lines")) std::printf("%d\\n", (int)fh::decode_in_whole_lines(a));
 }
 ''')
     subprocess.run([cxx, "-std=c++17", "-I", CSRC, src, "-o", exe], check=True)
@@ -53,3 +54,10 @@ def test_count_pass_fills_the_device_before_a_wave_gets_a_second_span(rules):
             assert spans == 1 or launch // spans >= 4096 or tensor // spans >= 2048, (launch, tensor, channels, spans)
             assert spans == 8 or tensor < 2048 * (spans + 1), (launch, tensor, channels, spans)
         assert spans == 8 or launch < 4096 * (spans + 1), (launch, tensor, channels, spans)
+
+
+def test_decoder_stores_whole_lines_where_no_cache_holds_the_output(rules):
+    """The memory-side cache has 256 MB: outputs well beyond it."""
+    mib = 1 << 20
+    rows = [(n, 0, 0, 0) for n in (0, 1, 64 * mib, 256 * mib, 384 * mib - 1, 384 * mib, 1 << 32, 26 << 32)]
+    assert rules("decode_in_whole_lines", rows) == [0, 0, 0, 0, 0, 1, 1, 1]
