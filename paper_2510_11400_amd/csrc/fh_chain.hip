@@ -18,6 +18,7 @@
 #include "../../include/fedhybrid.h"
 
 #include "fh_batch.hpp"
+#include "fh_rules.hpp"
 #include "fh_scan.hpp"
 #include "fh_stages.hpp"
 
@@ -419,7 +420,13 @@ fh_status fh_mix_decompress_batch(const fh_mix_item* items, int32_t count, void*
         sp.push_back(d);
     }
     if (!hf.empty() && (st = fh_huffman_decode_batch(hf.data(), (int32_t)hf.size(), stream)) != FH_OK) return st;
-    if (!sp.empty() && (st = sparse_decode_for_next(sp.data(), (int32_t)sp.size(), static_cast<hipStream_t>(stream))) != FH_OK) return st;
+    uint64_t map_bytes = 0;
+    for (const fh_sparse_decode_item& d : sp) map_bytes += d.out_cap;
+    if (!sp.empty()) {
+        st = maps_stay_in_cache(map_bytes) ? sparse_decode_for_next(sp.data(), (int32_t)sp.size(), static_cast<hipStream_t>(stream))
+                                           : fh_sparse_decode_batch(sp.data(), (int32_t)sp.size(), stream);
+        if (st != FH_OK) return st;
+    }
 
     std::vector<fh_mixed_item> mix((size_t)count);
     for (int32_t i = 0; i < count; ++i) {

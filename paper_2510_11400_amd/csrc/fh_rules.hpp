@@ -34,4 +34,11 @@ inline int32_t marked_spans_per_wave(int64_t launch_spans, int64_t tensor_spans,
 // 523 and 491.
 inline bool decode_in_whole_lines(uint64_t symbols) { return symbols >= (uint64_t)384 << 20; }
 
+// The whole chain's maps, `bytes` in a call: whether the sparse stage leaves them in the memory-side cache for the restore.
+// All maps of a call are written before the restore begins; beyond a part of the cache's 256 MB the first are gone when it
+// reads them, and ordinary stores then only write back beside it.  Restore of feature maps, both stages, ordinary stores
+// against stores that pass the caches by: fp32 34 MB 142 and 172 us, 85 MB 176 and 206, 132 MB 242 and 230, 157 MB 268 and
+// 243; one tensor 77 MB 140 and 148, 154 MB 214 and 192; bf16 79 MB 214 and 250, 103 MB 276 and 278, 132 MB 336 and 328.
+inline bool maps_stay_in_cache(uint64_t bytes) { return bytes <= (uint64_t)96 << 20; }
+
 }  // namespace fh

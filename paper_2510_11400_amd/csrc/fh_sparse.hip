@@ -341,9 +341,9 @@ __device__ __forceinline__ void load_tile(const Bits* x, const TilePos& t, uint3
 
 // The tile back to the map (only elements that exist).
 // READ_NEXT: ordinary stores, so that the maps are in the memory-side cache when the next kernel reads them (the
-// restore of the whole chain: 24 bf16 activations with 47 MB of maps 197 -> 163 us, feature maps with 36 MB 122 -> 112);
-// otherwise no kernel of this library reads them, and they pass the caches by (ordinary stores of 93 MB of maps cost the
-// next call's first pass 24 us instead of 18).
+// restore of the whole chain: 24 bf16 activations with 47 MB of maps 197 -> 163 us, feature maps with 36 MB 122 -> 112; up to
+// which size, fh_rules.hpp); otherwise they pass the caches by (ordinary stores of 93 MB of maps that no kernel of this
+// library reads cost the next call's first pass 24 us instead of 18).
 template <typename Bits, int N, bool READ_NEXT>
 __device__ __forceinline__ void store_tile(Bits* out, const TilePos& t, uint32_t w, bool rows_are_vectors,
                                            const Bits (&e)[N][N])

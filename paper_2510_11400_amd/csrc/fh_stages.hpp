@@ -30,7 +30,7 @@ fh_status compress_first(const fh_mixed_item* items, const fh_classify_item* cla
 fh_status compress_kept(const fh_mixed_item* items, int32_t count, hipStream_t s);
 constexpr int64_t kFirstSpan = 2048;               // elements of such a span at most
 
-// fh_sparse_decode_batch for maps that the next kernel on the stream reads: they are left in the caches.
+// fh_sparse_decode_batch for maps that the next kernel on the stream finds in the caches (maps_stay_in_cache).
 fh_status sparse_decode_for_next(const fh_sparse_decode_item* items, int32_t count, hipStream_t s);
 
 // fh_huffman_encode_batch for histograms (the first 256 words of the items' workspaces) that have been cleared, and

@@ -223,6 +223,36 @@ def test_batched_chain_item_by_item_and_in_a_captured_graph(api):
             _compare(api, batch, i, x, c, "f32")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_maps_beyond_the_caches_share_restore_as_each_tensor_does_alone(api, dtype):
+    """Two tensors whose maps have 74 MiB each: one alone is restored from maps that the caches hold, both in one call from maps
+    that pass them by."""
+    print(f"[chain] maps on both sides of the caches' share, {dtype}", flush=True)
+    outer, C, hw, kept = (64, 48, 112, 24) if dtype == "f32" else (128, 48, 112, 24)
+    rng = np.random.default_rng(4)
+    entries, singles = [], []
+    for k in range(2):
+        x = np.clip(rng.standard_normal((outer, C, hw * hw), dtype=np.float32), 0, 6)
+        x[:, ::3] *= np.where(rng.random((outer, C // 3, hw * hw), dtype=np.float32) < 0.05, np.float32(81), np.float32(1))
+        xd = torch.from_numpy(x.reshape(-1)).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+        case = (outer, C, hw * hw, (hw, hw), kept, 128, 4, "nearest", 4, 0.5, 0.02, True, dtype, 1)
+        entries.append(_entry(api, xd, case, "f32"))
+        singles.append(torch.empty_like(entries[-1].out))
+    assert 2 * outer * kept * hw * hw * (4 if dtype == "f32" else 2) > 96 << 20 > outer * kept * hw * hw * (4 if dtype == "f32" else 2)
+    both = api.MixBatch(entries)
+    api.fh_mix_compress_batch(both)
+    for e, single in zip(entries, singles):
+        api.fh_mix_decompress_batch(api.MixBatch([e]))
+        torch.cuda.synchronize()
+        single.copy_(e.out)
+        e.out.fill_(-1.0)
+    assert all(int(both.header(k)[7]) == C // 3 for k in range(2))
+    api.fh_mix_decompress_batch(both)
+    torch.cuda.synchronize()
+    for k, (e, single) in enumerate(zip(entries, singles)):
+        assert torch.equal(e.out.view(torch.int32), single.view(torch.int32)), f"tensor {k}"
+
+
 def test_chain_rejects_bad_arguments_before_any_launch(api):
     print("[chain] argument checks", flush=True)
     import ctypes

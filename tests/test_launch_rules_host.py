@@ -28,6 +28,7 @@ int main(int, char** argv)
     long long a, b, c, d;
     while (std::scanf("%lld %lld %lld %lld", &a, &b, &c, &d) == 4)
         if (!std::strcmp(argv[1], "marked_spans_per_wave")) std::printf("%lld\\n", (long long)fh::marked_spans_per_wave(a, b, c, d));
+        else if (!std::strcmp(argv[1], "maps_stay_in_cache")) std::printf("%d\\n", (int)fh::maps_stay_in_cache(a));
         else if (!std::strcmp(argv[1], "decode_in_whole_lines")) std::printf("%d\\n", (int)fh::decode_in_whole_lines(a));
 }
 ''')
@@ -61,3 +62,10 @@ def test_decoder_stores_whole_lines_where_no_cache_holds_the_output(rules):
     mib = 1 << 20
     rows = [(n, 0, 0, 0) for n in (0, 1, 64 * mib, 256 * mib, 384 * mib - 1, 384 * mib, 1 << 32, 26 << 32)]
     assert rules("decode_in_whole_lines", rows) == [0, 0, 0, 0, 0, 1, 1, 1]
+
+
+def test_the_chains_maps_pass_the_caches_by_where_these_do_not_hold_them(rules):
+    """Ordinary stores up to 96 MiB of maps in a call; from 126 MiB on they were measured to be slower."""
+    mib = 1 << 20
+    rows = [(n, 0, 0, 0) for n in (0, mib, 47 * 10 ** 6, 96 * mib, 96 * mib + 1, 126 * mib, 1 << 33)]
+    assert rules("maps_stay_in_cache", rows) == [1, 1, 1, 1, 0, 0, 0]
