@@ -17,8 +17,8 @@
 //   count       a wave reads four chunks at a time with one 16-byte load per lane and adds the
 //               code lengths up over each chunk's sixteen lanes: the chunk's length in words;
 //   scan        the sums of groups of 256 chunks (a workgroup of the count pass) are scanned by
-//               one workgroup, in long streams; in others every workgroup of the write pass
-//               adds up the sums before its own;
+//               one workgroup, in launches of many groups; in others every workgroup of the
+//               write pass adds up the sums before its own;
 //   write       word counts become offsets (group base + a scan over the workgroup); a wave
 //               then codes four chunks at a time, every lane placing the bits of its sixteen
 //               symbols in an LDS area by OR, and stores the four chunks' words -- one
@@ -73,11 +73,6 @@ constexpr int kGroup = 256;                        // chunks of a group
 constexpr int kGroupThreads = 1024;
 constexpr int kWaves = kGroupThreads / 64;
 constexpr int kRounds = kGroup / kWaves / 4;
-// Streams of up to this many groups have no scan of the group sums between the two passes: a workgroup of the write pass
-// adds up the sums before its own, two to four per thread, which takes no longer than reading the scanned one (32.7
-// against 32.6 us at 51 MB, the longest stream 335 groups) and saves a launch of 4.8 us.  The sums read grow with the square of the
-// groups: at this limit 34 MB from the L2, which is less than that launch takes still.
-constexpr uint32_t kUnscannedGroups = 4096;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -510,7 +505,7 @@ __global__ __launch_bounds__(kGroupThreads) void huffman_count_kernel(const Batc
     }
 }
 
-// ---- scan of the group sums (in place, exclusive) of long streams; the stream's size ------------------
+// ---- scan of the group sums (in place, exclusive); the stream's size --------------------------------------
 // `words`: of the stream's payload; one thread
 __device__ __forceinline__ void leave_size(const Layout& lay, uint32_t words)
 {
@@ -1265,7 +1260,6 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
         // the same streams three times: a workgroup each | by histogram workgroups | by groups of chunks
         Batch<Layout> each, hist, grouped;
         reset(each); reset(hist); reset(grouped);
-        uint32_t most = 0;                                    // groups of a stream
         while (i < count && each.count < kBatch) {
             const fh_huffman_encode_item& it = items[i];
             Layout lay;
@@ -1293,7 +1287,6 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
             push(each, lay, 1);
             push(hist, lay, lay.hist_blocks);
             push(grouped, lay, lay.groups > 0 ? lay.groups : 1);       // one writes an empty stream's size
-            if (lay.groups > most) most = lay.groups;
             ++i;
         }
         seal(each); seal(hist); seal(grouped);
@@ -1302,7 +1295,7 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
         launch(huffman_code_kernel, each, (uint32_t)each.count, s, kCodeThreads);
         const uint32_t all = grouped.block_start[grouped.count];
         launch(huffman_count_kernel, grouped, all, s, kGroupThreads);
-        if (most > kUnscannedGroups) {
+        if (group_sums_are_scanned(all)) {
             launch(huffman_scan_kernel, each, (uint32_t)each.count, s);
             launch(huffman_write_kernel<true>, grouped, all, s, kGroupThreads);
         } else {

@@ -27,6 +27,13 @@ inline int32_t marked_spans_per_wave(int64_t launch_spans, int64_t tensor_spans,
     return (int32_t)(spans < 1 ? 1 : spans > 8 ? 8 : spans);
 }
 
+// The Huffman encoder's group sums in a launch of `groups` altogether: scanned by a kernel between the count and the write
+// pass, or every workgroup of the write pass adds up those before its own.  Adding up saves that launch and makes every
+// workgroup of the write pass take longer, so what counts is how many of those there are.  Encoding, scanned and not: one
+// stream of 64 groups 36.9 and 36.3 us, of 1024 76.4 and 73.7, of 4096 203.4 and 200.8, of 6000 317 and 317, of 12288
+// 599 and 609; 24 streams of 335 groups 394.5 and 395.7, 24 of 1024 1108 and 1124, six of 4096 1122 and 1151.
+inline bool group_sums_are_scanned(int64_t groups) { return groups > 4096; }
+
 // The Huffman decoder's stores, in a call of `symbols`: whether half a cache line waits for its other half.
 // Where the memory-side cache holds the output, half lines meet there, and storing early is better: the last stores of a
 // pass are fewer (51 MB 41.4 us, 42.8 in whole lines; 268 MB of two bits a symbol 168 and 175).  Beyond, half lines reach

@@ -88,6 +88,21 @@ def test_streams_on_both_sides_of_the_scan(api, more):
     _check(api, data, f"{data.size} symbols")
 
 
+@pytest.mark.parametrize("groups", [[4000, 95, 1], [4000, 95, 2], [1, 0, 1, 4093, 1]])
+def test_launches_of_several_streams_on_both_sides_of_the_scan(api, groups):
+    # 4096 groups of a launch, and 4097, an empty stream has a workgroup too; scanned launches with short streams in them
+    rng = np.random.default_rng(8)
+    piece = np.clip(np.rint(rng.normal(128, 3.0, 99991)), 0, 255).astype(np.uint8)
+    datas = [np.resize(piece, g * 65536 - (17 if g else 0)) for g in groups]
+    print(f"[huffman] streams of {groups} groups", flush=True)
+    batch = api.HuffmanBatch([torch.from_numpy(d).cuda() if d.size else torch.empty(0, dtype=torch.uint8, device="cuda") for d in datas])
+    api.fh_huffman_encode_batch(batch)
+    torch.cuda.synchronize()
+    for d, stream, total in zip(datas, batch.streams, batch.totals.cpu().tolist()):
+        want, bits = oracle.huffman_encode(d)
+        assert total == [want.size, bits] and np.array_equal(stream[:want.size].cpu().numpy(), want), f"{d.size} symbols"
+
+
 @pytest.mark.parametrize("kind", ["2.5", "14", "mixed"])
 def test_outputs_stored_in_whole_cache_lines(api, kind):
     # a call of 384 MiB and more, as two streams that end inside a line, inside a half of one and inside a vector; 14: passes

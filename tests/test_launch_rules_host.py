@@ -29,6 +29,7 @@ int main(int, char** argv)
     while (std::scanf("%lld %lld %lld %lld", &a, &b, &c, &d) == 4)
         if (!std::strcmp(argv[1], "marked_spans_per_wave")) std::printf("%lld\\n", (long long)fh::marked_spans_per_wave(a, b, c, d));
         else if (!std::strcmp(argv[1], "maps_stay_in_cache")) std::printf("%d\\n", (int)fh::maps_stay_in_cache(a));
+        else if (!std::strcmp(argv[1], "group_sums_are_scanned")) std::printf("%d\\n", (int)fh::group_sums_are_scanned(a));
         else if (!std::strcmp(argv[1], "decode_in_whole_lines")) std::printf("%d\\n", (int)fh::decode_in_whole_lines(a));
 }
 ''')
@@ -69,3 +70,8 @@ def test_the_chains_maps_pass_the_caches_by_where_these_do_not_hold_them(rules):
     mib = 1 << 20
     rows = [(n, 0, 0, 0) for n in (0, mib, 47 * 10 ** 6, 96 * mib, 96 * mib + 1, 126 * mib, 1 << 33)]
     assert rules("maps_stay_in_cache", rows) == [1, 1, 1, 1, 0, 0, 0]
+
+
+def test_group_sums_are_scanned_in_launches_of_many_groups(rules):
+    """Up to 4096 groups in a launch, however many streams they belong to, there is no scan."""
+    assert rules("group_sums_are_scanned", [(n, 0, 0, 0) for n in (0, 1, 335, 4096, 4097, 24 * 335, 1 << 31)]) == [0, 0, 0, 0, 1, 1, 1]
