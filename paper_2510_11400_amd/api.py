@@ -674,8 +674,8 @@ def compress_channel_wise(xs: Sequence[torch.Tensor], splits, k_sigma: float, ou
                           rounding, seed: int, tensor_ids: Sequence[int]) -> "List[ChannelWiseStore]":
     """Classification, slot numbering and routed quantisation of several tensors, contiguous and 16-byte
     aligned, on the current stream; splits: (outer, channels, inner, raw_channels) of each.  The batched entry points on
-    items that are filled in directly: two buffers a tensor are allocated where the batch objects allocate eight, and
-    what only the classification needs is one buffer for all."""
+    items that are filled in directly: one buffer a tensor is allocated for what is kept of it, where the batch objects
+    allocate eight, and one for all that only the classification needs."""
     count = len(xs)
     if count == 0:
         return []

@@ -150,7 +150,7 @@ __device__ __forceinline__ float from_pair_lane(float v)
 // the key advancing by the Weyl constants between rounds.  The key schedule is
 // wave-uniform, so it lives in scalar registers.
 // Returns the complement of the four words, which is what the quantiser adds: for the two that end in an xor it is in
-// the last round's truth table (8 of 690 vector instructions per bf16 wave; routed encoder set 377.7 -> 375.4 us).
+// the last round's truth table (8 of 690 vector instructions per bf16 wave; routed encoder set 374.5 -> 371.3 us).
 __device__ __forceinline__ u32x4 philox4x32_10_complement(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                uint32_t k0, uint32_t k1)
 {

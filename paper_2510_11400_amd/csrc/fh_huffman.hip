@@ -45,13 +45,13 @@ constexpr int kChunkWordsMax = kChunk * kMaxLen / 32;
 constexpr int kHistCopies = 32;                     // one per LDS bank
 constexpr int kHistThreads = 1024;
 constexpr int kHistBlocksMax = 512;                // histogram workgroups per stream: two per compute unit
-// decode: 16-byte output vectors held back and stored together; at 51 MB one at a time 67 us, 2 51, 4 49, with 8 the code no
-// longer fits the instruction cache and takes 53 (the rings' form likewise: half of 51 MB noise 102 us with 8, 89 with 4)
+// decode: 16-byte output vectors held back and stored together; 51 MB of index streams one at a time 61.4 us, 2 52.3, 4 52.0,
+// with 8 the code no longer fits the instruction cache and takes 55.6 (the rings likewise: half of 51 MB noise 102 and 89)
 constexpr int kBurst = 4;
 // decode: threads per workgroup, one workgroup per compute unit.  The payload slice in LDS is what limits the chunks in
-// flight on a unit.  With 1024 threads the stage holds 768 chunks at 46 words (5.75 bits per symbol) and 1024 at 34: a
+// flight on a unit.  With 1024 threads the stage holds 768 chunks at 46 words (5.75 bits per symbol) and 1024 at 34.5: a
 // stream whose chunks come to slightly more than 768 per unit (51 MB of index streams: 788) takes one pass and not two;
-// four waves per SIMD then keep the LDS busy (54 us before four symbols shared a window of the stream, 49 now).
+// four waves per SIMD then keep the LDS busy (53.9 us before four symbols shared a window of the stream, 51.5 now).
 // A launch of fewer chunks has 512 threads and two waves per SIMD, and there a symbol's chain of dependent steps is the
 // time: 158 cycles for a code that the first table has, some 400 more for the whole wave when a lane's is longer.  So the
 // LDS that the chunks leave goes to that table: 14 bits, where 12 had some lane of the wave in the second table at two
@@ -1078,8 +1078,8 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
 
     // The tables serve an equal share of the stream's chunks (a wave's worth at least), in passes of as many chunks as
     // there are threads at most.  The payload words of consecutive chunks are one contiguous slice.  A pass takes the
-    // chunks whose slice fits the stage -- all of them up to 46 (61) words per chunk on average, fewer on streams that
-    // hardly compress, where the threads beyond sit the pass out -- brings the slice into LDS with contiguous loads, and
+    // chunks whose slice fits the stage -- all there are threads for at up to 34.5 words per chunk on average (61 with 512
+    // threads), fewer on streams that compress less, where the threads beyond sit the pass out -- brings the slice into LDS with contiguous loads, and
     // the threads read their words from there (a thread walking its chunk in memory would fetch a cache line per
     // word).  A pass that could seat few of its chunks, and offsets that do not describe a slice (no encoder wrote
     // them), go through per-thread rings instead.
@@ -1118,8 +1118,8 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
         }
         __syncthreads();
         const uint32_t fitting = local.fitting;
-        // (workgroup-uniform) Below three quarters of twelve waves the rings do better: at eight bits per symbol every
-        // chunk is 64 words long, the threads' words lie 64 apart in the stage and all in one LDS bank.
+        // (workgroup-uniform) Below three quarters of its threads, of twelve waves at most, the rings do better: at some eight bits per
+        // symbol chunks are 64 words long, the threads' words lie 64 apart in the stage and all in one LDS bank.
         const bool staged = fitting > 0u && 4u * fitting >= 3u * (want < 768u ? want : 768u);
         const uint32_t take = staged ? fitting : want;        // chunks of this pass
         const uint32_t slice_end = staged ? offsets[chunk0 + fitting] : slice_at;
@@ -1129,8 +1129,8 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
         const uint32_t valid = !live ? 0u : n - base < (uint64_t)kChunk ? (uint32_t)(n - base) : (uint32_t)kChunk;
         const uint32_t first_word = live ? offsets[chunk] : 0u;
         uint8_t* dst = out + base;
-        // 16 bytes per load, twelve loads of a thread in flight: one at a time, a slice of ~50 words per thread
-        // would cost as many memory latencies.  The stage starts at the 16-byte boundary at or below the
+        // 16 bytes per load, nine loads of a thread in flight (twelve with 512 threads): one at a time, a slice of ~50 words
+        // per thread would cost as many memory latencies.  The stage starts at the 16-byte boundary at or below the
         // slice's first word (`phase` words earlier); what the vectors cover beyond the payload's ends is
         // read as zero.
         const uint32_t slice_words = slice_end - slice_at;    // none where the pass is not staged

@@ -24,10 +24,10 @@
 // of step 2*eps (same section: prediction from decompressed neighbours, errors within the bound
 // quantised to a byte, outliers kept intact) instead of verbatim; a thread runs the recurrence
 // of its block in registers.
-// Apart from one division and one multiplication per element in that mode, everything here is
-// integer and byte work; results do not depend on launch geometry.
-// All three passes that touch the maps are bound by vector instructions (400, 600 and 830 per wave of 64 4 x 4 tiles with
-// an error bound).  93 MB of fp32 maps, count, write and read: 20.6, 33.1 and 36.5 us with the general division, a
+// Apart from the division by the step in that mode (over_step: a scaling, a multiplication and four fused multiply-adds per
+// element) and the multiplication back, everything here is integer and byte work; results do not depend on launch geometry.
+// All three passes that touch the maps are bound by vector instructions (400, 590 and 785 per wave of 64 4 x 4 fp32 tiles
+// with an error bound).  93 MB of fp32 maps, count, write and read: 20.6, 33.1 and 36.5 us with the general division, a
 // byte of LDS at a time and three 64-bit sums per tile, 18.6, 29.7 and 32.4 now; 47 MB of bf16: 21.8, 32.7 and 38.0, now 17.4, 26.5
 // and 35.0.  (The dense tiles dealt to the first threads of the read pass, so that a wave has tiles of one kind, save a
 // third of its instructions and cost more in stores of single tile rows: 36 us.)
@@ -53,7 +53,13 @@ template <int N> struct Group {
 };
 constexpr int kScanThreads = 512;
 constexpr uint64_t kStreamedFrom = (uint64_t)128 << 20;    // bytes of maps in a launch from which the first pass streams
-constexpr uint32_t kSelfScanLimit = 2048;          // up to this many workgroups each adds up the sums before it
+// Sets of up to this many workgroups have no scan of the workgroups' sums between the passes: each adds up those before it.
+// Encode and decode of one set, scanned and not, window 4: of 1024 workgroups 17.6 and 14.0, 17.9 and 14.2 us, of 2048 23.6 and
+// 21.0, 22.2 and 18.9, of 3136 33.2 and 32.5, 27.8 and 24.3, of 4096 38.9 and 40.7, 31.0 and 29.4; window 2, 2048: 16.4 and 13.0,
+// 16.8 and 12.9; window 8, whose workgroups do the most, 1500: 44.5 and 43.6, 44.5 and 43.1, 2048: 55.9 and 56.9, 58.4 and 58.4.
+// Several such sets in a launch gain up to some 5000 workgroups together (window 8: 2500) and lose beyond: five of 2048, window 4,
+// 76.0 and 87.3, 56.9 and 58.2.
+constexpr uint32_t kSelfScanLimit = 2048;
 
 struct Sums {                                      // what a run of tiles writes
     uint64_t values, index_bytes, sparse_tiles;
