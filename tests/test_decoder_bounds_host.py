@@ -268,6 +268,55 @@ def test_sparse_foreign_streams_stay_in_bounds(decoders):
     assert all(st == FH_OK for st, _ in decoders(cases))
 
 
+@pytest.mark.parametrize("n", [2, 4, 8])
+def test_sparse_tiles_of_any_bytes_decode_the_same_in_every_window(decoders, n):
+    """Index bytes that are noise, small numbers, or valid ones with some changed: row pointers that fall or overlap, columns
+    that a tile does not have or that repeat.  The word-wise reading of a window of 4 is held to the byte-wise rule."""
+    rng = np.random.default_rng(40 + n)
+    cases, wants = [], []
+    for maps, h, w in ((6, 16, 16), (5, 13, 11), (7, 3, 2)):
+        x = W.salient_feature_maps(maps, h, w, seed=n)
+        info, values, indices, _ = oracle.sparse_encode(x, maps, h, w, n, 0.8)
+        for kind in ("noise", "small", "changed"):
+            idx = indices.copy()
+            if kind == "changed":
+                hit = rng.random(idx.size) < 0.2
+                idx[hit] = rng.integers(0, n + 3, int(hit.sum()))
+            else:
+                idx[:] = rng.integers(0, 256 if kind == "noise" else n + 2, idx.size)
+            want, at_v, at_i, tile = np.zeros((maps, h, w), np.float32), 0, 0, 0
+            for m in range(maps):
+                for r0 in range(0, h, n):
+                    for c0 in range(0, w, n):
+                        rows, cols, byte = min(n, h - r0), min(n, w - c0), int(info[tile])
+                        tile += 1
+                        count = min(byte & 0x7F, rows * cols)
+                        if byte & 0x80:
+                            mask = np.ones((rows, cols), bool)
+                        else:
+                            size = rows + 1 + count
+                            piece = idx[at_i: at_i + size]
+                            pointers = piece[:rows + 1].astype(int)
+                            lengths = np.clip(pointers[1:] - pointers[:-1], 0, n)
+                            mask = np.zeros((rows, cols), bool)
+                            for r in range(rows):
+                                first = min(int(pointers[r]), count)
+                                for j in range(int(lengths[r])):
+                                    if first + j < count and piece[rows + 1 + first + j] < cols:
+                                        mask[r, piece[rows + 1 + first + j]] = True
+                            at_i += size
+                        rank = np.minimum(np.cumsum(mask.reshape(-1)) - 1, max(count - 1, 0))
+                        if count:
+                            put = want[m, r0:r0 + rows, c0:c0 + cols]
+                            put[mask] = values[at_v + rank[mask.reshape(-1)]]
+                        at_v += count
+            cases.append(_sparse_case(info, values, idx, "f32", n, maps, h, w, 0.0))
+            wants.append(want)
+    for want, (st, got) in zip(wants, decoders(cases)):
+        assert st == FH_OK
+        assert np.array_equal(got, want.reshape(-1).view(np.uint8))
+
+
 def test_sparse_random_shapes_on_the_cpu(decoders):
     """Seeded random shapes, windows, thresholds, error bounds and dtypes (maps narrower or lower than the window,
     single maps, ragged edges): the encoder's streams and the decoder's maps against the oracle's."""
