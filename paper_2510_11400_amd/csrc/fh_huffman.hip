@@ -25,8 +25,8 @@
 //               contiguous piece -- with consecutive lanes on consecutive words.
 // Decoding needs no pass but one: the offsets are part of the stream.  A workgroup has the whole LDS of a compute unit.
 // While the payload slice of up to 1024 chunks is on its way there it rebuilds the canonical tables from the 256 lengths
-// (a lookup table for the short codes, a second one for the longer, comparisons for the longest), and a thread decodes
-// its chunk from LDS; the tables serve several such groups in long streams.
+// (a lookup table, coarser for the short codes than for the longer; comparisons for the longest), and a thread decodes
+// its chunk from LDS; the table serves several such groups in long streams.
 // Everything here is integer work; results do not depend on launch geometry.
 #include "../../include/fedhybrid.h"
 
@@ -52,18 +52,14 @@ constexpr int kBurst = 4;
 // flight on a unit.  With 1024 threads the stage holds 768 chunks at 46 words (5.75 bits per symbol) and 1024 at 34.5: a
 // stream whose chunks come to slightly more than 768 per unit (51 MB of index streams: 788) takes one pass and not two;
 // four waves per SIMD then keep the LDS busy (53.9 us before four symbols shared a window of the stream, 51.5 now).
-// A launch of fewer chunks has 512 threads and two waves per SIMD, and there a symbol's chain of dependent steps is the
-// time: 158 cycles for a code that the first table has, some 400 more for the whole wave when a lane's is longer.  So the
-// LDS that the chunks leave goes to that table: 14 bits, where 12 had some lane of the wave in the second table at two
-// symbols in five.  Index streams of 25 MB: 46.8 us as two workgroups of 256 with 12 bits each, 35.5 now.
+// A launch of fewer chunks has 512 threads, half as many waves to a SIMD, and a stage of 61 words for each: 25 MB of index
+// streams 46.8 us as two workgroups of 256, 35.5 as one of 512.
 constexpr int kDecodeThreads = 1024;
 constexpr int kDecodeThreadsSmall = 512;
-template <int THREADS> struct FastBits { static constexpr int kAll = THREADS >= 768 ? 12 : 14; };
 // LDS for the payload slice, in words: what fits beside the tables
 constexpr int kSmallWords = 61;
 template <int THREADS> struct StageWords { static constexpr int kAll = THREADS >= 768 ? 768 * 46 : THREADS * kSmallWords; };
 constexpr uint64_t kSmallSeats = kSmallWords * kDecodeThreadsSmall / 64;    // chunks of 8 bits per symbol that fit it: in practice, any
-constexpr int kSecondEntries = 2048;               // decode: entries of the table behind the fast one
 constexpr int kComputeUnits = 256;                 // MI355X
 // encode: a group of the count and write passes has sixteen waves, four rounds of four chunks each.  With four waves of
 // sixteen rounds a launch of fewer groups than the device holds at once waits for every round's loads in turn.  Count and
@@ -396,6 +392,23 @@ __device__ __forceinline__ void load_symbols(const uint8_t* in, uint64_t first, 
     }
 }
 
+__device__ __forceinline__ uint32_t larger(uint32_t a, uint32_t b) { return a > b ? a : b; }
+// the largest of the values of the lanes up to this one; every lane of the wave must be active
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ uint32_t dpp_larger(uint32_t v)
+{
+    return larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false));
+}
+__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v)
+{
+    v = dpp_larger<0x111, 0xf>(v);                            // as the sums of fh_scan.hpp
+    v = dpp_larger<0x112, 0xf>(v);
+    v = dpp_larger<0x114, 0xf>(v);
+    v = dpp_larger<0x118, 0xf>(v);
+    v = dpp_larger<0x142, 0xa>(v);
+    v = dpp_larger<0x143, 0xc>(v);
+    return v;
+}
+
 // exclusive prefix over the workgroup of one value per thread; all = the workgroup's total
 __device__ __forceinline__ uint32_t workgroup_exclusive_scan(uint32_t mine, uint32_t* lds /* [4] */, uint32_t* all)
 {
@@ -664,11 +677,10 @@ __global__ __launch_bounds__(kGroupThreads) void huffman_write_kernel(const Batc
     }
 }
 
-// The per-length tables of a stream, in LDS: what a code longer than the fast table's index is decoded with.
+// What a stream's codes are decoded with when the lookup table does not have them, in LDS.
 struct LongCodes {
-    uint32_t per_length[kMaxLen + 2];                         // [k]: codes of length k
-    uint32_t first[kMaxLen + 2];                              // [k]: the first (smallest) code of length k
-    uint32_t start[kMaxLen + 2];                              // [k]: position in `sorted` of that code's symbol
+    uint32_t last[32];                                        // [k]: the largest window that starts with a code of length <= k
+    uint32_t place[32];                                       // [k]: place in `sorted` of the first code of length k, less that code
     uint8_t  sorted[256];                                     // symbols by (length, symbol)
 };
 
@@ -677,7 +689,7 @@ struct LongCodes {
 __device__ __forceinline__ uint32_t entry_of(uint32_t symbol, uint32_t length) { return (symbol << 8) | (32u - length); }
 __device__ __forceinline__ uint32_t symbols_in(const uint32_t (&e)[4])                              // a byte each
 {
-    return (e[0] >> 8) | (e[1] & 0xff00u) | ((e[2] & 0xff00u) << 8) | ((e[3] & 0xff00u) << 16);
+    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(e[3], e[2], 0x05010501u), __builtin_amdgcn_perm(e[1], e[0], 0x05010501u), 0x05040100u);
 }
 __device__ __forceinline__ uint32_t length_in(uint32_t entry) { return 32u - (entry & 0xffu); }     // 32 where there is none
 
@@ -693,11 +705,11 @@ __device__ __forceinline__ Ahead drop_code(const Ahead& a, uint32_t entry)      
     return Ahead{align_right(a.high, a.low, entry), a.low << ((0u - entry) & 31u)};
 }
 
-// The entry of the symbol whose code, longer than SHORT bits, is on top of the stream.
+// The entry of a code longer than SHORT bits that is on top of the stream.
 // Canonical codes grow with their length, so the 32-bit windows that start with a code of length <= k are those up
 // to last[k]: the length of the code on top is one more than the number of those bounds that the window exceeds -- a
 // compare and an add per length, the bounds (the same for the whole workgroup) in scalar registers -- and its place
-// among the symbols sorted by (length, symbol) is its value less `first - start` of its length.  `top`: the next
+// among the symbols sorted by (length, symbol) is its value plus `place` of its length.  `top`: the next
 // 32 bits of the stream.
 template <int SHORT> struct LongRegs {
     uint32_t last[kMaxLen - SHORT - 1];            // [i]: the largest window that starts with a code of length <= SHORT + 1 + i
@@ -707,13 +719,7 @@ __device__ __forceinline__ LongRegs<SHORT> long_regs(const LongCodes* t)
 {
     LongRegs<SHORT> r;
 #pragma unroll
-    for (int i = 0; i < kMaxLen - SHORT - 1; ++i) {
-        const int k = SHORT + 1 + i;
-        // left-justified: one past the windows of length <= k (lengths no encoder wrote can claim more than there is)
-        const uint64_t end = ((uint64_t)t->first[k] + t->per_length[k]) << (32 - k);
-        const uint32_t last = end > 0xffffffffull ? 0xffffffffu : end ? (uint32_t)end - 1u : 0u;
-        r.last[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)last);
-    }
+    for (int i = 0; i < kMaxLen - SHORT - 1; ++i) r.last[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)t->last[SHORT + 1 + i]);
     return r;
 }
 // its entry; the length is SHORT + 1 at least, whatever the tables say
@@ -723,70 +729,32 @@ __device__ __forceinline__ uint32_t decode_long(uint32_t top, const LongRegs<SHO
     uint32_t length = SHORT + 1;
 #pragma unroll
     for (int i = 0; i < kMaxLen - SHORT - 1; ++i) length += top > r.last[i] ? 1u : 0u;
-    return entry_of(t->sorted[((top >> (32u - length)) + t->start[length] - t->first[length]) & 0xffu], length);
+    return entry_of(t->sorted[((top >> (32u - length)) + t->place[length]) & 0xffu], length);
 }
 
-// A long code is rare per symbol, but a wave pays for one whenever ANY of its 64 lanes meets one -- one step in six
-// on streams of five bits per symbol -- and the walk over the lengths costs several times a short code's step.  So
-// there is a second table behind the fast one.  The long codes are the upper end of the code space: the windows
-// whose first kFastBits bits are `from` or more.  Those windows' first kFastBits + extra bits, less from << extra,
-// index the second table, whose entries are like the fast one's (0: longer still, walk the lengths).  `extra` is
-// as large as kSecondEntries allow, the longest code at most; with no long codes, or more long prefixes than
-// entries, there is no second table.
-struct Second {
-    uint32_t extra;                                // bits beyond FAST that index the table; 0: no table
-    uint32_t from;                                 // the first index (of FAST + extra bits) it covers
-    uint32_t entries;
-};
-template <int FAST>
-__device__ __forceinline__ Second second_of(const LongCodes* t)
-{
-    Second s{0u, 0u, 0u};
-    uint32_t longest = 0;
-#pragma unroll
-    for (int k = FAST + 1; k <= kMaxLen; ++k)
-        if (__builtin_amdgcn_readfirstlane((int)t->per_length[k])) longest = (uint32_t)k;
-    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)t->first[FAST + 1]) >> 1;   // as FAST bits
-    if (longest == 0u || first >= (1u << FAST)) return s;
-    const uint32_t prefixes = (1u << FAST) - first;
-    if (prefixes > (uint32_t)kSecondEntries / 2u) return s;
-    uint32_t extra = 1;
-    while (extra < longest - FAST && (prefixes << (extra + 1u)) <= (uint32_t)kSecondEntries) ++extra;
-    s.extra = extra;
-    s.from = first << extra;
-    s.entries = prefixes << extra;
-    return s;
-}
-
-// The tables of a stream in LDS, and what the threads hold of them in registers.
+// The lookup table of a stream, indexed by the stream's next bits.  Canonical codes grow with their length, so the codes
+// longer than kFastBits are the upper end of the code space: the windows whose first kFastBits bits are `from` or more.
+// Up to there an entry stands for kFastBits bits, behind it for kFastBits + extra, and the index is the larger of the two
+// readings: top >> (32 - kFastBits), and (top >> shift) + add with shift = 32 - kFastBits - extra, add = from - (from << extra).
+// (Below `from` the second falls behind the first by a step of the finer reading where the first falls by one of the coarser.)
+// `extra` is as large as the table's room allows, the longest code and kReach at most; 0 makes both readings the same.
+// Entries of codes longer still are 0: these walk the lengths.  One read and no branch for a code of either kind: as two
+// tables, the second read where the first had nothing, some lane of a wave took the branch at two symbols in five
+// (12 bits, 51 MB of index streams), 400 cycles for all of them; those streams decode in 45.5 us, 50.6 with two tables.
+constexpr int kFastBits = 12;
+constexpr int kSecondEntries = 2048;               // room behind 1 << kFastBits entries
+constexpr int kTableEntries = (1 << kFastBits) + kSecondEntries;
+constexpr uint32_t kReach = 21;                    // bits that a lookup looks at, at most: three codes fit a window of 64
 struct Lookup {
-    const uint16_t*  fast;
-    const uint16_t*  second;
+    const uint16_t*  table;
     const LongCodes* tables;
-    Second           behind;
+    uint32_t         shift;
+    int32_t          add;
 };
-// The entry of the next symbol's code, from the stream's next 32 bits; behind_fast: of a code that the fast table
-// does not have.
-template <int FAST>
-__device__ __forceinline__ uint32_t behind_fast(const uint16_t* second, const Second& behind, const LongRegs<FAST>& longer,
-                                                const LongCodes* tables, uint32_t top)
+__device__ __forceinline__ uint32_t table_index(uint32_t shift, int32_t add, uint32_t top)
 {
-    uint32_t e = 0;
-    if (behind.extra) {                                       // workgroup-uniform
-        // below `from` only in a stream that no encoder wrote: any entry will do
-        const uint32_t i = (top >> (32u - FAST - behind.extra)) - behind.from;
-        e = second[i < behind.entries ? i : behind.entries - 1u];
-    }
-    if (!e) e = decode_long<FAST>(top, longer, tables);
-    return e;
-}
-template <int FAST>
-__device__ __forceinline__ uint32_t decode_symbol(const uint16_t* fast, const uint16_t* second, const Second& behind,
-                                                  const LongRegs<FAST>& longer, const LongCodes* tables, uint32_t top)
-{
-    uint32_t e = fast[top >> (32 - FAST)];
-    if (__builtin_expect(e == 0u, 0)) e = behind_fast<FAST>(second, behind, longer, tables, top);
-    return e;
+    const int32_t coarse = (int32_t)(top >> (32 - kFastBits)), fine = (int32_t)(top >> shift) + add;
+    return (uint32_t)(coarse > fine ? coarse : fine);
 }
 
 // What a thread has decoded goes out kBurst vectors at a time.  LINES: half of a cache line waits for the other half, and the
@@ -824,14 +792,10 @@ template <bool LINES> struct Output {
 // A lane in three or four takes a word at any step, so the wave steps aside for it nearly always: the word that it takes then
 // has been read before, and only the table is waited for (51 MB, half of it noise, 107 us with the word read when it is
 // needed, 89 now; with eight vectors held back, the word read ahead alone 102).
-template <int FAST, typename NextWord>
-__device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const Lookup table, uint32_t first_word, NextWord next_word)
+template <typename NextWord>
+__device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const Lookup look, uint32_t first_word, NextWord next_word)
 {
-    const LongRegs<FAST> longer = long_regs<FAST>(table.tables);
-    const Second behind = table.behind;
-    const uint16_t* fast = table.fast;
-    const uint16_t* second = table.second;
-    const LongCodes* tables = table.tables;
+    const LongRegs<kFastBits> longer = long_regs<kFastBits>(look.tables);
     uint32_t word = first_word, taken = 1;                    // the word that comes behind `next`; words taken up to it
     Ahead next = {0u, 0u};
     uint32_t have = 0;                                        // bits of it that are there
@@ -856,7 +820,8 @@ __device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const
                         word = next_word(taken);
                         ++taken;
                     }
-                    e[b] = decode_symbol<FAST>(fast, second, behind, longer, tables, next.high);
+                    e[b] = look.table[table_index(look.shift, look.add, next.high)];
+                    if (__builtin_expect(e[b] == 0u, 0)) e[b] = decode_long<kFastBits>(next.high, longer, look.tables);
                     next = Ahead{align_right(next.high, next.low, e[b]), align_right(next.low, 0u, e[b])};
                     have -= length_in(e[b]);
                 }
@@ -869,9 +834,9 @@ __device__ __forceinline__ void decode_chunk(uint32_t valid, uint8_t* dst, const
 }
 
 // The same from words in LDS.  What a symbol costs is the chain from one table read to the next, so four symbols come
-// from one 64-bit window of the stream, kept in registers: a table read, a shift by what it says.  Four codes of the
-// fast table fit it; around a longer one (rare, and then the wave steps aside anyway) there may be too few bits left, and
-// a new window is taken.  The words of the next window are requested before the fourth symbol's table read: its code moves the
+// from one 64-bit window of the stream, kept in registers: a table read, a shift by what it says.  Three codes that the table has
+// fit it; the fourth may find too few bits left (rare), and codes that walk the lengths (rarer) start a new window behind
+// them.  The words of the next window are requested before the fourth symbol's table read: its code moves the
 // window's first word by one at most, so four words hold it either way.
 // A window at bit `pos` starts in word (pos - 1) / 32, rounded down, so that its shift is 0 .. 31: at the chunk's first
 // bit that is words[-1], shifted out whole.
@@ -883,14 +848,11 @@ __device__ __forceinline__ Ahead window_bits(const Window& w, uint32_t pos)
 {
     return Ahead{align_right(w.w0, w.w1, 0u - pos), align_right(w.w1, w.w2, 0u - pos)};
 }
-template <int FAST, bool LINES>
-__device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst, const Lookup table, const uint32_t* words)
+template <bool LINES>
+__device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst, const Lookup look, const uint32_t* words)
 {
-    const LongRegs<FAST> longer = long_regs<FAST>(table.tables);
-    const Second behind = table.behind;
-    const uint16_t* fast = table.fast;
-    const uint16_t* second = table.second;
-    const LongCodes* tables = table.tables;
+    const LongRegs<kFastBits> longer = long_regs<kFastBits>(look.tables);
+    const uint32_t room = 64u - (32u - look.shift);           // bits of a window that may be gone before a lookup
     uint32_t pos = 0;                                         // bits of the chunk consumed
     Window w = {0u, words[0], words[1]};
     Output<LINES> out;
@@ -905,36 +867,38 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 Ahead next = window_bits(w, pos);
-                uint32_t window_end = pos + 64u;
-                const auto new_window = [&] {
-                    const uint32_t* from = words + window_word(pos);
-                    window_end = pos + 64u;
-                    return window_bits(Window{from[0], from[1], from[2]}, pos);
+                uint32_t window = pos;                        // where it starts
+                const auto new_window = [&](uint32_t from) {
+                    const uint32_t* first = words + window_word(from);
+                    window = from;
+                    next = window_bits(Window{first[0], first[1], first[2]}, from);
                 };
                 uint32_t e[4];
+                uint32_t sum = 0;                             // of the entries, whose low bytes are 32 - length: below 128 together
                 int32_t at = 0;                               // where the fourth symbol's window starts
                 uint32_t ahead[4];
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
                     if (b == 3) {
-                        at = window_word(pos);
+                        const uint32_t here = pos + 96u - (sum & 0xffu);
+                        at = window_word(here);
 #pragma unroll
                         for (int k = 0; k < 4; ++k) ahead[k] = words[at + k];
+                        if (__builtin_expect(here - window > room, 0)) next = window_bits(Window{ahead[0], ahead[1], ahead[2]}, here);
                     }
-                    Ahead here = next;
-                    e[b] = fast[here.high >> (32 - FAST)];
-                    next = drop_code(here, e[b]);             // (put right below where there is no entry)
-                    pos += length_in(e[b]);
+                    const Ahead before = next;
+                    e[b] = look.table[table_index(look.shift, look.add, before.high)];
+                    next = drop_code(before, e[b]);           // (put right below where there is no entry)
                     if (__builtin_expect(e[b] == 0u, 0)) {
-                        pos -= 32u;
-                        // it may need more bits than the window has left, or leave fewer than the codes behind it may need
-                        if ((int32_t)(window_end - pos) < kMaxLen) here = new_window();
-                        e[b] = behind_fast<FAST>(second, behind, longer, tables, here.high);
-                        next = drop_code(here, e[b]);
-                        pos += length_in(e[b]);
-                        if (b < 3 && (int32_t)(window_end - pos) < FAST * (3 - b)) next = new_window();
+                        const uint32_t here = pos + 32u * b - (sum & 0xffu);
+                        next = before;
+                        if (b > 0 && window + 64u - here < (uint32_t)kMaxLen) new_window(here);
+                        e[b] = decode_long<kFastBits>(next.high, longer, look.tables);
+                        if (b < 3) new_window(here + length_in(e[b]));
                     }
+                    sum += e[b];
                 }
+                pos += 128u - (sum & 0xffu);
                 const bool crossed = window_word(pos) != at;  // a code has at most 24 bits
                 w = Window{crossed ? ahead[1] : ahead[0], crossed ? ahead[2] : ahead[1], crossed ? ahead[3] : ahead[2]};
                 sixteen[q] = symbols_in(e);
@@ -952,7 +916,7 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
 template <int kDecodeThreads, bool LINES>
 __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Batch<DecodeJob> batch)
 {
-    constexpr int kStageWords = StageWords<kDecodeThreads>::kAll, kFastBits = FastBits<kDecodeThreads>::kAll;
+    constexpr int kStageWords = StageWords<kDecodeThreads>::kAll;
     uint32_t block;
     const DecodeJob& job = batch.item[batch_item(batch, blockIdx.x, block)];
     const uint8_t* len_in = job.len;
@@ -970,13 +934,16 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
         payload_words = (uint32_t)(words < 0xffffffffu ? words : 0xffffffffu);
     }
     uint8_t* out = job.out;
-    // One object, so that the order is the one written here: the tables that every symbol is looked up in come first,
+    // One object, so that the order is the one written here: the table that every symbol is looked up in comes first,
     // at addresses small enough for the offset field of an LDS instruction (one addition less per symbol).
     struct Local {
-        uint16_t  fast[1 << kFastBits];                       // next kFastBits bits -> entry; 0: longer code
-        uint16_t  second[kSecondEntries];                     // the same for the long codes' first kFastBits + extra bits
+        uint16_t  table[kTableEntries];                       // while it is being filled: ranks, one up
         LongCodes tables;
-        uint32_t  in_wave[kThreads / 64][kMaxLen + 2];        // [w][k]: symbols of length k among wave w's 64
+        uint32_t  in_wave[kThreads / 64][32];                 // [w][k]: symbols of length k among wave w's 64
+        uint32_t  first_code[kThreads / 64][32];              // [w][k]: wave w's copy of: the first code of length k, from the 24th bit down
+        uint32_t  first_rank[kThreads / 64][32];              // ... the place of its symbol by (length, symbol)
+        uint16_t  entry_of_rank[256 + 2];                     // [rank + 1]; 0 at either end
+        uint16_t  upto[kDecodeThreads];                       // the last rank in the table up to a thread's part, in its wave
         uint32_t  all_eight[4];                               // [w]: the codes of wave w's 64 symbols are eight bits long
         uint32_t  fitting;                                    // chunks of a pass whose slice fits the stage
         // the workgroup's slice of the payload, or the rings; four words lead in (a chunk's first window reads the one before it)
@@ -984,11 +951,6 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
     };
     __shared__ Local local;
     LongCodes& tables = local.tables;
-    uint32_t (&per_length)[kMaxLen + 2] = tables.per_length, (&first)[kMaxLen + 2] = tables.first, (&start)[kMaxLen + 2] = tables.start;
-    uint8_t (&sorted)[256] = tables.sorted;
-    uint32_t (&in_wave)[kThreads / 64][kMaxLen + 2] = local.in_wave;
-    uint16_t (&fast)[1 << kFastBits] = local.fast;
-    uint16_t (&second)[kSecondEntries] = local.second;
     uint32_t* const stage = local.slice + 4;
     const uint32_t s = threadIdx.x, wave = s >> 6, lane = s & 63u;
     uint32_t l = s < 256u ? len_in[s] : 0u;
@@ -997,81 +959,91 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
         const uint64_t eight = __ballot(l == 8u);
         if (lane == 0) local.all_eight[wave] = eight == ~(uint64_t)0 ? 1u : 0u;
     }
+    uint32_t* const table_words = reinterpret_cast<uint32_t*>(local.table);       // two entries each
+    for (uint32_t i = s; i < (uint32_t)kTableEntries / 2u; i += kDecodeThreads) table_words[i] = 0u;
+    if (s < kThreads / 64 * 32u) local.in_wave[s >> 5][s & 31u] = 0u;
     __syncthreads();
     const bool flat = (local.all_eight[0] & local.all_eight[1] & local.all_eight[2] & local.all_eight[3]) != 0u;
-    Second behind = {0u, 0u, 0u};
-    // Threads 0..255 stand for the 256 symbols while the tables are built; the others only fill and wait.
+    uint32_t shift = 32u - kFastBits;
+    int32_t add = 0;
+    // Threads 0..255 stand for the 256 symbols: a symbol's place by (length, symbol), its code, and its rank written where
+    // its part of the table starts; then every entry takes the last rank up to it, a scan over the workgroup, and the rank's
+    // entry.  (Each entry by itself, its length from comparisons with all bounds and its symbol from that, was 7 us of the
+    // 36 that a launch of few chunks took; this way it is 2.5.)
     const auto build_tables = [&] {
-        // thread s is symbol s: its rank among the symbols of its length, by lane masks inside the wave ...
-        uint32_t before = 0;
+        uint32_t before = 0;                                  // symbols of this one's length before it in its wave
         if (wave < 4u) {                                      // wave-uniform
+            uint64_t same = ~(uint64_t)0;
 #pragma unroll
-            for (int k = 1; k <= kMaxLen; ++k) {
-                const uint64_t same = __ballot(l == (uint32_t)k);
-                if (l == (uint32_t)k) before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-                if (lane == 0) in_wave[wave][k] = (uint32_t)__popcll(same);
+            for (int k = 0; k < 5; ++k) {
+                const uint64_t has = __ballot((l >> k) & 1u);
+                same &= (l >> k) & 1u ? has : ~has;
             }
+            before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+            if (l && before == 0u) local.in_wave[wave][l] = (uint32_t)__popcll(same);
         }
         __syncthreads();
-        if (s < (uint32_t)kMaxLen + 2u) {
-            uint32_t total = 0;
-            if (s >= 1u && s <= (uint32_t)kMaxLen)
-                for (int w = 0; w < kThreads / 64; ++w) total += in_wave[w][s];
-            per_length[s] = total;
+        // Lane k of every wave stands for length k.  The first code of length k is the sum over the shorter lengths j of their
+        // symbols << (k - j); scaled by 2^(24 - k) that is a prefix sum (at most 2^31, whatever the lengths are).
+        const bool a_length = lane >= 1u && lane <= (uint32_t)kMaxLen;
+        const uint32_t of_length = a_length ? local.in_wave[0][lane & 31u] + local.in_wave[1][lane & 31u] + local.in_wave[2][lane & 31u] +
+                                                  local.in_wave[3][lane & 31u] : 0u;
+        const uint32_t scaled = a_length ? of_length << ((uint32_t)kMaxLen - lane) : 0u;
+        const uint32_t codes_upto = wave_inclusive_scan(scaled), rank_upto = wave_inclusive_scan(of_length);
+        const uint32_t first_code = codes_upto - scaled, first_rank = rank_upto - of_length;
+        const uint32_t all_codes = last_lane(codes_upto);
+        const uint64_t lengths = __ballot(of_length != 0u);
+        const uint32_t longest = lengths ? 63u - (uint32_t)__builtin_clzll(lengths) : 0u;
+        const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)first_code, kFastBits + 1) >> (kMaxLen - kFastBits);
+        uint32_t extra = 0;
+        if (longest > (uint32_t)kFastBits && from < (1u << kFastBits)) {
+            const uint32_t prefixes = (1u << kFastBits) - from;
+            while (extra < longest - kFastBits && extra < kReach - kFastBits && from + (prefixes << (extra + 1u)) <= (uint32_t)kTableEntries) ++extra;
         }
-        __syncthreads();
-        if (s == 0) {
-            uint32_t count[kMaxLen + 1];
-#pragma unroll
-            for (int k = 1; k <= kMaxLen; ++k) count[k] = per_length[k];
-            uint32_t code = 0, at = 0;
-            first[0] = first[1] = 0u;
-            start[0] = start[1] = 0u;
-#pragma unroll
-            for (int k = 2; k <= kMaxLen; ++k) {
-                code = (code + count[k - 1]) << 1;
-                at += count[k - 1];
-                first[k] = code;
-                start[k] = at;
+        shift = 32u - kFastBits - extra;
+        add = (int32_t)from - (int32_t)(from << extra);
+        if (wave == 0 && a_length) {
+            const uint64_t end = (uint64_t)codes_upto << (32 - kMaxLen);       // lengths no encoder wrote can claim more than there is
+            tables.last[lane] = end > 0xffffffffull ? 0xffffffffu : end ? (uint32_t)end - 1u : 0u;
+            tables.place[lane] = first_rank - (first_code >> ((uint32_t)kMaxLen - lane));
+        }
+        if (wave < 4u) {
+            if (lane < 32u) {
+                local.first_code[wave][lane] = first_code;
+                local.first_rank[wave][lane] = first_rank;
             }
-        }
-        __syncthreads();
-        if (l) {                                              // ... plus those in the waves below
-            for (uint32_t w = 0; w < wave; ++w) before += in_wave[w][l];
-            sorted[(start[l] + before) & 0xffu] = (uint8_t)s;
-        }
-        __syncthreads();
-        // The first kSure bits settle most entries, kEach of the table at a time; those that they do not settle, the
-        // prefixes of longer codes at the upper end, one by one.
-        constexpr int kSure = 12, kEach = 1 << (kFastBits - kSure);
-        const LongRegs<0> any = long_regs<0>(&tables);
-        for (uint32_t i = s; i < (1u << kSure); i += kDecodeThreads) {
-            const uint32_t top = (i << (32 - kSure)) | 1u;    // (above the bound 0 of lengths that have no codes below them)
-            uint32_t length = 1;
-#pragma unroll
-            for (int k = 0; k < kSure; ++k) length += top > any.last[k] ? 1u : 0u;
-            const uint32_t symbol_at = (i >> ((uint32_t)kSure - (length < (uint32_t)kSure ? length : (uint32_t)kSure))) + start[length] - first[length];
-            const bool there = length <= (uint32_t)kSure && symbol_at - start[length] < per_length[length];
-            const uint16_t e = there ? (uint16_t)entry_of(sorted[symbol_at & 0xffu], length) : (uint16_t)0;
-#pragma unroll
-            for (int j = 0; j < kEach; ++j) fast[i * kEach + j] = e;
-        }
-        if constexpr (kEach > 1) {
-            __syncthreads();
-            const LongRegs<kSure> longer = long_regs<kSure>(&tables);
-            const uint32_t from = (uint32_t)__builtin_amdgcn_readfirstlane((int)first[kSure + 1]) >> 1;   // of kSure bits: the first that is none
-            for (uint32_t i = from * kEach + s; i < (1u << kFastBits); i += kDecodeThreads) {
-                if (fast[i]) continue;                        // only where the lengths are no encoder's
-                const uint32_t e = decode_long<kSure>(i << (32 - kFastBits), longer, &tables);
-                fast[i] = length_in(e) <= (uint32_t)kFastBits ? (uint16_t)e : (uint16_t)0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS operations of one wave complete in order
+            if (l) {
+                for (uint32_t w = 0; w < wave; ++w) before += local.in_wave[w][l];
+                const uint32_t rank = (local.first_rank[wave][l] + before) & 0xffu;
+                const uint32_t code = local.first_code[wave][l] + (before << ((uint32_t)kMaxLen - l));
+                tables.sorted[rank] = (uint8_t)s;
+                local.entry_of_rank[rank + 1u] = l <= kFastBits + extra ? (uint16_t)entry_of(s, l) : (uint16_t)0;
+                // (codes longer than what an entry stands for may share one: none of them has an entry)
+                if (code < (1u << kMaxLen)) local.table[table_index(shift, add, code << (32 - kMaxLen))] = (uint16_t)(rank + 1u);
             }
+        } else if (s == 256u) {                               // and where the codes end
+            local.entry_of_rank[0] = local.entry_of_rank[256 + 1] = (uint16_t)0;
+            if (all_codes < (1u << kMaxLen)) local.table[table_index(shift, add, all_codes << (32 - kMaxLen))] = (uint16_t)(256u + 1u);
         }
-        behind = second_of<kFastBits>(&tables);
-        const LongRegs<kFastBits> longer = long_regs<kFastBits>(&tables);
-        for (uint32_t i = s; i < behind.entries; i += kDecodeThreads) {
-            const uint32_t width = (uint32_t)kFastBits + behind.extra;
-            const uint32_t e = decode_long<kFastBits>((behind.from + i) << (32u - width), longer, &tables);
-            second[i] = length_in(e) <= width ? (uint16_t)e : (uint16_t)0;
+        __syncthreads();
+        constexpr int kWords = kTableEntries / 2 / kDecodeThreads;
+        static_assert(kWords * 2 * kDecodeThreads == kTableEntries, "the threads share the table evenly");
+        uint32_t two[kWords], upto = 0;
+#pragma unroll
+        for (int k = 0; k < kWords; ++k) {
+            two[k] = table_words[s * kWords + k];
+            upto = larger(upto, larger(two[k] & 0xffffu, two[k] >> 16));
+        }
+        local.upto[s] = (uint16_t)wave_inclusive_max(upto);
+        __syncthreads();
+        uint32_t rank = lane ? local.upto[s - 1u] : 0u;
+        for (uint32_t w = 0; w < wave; ++w) rank = larger(rank, local.upto[64u * w + 63u]);
+#pragma unroll
+        for (int k = 0; k < kWords; ++k) {
+            const uint32_t low = larger(rank, two[k] & 0xffffu);
+            rank = larger(low, two[k] >> 16);
+            table_words[s * kWords + k] = local.entry_of_rank[low] | (uint32_t)local.entry_of_rank[rank] << 16;
         }
         __syncthreads();
     };
@@ -1164,7 +1136,7 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
             __syncthreads();
             // anything at all for a foreign stream: clamped, the reads stay inside the array (a chunk is at most 192 words)
             const uint32_t at = first_word - slice_at < slice_words ? first_word - slice_at : slice_words;
-            decode_chunk_staged<kFastBits, LINES>(valid, dst, Lookup{fast, second, &tables, behind}, stage + phase + at);
+            decode_chunk_staged<LINES>(valid, dst, Lookup{local.table, &tables, shift, add}, stage + phase + at);
         } else if (live) {
             // a ring of eight words per thread: when four have been consumed, the four loaded at the
             // previous refill take their place and the next four are requested, so a load has the time
@@ -1175,7 +1147,7 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
             for (int k = 0; k < 8; ++k) mine[k * kDecodeThreads] = first_word + k < payload_words ? payload[first_word + k] : 0u;
 #pragma unroll
             for (int k = 0; k < 4; ++k) pending[k] = first_word + 8 + k < payload_words ? payload[first_word + 8 + k] : 0u;
-            decode_chunk<kFastBits>(valid, dst, Lookup{fast, second, &tables, behind}, mine[0], [&](uint32_t taken) {
+            decode_chunk(valid, dst, Lookup{local.table, &tables, shift, add}, mine[0], [&](uint32_t taken) {
                 if ((taken & 3u) == 0u) {                     // a block of four used up: refill the half of the ring just freed
                     const uint32_t slot = (taken + 4u) & 7u;
 #pragma unroll

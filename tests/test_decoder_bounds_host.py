@@ -129,6 +129,32 @@ def test_huffman_rings_decode_as_the_oracle_does(decoders):
         assert np.array_equal(got, data)
 
 
+@pytest.mark.parametrize("kind", ["one symbol", "comb", "room to spare", "room exactly", "no room", "beyond the reach"])
+def test_huffman_codes_around_the_edges_of_the_lookup_table(decoders, kind):
+    """Codes of 12 and 13 bits (where the table turns finer), of 21 and 22 (where it ends), finer entries that just fit its room and
+    that do not, and code space without a code; every symbol as likely as any other, so that long codes stand side by side."""
+    lengths = np.zeros(256, np.int64)
+    if kind == "one symbol":
+        lengths[7] = 1
+    elif kind == "comb":
+        lengths[:24] = np.arange(1, 25)
+        lengths[24] = 24
+    elif kind == "room to spare":
+        lengths[:12], lengths[12:] = np.arange(1, 13), 20
+    elif kind == "room exactly":                              # 2048 prefixes of 12 bits behind the first two codes
+        lengths[:2], lengths[2:] = 2, 13
+    elif kind == "no room":
+        lengths[0], lengths[1:] = 2, 13
+    else:
+        lengths[:20], lengths[20:26], lengths[26:31] = np.arange(1, 21), 24, 23
+    rng = np.random.default_rng(len(kind))
+    data = rng.permutation(np.resize(np.flatnonzero(lengths), 5000 + 13)).astype(np.uint8)
+    stream = HS.canonical_stream(data, lengths)
+    assert np.array_equal(oracle.huffman_decode(stream, data.size), data)
+    (st, got), = decoders([_huffman_case(stream, data.size)])
+    assert st == FH_OK and np.array_equal(got, data)
+
+
 def test_huffman_encoder_on_the_cpu_writes_the_oracles_streams(decoders):
     """The encoder's kernels through the same stand-in (histogram, code construction, count, scan, write): the
     stream and its totals byte for byte, with the buffers sized to the byte."""
