@@ -40,7 +40,7 @@ struct PrepItem {
     uint32_t*       hist;                          // 256 words, cleared; or null
     uint8_t*        raw;                           // the raw store: [outer][raw_channels][row_bytes]
     uint64_t        row_bytes;
-    uint32_t        outer;
+    uint32_t        outer;                         // samples whose unused rows are to be cleared
     int32_t         channels, raw_channels;
     uint32_t        blocks;                        // workgroups of this item
 };
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kPrepThreads) void chain_prepare_kernel(const Batch
     }
     // The unused rows of a sample are one piece; a wave takes a part of one at a time.  Pieces of a few hundred bytes
     // ([tokens][hidden] tensors) are cleared together with what lies between them: one by one they took 56 us for
-    // the 24 tensors of an encoder, whole 13 us.
+    // the 24 tensors of an encoder, whole 13 us, and as the 16-byte vectors that have a part in an unused row 12.
     const uint64_t sample = (uint64_t)it.raw_channels * it.row_bytes, unused = (uint64_t)(it.raw_channels - (int)used) * it.row_bytes;
     const bool whole = sample < kWholeBelow;
     const uint64_t samples = whole ? 1u : it.outer, piece = whole ? (used < (uint32_t)it.raw_channels ? it.outer * sample : 0u) : unused;
@@ -224,6 +224,16 @@ fh_status check_item(const fh_mix_item& it, bool forward, fh_mix_regions* r, int
 
 uint8_t* at(void* base, size_t off) { return static_cast<uint8_t*>(base) + off; }
 
+// Which maps of an item's raw store hold anything.  Where a map is a row of the store, the sparse stage is told and leaves
+// the others alone; where it is not ([tokens][hidden] tensors), or an empty tile would not be a sparse one, those
+// rows are cleared and stored as the zeros they are.
+MapsInUse rows_in_use(const fh_mix_item& it, const fh_mix_regions& reg)
+{
+    const bool by_rows = it.h * it.w == it.inner && it.tau >= 0.0f;
+    return by_rows ? maps_in_use(reinterpret_cast<const uint64_t*>(at(it.store, reg.header)) + 7, (uint32_t)it.raw_channels)
+                   : MapsInUse{nullptr, 1, 0};
+}
+
 }  // namespace
 }  // namespace fh
 
@@ -316,11 +326,11 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
             p.hist = it.entropy && reg[i].raw_bytes ? reinterpret_cast<uint32_t*>(at(it.workspace, reg[i].huffman_ws)) : nullptr;
             p.raw = at(it.workspace, reg[i].raw);
             p.row_bytes = (uint64_t)it.inner * elem_size(it.x_dtype);
-            p.outer = reg[i].raw_bytes ? (uint32_t)it.outer : 0u;
+            p.outer = reg[i].raw_bytes && !rows_in_use(it, reg[i]).count ? (uint32_t)it.outer : 0u;
             p.channels = (int32_t)it.channels;
             p.raw_channels = (int32_t)it.raw_channels;
             // every workgroup counts the salient channels first: 16 KiB of rows for each of its waves at least
-            const uint64_t want = reg[i].raw_bytes / ((kPrepThreads / 64) * kClearUnit) + 1u;
+            const uint64_t want = p.outer ? reg[i].raw_bytes / ((kPrepThreads / 64) * kClearUnit) + 1u : 1u;
             p.blocks = (uint32_t)(want < 512u ? want : 512u);
             push(b, p, p.blocks);
         }
@@ -333,6 +343,7 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
 
     // 4. the raw stores as sparse / predicted blocks; 5. their index streams Huffman-coded
     std::vector<fh_sparse_encode_item> sp;
+    std::vector<MapsInUse> use;
     std::vector<fh_huffman_encode_item> hf;
     std::vector<StoredForm> stored;
     const auto fixed_bytes = [&](int32_t i) {                 // of the stored form: header, codes, meta, slots and info bytes
@@ -352,6 +363,7 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
         e.totals = header;
         e.workspace = at(it.workspace, reg[i].sparse_ws); e.workspace_cap = reg[i].sparse_ws_bytes;
         sp.push_back(e);
+        use.push_back(rows_in_use(it, reg[i]));
         if (it.entropy) {
             fh_huffman_encode_item h = {};
             h.bytes = e.indices; h.n = reg[i].indices_cap; h.n_device = header + 1;
@@ -362,7 +374,7 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
             stored.push_back(StoredForm{header, fixed_bytes(i), (uint32_t)elem_size(it.x_dtype)});
         }
     }
-    if (!sp.empty() && (st = fh_sparse_encode_batch(sp.data(), (int32_t)sp.size(), stream)) != FH_OK) return st;
+    if (!sp.empty() && (st = sparse_encode_rows(sp.data(), use.data(), (int32_t)sp.size(), s)) != FH_OK) return st;
     if (!hf.empty() && (st = huffman_encode_stored(hf.data(), stored.data(), (int32_t)hf.size(), s)) != FH_OK) return st;
 
     // 6. what each stored form occupies, where the entropy stage has not said so
@@ -398,6 +410,7 @@ fh_status fh_mix_decompress_batch(const fh_mix_item* items, int32_t count, void*
     // the index streams back, then the maps (the raw stores), then the tensors
     std::vector<fh_huffman_decode_item> hf;
     std::vector<fh_sparse_decode_item> sp;
+    std::vector<MapsInUse> use;
     for (int32_t i = 0; i < count; ++i) {
         const fh_mix_item& it = items[i];
         if (reg[i].raw_bytes == 0) continue;
@@ -418,13 +431,13 @@ fh_status fh_mix_decompress_batch(const fh_mix_item* items, int32_t count, void*
         d.out = at(it.workspace, reg[i].raw); d.out_cap = reg[i].raw_bytes;
         d.workspace = at(it.workspace, reg[i].sparse_ws); d.workspace_cap = reg[i].sparse_ws_bytes;
         sp.push_back(d);
+        use.push_back(rows_in_use(it, reg[i]));
     }
     if (!hf.empty() && (st = fh_huffman_decode_batch(hf.data(), (int32_t)hf.size(), stream)) != FH_OK) return st;
     uint64_t map_bytes = 0;
     for (const fh_sparse_decode_item& d : sp) map_bytes += d.out_cap;
     if (!sp.empty()) {
-        st = maps_stay_in_cache(map_bytes) ? sparse_decode_for_next(sp.data(), (int32_t)sp.size(), static_cast<hipStream_t>(stream))
-                                           : fh_sparse_decode_batch(sp.data(), (int32_t)sp.size(), stream);
+        st = sparse_decode_rows(sp.data(), use.data(), maps_stay_in_cache(map_bytes), (int32_t)sp.size(), static_cast<hipStream_t>(stream));
         if (st != FH_OK) return st;
     }
 

@@ -294,6 +294,16 @@ def test_sparse_foreign_streams_stay_in_bounds(decoders):
     assert all(st == FH_OK for st, _ in decoders(cases))
 
 
+def test_sparse_sets_of_many_groups_decode_on_the_cpu(decoders):
+    """More than 2048 groups of 128 tiles: the groups' sums go through the scan, which leaves no totals behind when it decodes."""
+    maps = 2049 * 128 - 5
+    x = np.random.default_rng(3).choice(np.array([0, 0, 1.5, -2.25], np.float32), maps)
+    info, values, indices, _ = oracle.sparse_encode(x, maps, 1, 1, 8, 0.5, dtype="f32", eps=0.02)
+    (st, got), = decoders([_sparse_case(info, values, indices, "f32", 8, maps, 1, 1, 0.02)])
+    assert st == FH_OK
+    assert np.array_equal(got, oracle.sparse_decode(info, values, indices, maps, 1, 1, 8, dtype="f32", eps=0.02).view(np.uint8).reshape(-1))
+
+
 @pytest.mark.parametrize("n", [2, 4, 8])
 def test_sparse_tiles_of_any_bytes_decode_the_same_in_every_window(decoders, n):
     """Index bytes that are noise, small numbers, or valid ones with some changed: row pointers that fall or overlap, columns

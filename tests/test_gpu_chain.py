@@ -187,6 +187,31 @@ def test_single_tensor_chain_matches_the_oracle_chain(api, k, out_dtype):
         assert 0 < st.used <= case[4]
 
 
+@pytest.mark.parametrize("window", [2, 4, 8])
+@pytest.mark.parametrize("tau", [-1.0, 0.0, 0.5, 1.5, float("nan")])
+def test_rows_of_the_raw_store_that_no_channel_uses(api, tau, window):
+    """Feature maps with room for one channel, for more than are salient, and for all; nothing salient; a threshold by which an
+    empty block is no sparse one.  The workspace is noise before either call."""
+    cases = []
+    for raw_channels, min_out in ((1, 3), (7, 3), (24, 3), (24, 10 ** 6)):
+        for hw in ((7, 7), (9, 13)):
+            cases.append((3, 24, hw[0] * hw[1], hw, raw_channels, 64, 4, "nearest", window, tau, 0.02 if hw[0] == 9 else 0.0, 1, "f32", min_out))
+    xs = [_input(c, 700 + i) for i, c in enumerate(cases)]
+    batch = api.MixBatch([_entry(api, _device(x, "f32"), c, "f32") for x, c in zip(xs, cases)], device=torch.device("cuda"))
+    print(f"[chain] unused rows, tau {tau}, window {window}", flush=True)
+    for e in batch.entries:
+        e.workspace.random_(0, 256)
+    api.fh_mix_compress_batch(batch)
+    for e in batch.entries:
+        e.workspace.random_(0, 256)
+    api.fh_mix_decompress_batch(batch)
+    api.fh_mix_compress_batch(batch)                # the classification's outputs live in the workspace
+    torch.cuda.synchronize()
+    for i, (x, c) in enumerate(zip(xs, cases)):
+        st = _compare(api, batch, i, x, c, "f32")
+        assert (st.used < c[4]) == (c[4] > 1), "the case is to leave rows unused"
+
+
 def test_batched_chain_item_by_item_and_in_a_captured_graph(api):
     print("[chain] batch of all cases, eager and as a replayed graph", flush=True)
     xs = [_input(c, 100 + k) for k, c in enumerate(CASES)]
