@@ -229,7 +229,34 @@ struct CountArgs {
     SmallDiv inner, channels;
     int32_t spans_per_wave;                                   // consecutive spans one wave walks
     const uint32_t* ranges;                                   // of the tensor's pieces (count_marked_kernel)
+    uint8_t* mask;                                            // cleared; null: the caller takes it from the counts
+    int64_t min_outliers;
 };
+
+// A workgroup's histogram to the tensor's counters.  The additions to a counter follow one another, so just one of them takes it
+// over the bound, and that one sets the mask: no launch behind the pass that reads the counters again (557 MiB set 108.5 -> 106.5
+// us).  An addition whose result is waited for costs more than one that is not, so that is for tensors of few channels (fh_rules.hpp).
+template <int THREADS>
+__device__ __forceinline__ void add_outliers(const CountArgs& args, const uint32_t* hist)
+{
+    const uint32_t channels = args.channels.d;
+    uint32_t* const counts = args.counts;
+    uint8_t* const mask = args.mask;
+    const int64_t bound = args.min_outliers;
+    if (!mask) {                                              // workgroup-uniform
+        for (uint32_t c = threadIdx.x; c < channels; c += THREADS) {
+            const uint32_t v = hist[c];
+            if (v) atomicAdd(&counts[c], v);
+        }
+        return;
+    }
+    for (uint32_t c = threadIdx.x; c < channels; c += THREADS) {
+        const uint32_t v = hist[c];
+        if (!v) continue;
+        const uint32_t before = atomicAdd(&counts[c], v);
+        if ((int64_t)before < bound && (int64_t)before + v >= bound) mask[c] = 1;
+    }
+}
 
 // AHEAD: a launch in which some wave walks more than one span.
 constexpr int kAhead = 3;                         // spans requested before the one that is looked at
@@ -341,10 +368,7 @@ __global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Batch<Co
         }
     }
     __syncthreads();
-    for (uint32_t c = threadIdx.x; c < C; c += kThreads) {
-        const uint32_t v = hist[c];
-        if (v) atomicAdd(&args.counts[c], v);
-    }
+    add_outliers<kThreads>(args, hist);
 }
 
 // The same where the first pass left ranges behind.  A wave looks at the ranges of eight spans at once, a lane per
@@ -441,10 +465,7 @@ __global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Batch
         }
     }
     __syncthreads();
-    for (uint32_t c = threadIdx.x; c < C; c += kThreads) {
-        const uint32_t v = hist[c];
-        if (v) atomicAdd(&args.counts[c], v);
-    }
+    add_outliers<kThreads>(args, hist);
 }
 
 __global__ __launch_bounds__(kThreads) void mask_kernel(const Batch<MaskItem> args)
@@ -536,8 +557,7 @@ fh_status check_item(const fh_classify_item& it, int64_t* numel_out)
     return FH_OK;
 }
 
-// One run of up to kBatch tensors of one dtype: five kinds of launches, each covering all of them (four without the
-// masks).  The tensors either all have a place for their ranges or all have none.
+// One run of up to kBatch tensors of one dtype: four kinds of launches, each covering all of them.  The tensors either all have a place for their ranges or all have none.
 fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, const int64_t* numels, int n, bool masks,
                        bool first_pass_done, hipStream_t s)
 {
@@ -622,10 +642,16 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
         a.spans_per_wave = marked ? marked_spans_per_wave(spans, ceil_div(numels[i], kSpan), ch, widest)
                                   : (int32_t)(ch <= 512 ? 1 : ch / 128 < 16 ? ch / 128 : 16);
         a.ranges = ranges[i];
+        if (marked) a.spans_per_wave *= marked_looks_per_wave(spans, ch);
+        // (counters of channels with 2^32 elements and more may wrap: the masks are then what they end at)
+        const bool here = mask_with_the_counts(ch) && items[i].outer * items[i].inner <= (int64_t)UINT32_MAX;
+        a.mask = masks && here ? static_cast<uint8_t*>(items[i].mask) : nullptr;
+        a.min_outliers = items[i].min_outliers;
         const int64_t per_block = (int64_t)a.spans_per_wave * waves * kSpan;
         if (!push(cb, a, ceil_div(numels[i], per_block))) return FH_ERR_BAD_NUMEL;
-        push(kb, MaskItem{a.counts, static_cast<uint8_t*>(items[i].mask), items[i].min_outliers, (int32_t)ch},
-             ceil_div(ch, kThreads));
+        if (masks && !here)
+            push(kb, MaskItem{a.counts, static_cast<uint8_t*>(items[i].mask), items[i].min_outliers, (int32_t)ch},
+                 ceil_div(ch, kThreads));
     }
     if (cb.count > 0) {
         seal(cb);
@@ -649,7 +675,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
             if (ahead) hipLaunchKernelGGL((count_outliers_kernel<uint16_t, true>), grid, block, lds, s, cb);
             else hipLaunchKernelGGL((count_outliers_kernel<uint16_t, false>), grid, block, lds, s, cb);
         }
-        if (masks) hipLaunchKernelGGL(mask_kernel, dim3(kb.block_start[kb.count]), block, 0, s, kb);
+        if (kb.count > 0) hipLaunchKernelGGL(mask_kernel, dim3(kb.block_start[kb.count]), block, 0, s, kb);
     }
     return hipGetLastError() == hipSuccess ? FH_OK : FH_ERR_LAUNCH;
 }

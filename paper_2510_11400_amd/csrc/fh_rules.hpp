@@ -27,6 +27,18 @@ inline int32_t marked_spans_per_wave(int64_t launch_spans, int64_t tensor_spans,
     return (int32_t)(spans < 1 ? 1 : spans > 8 ? 8 : spans);
 }
 
+// How often a wave of a large launch looks at that many spans.  A workgroup's histogram of a wide tensor is 3072 counters to clear
+// and to add in for the outliers of 64 spans; once there are waves for a whole round of the device (8192 of eight spans), twice the
+// spans to a histogram save half of that, the ranges of the second eight on their way meanwhile.  Count pass of the 720 MiB
+// encoder set 56 -> 45 us; classification of three tensors of 3072 channels (151 MB) 56 -> 50, of twelve 154 -> 144, three of 16384
+// channels 154 -> 134; with 768 channels, whose histograms are short, 76 -> 77, feature maps 16 -> 20: these keep one.
+inline int32_t marked_looks_per_wave(int64_t launch_spans, int64_t channels) { return channels > 1024 && launch_spans > 65536 ? 2 : 1; }
+
+// Whether the count pass sets the mask as it adds to the counters, or a launch behind it does.  The additions are then waited for, and
+// a wide tensor's workgroup has many: 3 tensors of 3072 channels 52 us with the launch and 56 without, 3 of 16384 128 and
+// 154, 24 of 768 78 and 76, 18 of 1024 131 and 126, one of 768 17.9 and 16.9.
+inline bool mask_with_the_counts(int64_t channels) { return channels <= 1024; }
+
 // The Huffman encoder's group sums in a launch of `groups` altogether: scanned by a kernel between the count and the write
 // pass, or every workgroup of the write pass adds up those before its own.  Adding up saves that launch and makes every
 // workgroup of the write pass take longer, so what counts is how many of those there are.  Encoding, scanned and not: one

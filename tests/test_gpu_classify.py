@@ -215,3 +215,34 @@ def test_batched_call_on_the_full_size_set(api):
         assert np.array_equal(e.stats.cpu().numpy().view(np.uint64), stats.view(np.uint64))
         assert np.array_equal(e.counts.cpu().numpy().view(np.uint32), counts)
         assert np.array_equal(e.mask.cpu().numpy(), mask)
+
+
+@pytest.mark.parametrize("channels", [1, 512, 1024, 1025, 3072])
+def test_masks_at_the_bound_whichever_launch_sets_them(api, channels):
+    """The bound on either side of what channels end at, counted by many workgroups: up to 1024 channels the mask comes with
+    the counts, beyond from a launch behind them."""
+    outer = max(64, (3 << 20) // channels)
+    x, _ = W.outlier_channel_tensor(outer, channels, 1, seed=channels, salient_fraction=0.3)
+    _, counts, _ = oracle.classify_channels(x, outer, channels, 1, 3.0, 1, dtype="f32")
+    for bound in (1, int(counts.max()), int(counts.max()) + 1, int(np.median(counts[counts > 0]))):
+        _check(api, x, outer, channels, 1, 3.0, max(1, bound), name="bound")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_waves_of_a_large_launch_look_twice(api, dtype):
+    """More than 65536 spans in a launch: a wave of a wide tensor takes sixteen, of a narrow one eight; and the same tensors one by one."""
+    entries = []
+    for i, (outer, channels) in enumerate(((12007, 3072), (12007, 3072), (3000, 1032), (9000, 64))):
+        g = torch.Generator(device="cuda").manual_seed(i)
+        x = torch.randn((outer, channels), generator=g, device="cuda")
+        x[:, ::25] = torch.where(torch.rand(x[:, ::25].shape, generator=g, device="cuda") < 0.05, x[:, ::25] * 81, x[:, ::25])
+        entries.append((x.reshape(-1).to(torch.bfloat16 if dtype == "bf16" else torch.float32), outer, channels, 1, 3.0, outer // 100))
+    assert sum(e[0].numel() for e in entries) // 1024 > 65536
+    print(f"[classify] two looks, {dtype}", flush=True)
+    batch = api.ClassifyBatch([api.ClassifyEntry(*e) for e in entries])
+    api.fh_classify_channels_batch(batch)
+    for e, b in zip(entries, batch.entries):
+        alone = api.fh_classify_channels(*e)
+        torch.cuda.synchronize()
+        for got, want in zip((b.stats, b.counts, b.mask), alone):
+            assert torch.equal(got, want)
