@@ -830,7 +830,7 @@ template <typename InT, int G, bool LISTED>
 __global__ __launch_bounds__(kCBlock) void compress_mixed_kernel(const Batch<MixedCompressJob> batch)
 {
     __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kMixedStageDwords];
-    __shared__ uint16_t listed[kListedRows];
+    __shared__ uint16_t listed[kListRoom];
     uint32_t tile;
     const MixedCompressJob& job = batch.item[batch_item(batch, blockIdx.x, tile)];
     const CompressItem& it = job.it;

@@ -363,7 +363,7 @@ __global__ __launch_bounds__(kDBlock) void decompress_mixed_kernel(const Batch<M
     const ChannelMap& cm = job.cm;
     const int raw_dtype = job.raw_dtype;
     __shared__ __attribute__((aligned(16))) uint8_t park[tile_elems<OutT>() * sizeof(OutT)];
-    __shared__ uint16_t listed[kListedRows];
+    __shared__ uint16_t listed[kListRoom];
     if (nothing_kept(cm)) {                                   // no channel of this tensor was kept: the plain code
         switch (it.bits) {
             case 2: decompress_tile<OutT, G, 2>(it, tile); break;
