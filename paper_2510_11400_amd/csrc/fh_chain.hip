@@ -11,8 +11,8 @@
 // Every stage is the library's own batched call; this file only lays the caller's two buffers
 // out, strings the calls together on one stream, and adds two small kernels: one that takes the
 // masks from the outlier counts, numbers the salient channels of every tensor of the call, clears
-// the rows of the raw stores that no channel uses (they must read as zero for the sparse stage),
-// the headers and the entropy stage's histograms, and one that adds up what a tensor's stored
+// the headers and, where the sparse stage cannot leave them out, the rows of the raw stores that no channel uses
+// (they must read as zero), and one that adds up what a tensor's stored
 // form occupies where the entropy stage does not do that.  Sizes that depend on the data (stream lengths) never visit the host:
 // the sparse stage's totals feed the Huffman stage through device memory.
 #include "../../include/fedhybrid.h"
@@ -37,7 +37,6 @@ struct PrepItem {
     uint8_t*        mask;
     int16_t*        slots;
     uint64_t*       header;                        // 8 words, cleared; [7] = slots in use
-    uint32_t*       hist;                          // 256 words, cleared; or null
     uint8_t*        raw;                           // the raw store: [outer][raw_channels][row_bytes]
     uint64_t        row_bytes;
     uint32_t        outer;                         // samples whose unused rows are to be cleared
@@ -61,7 +60,7 @@ __device__ __forceinline__ void clear_bytes(uint8_t* p, uint64_t bytes, uint32_t
 // Workgroup 0 of an item: mask[c] = channel c has min_outliers outliers or more, slots[c] = number
 // of salient channels before c while that is below raw_channels, -1 for every other channel (each
 // thread owns 16 consecutive channels, the per-thread counts are scanned over the workgroup), and the
-// header and the histogram cleared.  All workgroups of the item: the raw store's rows that no
+// header cleared.  All workgroups of the item: the raw store's rows that no
 // channel uses cleared.  (The rows in use are written whole by the quantiser: with 4 % of the channels salient and room
 // for a sixteenth, clearing them as well wrote 36 MB instead of 13 MB for the MobileNetV2-style set, 13 us against 8.6.)
 __global__ __launch_bounds__(kPrepThreads) void chain_prepare_kernel(const Batch<PrepItem> batch)
@@ -98,7 +97,6 @@ __global__ __launch_bounds__(kPrepThreads) void chain_prepare_kernel(const Batch
         }
         if (t < 7) it.header[t] = 0u;
         if (t == 7) it.header[7] = used;
-        if (it.hist && t < 256) it.hist[t] = 0u;
     }
     // The unused rows of a sample are one piece; a wave takes a part of one at a time.  Pieces of a few hundred bytes
     // ([tokens][hidden] tensors) are cleared together with what lies between them: one by one they took 56 us for
@@ -311,7 +309,7 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
     if (first && (st = compress_first(mix.data(), cls.data(), ranges.data(), count, s)) != FH_OK) return st;
     if ((st = classify_counts(cls.data(), ranges.data(), count, first, s)) != FH_OK) return st;
 
-    // 2. masks from the counts, slots from the masks; headers, histograms and the raw stores' unused rows cleared
+    // 2. masks from the counts, slots from the masks; headers and the raw stores' unused rows cleared
     for (int32_t i = 0; i < count;) {
         Batch<PrepItem> b;
         reset(b);
@@ -323,7 +321,6 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
             p.mask = at(it.workspace, reg[i].mask);
             p.slots = reinterpret_cast<int16_t*>(at(it.store, reg[i].slots));
             p.header = reinterpret_cast<uint64_t*>(at(it.store, reg[i].header));
-            p.hist = it.entropy && reg[i].raw_bytes ? reinterpret_cast<uint32_t*>(at(it.workspace, reg[i].huffman_ws)) : nullptr;
             p.raw = at(it.workspace, reg[i].raw);
             p.row_bytes = (uint64_t)it.inner * elem_size(it.x_dtype);
             p.outer = reg[i].raw_bytes && !rows_in_use(it, reg[i]).count ? (uint32_t)it.outer : 0u;

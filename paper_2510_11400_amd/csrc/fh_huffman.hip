@@ -90,6 +90,16 @@ struct Layout {                                    // where things are in the st
 
 __device__ __forceinline__ uint64_t chunks_for(uint64_t n) { return (n + 255u) >> 8; }
 
+// Histogram workgroups of a stream: four vectors per thread up to 4 Mi symbols, eight of what lies beyond, more in long streams,
+// since a workgroup clears and adds up 32 KiB of counters whatever it counts.  (Eight throughout, the five streams of 8 MB
+// of the whole chain take 7.5 us, this way 5.5.)
+__host__ __device__ __forceinline__ uint32_t hist_blocks_for(uint64_t n)
+{
+    constexpr uint64_t each = (uint64_t)kHistThreads * 16u * 4u, few = 64;
+    const uint64_t want = n == 0 ? 0 : n <= few * each ? n / each + 1u : few + (n - few * each) / (2u * each) + 1u;
+    return (uint32_t)(want < (uint64_t)kHistBlocksMax ? want : (uint64_t)kHistBlocksMax);
+}
+
 // The layout a kernel works with.  When the symbol count lives in device memory (it is the
 // output of an earlier call on the same stream), the host has sized buffers and grids for an
 // upper bound; the count itself, and what follows from it -- chunks, groups, where the payload
@@ -103,8 +113,15 @@ __device__ __forceinline__ Layout resolved(const Layout& given)
         lay.chunks = (uint32_t)chunks_for(lay.n);
         lay.groups = (lay.chunks + 255u) >> 8;
         lay.payload = lay.offsets + lay.chunks + 1;
+        lay.hist_blocks = hist_blocks_for(lay.n);
     }
     return lay;
+}
+// Where several histogram workgroups leave their 256 counts each, 16-byte aligned: in the payload's place, which is written after
+// they have been read, and is longer than they are (a bit per symbol at least, where they are 1 KiB to 64 Ki symbols).
+__device__ __forceinline__ uint32_t* hist_rows(const Layout& lay)
+{
+    return reinterpret_cast<uint32_t*>((reinterpret_cast<uintptr_t>(lay.payload) + 15u) & ~(uintptr_t)15u);
 }
 
 struct DecodeJob {
@@ -120,19 +137,19 @@ struct DecodeJob {
 };
 
 // Every pass serves up to kBatch streams (fh_batch.hpp); the per-stream passes take a workgroup per stream.
-__global__ __launch_bounds__(256) void huffman_clear_kernel(const Batch<Layout> batch) { batch.item[blockIdx.x].hist[threadIdx.x] = 0u; }
 
 // ---- histogram ------------------------------------------------------------------------------------
-// A workgroup clears, adds up and sends off 32 KiB of counters whatever it counts; the atomics of all workgroups meet
-// on the stream's 256 counters.  So the workgroup has the most threads there are: at 51 MB in five streams 29 us
-// with 256 threads (1340 workgroups), 18 us with 1024.
+// A workgroup clears and adds up 32 KiB of counters whatever it counts, so it has the most threads there are: at 51 MB in five
+// streams 29 us with 256 threads (1340 workgroups), 18 us with 1024.  The code kernel adds up what the workgroups leave: with
+// counters that they all add to, these had to be cleared by a launch before this one (encode and decode of 51 MB 125.4 us, 122.4 now).
 __global__ __launch_bounds__(kHistThreads) void huffman_histogram_kernel(const Batch<Layout> batch)
 {
     uint32_t block;
     const Layout lay = resolved(batch.item[batch_item(batch, blockIdx.x, block)]);
+    if (block >= lay.hist_blocks) return;                     // workgroup-uniform: past the real extent
     const uint8_t* in = lay.in;
     const uint64_t n = lay.n;
-    uint32_t* hist = lay.hist;
+    uint32_t* const counts = lay.hist_blocks == 1u ? lay.hist : hist_rows(lay) + 256u * block;
     // One copy of the histogram per LDS bank, the copies interleaved so that copy c of every bin lies in bank c:
     // lane l counts in copy l mod 32, and whatever the bytes are no two lanes of a half-wave meet in a bank
     // (bytes clustered around one value would otherwise serialise on the few bins they share).
@@ -166,7 +183,7 @@ __global__ __launch_bounds__(kHistThreads) void huffman_histogram_kernel(const B
     for (uint32_t c = 0; c < 8u; ++c) total += local[bin][first + ((c + bin) & 7u)];
     total = dpp_add<0x111, 0xf>(total);                       // row_shr:1, then 2: over the lane and the three below it
     total = dpp_add<0x112, 0xf>(total);
-    if ((threadIdx.x & 3u) == 3u && total) atomicAdd(&hist[bin], total);
+    if ((threadIdx.x & 3u) == 3u) counts[bin] = total;
 }
 
 // ---- code lengths and canonical codes ---------------------------------------------------------------
@@ -246,6 +263,18 @@ __device__ __forceinline__ void merge_in_rounds(const uint32_t m, uint32_t* weig
     }
 }
 
+// the lanes whose code length, 24 at most, is this one's; every lane of the wave must be active
+__device__ __forceinline__ uint64_t lanes_alike(uint32_t length)
+{
+    uint64_t same = ~(uint64_t)0;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const uint64_t has = __builtin_amdgcn_ballot_w64(((length >> k) & 1u) != 0u);
+        same &= (length >> k) & 1u ? has : ~has;
+    }
+    return same;
+}
+
 // One workgroup per stream.  It runs once, alone on its compute unit, and every phase is a chain of dependent steps,
 // so what counts is the length of the chains: the sixteen waves compare a quarter of the counts each for the ranks
 // (four waves on a SIMD hide each other's latencies), threads 0..255 stand for the symbols elsewhere.  A 50 MB stream of 256
@@ -254,7 +283,7 @@ __device__ __forceinline__ void merge_in_rounds(const uint32_t m, uint32_t* weig
 constexpr int kCodeThreads = 1024;
 __global__ __launch_bounds__(kCodeThreads) void huffman_code_kernel(const Batch<Layout> batch)
 {
-    const Layout& lay = batch.item[blockIdx.x];
+    const Layout lay = resolved(batch.item[blockIdx.x]);
     // counts and weights are sums of at most 2^32 - 1 symbols: 32 bits hold them
     __shared__ __align__(16) uint32_t count[256];             // this round's counts, by symbol
     __shared__ uint32_t rank_of[256];
@@ -265,12 +294,31 @@ __global__ __launch_bounds__(kCodeThreads) void huffman_code_kernel(const Batch<
     __shared__ uint32_t in_wave[4][kMaxLen + 2];              // [w][k]: wave w's symbols that are unused (k = 0) / of length k
     __shared__ uint32_t first_code[64];
     __shared__ uint32_t bits_in_wave[4][2];
-    __shared__ uint32_t deepest;
+    __shared__ __align__(16) uint32_t of_rows[kCodeThreads / 64][256];     // the histogram workgroups' counts, as many sums as waves
+    __shared__ uint32_t too_deep;
     const uint32_t thread = threadIdx.x, lane = thread & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(thread >> 6));
     const uint32_t s = thread & 255u, symbols = wave & 3u, quarter = wave >> 2;   // the wave's symbols: 64 symbols + lane
     const bool symbol = wave < 4u;
-    const uint32_t original = lay.hist[s];
+    uint32_t original = 0;
+    if (lay.hist_blocks > 1u) {                               // workgroup-uniform; a wave a row at a time, four in flight
+        const u32x4* rows = reinterpret_cast<const u32x4*>(hist_rows(lay)) + lane;
+        u32x4 sum = {0u, 0u, 0u, 0u};
+        constexpr uint32_t kAtOnce = 4, kStep = kCodeThreads / 64;
+        for (uint32_t r = wave; r < lay.hist_blocks; r += kAtOnce * kStep) {
+            u32x4 got[kAtOnce];
+#pragma unroll
+            for (uint32_t k = 0; k < kAtOnce; ++k) got[k] = r + k * kStep < lay.hist_blocks ? rows[64u * (r + k * kStep)] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (uint32_t k = 0; k < kAtOnce; ++k) sum += got[k];
+        }
+        reinterpret_cast<u32x4*>(of_rows[wave])[lane] = sum;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t w = 0; w < kStep; ++w) original += of_rows[w][s];
+    } else if (lay.hist_blocks == 1u) {
+        original = lay.hist[s];
+    }
     uint32_t c = original, my_length = 0;
     for (;;) {                                                // workgroup-uniform; counts halve, so it ends
         if (symbol) {
@@ -278,7 +326,7 @@ __global__ __launch_bounds__(kCodeThreads) void huffman_code_kernel(const Batch<
             rank_of[s] = 0u;
             const uint64_t unused = __builtin_amdgcn_ballot_w64(c == 0u);
             if (lane == 0) in_wave[wave][0] = (uint32_t)__popcll(unused);
-            if (s == 0) deepest = 0u;
+            if (s == 0) too_deep = 0u;
         }
         __syncthreads();
         const uint32_t m = 256u - (in_wave[0][0] + in_wave[1][0] + in_wave[2][0] + in_wave[3][0]);   // used symbols
@@ -330,24 +378,23 @@ __global__ __launch_bounds__(kCodeThreads) void huffman_code_kernel(const Batch<
         if (symbol && c != 0) {
             const uint32_t mine = up[1][rank];
             my_length = m == 1u ? 1u : (mine & 0xffffu) == root ? mine >> 16 : 255u;
-            atomicMax(&deepest, my_length);
+            if (my_length > (uint32_t)kMaxLen) too_deep = 1u;
         }
         __syncthreads();
-        if (deepest <= (uint32_t)kMaxLen) break;
+        if (!too_deep) break;
         if (c != 0) c = (c + 1) >> 1;
-        __syncthreads();                                      // everyone has read `deepest` before it is written again
+        __syncthreads();                                      // everyone has read `too_deep` before it is written again
     }
     // canonical codes: by increasing (length, symbol); a symbol's place among those of its length from lane masks
     // inside the wave plus the counts of the waves below.  Payload bits: every symbol's count times its length (the
     // counts as they were), the counts' halves apart so that a wave's sums fit 32 bits.
     uint32_t before = 0;
     if (symbol) {
-#pragma unroll
-        for (int k = 1; k <= kMaxLen; ++k) {
-            const uint64_t same = __builtin_amdgcn_ballot_w64(my_length == (uint32_t)k);
-            if (my_length == (uint32_t)k) before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-            if (lane == 0) in_wave[wave][k] = (uint32_t)__popcll(same);
-        }
+        if (lane <= (uint32_t)kMaxLen + 1u) in_wave[wave][lane] = 0u;
+        const uint64_t same = lanes_alike(my_length);
+        before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); // LDS operations of one wave complete in order
+        if (my_length && before == 0u) in_wave[wave][my_length] = (uint32_t)__popcll(same);
         const uint32_t low = wave_inclusive_scan((original & 0xffffu) * my_length), high = wave_inclusive_scan((original >> 16) * my_length);
         if (lane == 63u) { bits_in_wave[wave][0] = low; bits_in_wave[wave][1] = high; }
     }
@@ -973,12 +1020,7 @@ __global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Ba
     const auto build_tables = [&] {
         uint32_t before = 0;                                  // symbols of this one's length before it in its wave
         if (wave < 4u) {                                      // wave-uniform
-            uint64_t same = ~(uint64_t)0;
-#pragma unroll
-            for (int k = 0; k < 5; ++k) {
-                const uint64_t has = __ballot((l >> k) & 1u);
-                same &= (l >> k) & 1u ? has : ~has;
-            }
+            const uint64_t same = lanes_alike(l);
             before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
             if (l && before == 0u) local.in_wave[wave][l] = (uint32_t)__popcll(same);
         }
@@ -1225,7 +1267,7 @@ void launch(Kernel kernel, const Batch<Item>& b, uint32_t grid, hipStream_t s, i
 }
 
 
-// The encoder's launches; `stored` null: the histograms are to be cleared, and there is no header to write to.
+// The encoder's launches; `stored` null: there is no header to write to.
 fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stored, int32_t count, hipStream_t s)
 {
     for (int32_t i = 0; i < count;) {
@@ -1248,10 +1290,7 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
             lay.n = it.n;
             lay.n_dev = static_cast<const uint64_t*>(it.n_device);
             lay.stored = stored ? stored[i] : StoredForm{nullptr, 0, 0};
-            // about eight vectors per thread, more in long streams: a workgroup clears and adds up 32 KiB of
-            // counters and sends 256 atomics to the stream's histogram whatever it counts
-            const uint64_t want = it.n == 0 ? 0 : (it.n / 16 + kHistThreads - 1) / kHistThreads / 8 + 1;
-            lay.hist_blocks = (uint32_t)(want < (uint64_t)kHistBlocksMax ? want : (uint64_t)kHistBlocksMax);
+            lay.hist_blocks = hist_blocks_for(it.n);
             if ((uint64_t)grouped.block_start[grouped.count] + lay.groups > (uint64_t)INT_MAX) {
                 if (each.count == 0) return FH_ERR_BAD_NUMEL;
                 break;
@@ -1262,7 +1301,6 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
             ++i;
         }
         seal(each); seal(hist); seal(grouped);
-        if (!stored) launch(huffman_clear_kernel, each, (uint32_t)each.count, s);
         launch(huffman_histogram_kernel, hist, hist.block_start[hist.count], s, kHistThreads);
         launch(huffman_code_kernel, each, (uint32_t)each.count, s, kCodeThreads);
         const uint32_t all = grouped.block_start[grouped.count];

@@ -42,8 +42,7 @@ inline MapsInUse maps_in_use(const uint64_t* count, uint32_t rows)
 fh_status sparse_encode_rows(const fh_sparse_encode_item* items, const MapsInUse* use, int32_t count, hipStream_t s);
 fh_status sparse_decode_rows(const fh_sparse_decode_item* items, const MapsInUse* use, bool read_next, int32_t count, hipStream_t s);
 
-// fh_huffman_encode_batch for histograms (the first 256 words of the items' workspaces) that have been cleared, and
-// with the bytes that the stored form of the tensor occupies written to header[6] on the way:
+// fh_huffman_encode_batch with the bytes that the stored form of the tensor occupies written to header[6] on the way:
 // fixed_bytes + header[0] * value_size + the stream's bytes.
 struct StoredForm { uint64_t* header; uint64_t fixed_bytes; uint32_t value_size; };
 fh_status huffman_encode_stored(const fh_huffman_encode_item* items, const StoredForm* stored, int32_t count, hipStream_t s);
