@@ -40,12 +40,9 @@ constexpr int kWavesPerBlock = kThreads / kWave;
 constexpr int kMaxChannels = 16384;
 
 // ---- per-kernel descriptors (fh_batch.hpp: up to kBatch tensors per launch) ----------------
-struct MomentsItem { const void* x; int64_t numel; f64x2* partial; uint32_t* ranges; };
+struct MomentsItem { const void* x; int64_t numel; f64x2* partial; uint32_t* ranges; Cleared cleared; };
 struct ReduceItem  { const f64x2* in; int64_t count; f64x2* out; };
-struct FinishItem  {
-    const f64x2* in; int64_t count; int64_t numel; double k_sigma;
-    double* stats; uint32_t* counts; uint8_t* mask; int32_t channels;
-};
+struct EmptyItem   { double* stats; Cleared cleared; };
 struct MaskItem    { const uint32_t* counts; uint8_t* mask; int64_t min_outliers; int32_t channels; };
 
 // ---- pass 1a: spans of the tensor ------------------------------------------------------
@@ -104,6 +101,7 @@ __global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsIt
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t span = ((int64_t)block * kWavesPerBlock + wave) * SPANS;
     const int64_t base = span * kSpan;
+    if (block == 0) clear_counters<kThreads>(it.cleared);     // workgroup-uniform
     if (base >= numel) return;                                // wave-uniform
     const InT* xs = x + base;
     float v[ROWS][EPL];
@@ -170,52 +168,60 @@ __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const Batch<R
     if (lane == 0) out[span] = f64x2{s1, s2};
 }
 
-// ---- pass 1c: last level of the tree (at most 1024 partial sums), then mean, variance and
-//      threshold; clears the counters and the mask ----------------------------------------------
-struct FinishBatch { FinishItem item[kBatch]; };           // one workgroup per tensor
-__global__ __launch_bounds__(kThreads) void finish_moments_kernel(const FinishBatch args)
+// A tensor without elements: nothing else is launched for it.
+struct EmptyBatch { EmptyItem item[kBatch]; };
+__global__ __launch_bounds__(kThreads) void no_elements_kernel(const EmptyBatch args)
 {
-    const FinishItem& it = args.item[blockIdx.x];
-    const f64x2* in = it.in;
-    const int64_t count = it.count, numel = it.numel;
-    const double k_sigma = it.k_sigma;
-    double* stats = it.stats;
-    uint32_t* counts = it.counts;
-    uint8_t* mask = it.mask;
-    const int channels = it.channels;
-    for (int c = threadIdx.x; c < channels; c += kThreads) { counts[c] = 0u; mask[c] = 0; }
-    if (threadIdx.x >= kWave) return;                         // the tree is one wave's work
+    const EmptyItem& it = args.item[blockIdx.x];
+    clear_counters<kThreads>(it.cleared);
+    if (threadIdx.x < 4) it.stats[threadIdx.x] = 0.0;
+}
+
+// ---- the last level of the tree (at most 1024 partial sums), then mean, variance and threshold -----------------
+// The first wave of every workgroup of the count pass does this for itself, the first workgroup of a tensor writes it down: as
+// a launch between the passes it was 4.7 us and the gap before it, here the other waves clear the histogram and the ranges are on
+// their way meanwhile.  One tensor of 12 MB 16.9 -> 15.8 us, of 50 MB 29.7 -> 28.4, three of 50 MB 50.7 -> 48.4; on large sets the pass
+// takes longer by as much as the launch took.
+struct LastLevel {
+    const f64x2* in;                                          // the partial sums
+    int32_t      count;
+    double       k_sigma;
+    double*      stats;
+};
+struct Limits { double mean, threshold; };
+__device__ __forceinline__ Limits limits_of(const LastLevel& it, int64_t numel, uint32_t lane, bool write)      // one wave
+{
     constexpr int ROWS = 4, EPL = 4, ROW = kWave * EPL;
-    const uint32_t lane = threadIdx.x;
     double a[ROWS], b[ROWS];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
+        a[r] = b[r] = 0.0;
+        if (r * ROW >= it.count) continue;                    // wave-uniform
         double d[EPL], q[EPL];
 #pragma unroll
         for (int j = 0; j < EPL; ++j) {
-            const int64_t i = r * ROW + lane * EPL + j;
-            const f64x2 p = i < count ? in[i] : f64x2{0.0, 0.0};
+            const int32_t i = r * ROW + (int32_t)lane * EPL + j;
+            const f64x2 p = i < it.count ? it.in[i] : f64x2{0.0, 0.0};
             d[j] = p.x; q[j] = p.y;
         }
         a[r] = local_tree<EPL>(d);
         b[r] = local_tree<EPL>(q);
     }
     double s1, s2;
-    both_moments(span_tree<1>(a, b, lane), lane, s1, s2);
-    if (lane == 0) {
-        double mean = 0.0, variance = 0.0;
-        if (numel > 0) {
-            const double n = (double)numel;
-            mean = (s1 + 0.0) / n;                            // a total of -0.0 counts as +0.0; IEEE division
-            const double mean_sq = mean * mean;
-            variance = s2 / n - mean_sq;
-            if (!(variance > 0.0)) variance = 0.0;
-        }
-        stats[0] = mean;
-        stats[1] = variance;
-        stats[2] = (k_sigma * k_sigma) * variance;
-        stats[3] = (double)numel;
+    both_moments(span_tree<1>(a, b, lane), lane, s1, s2);     // in every lane
+    const double n = (double)numel;
+    const double mean = (s1 + 0.0) / n;                       // a total of -0.0 counts as +0.0; IEEE division
+    const double mean_sq = mean * mean;
+    double variance = s2 / n - mean_sq;
+    if (!(variance > 0.0)) variance = 0.0;
+    const double threshold = (it.k_sigma * it.k_sigma) * variance;
+    if (write && lane == 0) {
+        it.stats[0] = mean;
+        it.stats[1] = variance;
+        it.stats[2] = threshold;
+        it.stats[3] = n;
     }
+    return Limits{mean, threshold};
 }
 
 // ---- pass 2: outliers per channel ----------------------------------------------------------
@@ -224,7 +230,7 @@ __global__ __launch_bounds__(kThreads) void finish_moments_kernel(const FinishBa
 struct CountArgs {
     const void* x;
     int64_t numel;
-    const double* stats;
+    LastLevel last;
     uint32_t* counts;
     SmallDiv inner, channels;
     int32_t spans_per_wave;                                   // consecutive spans one wave walks
@@ -258,6 +264,14 @@ __device__ __forceinline__ void add_outliers(const CountArgs& args, const uint32
     }
 }
 
+__device__ __forceinline__ double uniform(double v)            // the same in all lanes, into scalar registers
+{
+    const u32x2 w = __builtin_bit_cast(u32x2, v);
+    const uint32_t low = w.x, high = w.y;
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)high) << 32) |
+                                          (uint32_t)__builtin_amdgcn_readfirstlane((int)low));
+}
+
 // AHEAD: a launch in which some wave walks more than one span.
 constexpr int kAhead = 3;                         // spans requested before the one that is looked at
 template <typename InT, bool AHEAD>
@@ -265,15 +279,19 @@ __global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Batch<Co
 {
     constexpr int ROWS = Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
     extern __shared__ uint32_t hist[];
+    __shared__ Limits limits;
     uint32_t block;
     const CountArgs& args = batch.item[batch_item(batch, blockIdx.x, block)];
     const uint32_t C = args.channels.d;
-    for (uint32_t c = threadIdx.x; c < C; c += kThreads) hist[c] = 0u;
-    __syncthreads();
-
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const double mean = args.stats[0], threshold = args.stats[2];
+    if (wave == 0) {
+        const Limits found = limits_of(args.last, args.numel, lane, block == 0);
+        if (lane == 0) limits = found;
+    }
+    for (uint32_t c = threadIdx.x; c < C; c += kThreads) hist[c] = 0u;
+    __syncthreads();
+    const double mean = uniform(limits.mean), threshold = uniform(limits.threshold);
     const InT* x = static_cast<const InT*>(args.x);
     const int64_t numel = args.numel;
     // this wave's spans: first_span, first_span + 1, ...
@@ -388,6 +406,7 @@ __global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Batch
     constexpr int kThreads = WAVES * kWave;
     constexpr int ROWS = Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
     extern __shared__ uint32_t hist[];
+    __shared__ Limits limits;
     uint32_t block;
     const CountArgs& args = batch.item[batch_item(batch, blockIdx.x, block)];
     const uint32_t C = args.channels.d;
@@ -399,9 +418,13 @@ __global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Batch
     const int64_t stop = first + args.spans_per_wave < all_spans ? first + args.spans_per_wave : all_spans;
     const auto range_of = [&](int64_t span) { return span + (lane >> 3) < stop ? args.ranges[span * kPieces + lane] : 0u; };
     uint32_t range = range_of(first);                         // in flight while the counters are cleared
+    if (wave == 0) {
+        const Limits found = limits_of(args.last, numel, lane, block == 0);
+        if (lane == 0) limits = found;
+    }
     for (uint32_t c = threadIdx.x; c < C; c += kThreads) hist[c] = 0u;
-    const double mean = args.stats[0], threshold = args.stats[2];
     __syncthreads();
+    const double mean = uniform(limits.mean), threshold = uniform(limits.threshold);
     for (int64_t span0 = first; span0 < stop; span0 += kLook) {          // wave-uniform
         const bool mark = span0 + (lane >> 3) < stop && may_hold_outliers(range, mean, threshold);
         const uint64_t marks = __ballot(mark);
@@ -557,7 +580,7 @@ fh_status check_item(const fh_classify_item& it, int64_t* numel_out)
     return FH_OK;
 }
 
-// One run of up to kBatch tensors of one dtype: four kinds of launches, each covering all of them.  The tensors either all have a place for their ranges or all have none.
+// One run of up to kBatch tensors of one dtype: two or three launches, each covering all of them.  The tensors either all have a place for their ranges or all have none.
 fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, const int64_t* numels, int n, bool masks,
                        bool first_pass_done, hipStream_t s)
 {
@@ -579,7 +602,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
     for (int i = 0; i < n; ++i) {
         level[i] = static_cast<f64x2*>(items[i].workspace);
         m[i] = numels[i] > 0 ? ceil_div(numels[i], kSpan) : 0;
-        if (numels[i] > 0 && !first_pass_done && !push(mb, MomentsItem{items[i].x, numels[i], level[i], ranges[i]}, ceil_div(m[i], per_block)))
+        if (numels[i] > 0 && !first_pass_done && !push(mb, MomentsItem{items[i].x, numels[i], level[i], ranges[i], cleared_of(items[i])}, ceil_div(m[i], per_block)))
             return FH_ERR_BAD_NUMEL;
     }
     if (mb.count > 0) {
@@ -597,7 +620,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
         Batch<ReduceItem> rb;
         reset(rb);
         for (int i = 0; i < n; ++i) {
-            if (m[i] <= kSpan) continue;                      // the last <= 1024 partials are the finish kernel's
+            if (m[i] <= kSpan) continue;                      // the last <= 1024 partials are the count pass's
             const int64_t next = ceil_div(m[i], kSpan);
             f64x2* out = level[i] + m[i];
             push(rb, ReduceItem{level[i], m[i], out}, ceil_div(next, kWavesPerBlock));
@@ -608,13 +631,14 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
         seal(rb);
         hipLaunchKernelGGL(reduce_partials_kernel, dim3(rb.block_start[rb.count]), block, 0, s, rb);
     }
-    FinishBatch fb;
+    EmptyBatch eb;
+    int empty = 0;
     for (int i = 0; i < n; ++i)
-        fb.item[i] = FinishItem{level[i], m[i], numels[i], items[i].k_sigma, static_cast<double*>(items[i].stats),
-                                static_cast<uint32_t*>(items[i].counts), static_cast<uint8_t*>(items[i].mask),
-                                (int32_t)items[i].channels};
-    for (int i = n; i < kBatch; ++i) fb.item[i] = fb.item[0];
-    hipLaunchKernelGGL(finish_moments_kernel, dim3(n), block, 0, s, fb);
+        if (numels[i] == 0) eb.item[empty++] = EmptyItem{static_cast<double*>(items[i].stats), cleared_of(items[i])};
+    if (empty > 0) {
+        for (int i = empty; i < kBatch; ++i) eb.item[i] = eb.item[0];
+        hipLaunchKernelGGL(no_elements_kernel, dim3(empty), block, 0, s, eb);
+    }
 
     Batch<CountArgs> cb;
     Batch<MaskItem> kb;
@@ -630,7 +654,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
         CountArgs a;
         a.x = items[i].x;
         a.numel = numels[i];
-        a.stats = static_cast<const double*>(items[i].stats);
+        a.last = LastLevel{level[i], (int32_t)m[i], items[i].k_sigma, static_cast<double*>(items[i].stats)};
         a.counts = static_cast<uint32_t*>(items[i].counts);
         a.inner = make_small_div((uint32_t)items[i].inner);
         a.channels = make_small_div((uint32_t)items[i].channels);

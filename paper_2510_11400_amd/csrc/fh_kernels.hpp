@@ -9,6 +9,7 @@
 
 #include "fh_batch.hpp"
 #include "fh_channels.hpp"
+#include "fh_stages.hpp"
 
 namespace fh {
 
@@ -96,6 +97,7 @@ struct FirstCompressJob {
     CompressItem it;
     double*      partial;              // {sum x, sum x * x} per 1024 elements
     uint32_t*    ranges;
+    Cleared      cleared;
 };
 // Tensors that have been: the spans with kept elements again, those elements to the raw store.  inner > 1.
 int compress_kept_block_elems(int dtype);          // elements whose spans one workgroup looks at

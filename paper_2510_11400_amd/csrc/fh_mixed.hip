@@ -259,7 +259,7 @@ fh_status fh::compress_first(const fh_mixed_item* items, const fh_classify_item*
             const fh_mixed_item& it = items[i];
             const int64_t numel = it.outer * it.channels * it.inner;
             if (numel == 0) { ++i; continue; }
-            const FirstCompressJob job = {quantiser_item(it, numel), static_cast<double*>(classify[i].workspace), ranges[i]};
+            const FirstCompressJob job = {quantiser_item(it, numel), static_cast<double*>(classify[i].workspace), ranges[i], cleared_of(classify[i])};
             if (!push(b, job, (numel + tile - 1) / tile)) break;
             ++i;
         }

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "fh_device.hpp"
+#include "fh_stages.hpp"
 
 namespace fh {
 
@@ -115,6 +116,13 @@ __device__ __forceinline__ double local_tree(const double (&v)[N])
 #pragma unroll
         for (int i = 0; i < n / 2; ++i) w[i] = w[2 * i] + w[2 * i + 1];
     return w[0];
+}
+
+// The counters and the mask of a tensor, by one workgroup of the first pass.
+template <int THREADS>
+__device__ __forceinline__ void clear_counters(const Cleared& c)
+{
+    for (int i = threadIdx.x; i < c.channels; i += THREADS) { c.counts[i] = 0u; c.mask[i] = 0; }
 }
 
 // ---- value ranges ------------------------------------------------------------------------

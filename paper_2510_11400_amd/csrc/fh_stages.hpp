@@ -21,6 +21,13 @@ inline size_t range_bytes(int64_t numel) { return numel > 0 ? (size_t)((numel + 
 fh_status classify_counts(const fh_classify_item* items, uint32_t* const* ranges, int32_t count, bool first_pass_done,
                           hipStream_t s);
 
+// What the classification adds to, cleared by its first pass.
+struct Cleared { uint32_t* counts; uint8_t* mask; int32_t channels; };
+inline Cleared cleared_of(const fh_classify_item& it)
+{
+    return Cleared{static_cast<uint32_t*>(it.counts), static_cast<uint8_t*>(it.mask), (int32_t)it.channels};
+}
+
 // The forward side in two steps, for tensors of which few elements are kept: compress_first quantises the tensors as if
 // nothing were kept and makes the classification's first pass on the way (partial sums at classify[i].workspace, ranges
 // at ranges[i]); compress_kept, once the slots are known, does fh_compress_mixed_batch's work for the spans of the
