@@ -82,7 +82,6 @@ __device__ __forceinline__ bool may_hold_outliers(uint32_t range, double mean, d
 // when the tensors come from HBM those few bytes cost as much as their lines travel.  First pass of a launch, one span in
 // order against LARGE, us:  bf16 8 MB 4.0 / 4.9, 50 MB 11.1 / 11.3, 100 MB 20.4 / 20.0, 180 MB 35.1 / 31.8,
 // 750 MB 137 / 121; fp32 40 MB 9.5 / 10.1, 134 MB 22.5 / 22.6, 557 MB 91 / 87.
-constexpr int kXcds = 8;
 constexpr int64_t kLargeLaunch = (int64_t)96 << 20;
 __device__ __forceinline__ uint32_t tile_of_block()
 {

@@ -25,6 +25,7 @@
 #include "fh_device.hpp"
 #include "fh_kernels.hpp"
 #include "fh_moments.hpp"
+#include "fh_rules.hpp"
 
 namespace fh {
 
@@ -792,10 +793,10 @@ __device__ __forceinline__ void compress_tile(const CompressItem& it, uint32_t t
     }
 }
 
-template <typename InT, int G>
+template <typename InT, int G, bool RUNS>
 __global__ __launch_bounds__(kCBlock) void compress_kernel(const CompressBatch args)
 {
-    const uint32_t bid = blockIdx.x;
+    const uint32_t bid = RUNS ? tile_in_run<128>(blockIdx.x, gridDim.x) : blockIdx.x;
     int lo = 0, hi = args.count;                              // last item with tile_start <= bid
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -958,15 +959,19 @@ hipError_t launch_compress(const CompressBatch& b, int dtype, int group_size, hi
     const uint32_t tiles = b.tile_start[b.count];
     if (tiles == 0) return hipSuccess;
     const dim3 grid(tiles), block(kCBlock);
-#define FH_LAUNCH(T, GS) hipLaunchKernelGGL((compress_kernel<T, GS>), grid, block, 0, s, b)
-    if (dtype == 0) {
-        if (group_size == 64) FH_LAUNCH(float, 64);
-        else if (group_size == 128) FH_LAUNCH(float, 128);
-        else FH_LAUNCH(float, 256);
+#define FH_LAUNCH(T, GS, RUNS) hipLaunchKernelGGL((compress_kernel<T, GS, RUNS>), grid, block, 0, s, b)
+    if (dtype == 0 && compress_in_runs(tiles)) {
+        if (group_size == 64) FH_LAUNCH(float, 64, true);
+        else if (group_size == 128) FH_LAUNCH(float, 128, true);
+        else FH_LAUNCH(float, 256, true);
+    } else if (dtype == 0) {
+        if (group_size == 64) FH_LAUNCH(float, 64, false);
+        else if (group_size == 128) FH_LAUNCH(float, 128, false);
+        else FH_LAUNCH(float, 256, false);
     } else {
-        if (group_size == 64) FH_LAUNCH(uint16_t, 64);
-        else if (group_size == 128) FH_LAUNCH(uint16_t, 128);
-        else FH_LAUNCH(uint16_t, 256);
+        if (group_size == 64) FH_LAUNCH(uint16_t, 64, false);
+        else if (group_size == 128) FH_LAUNCH(uint16_t, 128, false);
+        else FH_LAUNCH(uint16_t, 256, false);
     }
 #undef FH_LAUNCH
     return hipGetLastError();

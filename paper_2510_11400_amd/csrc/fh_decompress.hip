@@ -18,6 +18,7 @@
 #include "fh_channels.hpp"
 #include "fh_device.hpp"
 #include "fh_kernels.hpp"
+#include "fh_rules.hpp"
 
 namespace fh {
 
@@ -332,13 +333,13 @@ __device__ __forceinline__ void decompress_tile(const DecompressItem& it, uint32
     }
 }
 
-template <typename OutT, int G>
+template <typename OutT, int G, bool RUNS>
 __global__ __launch_bounds__(kDBlock) void decompress_kernel(const DecompressBatch args)
 {
     // Tiles are taken from the end of the set backwards: the backward pass needs the
     // tensors in the reverse of the order the forward pass saved them, and the codes
     // written last are the ones most likely still held by the memory-side cache.
-    const uint32_t bid = gridDim.x - 1u - blockIdx.x;
+    const uint32_t bid = gridDim.x - 1u - (RUNS ? tile_in_run<64>(blockIdx.x, gridDim.x) : blockIdx.x);
     const int lo = find_item(args.tile_start, bid);
     const DecompressItem it = args.item[lo];                  // by value: one batch of scalar loads
     const uint32_t tile = bid - args.tile_start[lo];
@@ -393,15 +394,19 @@ hipError_t launch_decompress(const DecompressBatch& b, int out_dtype, int group_
     const uint32_t tiles = b.tile_start[b.count];
     if (tiles == 0) return hipSuccess;
     const dim3 grid(tiles), block(kDBlock);
-#define FH_LAUNCH(T, GS) hipLaunchKernelGGL((decompress_kernel<T, GS>), grid, block, 0, s, b)
-    if (out_dtype == 0) {
-        if (group_size == 64) FH_LAUNCH(float, 64);
-        else if (group_size == 128) FH_LAUNCH(float, 128);
-        else FH_LAUNCH(float, 256);
+#define FH_LAUNCH(T, GS, RUNS) hipLaunchKernelGGL((decompress_kernel<T, GS, RUNS>), grid, block, 0, s, b)
+    if (out_dtype == 0 && restore_in_runs(tiles)) {
+        if (group_size == 64) FH_LAUNCH(float, 64, true);
+        else if (group_size == 128) FH_LAUNCH(float, 128, true);
+        else FH_LAUNCH(float, 256, true);
+    } else if (out_dtype == 0) {
+        if (group_size == 64) FH_LAUNCH(float, 64, false);
+        else if (group_size == 128) FH_LAUNCH(float, 128, false);
+        else FH_LAUNCH(float, 256, false);
     } else {
-        if (group_size == 64) FH_LAUNCH(uint16_t, 64);
-        else if (group_size == 128) FH_LAUNCH(uint16_t, 128);
-        else FH_LAUNCH(uint16_t, 256);
+        if (group_size == 64) FH_LAUNCH(uint16_t, 64, false);
+        else if (group_size == 128) FH_LAUNCH(uint16_t, 128, false);
+        else FH_LAUNCH(uint16_t, 256, false);
     }
 #undef FH_LAUNCH
     return hipGetLastError();

@@ -27,6 +27,15 @@ inline int32_t marked_spans_per_wave(int64_t launch_spans, int64_t tensor_spans,
     return (int32_t)(spans < 1 ? 1 : spans > 8 ? 8 : spans);
 }
 
+// Whether the tiles of the plain quantiser of fp32 and of the restore to fp32 go to the XCDs in runs (fh_device.hpp), in a launch of `tiles`: 16 KiB of input
+// each, respectively 8 KiB of fp32 output.  The quantiser gains in fp32 from some 200 MB on: with runs of 128 a plan's 2 GiB both
+// ways 868 -> 819 us, 1 GiB 398 -> 390, 240 MB of feature maps 89.5 -> 88.4; 278 MB 103.4 and 103.0, 60 MB 26.5 and 27.0; bf16 loses
+// (encoder set 398 -> 407).  The restore of fp32 with runs of 64: encoder set 398 -> 379 us, 126 MB of it 41.0 -> 39.1, the plan
+// 868 -> 854, MobileNetV2-style set 201 -> 197, 60 MB 26.5 and 26.3; runs of 32 gain a half of that, of 128 as much.  Restoring bf16 gains
+// nothing (280 to 286 us), nor do the routed forms.  (A kernel of its own each: the test in the others cost a set of 60 MB 0.3 us of 25.6.)
+inline bool compress_in_runs(uint32_t tiles) { return tiles >= 12288; }
+inline bool restore_in_runs(uint32_t tiles) { return tiles >= 8192; }
+
 // How often a wave of a large launch looks at that many spans.  A workgroup's histogram of a wide tensor is 3072 counters to clear
 // and to add in for the outliers of 64 spans; once there are waves for a whole round of the device (8192 of eight spans), twice the
 // spans to a histogram save half of that, the ranges of the second eight on their way meanwhile.  Count pass of the 720 MiB

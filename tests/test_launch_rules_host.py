@@ -30,6 +30,8 @@ int main(int, char** argv)
         if (!std::strcmp(argv[1], "marked_spans_per_wave")) std::printf("%lld\\n", (long long)fh::marked_spans_per_wave(a, b, c, d));
         else if (!std::strcmp(argv[1], "marked_looks_per_wave")) std::printf("%d\\n", (int)fh::marked_looks_per_wave(a, b));
         else if (!std::strcmp(argv[1], "mask_with_the_counts")) std::printf("%d\\n", (int)fh::mask_with_the_counts(a));
+        else if (!std::strcmp(argv[1], "compress_in_runs")) std::printf("%d\\n", (int)fh::compress_in_runs((unsigned)a));
+        else if (!std::strcmp(argv[1], "restore_in_runs")) std::printf("%d\\n", (int)fh::restore_in_runs((unsigned)a));
         else if (!std::strcmp(argv[1], "maps_stay_in_cache")) std::printf("%d\\n", (int)fh::maps_stay_in_cache(a));
         else if (!std::strcmp(argv[1], "group_sums_are_scanned")) std::printf("%d\\n", (int)fh::group_sums_are_scanned(a));
         else if (!std::strcmp(argv[1], "decode_in_whole_lines")) std::printf("%d\\n", (int)fh::decode_in_whole_lines(a));
@@ -77,6 +79,13 @@ def test_the_chains_maps_pass_the_caches_by_where_these_do_not_hold_them(rules):
 def test_group_sums_are_scanned_in_launches_of_many_groups(rules):
     """Up to 4096 groups in a launch, however many streams they belong to, there is no scan."""
     assert rules("group_sums_are_scanned", [(n, 0, 0, 0) for n in (0, 1, 335, 4096, 4097, 24 * 335, 1 << 31)]) == [0, 0, 0, 0, 1, 1, 1]
+
+
+def test_tiles_go_to_the_xcds_in_runs_in_large_launches_of_fp32(rules):
+    tiles = (1, 8191, 8192, 12287, 12288, 1 << 31)
+    rows = [(n, 0, 0, 0) for n in tiles]
+    assert rules("compress_in_runs", rows) == [0, 0, 0, 0, 1, 1]
+    assert rules("restore_in_runs", rows) == [0, 0, 1, 1, 1, 1]
 
 
 def test_looks_and_masks_of_the_count_pass(rules):
