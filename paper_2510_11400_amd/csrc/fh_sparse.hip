@@ -53,13 +53,16 @@ template <int N> struct Group {
 };
 constexpr int kScanThreads = 512;
 constexpr uint64_t kStreamedFrom = (uint64_t)128 << 20;    // bytes of maps in a launch from which the first pass streams
-// Sets of up to this many workgroups have no scan of the workgroups' sums between the passes: each adds up those before it.
-// Encode and decode of one set, scanned and not, window 4: of 1024 workgroups 17.6 and 14.0, 17.9 and 14.2 us, of 2048 23.6 and
-// 21.0, 22.2 and 18.9, of 3136 33.2 and 32.5, 27.8 and 24.3, of 4096 38.9 and 40.7, 31.0 and 29.4; window 2, 2048: 16.4 and 13.0,
-// 16.8 and 12.9; window 8, whose workgroups do the most, 1500: 44.5 and 43.6, 44.5 and 43.1, 2048: 55.9 and 56.9, 58.4 and 58.4.
-// Several such sets in a launch gain up to some 5000 workgroups together (window 8: 2500) and lose beyond: five of 2048, window 4,
-// 76.0 and 87.3, 56.9 and 58.2.
-constexpr uint32_t kSelfScanLimit = 2048;
+// Is there a scan of a set's workgroups' sums between the passes?  Without one each workgroup adds up those before it, eight bytes
+// for a group.  Encode and decode of one set, window 4, scanned and not: 2300 workgroups 28.7 and 26.0, 22.9 and 20.0 us, 3000 33.2 and
+// 31.4, 26.5 and 23.5, 4000 39.2 and 38.4, 31.3 and 29.1.  Several large sets in a launch lose: five of 4000 136.8 and 147.7, 102.3 and
+// 109.2, so beyond 8192 workgroups together sets of more than 2048 are scanned, as other windows' always are (window 8, whose
+// workgroups do the most, 2048: 55.9 and 56.9, 58.4 and 58.4, with 24 bytes for a group).
+constexpr uint32_t kMostAddedUp = 4096;
+inline bool sums_are_scanned(uint32_t groups, uint32_t of_launch, int window)
+{
+    return groups > (window == 4 && of_launch <= 8192 ? kMostAddedUp : 2048u);
+}
 
 struct Sums {                                      // what a run of tiles writes
     uint64_t values, index_bytes, sparse_tiles;
@@ -110,7 +113,7 @@ __device__ __forceinline__ TilePos tile_pos(const MapShape& s, uint32_t b)
 struct Job {
     MapShape  shape;           // x: the maps (encode: input; decode: output)
     uint8_t*  info;            // one byte per tile (encode: written; decode: read)
-    Sums*     wg;              // per-workgroup sums, or their exclusive prefixes once `scanned`
+    void*     wg;              // per-workgroup sums (GroupSums), or Sums, and their exclusive prefixes behind the scan, where `scanned`
     void*     values;          // the two streams (encode: written; decode: read)
     uint8_t*  indices;
     union {
@@ -260,6 +263,9 @@ __device__ __forceinline__ uint64_t uniform(uint64_t v)
     return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
 }
 
+// What a workgroup's tiles write, as the passes that place tiles add it up themselves.
+struct GroupSums { uint32_t packed, sparse_tiles; };
+
 // Where a tile's pieces go: the workgroup's slices of the streams and the tile's place in them.
 struct Place {
     Sums     base;                                 // of all earlier workgroups (wave-uniform); sparse_tiles only when asked for
@@ -269,26 +275,42 @@ template <int WAVES> struct PlaceLds {
     uint32_t packed[WAVES];
     Sums32   part[WAVES];
 };
-// `scanned`: wg[] holds exclusive prefixes (the scan kernel ran); otherwise it holds per-workgroup sums, of at most
-// kSelfScanLimit workgroups, and they are added up here, a workgroup's width at a time: below 2^32 together.
+// `scanned`: wg holds exclusive prefixes (the scan kernel ran); otherwise it holds per-workgroup sums, of at most
+// kMostAddedUp workgroups, and they are added up here, eight of a thread's in flight: below 2^32 together.
 template <int N, bool SPARSE_TILES>
-__device__ __forceinline__ Place place_tiles(uint32_t mine, const Sums* wg, bool scanned, uint32_t block,
+__device__ __forceinline__ Place place_tiles(uint32_t mine, const void* wg, bool scanned, uint32_t block,
                                              PlaceLds<Group<N>::kWaves>& lds)
 {
     constexpr int WAVES = Group<N>::kWaves;
-    static_assert(sizeof(Packed<N>) > 0 && (uint64_t)kSelfScanLimit * 65536u < ((uint64_t)1 << 32), "32 bits hold the sums");
+    static_assert(sizeof(Packed<N>) > 0 && (uint64_t)kMostAddedUp * 65536u < ((uint64_t)1 << 32), "32 bits hold the sums");
     const uint32_t lane = threadIdx.x & 63u, wave = uniform(threadIdx.x >> 6);
     Place p;
-    if (scanned) p.base = wg[block];
+    if (scanned) p.base = static_cast<const Sums*>(wg)[block];
     const uint32_t upto = wave_inclusive_scan(mine);
     if (lane == 63u) lds.packed[wave] = upto;
     if (!scanned) {
         Sums32 part = {0, 0, 0};
-        for (uint32_t i = threadIdx.x; i < block; i += WAVES * 64) {
-            part.values += (uint32_t)wg[i].values;
-            part.index_bytes += (uint32_t)wg[i].index_bytes;
-            if (SPARSE_TILES) part.sparse_tiles += (uint32_t)wg[i].sparse_tiles;
-        }
+        const GroupSums* before = static_cast<const GroupSums*>(wg);
+        const auto add_up = [&](auto at_once) {
+            constexpr uint32_t kAtOnce = decltype(at_once)::value;
+            for (uint32_t i = threadIdx.x; i < block; i += kAtOnce * WAVES * 64) {
+                GroupSums g[kAtOnce];
+#pragma unroll
+                for (uint32_t k = 0; k < kAtOnce; ++k) {
+                    const uint32_t at = i + k * WAVES * 64;
+                    g[k] = GroupSums{0, 0};
+                    if (at < block) g[k] = before[at];
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < kAtOnce; ++k) {
+                    part.values += values_in(g[k].packed);
+                    part.index_bytes += index_bytes_in(g[k].packed);
+                    if (SPARSE_TILES) part.sparse_tiles += g[k].sparse_tiles;
+                }
+            }
+        };
+        if (block <= 2u * WAVES * 64) add_up(std::integral_constant<uint32_t, 1>());      // wave-uniform
+        else add_up(std::integral_constant<uint32_t, 8>());
         part.values = wave_inclusive_scan(part.values);
         part.index_bytes = wave_inclusive_scan(part.index_bytes);
         if (SPARSE_TILES) part.sparse_tiles = wave_inclusive_scan(part.sparse_tiles);
@@ -665,7 +687,8 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_count_kernel(const Ba
             all += of_wave[v];
             tiles += sparse_in_wave[v];
         }
-        job.wg[block] = Sums{values_in(all), index_bytes_in(all), tiles};
+        if (job.scanned) static_cast<Sums*>(job.wg)[block] = Sums{values_in(all), index_bytes_in(all), tiles};
+        else static_cast<GroupSums*>(job.wg)[block] = GroupSums{all, tiles};
     }
 }
 
@@ -693,7 +716,10 @@ __global__ __launch_bounds__(64 * kGroupsPerWorkgroup) void sparse_sums_kernel(c
         if (b < s.tiles) mine = mine + tile_sums(byte[j], tile_pos<N>(s, b), s.step.two_eps > 0.0f);
     }
     const Sums total = wave_total(wave_inclusive_scans(narrow(mine)));
-    if (lane == 0u) job.wg[group] = total;
+    if (lane == 0u) {
+        if (job.scanned) static_cast<Sums*>(job.wg)[group] = total;
+        else static_cast<GroupSums*>(job.wg)[group] = GroupSums{(uint32_t)total.values | (uint32_t)total.index_bytes << 16, (uint32_t)total.sparse_tiles};
+    }
 }
 
 // ---- pass 2: exclusive scan of the group sums, in place; totals -----------------------------------
@@ -712,7 +738,7 @@ __global__ __launch_bounds__(kScanThreads) void sparse_scan_kernel(const Batch<J
     static_assert(CELLS < 64, "one wave scans a round's (row, wave) totals");
     const Job& job = batch.item[blockIdx.x];
     if (!job.scanned) return;                                 // workgroup-uniform
-    Sums* wg_sums = job.wg;
+    Sums* wg_sums = static_cast<Sums*>(job.wg);
     const uint32_t count = job.wg_count, tiles = job.shape.tiles;
     __shared__ Sums32 cell_total[CELLS];                      // inclusive end of wave w's part of row j, at [j * WAVES + w]
     __shared__ Sums32 cell_before[CELLS + 1];                 // what precedes a cell in its round; [CELLS]: the whole round
@@ -783,7 +809,7 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_write_kernel(const Ba
     const Job& job = batch.item[batch_item(batch, blockIdx.x, block)];
     const MapShape& s = job.shape;
     const uint8_t* info = job.info;
-    const Sums* wg = job.wg;
+    const void* wg = job.wg;
     const bool scanned = job.scanned != 0u;
     uint64_t* totals = job.totals;
     const uint32_t b = block * T + threadIdx.x;
@@ -804,7 +830,7 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_write_kernel(const Ba
     const Sums& base = place.base;
     const uint32_t total_values = values_in(place.total), total_index_bytes = index_bytes_in(place.total);
     if (!scanned && block == job.wg_count - 1 && threadIdx.x == 0) {
-        const uint64_t sparse_tiles = base.sparse_tiles + wg[block].sparse_tiles;
+        const uint64_t sparse_tiles = base.sparse_tiles + static_cast<const GroupSums*>(wg)[block].sparse_tiles;
         totals[0] = base.values + total_values;
         totals[1] = base.index_bytes + total_index_bytes;
         totals[2] = sparse_tiles;
@@ -892,7 +918,7 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Bat
     const Job& job = batch.item[batch_item(batch, blockIdx.x, block)];
     const MapShape& s = job.shape;
     const uint8_t* info = job.info;
-    const Sums* wg = job.wg;
+    const void* wg = job.wg;
     const bool scanned = job.scanned != 0u;
     const uint64_t value_count = job.value_count, index_count = job.index_count;
     const uint32_t b = block * T + threadIdx.x;
@@ -1146,14 +1172,25 @@ struct Run {
 void add_job(Run& run, Job job, int64_t tiles, int n)
 {
     job.wg_count = workgroups(tiles, n);
-    job.scanned = (tiles == 0 || job.wg_count > kSelfScanLimit) ? 1u : 0u;   // an empty set: the scan kernel writes its totals
-    if (job.scanned) run.any_scan = true;
+    job.scanned = 0u;                                         // settled once the run is known (settle_scans)
     if (job.use.count) run.any_rows = true;
     if (tiles > 0) {
         push(run.tiled, job, job.wg_count);
         push(run.grouped, job, (job.wg_count + kGroupsPerWorkgroup - 1) / kGroupsPerWorkgroup);
     }
     push(run.all, job, 1);
+}
+
+// which sets of a run are scanned; an empty one is, since the scan kernel writes its totals
+void settle_scans(Run& run, int n)
+{
+    const uint32_t all = run.tiled.block_start[run.tiled.count];
+    for (Batch<Job>* b : {&run.tiled, &run.grouped, &run.all})
+        for (int k = 0; k < b->count; ++k) {
+            Job& job = b->item[k];
+            job.scanned = job.shape.tiles == 0 || sums_are_scanned(job.wg_count, all, n) ? 1u : 0u;
+            run.any_scan = run.any_scan || job.scanned;
+        }
 }
 
 fh_status encode_all(const fh_sparse_encode_item* items, const MapsInUse* use, int32_t count, hipStream_t s);
@@ -1218,7 +1255,7 @@ fh_status encode_all(const fh_sparse_encode_item* items, const MapsInUse* use, i
             Job job;
             job.shape = make_shape(it.x, it.h, it.w, it.n, tiles, it.eps);
             job.info = static_cast<uint8_t*>(it.info);
-            job.wg = static_cast<Sums*>(it.workspace);
+            job.wg = it.workspace;
             job.values = it.values;
             job.indices = static_cast<uint8_t*>(it.indices);
             job.totals = static_cast<uint64_t*>(it.totals);
@@ -1231,6 +1268,7 @@ fh_status encode_all(const fh_sparse_encode_item* items, const MapsInUse* use, i
             ++i;
         }
         launched = true;
+        settle_scans(run, n);
         seal(run.tiled);
         seal(run.grouped);
         seal(run.all);
@@ -1276,7 +1314,7 @@ fh_status decode_all(const fh_sparse_decode_item* items, const MapsInUse* use, b
             Job job;
             job.shape = make_shape(it.out, it.h, it.w, it.n, tiles, it.eps);
             job.info = const_cast<uint8_t*>(static_cast<const uint8_t*>(it.info));
-            job.wg = static_cast<Sums*>(it.workspace);
+            job.wg = it.workspace;
             job.values = const_cast<void*>(it.values);
             job.indices = const_cast<uint8_t*>(static_cast<const uint8_t*>(it.indices));
             job.value_count = it.values_bytes / elem_size(it.dtype);
@@ -1289,6 +1327,7 @@ fh_status decode_all(const fh_sparse_decode_item* items, const MapsInUse* use, b
         }
         if (run.tiled.count == 0) continue;                   // only empty sets in this run
         launched = true;
+        settle_scans(run, n);
         seal(run.tiled);
         seal(run.grouped);
         seal(run.all);

@@ -102,6 +102,16 @@ def test_more_groups_than_the_write_pass_adds_up_itself(api):
     _check(api, x, maps, h, w, n, 0.5, name="scan kernel")
 
 
+@pytest.mark.parametrize("groups", [2047, 2048, 2049, 4095, 4096, 4097])
+def test_groups_on_both_sides_of_the_scan(api, groups):
+    """Windows of 4: up to 4096 groups the write and read passes add the groups' sums up themselves."""
+    maps, h, w = 16 * groups, 16, 16                        # sixteen tiles to a map
+    if groups % 2:
+        maps -= 3                                           # a ragged last group
+    x = W.salient_feature_maps(maps, h, w, seed=groups)
+    _check(api, x, maps, h, w, 4, 0.5, name="scan or none", eps=0.02)
+
+
 def test_many_rows_of_the_scan_kernel(api):
     # a row of the scan kernel covers 512 groups; this set needs 17, the last one ragged
     maps, h, w, n = 700, 112, 112, 2                        # 2 195 200 tiles -> 8575 groups
