@@ -793,18 +793,9 @@ __device__ __forceinline__ void compress_tile(const CompressItem& it, uint32_t t
     }
 }
 
-template <typename InT, int G, bool RUNS>
-__global__ __launch_bounds__(kCBlock) void compress_kernel(const CompressBatch args)
+template <typename InT, int G>
+__device__ __forceinline__ void compress_any(const CompressItem& it, uint32_t tile, uint32_t* stage)
 {
-    const uint32_t bid = RUNS ? tile_in_run<128>(blockIdx.x, gridDim.x) : blockIdx.x;
-    int lo = 0, hi = args.count;                              // last item with tile_start <= bid
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (args.tile_start[mid] <= bid) lo = mid; else hi = mid;
-    }
-    const CompressItem& it = args.item[lo];
-    const uint32_t tile = bid - args.tile_start[lo];
-    __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kStageDwords];
     switch (it.bits * 2 + it.stochastic) {
         case 4:  compress_tile<InT, G, 2, false>(it, tile, stage); break;
         case 5:  compress_tile<InT, G, 2, true >(it, tile, stage); break;
@@ -815,6 +806,28 @@ __global__ __launch_bounds__(kCBlock) void compress_kernel(const CompressBatch a
         default: break;
     }
 }
+
+template <typename InT, int G, bool RUNS>
+__global__ __launch_bounds__(kCBlock) void compress_kernel(const CompressBatch args)
+{
+    const uint32_t bid = RUNS ? tile_in_run<128>(blockIdx.x, gridDim.x) : blockIdx.x;
+    int lo = 0, hi = args.count;                              // last item with tile_start <= bid
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (args.tile_start[mid] <= bid) lo = mid; else hi = mid;
+    }
+    __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kStageDwords];
+    compress_any<InT, G>(args.item[lo], bid - args.tile_start[lo], stage);
+}
+
+// One tensor by itself: its descriptor is all there is (kOneLaunchArgs).
+template <typename InT, int G>
+__global__ __launch_bounds__(kCBlock) void compress_one_kernel(const CompressItem it)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kStageDwords];
+    compress_any<InT, G>(it, blockIdx.x, stage);
+}
+static_assert(sizeof(CompressItem) <= kOneLaunchArgs, "the descriptor of one tensor is a short argument segment");
 
 // Tensors whose kept channels go to the raw store.  A wave's staging area also parks the span's
 // input while its kept elements are taken out (4 KiB: 2048 bf16 or 1024 fp32 elements).
@@ -964,6 +977,17 @@ hipError_t launch_compress(const CompressBatch& b, int dtype, int group_size, hi
         if (group_size == 64) FH_LAUNCH(float, 64, true);
         else if (group_size == 128) FH_LAUNCH(float, 128, true);
         else FH_LAUNCH(float, 256, true);
+    } else if (b.count == 1) {
+        const CompressItem& it = b.item[0];
+#define FH_LAUNCH_ONE(T) \
+    do { \
+        if (group_size == 64) hipLaunchKernelGGL((compress_one_kernel<T, 64>), grid, block, 0, s, it); \
+        else if (group_size == 128) hipLaunchKernelGGL((compress_one_kernel<T, 128>), grid, block, 0, s, it); \
+        else hipLaunchKernelGGL((compress_one_kernel<T, 256>), grid, block, 0, s, it); \
+    } while (0)
+        if (dtype == 0) FH_LAUNCH_ONE(float);
+        else FH_LAUNCH_ONE(uint16_t);
+#undef FH_LAUNCH_ONE
     } else if (dtype == 0) {
         if (group_size == 64) FH_LAUNCH(float, 64, false);
         else if (group_size == 128) FH_LAUNCH(float, 128, false);

@@ -333,6 +333,17 @@ __device__ __forceinline__ void decompress_tile(const DecompressItem& it, uint32
     }
 }
 
+template <typename OutT, int G>
+__device__ __forceinline__ void decompress_any(const DecompressItem& it, uint32_t tile)
+{
+    switch (it.bits) {
+        case 2: decompress_tile<OutT, G, 2>(it, tile); break;
+        case 4: decompress_tile<OutT, G, 4>(it, tile); break;
+        case 8: decompress_tile<OutT, G, 8>(it, tile); break;
+        default: break;
+    }
+}
+
 template <typename OutT, int G, bool RUNS>
 __global__ __launch_bounds__(kDBlock) void decompress_kernel(const DecompressBatch args)
 {
@@ -342,14 +353,17 @@ __global__ __launch_bounds__(kDBlock) void decompress_kernel(const DecompressBat
     const uint32_t bid = gridDim.x - 1u - (RUNS ? tile_in_run<64>(blockIdx.x, gridDim.x) : blockIdx.x);
     const int lo = find_item(args.tile_start, bid);
     const DecompressItem it = args.item[lo];                  // by value: one batch of scalar loads
-    const uint32_t tile = bid - args.tile_start[lo];
-    switch (it.bits) {
-        case 2: decompress_tile<OutT, G, 2>(it, tile); break;
-        case 4: decompress_tile<OutT, G, 4>(it, tile); break;
-        case 8: decompress_tile<OutT, G, 8>(it, tile); break;
-        default: break;
-    }
+    decompress_any<OutT, G>(it, bid - args.tile_start[lo]);
 }
+
+// One tensor by itself, its tiles from the end backwards too.  Their number is an argument: the launch's own grid
+// would be one of the hidden arguments, which make the segment long again (kOneLaunchArgs).
+template <typename OutT, int G>
+__global__ __launch_bounds__(kDBlock) void decompress_one_kernel(const DecompressItem it, const uint32_t tiles)
+{
+    decompress_any<OutT, G>(it, tiles - 1u - blockIdx.x);
+}
+static_assert(sizeof(DecompressItem) + sizeof(uint32_t) <= kOneLaunchArgs, "the descriptor of one tensor is a short argument segment");
 
 // Tensors whose kept channels come from the raw store.  LISTED: every one of the launch has its rows listed.  Restoring
 // bf16, the kernel then takes 54 vector registers and eight waves fit a SIMD; with the values of kept runs beside it, 74
@@ -365,15 +379,7 @@ __global__ __launch_bounds__(kDBlock) void decompress_mixed_kernel(const Batch<M
     const int raw_dtype = job.raw_dtype;
     __shared__ __attribute__((aligned(16))) uint8_t park[tile_elems<OutT>() * sizeof(OutT)];
     __shared__ uint16_t listed[kListRoom];
-    if (nothing_kept(cm)) {                                   // no channel of this tensor was kept: the plain code
-        switch (it.bits) {
-            case 2: decompress_tile<OutT, G, 2>(it, tile); break;
-            case 4: decompress_tile<OutT, G, 4>(it, tile); break;
-            case 8: decompress_tile<OutT, G, 8>(it, tile); break;
-            default: break;
-        }
-        return;
-    }
+    if (nothing_kept(cm)) return decompress_any<OutT, G>(it, tile);   // no channel of this tensor was kept: the plain code
     switch (it.bits) {
         case 2: decompress_tile<OutT, G, 2, true, LISTED>(it, tile, &cm, raw_dtype, listed, park); break;
         case 4: decompress_tile<OutT, G, 4, true, LISTED>(it, tile, &cm, raw_dtype, listed, park); break;
@@ -399,6 +405,17 @@ hipError_t launch_decompress(const DecompressBatch& b, int out_dtype, int group_
         if (group_size == 64) FH_LAUNCH(float, 64, true);
         else if (group_size == 128) FH_LAUNCH(float, 128, true);
         else FH_LAUNCH(float, 256, true);
+    } else if (b.count == 1) {
+        const DecompressItem& it = b.item[0];
+#define FH_LAUNCH_ONE(T) \
+    do { \
+        if (group_size == 64) hipLaunchKernelGGL((decompress_one_kernel<T, 64>), grid, block, 0, s, it, tiles); \
+        else if (group_size == 128) hipLaunchKernelGGL((decompress_one_kernel<T, 128>), grid, block, 0, s, it, tiles); \
+        else hipLaunchKernelGGL((decompress_one_kernel<T, 256>), grid, block, 0, s, it, tiles); \
+    } while (0)
+        if (out_dtype == 0) FH_LAUNCH_ONE(float);
+        else FH_LAUNCH_ONE(uint16_t);
+#undef FH_LAUNCH_ONE
     } else if (out_dtype == 0) {
         if (group_size == 64) FH_LAUNCH(float, 64, false);
         else if (group_size == 128) FH_LAUNCH(float, 128, false);

@@ -77,6 +77,15 @@ def test_no_kernel_needs_scratch_memory(code_objects):
         assert r["vgpr_spill_count"] == 0 and r["private_segment_fixed_size"] == 0, f"{name}: {r}"
 
 
+def test_launches_of_one_tensor_have_short_arguments(code_objects):
+    """Up to 112 bytes of arguments a launch is enqueued a microsecond sooner; a hidden argument (the grid's size, for
+    one) would make the segment some 300 bytes long."""
+    kernels = {name: r for name, r in _resources(code_objects).items() if "_one_kernel" in name}
+    assert len(kernels) == 12
+    for name, r in kernels.items():
+        assert r["kernarg_segment_size"] <= 112, f"{name}: {r['kernarg_segment_size']}"
+
+
 def test_the_rows_of_a_wave_are_requested_together(code_objects):
     """The classification's first pass: a wave's whole rows are read by non-temporal 16-byte loads with no wait for
     one of them before the last is on its way (a test around each row's load makes the compiler wait for the first, which
