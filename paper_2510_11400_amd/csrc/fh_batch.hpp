@@ -7,12 +7,14 @@
 #include <limits.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace fh {
 
 // Tensors per launch: as many as the largest descriptor (the routed quantiser's, 152 bytes) lets into 4 KiB of kernel
-// arguments (fh_kernels.hpp holds it to that).  A stage's serial kernels (the Huffman tables and codes, the finishing
-// kernels) take as long for a full launch as for one tensor: the whole chain on 24 activations takes 871 us in one launch
-// per stage, 1047 in launches of 16.  Launches of one tensor pay for the longer argument segment with some 0.1 us each.
+// arguments (fh_kernels.hpp holds it to that).  A stage's serial kernels (the Huffman tables and codes) take as long
+// for a full launch as for one tensor: the whole chain on 24 activations takes 871 us in one launch per stage, 1047 in
+// launches of 16.
 constexpr int kBatch = 26;
 constexpr int kBatchStated = 16;                   // what the *_batch_capacity() calls promise
 
@@ -51,5 +53,31 @@ template <typename Item> inline void seal(Batch<Item>& b)
     for (int k = b.count + 1; k <= kBatch; ++k) b.block_start[k] = b.block_start[b.count];
 }
 template <typename Item> inline void reset(Batch<Item>& b) { b.count = 0; b.block_start[0] = 0; }
+
+// A launch of one tensor carries its descriptor alone.  Up to 112 bytes of arguments a launch is enqueued in 2.8 us, with 120 in 3.7,
+// with 1000 to 4000 in 4.1 to 4.3 (launches of an empty kernel in a row); hidden arguments, the grid's size for one, count.  One tensor
+// of 1 MiB, quantised and restored: 18.4 us with the batch's arguments, 16.8 with these.  (Launches with tiles in runs take 40 us and
+// more: they keep the batch's.)  Classification of one tensor of 1.6 MB 15.5 -> 14.7 us, of 26 MB 19.3 -> 17.9; the whole chain on them
+// 93.5 -> 90.3 and 119.7 -> 116.7.  The descriptors of the routed quantiser and of the sparse stage are longer: these keep the batch's.
+constexpr size_t kOneLaunchArgs = 112;
+template <typename Item> struct One {
+    Item item;
+};
+// the descriptor of workgroup `bid`, and the workgroup's number inside that tensor
+template <typename Item>
+__device__ __forceinline__ const Item& item_of(const Batch<Item>& b, uint32_t bid, uint32_t& local) { return b.item[batch_item(b, bid, local)]; }
+template <typename Item>
+__device__ __forceinline__ const Item& item_of(const One<Item>& b, uint32_t bid, uint32_t& local) { local = bid; return b.item; }
+// the same where every tensor has one workgroup
+template <typename Item> __device__ __forceinline__ const Item& item_of(const Batch<Item>& b, uint32_t bid) { return b.item[bid]; }
+template <typename Item> __device__ __forceinline__ const Item& item_of(const One<Item>& b, uint32_t) { return b.item; }
+// host side: `launch` with the arguments that the launch needs
+template <typename Item, typename Launch> inline void with_arguments(const Batch<Item>& b, const Launch& launch)
+{
+    static_assert(sizeof(One<Item>) <= kOneLaunchArgs, "the descriptor of one tensor is a short argument segment");
+    if (b.count == 1) launch(One<Item>{b.item[0]});
+    else launch(b);
+}
+#define FH_ARGS std::decay_t<decltype(args)>
 
 }  // namespace fh

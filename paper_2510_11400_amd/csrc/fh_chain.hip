@@ -63,10 +63,11 @@ __device__ __forceinline__ void clear_bytes(uint8_t* p, uint64_t bytes, uint32_t
 // header cleared.  All workgroups of the item: the raw store's rows that no
 // channel uses cleared.  (The rows in use are written whole by the quantiser: with 4 % of the channels salient and room
 // for a sixteenth, clearing them as well wrote 36 MB instead of 13 MB for the MobileNetV2-style set, 13 us against 8.6.)
-__global__ __launch_bounds__(kPrepThreads) void chain_prepare_kernel(const Batch<PrepItem> batch)
+template <typename Args>
+__global__ __launch_bounds__(kPrepThreads) void chain_prepare_kernel(const Args batch)
 {
     uint32_t block;
-    const PrepItem& it = batch.item[batch_item(batch, blockIdx.x, block)];
+    const PrepItem& it = item_of(batch, blockIdx.x, block);
     __shared__ uint32_t of_wave[kPrepThreads / 64];
     const int t = threadIdx.x;
     const uint32_t wave_here = (uint32_t)__builtin_amdgcn_readfirstlane(t >> 6);
@@ -332,7 +333,8 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
             push(b, p, p.blocks);
         }
         seal(b);
-        hipLaunchKernelGGL(chain_prepare_kernel, dim3(b.block_start[b.count]), dim3(kPrepThreads), 0, s, b);
+        const dim3 grid(b.block_start[b.count]);
+        with_arguments(b, [&](const auto& args) { hipLaunchKernelGGL((chain_prepare_kernel<FH_ARGS>), grid, dim3(kPrepThreads), 0, s, args); });
     }
 
     // 3. normal channels quantised, salient channels to the raw store

@@ -89,11 +89,9 @@ __device__ __forceinline__ uint32_t tile_of_block()
     return blockIdx.x < each * kXcds ? (blockIdx.x % kXcds) * each + blockIdx.x / kXcds : blockIdx.x;
 }
 template <typename InT, bool LARGE>
-__global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsItem> args)
+__device__ __forceinline__ void moments_of(const MomentsItem& it, const uint32_t block)
 {
     constexpr int SPANS = LARGE ? 4 / Span<InT>::ROWS : 1, ROWS = SPANS * Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
-    uint32_t block;
-    const MomentsItem& it = args.item[batch_item(args, LARGE ? tile_of_block() : blockIdx.x, block)];
     const InT* x = static_cast<const InT*>(it.x);
     const int64_t numel = it.numel;
     const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -135,12 +133,26 @@ __global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsIt
                          (numel - base + kSpan - 1) / kSpan, lane);
 }
 
+template <typename InT, bool LARGE>
+__global__ __launch_bounds__(kThreads) void moments_kernel(const Batch<MomentsItem> args)
+{
+    uint32_t block;
+    const MomentsItem& it = args.item[batch_item(args, LARGE ? tile_of_block() : blockIdx.x, block)];
+    moments_of<InT, LARGE>(it, block);
+}
+template <typename InT>
+__global__ __launch_bounds__(kThreads) void moments_one_kernel(const MomentsItem it)
+{
+    moments_of<InT, false>(it, blockIdx.x);
+}
+
 // ---- pass 1b: spans of partial sums (4 rows of 256 pairs, 4 consecutive pairs per lane) --
-__global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const Batch<ReduceItem> args)
+template <typename Args>
+__global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const Args args)
 {
     constexpr int ROWS = 4, EPL = 4, ROW = kWave * EPL;
     uint32_t block;
-    const ReduceItem& it = args.item[batch_item(args, blockIdx.x, block)];
+    const ReduceItem& it = item_of(args, blockIdx.x, block);
     const f64x2* in = it.in;
     const int64_t count = it.count;
     f64x2* out = it.out;
@@ -273,14 +285,14 @@ __device__ __forceinline__ double uniform(double v)            // the same in al
 
 // AHEAD: a launch in which some wave walks more than one span.
 constexpr int kAhead = 3;                         // spans requested before the one that is looked at
-template <typename InT, bool AHEAD>
-__global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Batch<CountArgs> batch)
+template <typename InT, bool AHEAD, typename Args>
+__global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Args batch)
 {
     constexpr int ROWS = Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
     extern __shared__ uint32_t hist[];
     __shared__ Limits limits;
     uint32_t block;
-    const CountArgs& args = batch.item[batch_item(batch, blockIdx.x, block)];
+    const CountArgs& args = item_of(batch, blockIdx.x, block);
     const uint32_t C = args.channels.d;
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -399,15 +411,15 @@ __global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Batch<Co
 // waves as the rules of fh_rules.hpp give the launch: 23 us for 100 MB of fp32 with 3072 channels, the kernel above 25.
 constexpr int kLook = 8;                          // spans whose ranges a wave looks at together: 64 pieces
 constexpr int kRounds = 2;                        // rounds of eight pieces requested together
-template <typename InT, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Batch<CountArgs> batch)
+template <typename InT, int WAVES, typename Args>
+__global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Args batch)
 {
     constexpr int kThreads = WAVES * kWave;
     constexpr int ROWS = Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
     extern __shared__ uint32_t hist[];
     __shared__ Limits limits;
     uint32_t block;
-    const CountArgs& args = batch.item[batch_item(batch, blockIdx.x, block)];
+    const CountArgs& args = item_of(batch, blockIdx.x, block);
     const uint32_t C = args.channels.d;
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -490,10 +502,11 @@ __global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Batch
     add_outliers<kThreads>(args, hist);
 }
 
-__global__ __launch_bounds__(kThreads) void mask_kernel(const Batch<MaskItem> args)
+template <typename Args>
+__global__ __launch_bounds__(kThreads) void mask_kernel(const Args args)
 {
     uint32_t block;
-    const MaskItem& it = args.item[batch_item(args, blockIdx.x, block)];
+    const MaskItem& it = item_of(args, blockIdx.x, block);
     const int c = block * kThreads + threadIdx.x;
     if (c < it.channels) it.mask[c] = (int64_t)it.counts[c] >= it.min_outliers ? 1 : 0;
 }
@@ -607,7 +620,11 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
     if (mb.count > 0) {
         seal(mb);
         const dim3 grid(mb.block_start[mb.count]);
-        if (dtype == FH_F32) {
+        if (mb.count == 1 && !large) {                        // (a large launch needs its grid's size)
+            static_assert(sizeof(MomentsItem) <= kOneLaunchArgs, "the descriptor of one tensor is a short argument segment");
+            if (dtype == FH_F32) hipLaunchKernelGGL((moments_one_kernel<float>), grid, block, 0, s, mb.item[0]);
+            else hipLaunchKernelGGL((moments_one_kernel<uint16_t>), grid, block, 0, s, mb.item[0]);
+        } else if (dtype == FH_F32) {
             if (large) hipLaunchKernelGGL((moments_kernel<float, true>), grid, block, 0, s, mb);
             else hipLaunchKernelGGL((moments_kernel<float, false>), grid, block, 0, s, mb);
         } else {
@@ -628,7 +645,8 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
         }
         if (rb.count == 0) break;
         seal(rb);
-        hipLaunchKernelGGL(reduce_partials_kernel, dim3(rb.block_start[rb.count]), block, 0, s, rb);
+        const dim3 grid(rb.block_start[rb.count]);
+        with_arguments(rb, [&](const auto& args) { hipLaunchKernelGGL((reduce_partials_kernel<FH_ARGS>), grid, block, 0, s, args); });
     }
     EmptyBatch eb;
     int empty = 0;
@@ -682,23 +700,26 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
         const dim3 grid(cb.block_start[cb.count]);
         bool ahead = false;
         for (int k = 0; k < cb.count; ++k) ahead = ahead || cb.item[k].spans_per_wave > 1;
-        if (marked) {
-            const dim3 threads(waves * kWave);
-            if (dtype == FH_F32) {
-                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<float, 4>), grid, threads, lds, s, cb);
-                else hipLaunchKernelGGL((count_marked_kernel<float, 8>), grid, threads, lds, s, cb);
+        const dim3 threads(marked ? waves * kWave : kThreads);
+        with_arguments(cb, [&](const auto& args) {
+            if (marked && dtype == FH_F32) {
+                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<float, 4, FH_ARGS>), grid, threads, lds, s, args);
+                else hipLaunchKernelGGL((count_marked_kernel<float, 8, FH_ARGS>), grid, threads, lds, s, args);
+            } else if (marked) {
+                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<uint16_t, 4, FH_ARGS>), grid, threads, lds, s, args);
+                else hipLaunchKernelGGL((count_marked_kernel<uint16_t, 8, FH_ARGS>), grid, threads, lds, s, args);
+            } else if (dtype == FH_F32) {
+                if (ahead) hipLaunchKernelGGL((count_outliers_kernel<float, true, FH_ARGS>), grid, threads, lds, s, args);
+                else hipLaunchKernelGGL((count_outliers_kernel<float, false, FH_ARGS>), grid, threads, lds, s, args);
             } else {
-                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<uint16_t, 4>), grid, threads, lds, s, cb);
-                else hipLaunchKernelGGL((count_marked_kernel<uint16_t, 8>), grid, threads, lds, s, cb);
+                if (ahead) hipLaunchKernelGGL((count_outliers_kernel<uint16_t, true, FH_ARGS>), grid, threads, lds, s, args);
+                else hipLaunchKernelGGL((count_outliers_kernel<uint16_t, false, FH_ARGS>), grid, threads, lds, s, args);
             }
-        } else if (dtype == FH_F32) {
-            if (ahead) hipLaunchKernelGGL((count_outliers_kernel<float, true>), grid, block, lds, s, cb);
-            else hipLaunchKernelGGL((count_outliers_kernel<float, false>), grid, block, lds, s, cb);
-        } else {
-            if (ahead) hipLaunchKernelGGL((count_outliers_kernel<uint16_t, true>), grid, block, lds, s, cb);
-            else hipLaunchKernelGGL((count_outliers_kernel<uint16_t, false>), grid, block, lds, s, cb);
+        });
+        if (kb.count > 0) {
+            const dim3 of_masks(kb.block_start[kb.count]);
+            with_arguments(kb, [&](const auto& args) { hipLaunchKernelGGL((mask_kernel<FH_ARGS>), of_masks, block, 0, s, args); });
         }
-        if (kb.count > 0) hipLaunchKernelGGL(mask_kernel, dim3(kb.block_start[kb.count]), block, 0, s, kb);
     }
     return hipGetLastError() == hipSuccess ? FH_OK : FH_ERR_LAUNCH;
 }

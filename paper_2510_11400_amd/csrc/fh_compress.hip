@@ -875,12 +875,12 @@ __global__ __launch_bounds__(kCBlock) void compress_mixed_kernel(const Batch<Mix
 // The plain quantiser and the classification's first pass over the same elements: one read of the tensor where two
 // kernels would make two.  The reads bound it: the 557 MiB set (fp32, G128, 4-bit nearest) takes 112 us, the quantiser
 // alone 105 and the first pass alone 87; some 400 vector instructions per span hide behind 4 KiB read and 0.7 KiB written.
-template <typename InT, int G>
-__global__ __launch_bounds__(kCBlock) void compress_first_kernel(const Batch<FirstCompressJob> batch)
+template <typename InT, int G, typename Args>
+__global__ __launch_bounds__(kCBlock) void compress_first_kernel(const Args batch)
 {
     __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kStageDwords];
     uint32_t tile;
-    const FirstCompressJob& job = batch.item[batch_item(batch, blockIdx.x, tile)];
+    const FirstCompressJob& job = item_of(batch, blockIdx.x, tile);
     const CompressItem& it = job.it;
     if (tile == 0) clear_counters<kCBlock>(job.cleared);      // workgroup-uniform
     switch (it.bits * 2 + it.stochastic) {
@@ -1006,7 +1006,7 @@ hipError_t launch_compress_first(const Batch<FirstCompressJob>& b, int dtype, in
     const uint32_t tiles = b.block_start[b.count];
     if (tiles == 0) return hipSuccess;
     const dim3 grid(tiles), block(kCBlock);
-#define FH_LAUNCH(T, GS) hipLaunchKernelGGL((compress_first_kernel<T, GS>), grid, block, 0, s, b)
+#define FH_LAUNCH(T, GS) with_arguments(b, [&](const auto& args) { hipLaunchKernelGGL((compress_first_kernel<T, GS, FH_ARGS>), grid, block, 0, s, args); })
     if (dtype == 0) {
         if (group_size == 64) FH_LAUNCH(float, 64);
         else if (group_size == 128) FH_LAUNCH(float, 128);

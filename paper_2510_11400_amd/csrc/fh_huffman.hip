@@ -72,6 +72,17 @@ constexpr int kRounds = kGroup / kWaves / 4;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+struct Stream {                                    // what a launch is told of a stream
+    uint8_t*  out;                                 // 256 lengths, chunks + 1 offsets, payload
+    uint32_t* scratch;                             // the workspace: histogram, codes, group sums
+    uint64_t* totals;                              // {stream bytes used, payload bits}
+    const uint8_t* in;
+    uint64_t  n;                                   // symbols (an upper bound when n_dev is set)
+    const uint64_t* n_dev;                         // device: the symbol count, known only on the stream; or null
+    StoredForm stored;                             // header: null outside the whole chain
+    uint32_t  chunks, groups;
+    uint32_t  hist_blocks;                         // workgroups of the histogram pass
+};
 struct Layout {                                    // where things are in the stream and in the workspace
     uint8_t*  len;                                 // [256]
     uint32_t* offsets;                             // [chunks + 1]
@@ -79,13 +90,11 @@ struct Layout {                                    // where things are in the st
     uint32_t* hist;                                // workspace: [256]
     uint32_t* table;                               // workspace: [256], the code from the top bit down | its length
     uint32_t* group_sums;                          // workspace: [groups]
-    uint64_t* totals;                              // {stream bytes used, payload bits}
+    uint64_t* totals;
     const uint8_t* in;
-    uint64_t  n;                                   // symbols (an upper bound when n_dev is set)
-    const uint64_t* n_dev;                         // device: the symbol count, known only on the stream; or null
-    uint32_t  chunks, groups;
-    uint32_t  hist_blocks;                         // workgroups of the histogram pass
-    StoredForm stored;                             // header: null outside the whole chain
+    uint64_t  n;
+    uint32_t  chunks, groups, hist_blocks;
+    StoredForm stored;
 };
 
 __device__ __forceinline__ uint64_t chunks_for(uint64_t n) { return (n + 255u) >> 8; }
@@ -104,17 +113,29 @@ __host__ __device__ __forceinline__ uint32_t hist_blocks_for(uint64_t n)
 // output of an earlier call on the same stream), the host has sized buffers and grids for an
 // upper bound; the count itself, and what follows from it -- chunks, groups, where the payload
 // starts -- is settled here, and workgroups beyond the real extent find nothing to do.
-__device__ __forceinline__ Layout resolved(const Layout& given)
+__device__ __forceinline__ Layout resolved(const Stream& given)
 {
-    Layout lay = given;
+    Layout lay;
+    lay.totals = given.totals;
+    lay.in = given.in;
+    lay.stored = given.stored;
+    lay.n = given.n;
+    lay.chunks = given.chunks;
+    lay.groups = given.groups;
+    lay.hist_blocks = given.hist_blocks;
     if (given.n_dev) {
         const uint64_t there = *given.n_dev;
         lay.n = there < given.n ? there : given.n;
         lay.chunks = (uint32_t)chunks_for(lay.n);
         lay.groups = (lay.chunks + 255u) >> 8;
-        lay.payload = lay.offsets + lay.chunks + 1;
         lay.hist_blocks = hist_blocks_for(lay.n);
     }
+    lay.len = given.out;
+    lay.offsets = reinterpret_cast<uint32_t*>(given.out + 256);
+    lay.payload = lay.offsets + lay.chunks + 1;
+    lay.hist = given.scratch;
+    lay.table = lay.hist + 256;
+    lay.group_sums = lay.table + 256;
     return lay;
 }
 // Where several histogram workgroups leave their 256 counts each, 16-byte aligned: in the payload's place, which is written after
@@ -142,10 +163,11 @@ struct DecodeJob {
 // A workgroup clears and adds up 32 KiB of counters whatever it counts, so it has the most threads there are: at 51 MB in five
 // streams 29 us with 256 threads (1340 workgroups), 18 us with 1024.  The code kernel adds up what the workgroups leave: with
 // counters that they all add to, these had to be cleared by a launch before this one (encode and decode of 51 MB 125.4 us, 122.4 now).
-__global__ __launch_bounds__(kHistThreads) void huffman_histogram_kernel(const Batch<Layout> batch)
+template <typename Args>
+__global__ __launch_bounds__(kHistThreads) void huffman_histogram_kernel(const Args batch)
 {
     uint32_t block;
-    const Layout lay = resolved(batch.item[batch_item(batch, blockIdx.x, block)]);
+    const Layout lay = resolved(item_of(batch, blockIdx.x, block));
     if (block >= lay.hist_blocks) return;                     // workgroup-uniform: past the real extent
     const uint8_t* in = lay.in;
     const uint64_t n = lay.n;
@@ -281,9 +303,10 @@ __device__ __forceinline__ uint64_t lanes_alike(uint32_t length)
 // clustered symbols: 19.1 us with the merges one by one, 16.2 now, of 250 symbols alike 57 and 15.3 (22 and 20 with the
 // 64 counts of a quarter in registers at once: 88 bytes of scratch per lane).
 constexpr int kCodeThreads = 1024;
-__global__ __launch_bounds__(kCodeThreads) void huffman_code_kernel(const Batch<Layout> batch)
+template <typename Args>
+__global__ __launch_bounds__(kCodeThreads) void huffman_code_kernel(const Args batch)
 {
-    const Layout lay = resolved(batch.item[blockIdx.x]);
+    const Layout lay = resolved(item_of(batch, blockIdx.x));
     // counts and weights are sums of at most 2^32 - 1 symbols: 32 bits hold them
     __shared__ __align__(16) uint32_t count[256];             // this round's counts, by symbol
     __shared__ uint32_t rank_of[256];
@@ -509,10 +532,11 @@ __device__ __forceinline__ uint32_t sum_to_lane_15_of_row(uint32_t v)
     return v;                                                 // inclusive prefix inside the row
 }
 
-__global__ __launch_bounds__(kGroupThreads) void huffman_count_kernel(const Batch<Layout> batch)
+template <typename Args>
+__global__ __launch_bounds__(kGroupThreads) void huffman_count_kernel(const Args batch)
 {
     uint32_t group;
-    const Layout lay = resolved(batch.item[batch_item(batch, blockIdx.x, group)]);
+    const Layout lay = resolved(item_of(batch, blockIdx.x, group));
     if (group >= lay.groups) return;                          // workgroup-uniform: past the real extent
     __shared__ uint8_t len[256];
     __shared__ uint32_t lds[kWaves];
@@ -575,9 +599,10 @@ __device__ __forceinline__ void leave_size(const Layout& lay, uint32_t words)
     const StoredForm& f = lay.stored;
     if (f.header) f.header[6] = f.fixed_bytes + f.header[0] * f.value_size + bytes;
 }
-__global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Batch<Layout> batch)
+template <typename Args>
+__global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Args batch)
 {
-    const Layout lay = resolved(batch.item[blockIdx.x]);
+    const Layout lay = resolved(item_of(batch, blockIdx.x));
     __shared__ uint32_t lds[4];
     uint32_t carry = 0;
     for (uint32_t base = 0; base < lay.groups; base += kThreads) {         // workgroup-uniform trip count
@@ -604,11 +629,11 @@ __global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Batch<Layo
 constexpr int kRoundWordsMax = 4 * kChunkWordsMax;          // 768 words per wave
 constexpr uint32_t kCodeMask = ~(uint32_t)0xffu;            // of an entry of the table: codes have 24 bits at most
 
-template <bool SCANNED>
-__global__ __launch_bounds__(kGroupThreads) void huffman_write_kernel(const Batch<Layout> batch)
+template <bool SCANNED, typename Args>
+__global__ __launch_bounds__(kGroupThreads) void huffman_write_kernel(const Args batch)
 {
     uint32_t group;
-    const Layout lay = resolved(batch.item[batch_item(batch, blockIdx.x, group)]);
+    const Layout lay = resolved(item_of(batch, blockIdx.x, group));
     if (group >= lay.groups) {                                // workgroup-uniform: past the real extent
         if (!SCANNED && lay.groups == 0u && group == 0u && threadIdx.x == 0) leave_size(lay, 0u);
         return;
@@ -960,12 +985,12 @@ __device__ __forceinline__ void decode_chunk_staged(uint32_t valid, uint8_t* dst
 // The stream may be foreign: the tables are built from whatever the 256 length bytes say
 // (lengths above 24 count as unused), reads of payload words are bounded by the stream's size
 // (words outside read as zero), and every loop is bounded by the symbol count.
-template <int kDecodeThreads, bool LINES>
-__global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Batch<DecodeJob> batch)
+template <int kDecodeThreads, bool LINES, typename Args>
+__global__ __launch_bounds__(kDecodeThreads) void huffman_decode_kernel(const Args batch)
 {
     constexpr int kStageWords = StageWords<kDecodeThreads>::kAll;
     uint32_t block;
-    const DecodeJob& job = batch.item[batch_item(batch, blockIdx.x, block)];
+    const DecodeJob& job = item_of(batch, blockIdx.x, block);
     const uint8_t* len_in = job.len;
     const uint32_t* offsets = job.offsets;
     const uint32_t* payload = job.payload;
@@ -1260,31 +1285,20 @@ fh_status check_decode(const fh_huffman_decode_item& it)
     return FH_OK;
 }
 
-template <typename Kernel, typename Item>
-void launch(Kernel kernel, const Batch<Item>& b, uint32_t grid, hipStream_t s, int threads = kThreads)
-{
-    if (grid > 0) hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, b);
-}
-
-
 // The encoder's launches; `stored` null: there is no header to write to.
 fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stored, int32_t count, hipStream_t s)
 {
     for (int32_t i = 0; i < count;) {
         // the same streams three times: a workgroup each | by histogram workgroups | by groups of chunks
-        Batch<Layout> each, hist, grouped;
+        Batch<Stream> each, hist, grouped;
         reset(each); reset(hist); reset(grouped);
         while (i < count && each.count < kBatch) {
             const fh_huffman_encode_item& it = items[i];
-            Layout lay;
+            Stream lay;
             lay.chunks = (uint32_t)chunks_of(it.n);
             lay.groups = (uint32_t)groups_of(it.n);
-            lay.len = static_cast<uint8_t*>(it.stream_out);
-            lay.offsets = reinterpret_cast<uint32_t*>(lay.len + 256);
-            lay.payload = lay.offsets + lay.chunks + 1;
-            lay.hist = static_cast<uint32_t*>(it.workspace);
-            lay.table = lay.hist + 256;
-            lay.group_sums = lay.table + 256;
+            lay.out = static_cast<uint8_t*>(it.stream_out);
+            lay.scratch = static_cast<uint32_t*>(it.workspace);
             lay.totals = static_cast<uint64_t*>(it.totals);
             lay.in = static_cast<const uint8_t*>(it.bytes);
             lay.n = it.n;
@@ -1301,15 +1315,18 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
             ++i;
         }
         seal(each); seal(hist); seal(grouped);
-        launch(huffman_histogram_kernel, hist, hist.block_start[hist.count], s, kHistThreads);
-        launch(huffman_code_kernel, each, (uint32_t)each.count, s, kCodeThreads);
-        const uint32_t all = grouped.block_start[grouped.count];
-        launch(huffman_count_kernel, grouped, all, s, kGroupThreads);
-        if (group_sums_are_scanned(all)) {
-            launch(huffman_scan_kernel, each, (uint32_t)each.count, s);
-            launch(huffman_write_kernel<true>, grouped, all, s, kGroupThreads);
-        } else {
-            launch(huffman_write_kernel<false>, grouped, all, s, kGroupThreads);
+        const dim3 streams((uint32_t)each.count), of_hist(hist.block_start[hist.count]), groups(grouped.block_start[grouped.count]);
+        const bool scanned = group_sums_are_scanned(groups.x);
+        if (of_hist.x > 0)
+            with_arguments(hist, [&](const auto& args) { hipLaunchKernelGGL((huffman_histogram_kernel<FH_ARGS>), of_hist, dim3(kHistThreads), 0, s, args); });
+        with_arguments(each, [&](const auto& args) { hipLaunchKernelGGL((huffman_code_kernel<FH_ARGS>), streams, dim3(kCodeThreads), 0, s, args); });
+        with_arguments(grouped, [&](const auto& args) {
+            hipLaunchKernelGGL((huffman_count_kernel<FH_ARGS>), groups, dim3(kGroupThreads), 0, s, args);
+            if (!scanned) hipLaunchKernelGGL((huffman_write_kernel<false, FH_ARGS>), groups, dim3(kGroupThreads), 0, s, args);
+        });
+        if (scanned) {
+            with_arguments(each, [&](const auto& args) { hipLaunchKernelGGL((huffman_scan_kernel<FH_ARGS>), streams, dim3(kThreads), 0, s, args); });
+            with_arguments(grouped, [&](const auto& args) { hipLaunchKernelGGL((huffman_write_kernel<true, FH_ARGS>), groups, dim3(kGroupThreads), 0, s, args); });
         }
     }
     if (count == 0) return FH_OK;
@@ -1399,15 +1416,12 @@ fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t c
         }
         seal(b);
         if (b.count > 0) {
-            if (small)
-                hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreadsSmall, false>), dim3(b.block_start[b.count]),
-                                   dim3(kDecodeThreadsSmall), 0, s, b);
-            else if (decode_in_whole_lines(symbols))
-                hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, true>), dim3(b.block_start[b.count]),
-                                   dim3(kDecodeThreads), 0, s, b);
-            else
-                hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, false>), dim3(b.block_start[b.count]),
-                                   dim3(kDecodeThreads), 0, s, b);
+            const dim3 grid(b.block_start[b.count]);
+            with_arguments(b, [&](const auto& args) {
+                if (small) hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreadsSmall, false, FH_ARGS>), grid, dim3(kDecodeThreadsSmall), 0, s, args);
+                else if (decode_in_whole_lines(symbols)) hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, true, FH_ARGS>), grid, dim3(kDecodeThreads), 0, s, args);
+                else hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, false, FH_ARGS>), grid, dim3(kDecodeThreads), 0, s, args);
+            });
             launched = true;
         }
     }

@@ -48,11 +48,6 @@ struct DecompressBatch {
     DecompressItem item[kMaxItems];
 };
 
-// A launch of one tensor has a kernel of its own that takes just the descriptor: up to 112 bytes of arguments a launch is enqueued in
-// 2.8 us, with 120 in 3.7, with 1000 to 4000 in 4.1 to 4.3 (launches of an empty kernel in a row).  One tensor of 1 MiB, quantised and
-// restored: 18.4 us with the batch's arguments, 16.8 with these.  (Launches with tiles in runs take 40 us and more: they keep the batch's.)
-constexpr size_t kOneLaunchArgs = 112;
-
 static_assert(sizeof(CompressBatch) <= 4096, "kernel arguments must fit the 4 KiB segment");
 static_assert(sizeof(DecompressBatch) <= 4096, "kernel arguments must fit the 4 KiB segment");
 
