@@ -58,7 +58,7 @@ template <typename Item> inline void reset(Batch<Item>& b) { b.count = 0; b.bloc
 // with 1000 to 4000 in 4.1 to 4.3 (launches of an empty kernel in a row); hidden arguments, the grid's size for one, count.  One tensor
 // of 1 MiB, quantised and restored: 18.4 us with the batch's arguments, 16.8 with these.  (Launches with tiles in runs take 40 us and
 // more: they keep the batch's.)  Classification of one tensor of 1.6 MB 15.5 -> 14.7 us, of 26 MB 19.3 -> 17.9; the whole chain on them
-// 93.5 -> 90.3 and 119.7 -> 116.7.  The descriptors of the routed quantiser and of the sparse stage are longer: these keep the batch's.
+// 93.5 -> 90.3 and 119.7 -> 116.7.  The routed quantiser's descriptor is shortened (fh_kernels.hpp); the sparse stage's is longer and keeps the batch's.
 constexpr size_t kOneLaunchArgs = 112;
 template <typename Item> struct One {
     Item item;

@@ -67,6 +67,36 @@ struct ChannelMap {
     SmallDiv       inner, channels, raw_div;   // raw_div: by raw_channels (1 when there are none)
 };
 
+// The same in 64 bytes, for the descriptor of a launch of one tensor (fh_batch.hpp, kOneLaunchArgs): nothing twice, shifts a byte each.
+struct ShortMap {
+    const int16_t* slots;
+    void*          raw;
+    const uint64_t* rows_in_use;
+    uint32_t       raw_channels, inner, channels;
+    uint32_t       inner_m, channels_m, inner_magic, channels_magic, raw_magic;
+    uint8_t        inner_sh1, inner_sh2, channels_sh1, channels_sh2;
+};
+inline ShortMap shortened(const ChannelMap& cm)
+{
+    return ShortMap{cm.slots, cm.raw, cm.rows_in_use, cm.raw_channels, cm.inner.d, cm.channels.d, cm.inner_exact.m, cm.channels_exact.m,
+                    cm.inner.magic, cm.channels.magic, cm.raw_div.magic, (uint8_t)cm.inner_exact.sh1, (uint8_t)cm.inner_exact.sh2,
+                    (uint8_t)cm.channels_exact.sh1, (uint8_t)cm.channels_exact.sh2};
+}
+__host__ __device__ __forceinline__ ChannelMap whole(const ShortMap& m)
+{
+    ChannelMap cm;
+    cm.slots = m.slots;
+    cm.raw = m.raw;
+    cm.raw_channels = m.raw_channels;
+    cm.rows_in_use = m.rows_in_use;
+    cm.inner_exact = ExactDiv{m.inner, m.inner_m, m.inner_sh1, m.inner_sh2};
+    cm.channels_exact = ExactDiv{m.channels, m.channels_m, m.channels_sh1, m.channels_sh2};
+    cm.inner = SmallDiv{m.inner, m.inner_magic};
+    cm.channels = SmallDiv{m.channels, m.channels_magic};
+    cm.raw_div = SmallDiv{m.raw_channels > 0u ? m.raw_channels : 1u, m.raw_magic};
+    return cm;
+}
+
 struct ElemPos {
     uint32_t o, c, pos;        // sample, channel, index inside the channel's run of `inner` elements
 };

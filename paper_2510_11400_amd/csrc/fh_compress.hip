@@ -841,26 +841,11 @@ static_assert(kMixedStageDwords >= kStageDwords && kMixedStageDwords * 4 == Layo
 // 64.1 us at 8 bits, 58.4 without.)  The 720 MiB encoder set takes 241 us at 2 bits stochastic and 179 at 4 bits nearest,
 // 259 and 192 in the common form; 100 MB of fp32 with 3072 channels 22.3, and 24.5.
 template <typename InT, int G, bool LISTED>
-__global__ __launch_bounds__(kCBlock) void compress_mixed_kernel(const Batch<MixedCompressJob> batch)
+__device__ __forceinline__ void compress_mixed_any(const MixedCompressJob& job, const uint32_t tile, uint32_t* stage, uint16_t* listed)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kMixedStageDwords];
-    __shared__ uint16_t listed[kListRoom];
-    uint32_t tile;
-    const MixedCompressJob& job = batch.item[batch_item(batch, blockIdx.x, tile)];
     const CompressItem& it = job.it;
     const ChannelMap& cm = job.cm;
-    if (nothing_kept(cm)) {                                   // the classification found no salient channel: the plain code
-        switch (it.bits * 2 + it.stochastic) {
-            case 4:  compress_tile<InT, G, 2, false>(it, tile, stage); break;
-            case 5:  compress_tile<InT, G, 2, true >(it, tile, stage); break;
-            case 8:  compress_tile<InT, G, 4, false>(it, tile, stage); break;
-            case 9:  compress_tile<InT, G, 4, true >(it, tile, stage); break;
-            case 16: compress_tile<InT, G, 8, false>(it, tile, stage); break;
-            case 17: compress_tile<InT, G, 8, true >(it, tile, stage); break;
-            default: break;
-        }
-        return;
-    }
+    if (nothing_kept(cm)) return compress_any<InT, G>(it, tile, stage);   // the classification found no salient channel: the plain code
     switch (it.bits * 2 + it.stochastic) {
         case 4:  compress_tile<InT, G, 2, false, true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
         case 5:  compress_tile<InT, G, 2, true , true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
@@ -870,6 +855,23 @@ __global__ __launch_bounds__(kCBlock) void compress_mixed_kernel(const Batch<Mix
         case 17: compress_tile<InT, G, 8, true , true, false, LISTED>(it, tile, stage, &cm, listed, kMixedStageDwords); break;
         default: break;
     }
+}
+
+template <typename InT, int G, bool LISTED>
+__global__ __launch_bounds__(kCBlock) void compress_mixed_kernel(const Batch<MixedCompressJob> batch)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kMixedStageDwords];
+    __shared__ uint16_t listed[kListRoom];
+    uint32_t tile;
+    const MixedCompressJob& job = batch.item[batch_item(batch, blockIdx.x, tile)];
+    compress_mixed_any<InT, G, LISTED>(job, tile, stage, listed);
+}
+template <typename InT, int G, bool LISTED>
+__global__ __launch_bounds__(kCBlock) void compress_mixed_one_kernel(const OneMixedCompress one)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t stage[kWaves * kMixedStageDwords];
+    __shared__ uint16_t listed[kListRoom];
+    compress_mixed_any<InT, G, LISTED>(whole(one), blockIdx.x, stage, listed);
 }
 
 // The plain quantiser and the classification's first pass over the same elements: one read of the tensor where two
@@ -1046,9 +1048,12 @@ hipError_t launch_compress_mixed(const Batch<MixedCompressJob>& b, int dtype, in
     const dim3 grid(tiles), block(kCBlock);
     bool listed = true;
     for (int k = 0; k < b.count; ++k) listed = listed && rows_listed(b.item[k].cm);
+    const bool one = one_by_itself(b.count, tiles);
 #define FH_LAUNCH(T, GS) \
     do { \
-        if (listed) hipLaunchKernelGGL((compress_mixed_kernel<T, GS, true>), grid, block, 0, s, b); \
+        if (one && listed) hipLaunchKernelGGL((compress_mixed_one_kernel<T, GS, true>), grid, block, 0, s, shortened(b.item[0])); \
+        else if (one) hipLaunchKernelGGL((compress_mixed_one_kernel<T, GS, false>), grid, block, 0, s, shortened(b.item[0])); \
+        else if (listed) hipLaunchKernelGGL((compress_mixed_kernel<T, GS, true>), grid, block, 0, s, b); \
         else hipLaunchKernelGGL((compress_mixed_kernel<T, GS, false>), grid, block, 0, s, b); \
     } while (0)
     if (dtype == 0) {

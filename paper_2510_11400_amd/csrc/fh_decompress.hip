@@ -370,15 +370,11 @@ static_assert(sizeof(DecompressItem) + sizeof(uint32_t) <= kOneLaunchArgs, "the 
 // and six.  (Held to 64 the common form spilled 68 bytes per lane: 205 MB of feature maps 74.4 us at 8 bits and 58.1 at 2,
 // 51.1 and 39.7 without.)  The 720 MiB encoder set takes 185 us from 2-bit codes, 195 in the common form.
 template <typename OutT, int G, bool LISTED>
-__global__ __launch_bounds__(kDBlock) void decompress_mixed_kernel(const Batch<MixedDecompressJob> batch)
+__device__ __forceinline__ void decompress_mixed_any(const MixedDecompressJob& job, const uint32_t tile, uint16_t* listed, uint8_t* park)
 {
-    uint32_t tile;
-    const MixedDecompressJob& job = batch.item[batch_item(batch, gridDim.x - 1u - blockIdx.x, tile)];
     const DecompressItem& it = job.it;
     const ChannelMap& cm = job.cm;
     const int raw_dtype = job.raw_dtype;
-    __shared__ __attribute__((aligned(16))) uint8_t park[tile_elems<OutT>() * sizeof(OutT)];
-    __shared__ uint16_t listed[kListRoom];
     if (nothing_kept(cm)) return decompress_any<OutT, G>(it, tile);   // no channel of this tensor was kept: the plain code
     switch (it.bits) {
         case 2: decompress_tile<OutT, G, 2, true, LISTED>(it, tile, &cm, raw_dtype, listed, park); break;
@@ -386,6 +382,24 @@ __global__ __launch_bounds__(kDBlock) void decompress_mixed_kernel(const Batch<M
         case 8: decompress_tile<OutT, G, 8, true, LISTED>(it, tile, &cm, raw_dtype, listed, park); break;
         default: break;
     }
+}
+
+template <typename OutT, int G, bool LISTED>
+__global__ __launch_bounds__(kDBlock) void decompress_mixed_kernel(const Batch<MixedDecompressJob> batch)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t park[tile_elems<OutT>() * sizeof(OutT)];
+    __shared__ uint16_t listed[kListRoom];
+    uint32_t tile;
+    const MixedDecompressJob& job = batch.item[batch_item(batch, gridDim.x - 1u - blockIdx.x, tile)];
+    decompress_mixed_any<OutT, G, LISTED>(job, tile, listed, park);
+}
+template <typename OutT, int G, bool LISTED>
+__global__ __launch_bounds__(kDBlock) void decompress_mixed_one_kernel(const OneMixedDecompress one)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t park[tile_elems<OutT>() * sizeof(OutT)];
+    __shared__ uint16_t listed[kListRoom];
+    const uint32_t last = (one.numel - 1u) / (uint32_t)tile_elems<OutT>();       // from the end backwards here too
+    decompress_mixed_any<OutT, G, LISTED>(whole(one), last - blockIdx.x, listed, park);
 }
 
 }  // namespace
@@ -436,9 +450,12 @@ hipError_t launch_decompress_mixed(const Batch<MixedDecompressJob>& b, int out_d
     const dim3 grid(tiles), block(kDBlock);
     bool listed = true;
     for (int k = 0; k < b.count; ++k) listed = listed && rows_listed(b.item[k].cm);
+    const bool one = one_by_itself(b.count, tiles);
 #define FH_LAUNCH(T, GS) \
     do { \
-        if (listed) hipLaunchKernelGGL((decompress_mixed_kernel<T, GS, true>), grid, block, 0, s, b); \
+        if (one && listed) hipLaunchKernelGGL((decompress_mixed_one_kernel<T, GS, true>), grid, block, 0, s, shortened(b.item[0])); \
+        else if (one) hipLaunchKernelGGL((decompress_mixed_one_kernel<T, GS, false>), grid, block, 0, s, shortened(b.item[0])); \
+        else if (listed) hipLaunchKernelGGL((decompress_mixed_kernel<T, GS, true>), grid, block, 0, s, b); \
         else hipLaunchKernelGGL((decompress_mixed_kernel<T, GS, false>), grid, block, 0, s, b); \
     } while (0)
     if (out_dtype == 0) {

@@ -91,6 +91,51 @@ struct MixedDecompressJob {
     int32_t        pad;
 };
 static_assert(sizeof(Batch<MixedCompressJob>) + sizeof(MixedCompressJob) + sizeof(uint32_t) > 4096, "a launch holds as many as fit");
+// One tensor by itself, in a short argument segment.  Its padded size follows from its own, which is at most 2^31.
+struct OneMixedCompress {
+    const void* x;
+    uint8_t*    packed;
+    float*      meta;
+    uint64_t    seed, tensor_id;
+    uint32_t    numel;
+    uint16_t    bits, stochastic;
+    ShortMap    map;
+};
+struct OneMixedDecompress {
+    const uint8_t* packed;
+    const float*   meta;
+    void*          out;
+    uint32_t       numel;
+    uint16_t       bits, raw_dtype;
+    ShortMap       map;
+};
+static_assert(sizeof(OneMixedCompress) <= kOneLaunchArgs && sizeof(OneMixedDecompress) <= kOneLaunchArgs, "a short argument segment");
+inline OneMixedCompress shortened(const MixedCompressJob& j)
+{
+    return OneMixedCompress{j.it.x, j.it.packed, j.it.meta, j.it.seed, j.it.tensor_id, (uint32_t)j.it.numel, (uint16_t)j.it.bits,
+                            (uint16_t)j.it.stochastic, shortened(j.cm)};
+}
+inline OneMixedDecompress shortened(const MixedDecompressJob& j)
+{
+    return OneMixedDecompress{j.it.packed, j.it.meta, j.it.out, (uint32_t)j.it.numel, (uint16_t)j.it.bits, (uint16_t)j.raw_dtype, shortened(j.cm)};
+}
+__host__ __device__ __forceinline__ MixedCompressJob whole(const OneMixedCompress& o)
+{
+    MixedCompressJob j;
+    const uint64_t bytes = ((uint64_t)o.numel * o.bits + 7u) >> 3;
+    j.it = CompressItem{o.x, o.packed, o.meta, (int64_t)o.numel, (bytes + 15u) & ~(uint64_t)15u, o.seed, o.tensor_id, (int32_t)o.bits, (int32_t)o.stochastic};
+    j.cm = whole(o.map);
+    return j;
+}
+__host__ __device__ __forceinline__ MixedDecompressJob whole(const OneMixedDecompress& o)
+{
+    MixedDecompressJob j;
+    j.it = DecompressItem{o.packed, o.meta, o.out, (int64_t)o.numel, (int32_t)o.bits, 0};
+    j.cm = whole(o.map);
+    j.raw_dtype = (int32_t)o.raw_dtype;
+    j.pad = 0;
+    return j;
+}
 // The plain quantiser that leaves the classification's first pass behind on its way (fh_moments.hpp): for tensors that
 // are quantised before it is known which of their channels are kept.
 struct FirstCompressJob {

@@ -36,6 +36,13 @@ inline int32_t marked_spans_per_wave(int64_t launch_spans, int64_t tensor_spans,
 inline bool compress_in_runs(uint32_t tiles) { return tiles >= 12288; }
 inline bool restore_in_runs(uint32_t tiles) { return tiles >= 8192; }
 
+// Whether the routed quantiser or its restore takes one tensor's descriptor in a short argument segment (fh_batch.hpp).  One tensor of
+// 1.6 MB, both ways, 10.0 us with the batch's arguments and 8.5 with these, the whole chain on it 90.3 and 88.9.  Putting the
+// descriptor together again costs scalar registers, and with them the 65th vector register of the bf16 form, so that seven
+// waves fit a SIMD: launches that the device holds at once in workgroups of four such waves, and whose kernel is over before
+// a longer one is enqueued.
+inline bool one_by_itself(int32_t tensors, uint32_t tiles) { return tensors == 1 && tiles <= 256u * 7u; }
+
 // How often a wave of a large launch looks at that many spans.  A workgroup's histogram of a wide tensor is 3072 counters to clear
 // and to add in for the outliers of 64 spans; once there are waves for a whole round of the device (8192 of eight spans), twice the
 // spans to a histogram save half of that, the ranges of the second eight on their way meanwhile.  Count pass of the 720 MiB

@@ -81,7 +81,7 @@ def test_launches_of_one_tensor_have_short_arguments(code_objects):
     """Up to 112 bytes of arguments a launch is enqueued a microsecond sooner; a hidden argument (the grid's size, for
     one) would make the segment some 300 bytes long."""
     kernels = {name: r for name, r in _resources(code_objects).items() if "_one_kernel" in name or "3OneI" in name}
-    assert len(kernels) == 40
+    assert len(kernels) == 64
     for name, r in kernels.items():
         assert r["kernarg_segment_size"] <= 112, f"{name}: {r['kernarg_segment_size']}"
 

@@ -338,3 +338,40 @@ def test_rows_in_use_of_zero_takes_the_plain_code_path(api, dtype):
         for od, got in zip(("f32", "bf16"), outs):
             want = oracle.decompress_mixed(p, m, r, outer, C, inner, want_slots, 4, 128, 4, raw_dtype=dtype, out_dtype=od)
             assert np.array_equal(_bits(_host(got, od)), _bits(want)), f"restored {od} differs"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("bits, rounding", [(2, "stochastic"), (4, "nearest"), (8, "stochastic")])
+def test_a_tensor_by_itself_gives_what_it_gives_in_a_batch(api, dtype, bits, rounding):
+    """One tensor has kernels of its own up to 1792 tiles (fp32: 4096 elements to quantise and 2048 to restore, bf16: 8192 and
+    4096); beside a second one it takes the batch's.  Feature maps and one channel per element, ragged, with a kept channel
+    and with none, with a power of two of everything, and on either side of both lines."""
+    shapes = [(3, 10, 7), (1, 1, 1), (8, 64, 64), (5, 33, 49), (64, 48, 1), (333, 769, 1), (4, 4096, 1), (7, 3, 5000),
+              (1792 if dtype == "f32" else 3584, 2048, 1), (1793 if dtype == "f32" else 3585, 2048, 1),
+              (3584 if dtype == "f32" else 7168, 2048, 1), (3585 if dtype == "f32" else 7169, 2048, 1)]
+    tdt = _tdtype(dtype)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    for i, (outer, C, inner) in enumerate(shapes):
+        x = torch.randn(outer * C * inner, generator=gen, device="cuda").to(tdt)
+        for kept in (0.0, 0.1):
+            mask = _mask(C, kept, i)
+            mask[0] = 1 if kept else 0
+            cap = max(1, int(mask.sum()))
+            slots = torch.from_numpy(oracle.channel_slots(mask, cap)[0]).cuda()
+            in_use = torch.tensor([int(mask.sum())], dtype=torch.int64, device="cuda")
+            two = [api.MixedEntry(outer, C, inner, slots, cap, 64, bits, rounding, 3, 100, x=x,
+                                  out=torch.empty(x.numel(), dtype=tdt, device="cuda")) for _ in range(2)]
+            batch = api.MixedBatch(two)
+            api.fh_compress_mixed_batch(batch)
+            api.fh_decompress_mixed_batch(batch)
+            packed, meta, raw = api.fh_compress_mixed(x, outer, C, inner, slots, cap, 64, bits, rounding, 3, 100, rows_in_use=in_use)
+            out = api.fh_decompress_mixed(packed, meta, raw, outer, C, inner, slots, cap, 64, bits, out_dtype=tdt, rows_in_use=in_use)
+            torch.cuda.synchronize()
+            what = f"{(outer, C, inner)}, {kept}"
+            assert torch.equal(packed, two[0].packed), what
+            assert torch.equal(meta.view(torch.int32), two[0].meta.view(torch.int32)), what
+            bits_of = torch.int32 if dtype == "f32" else torch.int16
+            assert torch.equal(out.view(bits_of), two[0].out.view(bits_of)), what
+            if kept:
+                rows = [r.reshape(outer, cap, inner)[:, :int(mask.sum())] for r in (raw, two[0].raw)]
+                assert torch.equal(rows[0].view(bits_of), rows[1].view(bits_of)), what

@@ -32,6 +32,7 @@ int main(int, char** argv)
         else if (!std::strcmp(argv[1], "mask_with_the_counts")) std::printf("%d\\n", (int)fh::mask_with_the_counts(a));
         else if (!std::strcmp(argv[1], "compress_in_runs")) std::printf("%d\\n", (int)fh::compress_in_runs((unsigned)a));
         else if (!std::strcmp(argv[1], "restore_in_runs")) std::printf("%d\\n", (int)fh::restore_in_runs((unsigned)a));
+        else if (!std::strcmp(argv[1], "one_by_itself")) std::printf("%d\\n", (int)fh::one_by_itself((int)a, (unsigned)b));
         else if (!std::strcmp(argv[1], "maps_stay_in_cache")) std::printf("%d\\n", (int)fh::maps_stay_in_cache(a));
         else if (!std::strcmp(argv[1], "group_sums_are_scanned")) std::printf("%d\\n", (int)fh::group_sums_are_scanned(a));
         else if (!std::strcmp(argv[1], "decode_in_whole_lines")) std::printf("%d\\n", (int)fh::decode_in_whole_lines(a));
@@ -92,3 +93,7 @@ def test_looks_and_masks_of_the_count_pass(rules):
     """Two looks for wide tensors of launches with a round of waves; masks with the counts for narrow ones."""
     assert rules("marked_looks_per_wave", [(n, c, 0, 0) for n in (1, 65536, 65537, 1 << 22) for c in (1, 1024, 1025, 16384)]) == [1] * 8 + [1, 1, 2, 2] * 2
     assert rules("mask_with_the_counts", [(c, 0, 0, 0) for c in (1, 1024, 1025, 16384)]) == [1, 1, 0, 0]
+
+
+def test_short_arguments_for_one_tensor_that_the_device_holds_at_once(rules):
+    assert rules("one_by_itself", [(n, tiles, 0, 0) for n in (1, 2, 26) for tiles in (1, 1792, 1793, 1 << 31)]) == [1, 1, 0, 0] + [0] * 8
