@@ -15,6 +15,7 @@ import glob
 import hashlib
 import json
 import os
+import re
 from collections import defaultdict
 from typing import Dict, Optional
 
@@ -191,8 +192,10 @@ def library_source_digest() -> str:
 
 
 def _short(name: str) -> Optional[str]:
+    """The kernel without namespaces, parameters and the type of its arguments (of a batch or of one tensor)."""
     if "fh::" not in name:
         return None
+    name = re.sub(r"(, |<)fh::(Batch|One)<.*?> ?>(?=\()", lambda m: ">" if m.group(1) == ", " else "", name)
     return name.split("fh::(anonymous namespace)::", 1)[-1].split("(")[0]
 
 
