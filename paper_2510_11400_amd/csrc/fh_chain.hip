@@ -11,9 +11,8 @@
 // Every stage is the library's own batched call; this file only lays the caller's two buffers
 // out, strings the calls together on one stream, and adds two small kernels: one that takes the
 // masks from the outlier counts, numbers the salient channels of every tensor of the call, clears
-// the headers and, where the sparse stage cannot leave them out, the rows of the raw stores that no channel uses
-// (they must read as zero), and one that adds up what a tensor's stored
-// form occupies where the entropy stage does not do that.  Sizes that depend on the data (stream lengths) never visit the host:
+// the rows of the raw stores that no channel uses (they read as zero) and the headers, and one that adds up what a
+// tensor's stored form occupies where the entropy stage does not do that.  Sizes that depend on the data (stream lengths) never visit the host:
 // the sparse stage's totals feed the Huffman stage through device memory.
 #include "../../include/fedhybrid.h"
 
@@ -39,7 +38,7 @@ struct PrepItem {
     uint64_t*       header;                        // 8 words, cleared; [7] = slots in use
     uint8_t*        raw;                           // the raw store: [outer][raw_channels][row_bytes]
     uint64_t        row_bytes;
-    uint32_t        outer;                         // samples whose unused rows are to be cleared
+    uint32_t        outer;
     int32_t         channels, raw_channels;
     uint32_t        blocks;                        // workgroups of this item
 };
@@ -223,9 +222,9 @@ fh_status check_item(const fh_mix_item& it, bool forward, fh_mix_regions* r, int
 
 uint8_t* at(void* base, size_t off) { return static_cast<uint8_t*>(base) + off; }
 
-// Which maps of an item's raw store hold anything.  Where a map is a row of the store, the sparse stage is told and leaves
-// the others alone; where it is not ([tokens][hidden] tensors), or an empty tile would not be a sparse one, those
-// rows are cleared and stored as the zeros they are.
+// Which maps of an item's raw store hold anything.  Where a map is a row of the store, the sparse encoder is told and does not
+// read the others; where it is not ([tokens][hidden] tensors), or an empty tile would not be a sparse one, it reads
+// the zeros they are.
 MapsInUse rows_in_use(const fh_mix_item& it, const fh_mix_regions& reg)
 {
     const bool by_rows = it.h * it.w == it.inner && it.tau >= 0.0f;
@@ -324,11 +323,11 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
             p.header = reinterpret_cast<uint64_t*>(at(it.store, reg[i].header));
             p.raw = at(it.workspace, reg[i].raw);
             p.row_bytes = (uint64_t)it.inner * elem_size(it.x_dtype);
-            p.outer = reg[i].raw_bytes && !rows_in_use(it, reg[i]).count ? (uint32_t)it.outer : 0u;
+            p.outer = reg[i].raw_bytes ? (uint32_t)it.outer : 0u;
             p.channels = (int32_t)it.channels;
             p.raw_channels = (int32_t)it.raw_channels;
             // every workgroup counts the salient channels first: 16 KiB of rows for each of its waves at least
-            const uint64_t want = p.outer ? reg[i].raw_bytes / ((kPrepThreads / 64) * kClearUnit) + 1u : 1u;
+            const uint64_t want = reg[i].raw_bytes / ((kPrepThreads / 64) * kClearUnit) + 1u;
             p.blocks = (uint32_t)(want < 512u ? want : 512u);
             push(b, p, p.blocks);
         }
@@ -409,7 +408,6 @@ fh_status fh_mix_decompress_batch(const fh_mix_item* items, int32_t count, void*
     // the index streams back, then the maps (the raw stores), then the tensors
     std::vector<fh_huffman_decode_item> hf;
     std::vector<fh_sparse_decode_item> sp;
-    std::vector<MapsInUse> use;
     for (int32_t i = 0; i < count; ++i) {
         const fh_mix_item& it = items[i];
         if (reg[i].raw_bytes == 0) continue;
@@ -430,13 +428,13 @@ fh_status fh_mix_decompress_batch(const fh_mix_item* items, int32_t count, void*
         d.out = at(it.workspace, reg[i].raw); d.out_cap = reg[i].raw_bytes;
         d.workspace = at(it.workspace, reg[i].sparse_ws); d.workspace_cap = reg[i].sparse_ws_bytes;
         sp.push_back(d);
-        use.push_back(rows_in_use(it, reg[i]));
     }
     if (!hf.empty() && (st = fh_huffman_decode_batch(hf.data(), (int32_t)hf.size(), stream)) != FH_OK) return st;
     uint64_t map_bytes = 0;
     for (const fh_sparse_decode_item& d : sp) map_bytes += d.out_cap;
     if (!sp.empty()) {
-        st = sparse_decode_rows(sp.data(), use.data(), maps_stay_in_cache(map_bytes), (int32_t)sp.size(), static_cast<hipStream_t>(stream));
+        st = maps_stay_in_cache(map_bytes) ? sparse_decode_for_next(sp.data(), (int32_t)sp.size(), static_cast<hipStream_t>(stream))
+                                           : fh_sparse_decode_batch(sp.data(), (int32_t)sp.size(), stream);
         if (st != FH_OK) return st;
     }
 

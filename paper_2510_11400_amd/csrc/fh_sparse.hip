@@ -128,11 +128,11 @@ struct Job {
     uint32_t  encode;          // `totals` is the member of the union
 };
 
-// Is the map one of those that hold nothing?  (False where the maps are not the rows of a raw store.)  They are neither read nor
-// written: a room of a sixteenth of the channels where 4 % are kept leaves 36 % of the maps unused.  `scale` is
+// Is the map one of those that hold nothing?  (False where the maps are not the rows of a raw store.)  The encoder does not read
+// them: a room of a sixteenth of the channels where 4 % are kept leaves 36 % of the maps unused.  `scale` is
 // floor(2^32 / rows), so that the quotient is the right one or one less.
-// With the clearing of those maps that saves 10 us of the 403 of the whole chain on the MobileNetV2-style set (count 10.9 -> 8.6,
-// write 16.4 -> 14.3, read 18.1 -> 16.7, the chain's preparing kernel 8.2 -> 4.9).
+// On the MobileNetV2-style set the count pass then takes 8.6 us in place of 10.9, the write pass 14.3 in place of 16.4.
+// (The decoder writes all maps: which of them are zeros is for the stream to say, not for a word of a header beside it.)
 __device__ __forceinline__ bool map_unused(const MapsInUse& use, uint32_t map)
 {
     if (!use.count) return false;                             // wave-uniform
@@ -903,14 +903,13 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_write_kernel(const Ba
 // only the part of a slice that lies inside the stream is staged, a tile whose piece would
 // leave the stream is zero-filled, and whatever the staged bytes say, a thread reads no further
 // than N bytes / one value past its own piece.
-// READ_NEXT (FORM & 1): the next kernel on the stream reads the maps.  ROWS (FORM & 2): some maps may be unused.
-template <typename Bits, int N, int FORM>
+// READ_NEXT: the next kernel on the stream reads the maps.
+template <typename Bits, int N, bool READ_NEXT>
 __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Batch<Job> batch)
 {
     constexpr int T = Group<N>::kTiles;
     typedef typename Alias<Bits>::type StagedBits;
     typedef typename TileMask<N>::type Mask;
-    constexpr bool READ_NEXT = FORM & 1, ROWS = FORM & 2;
     __shared__ PlaceLds<Group<N>::kWaves> lds;
     __shared__ __attribute__((aligned(16))) uint8_t stage_v[Stage<Bits, N>::kValueBytes];
     __shared__ __attribute__((aligned(16))) uint8_t stage_i[Stage<Bits, N>::kIndexBytes];
@@ -926,11 +925,9 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Bat
     TilePos t = {0, 1, 1, 0};
     uint32_t byte = 0x80u;
     uint32_t mine = 0;
-    bool unused = false;
     if (live) {
         t = tile_pos<N>(s, b);
         byte = info[b];
-        unused = ROWS && map_unused(job.use, t.map);
         mine = tile_packed(byte, t, s.step.two_eps > 0.0f);
     }
     const Place place = place_tiles<N, false>(mine, wg, scanned, block, lds);
@@ -955,7 +952,7 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_read_kernel(const Bat
     }
     const bool any = __builtin_amdgcn_ballot_w64((byte & 0x80u) && values_in(mine) != 0u) != 0u;     // dense tiles with outliers
     __syncthreads();
-    if (!live || unused) return;
+    if (!live) return;
 
     const StagedBits* v = reinterpret_cast<const StagedBits*>(stage_v + phase_of(value_slice)) + values_before;
     const uint8_t* idx = stage_i + phase_of(index_slice) + index_before;
@@ -1155,7 +1152,7 @@ void launch_tiles(Kernel kernel, const Batch<Job>& b, int threads, hipStream_t s
     if (b.count > 0) hipLaunchKernelGGL(kernel, dim3(b.block_start[b.count]), dim3(threads), 0, s, b);
 }
 
-// the (dtype, window) instantiation of a templated pass in one of its four forms
+// the (dtype, window) instantiation of a templated pass in one form, and of an encoder's pass in the one of its four that is asked for
 #define FH_SPARSE_OF(KERNEL, DTYPE, NN, FORM)                                                      \
     ((DTYPE) == FH_F32 ? ((NN) == 2 ? KERNEL<uint32_t, 2, FORM> : (NN) == 4 ? KERNEL<uint32_t, 4, FORM> : KERNEL<uint32_t, 8, FORM>)  \
                        : ((NN) == 2 ? KERNEL<uint16_t, 2, FORM> : (NN) == 4 ? KERNEL<uint16_t, 4, FORM> : KERNEL<uint16_t, 8, FORM>))
@@ -1194,7 +1191,7 @@ void settle_scans(Run& run, int n)
 }
 
 fh_status encode_all(const fh_sparse_encode_item* items, const MapsInUse* use, int32_t count, hipStream_t s);
-fh_status decode_all(const fh_sparse_decode_item* items, const MapsInUse* use, bool read_next, int32_t count, hipStream_t s);
+fh_status decode_all(const fh_sparse_decode_item* items, bool read_next, int32_t count, hipStream_t s);
 
 }  // namespace
 
@@ -1209,7 +1206,7 @@ fh_status fh_sparse_encode_batch(const fh_sparse_encode_item* items, int32_t cou
 
 fh_status fh_sparse_decode_batch(const fh_sparse_decode_item* items, int32_t count, void* stream)
 {
-    return decode_all(items, nullptr, false, count, static_cast<hipStream_t>(stream));
+    return decode_all(items, false, count, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"
@@ -1218,9 +1215,9 @@ fh_status fh::sparse_encode_rows(const fh_sparse_encode_item* items, const MapsI
 {
     return encode_all(items, use, count, s);
 }
-fh_status fh::sparse_decode_rows(const fh_sparse_decode_item* items, const MapsInUse* use, bool read_next, int32_t count, hipStream_t s)
+fh_status fh::sparse_decode_for_next(const fh_sparse_decode_item* items, int32_t count, hipStream_t s)
 {
-    return decode_all(items, use, read_next, count, s);
+    return decode_all(items, true, count, s);
 }
 
 namespace {
@@ -1284,7 +1281,7 @@ fh_status encode_all(const fh_sparse_encode_item* items, const MapsInUse* use, i
     return hipGetLastError() == hipSuccess ? FH_OK : FH_ERR_LAUNCH;
 }
 
-fh_status decode_all(const fh_sparse_decode_item* items, const MapsInUse* use, bool read_next, int32_t count, hipStream_t s)
+fh_status decode_all(const fh_sparse_decode_item* items, bool read_next, int32_t count, hipStream_t s)
 {
     if (count < 0) return FH_ERR_BAD_COUNT;
     if (count > 0 && !items) return FH_ERR_NULL;
@@ -1320,7 +1317,7 @@ fh_status decode_all(const fh_sparse_decode_item* items, const MapsInUse* use, b
             job.value_count = it.values_bytes / elem_size(it.dtype);
             job.index_count = it.indices_bytes;
             job.encode = 0;
-            job.use = use ? use[i] : MapsInUse{nullptr, 1, 0};
+            job.use = MapsInUse{nullptr, 1, 0};
             job.tau = 0.0f;
             add_job(run, job, tiles, n);
             ++i;
@@ -1335,8 +1332,8 @@ fh_status decode_all(const fh_sparse_decode_item* items, const MapsInUse* use, b
                      64 * kGroupsPerWorkgroup, s);
         if (run.any_scan)
             hipLaunchKernelGGL(sparse_scan_kernel, dim3(run.all.count), dim3(kScanThreads), 0, s, run.all);
-        const int form = (read_next ? 1 : 0) + (run.any_rows ? 2 : 0);
-        launch_tiles(FH_SPARSE_PICK(sparse_read_kernel, dtype, n, form), run.tiled, tiles_per_workgroup(n), s);
+        if (read_next) launch_tiles(FH_SPARSE_OF(sparse_read_kernel, dtype, n, true), run.tiled, tiles_per_workgroup(n), s);
+        else launch_tiles(FH_SPARSE_OF(sparse_read_kernel, dtype, n, false), run.tiled, tiles_per_workgroup(n), s);
     }
     if (!launched) return FH_OK;
     return hipGetLastError() == hipSuccess ? FH_OK : FH_ERR_LAUNCH;

@@ -37,17 +37,17 @@ fh_status compress_first(const fh_mixed_item* items, const fh_classify_item* cla
 fh_status compress_kept(const fh_mixed_item* items, int32_t count, hipStream_t s);
 constexpr int64_t kFirstSpan = 2048;               // elements of such a span at most
 
-// Maps that are the rows of a raw store, `rows` to a sample, of which the first *count (device) are in use: the others count as
-// zeros and are neither read nor written.  scale: floor(2^32 / rows), all ones for a single row.  count null: all maps are in use.
+// Maps that are the rows of a raw store, `rows` to a sample, of which the first *count (device) are in use: the others are
+// zeros and are not read.  scale: floor(2^32 / rows), all ones for a single row.  count null: all maps are in use.
 struct MapsInUse { const uint64_t* count; uint32_t rows, scale; };
 inline MapsInUse maps_in_use(const uint64_t* count, uint32_t rows)
 {
     return MapsInUse{count, rows, rows > 1u ? (uint32_t)(((uint64_t)1 << 32) / rows) : 0xffffffffu};
 }
-// fh_sparse_encode_batch and fh_sparse_decode_batch with use[i] of item i (whose tau is not below 0); read_next: the next kernel
-// on the stream finds the maps in the caches (maps_stay_in_cache).
+// fh_sparse_encode_batch with use[i] of item i (whose tau is not below 0).
 fh_status sparse_encode_rows(const fh_sparse_encode_item* items, const MapsInUse* use, int32_t count, hipStream_t s);
-fh_status sparse_decode_rows(const fh_sparse_decode_item* items, const MapsInUse* use, bool read_next, int32_t count, hipStream_t s);
+// fh_sparse_decode_batch for maps that the next kernel on the stream finds in the caches (maps_stay_in_cache).
+fh_status sparse_decode_for_next(const fh_sparse_decode_item* items, int32_t count, hipStream_t s);
 
 // fh_huffman_encode_batch with the bytes that the stored form of the tensor occupies written to header[6] on the way:
 // fixed_bytes + header[0] * value_size + the stream's bytes.

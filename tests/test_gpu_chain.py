@@ -8,6 +8,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
+import oracle
 import oracle_chain as OC
 from paper_2510_11400_amd import workloads as W
 
@@ -210,6 +211,60 @@ def test_rows_of_the_raw_store_that_no_channel_uses(api, tau, window):
     for i, (x, c) in enumerate(zip(xs, cases)):
         st = _compare(api, batch, i, x, c, "f32")
         assert (st.used < c[4]) == (c[4] > 1), "the case is to leave rows unused"
+
+
+@pytest.mark.parametrize("tau", [-1.0, 0.5])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_the_raw_store_holds_zeros_where_no_channel_is_kept(api, dtype, tau):
+    """What the workspace holds where the layout says that the raw store lies: after compress the kept channels' rows and zeros,
+    after decompress the maps that the stored form describes.  Feature maps and a column per channel, with value ranges parked
+    in the raw store meanwhile (the fourth case: few spans hold kept elements) or in the codes' place."""
+    cases = [(3, 24, 63, (7, 9), 7, 64, 4, "nearest", 4, tau, 0.02, 1, dtype, 3),
+             (3, 24, 63, (7, 9), 24, 64, 4, "nearest", 2, tau, 0.0, 1, dtype, 10 ** 6),
+             (40, 96, 1, None, 12, 64, 4, "nearest", 8, tau, 0.02, 0, dtype, 2),
+             (2, 40, 16384, (128, 128), 2, 128, 4, "nearest", 4, tau, 0.02, 1, dtype, 300),
+             (4, 16, 256, (16, 16), 16, 256, 4, "nearest", 4, tau, 0.02, 1, dtype, 1)]
+    for i, c in enumerate(cases):
+        (outer, C, inner, hw, raw_channels, G, B, rounding, window, tau, eps, entropy, dtype, min_out) = c
+        print(f"[chain] raw store of case {i}, {dtype}, tau {tau}", flush=True)
+        x = _input(c, 900 + i)
+        batch = api.MixBatch([_entry(api, _device(x, dtype), c, "f32")])
+        e = batch.entries[0]
+        e.workspace.random_(0, 256)
+        api.fh_mix_compress_batch(batch)
+        torch.cuda.synchronize()
+        maps, h, w = _maps(outer, raw_channels, inner, hw)
+        st = OC.mix_compress(x, outer, C, inner, raw_channels, G, B, rounding, 11, 3, 3.0, min_out, maps, h, w, window,
+                             tau, eps, entropy, dtype=dtype)
+        assert np.array_equal(batch.part(0, "raw").cpu().numpy(), st.raw.view(np.uint8)), f"case {i}: after compress"
+        e.workspace.random_(0, 256)
+        api.fh_mix_decompress_batch(batch)
+        torch.cuda.synchronize()
+        indices = oracle.huffman_decode(st.huffman, st.indices.size) if entropy else st.indices
+        want = oracle.sparse_decode(st.info, st.values, indices, maps, h, w, window, dtype=dtype, eps=eps)
+        assert np.array_equal(batch.part(0, "raw").cpu().numpy(), want.view(np.uint8)), f"case {i}: after decompress"
+
+
+def test_a_header_that_counts_too_few_rows_changes_nothing(api):
+    """The restore takes the kept rows from the slots and the maps from the streams; the header's word for the rows in use only says
+    whether there are any."""
+    case = (3, 24, 63, (7, 9), 7, 64, 4, "nearest", 4, 0.5, 0.02, 1, "f32", 3)
+    x = _input(case, 31)
+    batch = api.MixBatch([_entry(api, _device(x, "f32"), case, "f32")])
+    print("[chain] rows in use understated", flush=True)
+    api.fh_mix_compress_batch(batch)
+    torch.cuda.synchronize()
+    used = int(batch.header(0)[7])
+    assert used >= 2
+    wants = []
+    for rows in (used, 1):
+        batch.header(0)[7] = rows
+        batch.entries[0].workspace.random_(0, 256)
+        batch.entries[0].out.fill_(-1.0)
+        api.fh_mix_decompress_batch(batch)
+        torch.cuda.synchronize()
+        wants.append(batch.entries[0].out.cpu().numpy().view(np.uint32))
+    assert np.array_equal(*wants)
 
 
 def test_batched_chain_item_by_item_and_in_a_captured_graph(api):
