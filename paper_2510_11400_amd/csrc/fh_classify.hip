@@ -98,7 +98,8 @@ __device__ __forceinline__ void moments_of(const MomentsItem& it, const uint32_t
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t span = ((int64_t)block * kWavesPerBlock + wave) * SPANS;
     const int64_t base = span * kSpan;
-    if (block == 0) clear_counters<kThreads>(it.cleared);     // workgroup-uniform
+    constexpr int64_t kOfBlock = (int64_t)kWavesPerBlock * SPANS * kSpan;
+    clear_counters<kThreads>(it.cleared, block, (uint32_t)((numel + kOfBlock - 1) / kOfBlock));
     if (base >= numel) return;                                // wave-uniform
     const InT* xs = x + base;
     float v[ROWS][EPL];
@@ -184,7 +185,7 @@ struct EmptyBatch { EmptyItem item[kBatch]; };
 __global__ __launch_bounds__(kThreads) void no_elements_kernel(const EmptyBatch args)
 {
     const EmptyItem& it = args.item[blockIdx.x];
-    clear_counters<kThreads>(it.cleared);
+    clear_counters<kThreads>(it.cleared, 0u, 1u);
     if (threadIdx.x < 4) it.stats[threadIdx.x] = 0.0;
 }
 

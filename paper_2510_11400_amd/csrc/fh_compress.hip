@@ -884,7 +884,7 @@ __global__ __launch_bounds__(kCBlock) void compress_first_kernel(const Args batc
     uint32_t tile;
     const FirstCompressJob& job = item_of(batch, blockIdx.x, tile);
     const CompressItem& it = job.it;
-    if (tile == 0) clear_counters<kCBlock>(job.cleared);      // workgroup-uniform
+    clear_counters<kCBlock>(job.cleared, tile, (uint32_t)((it.numel + Layout<InT>::TILE - 1) / Layout<InT>::TILE));
     switch (it.bits * 2 + it.stochastic) {
         case 4:  compress_tile<InT, G, 2, false, false, true>(it, tile, stage, nullptr, nullptr, kStageDwords, &job); break;
         case 5:  compress_tile<InT, G, 2, true , false, true>(it, tile, stage, nullptr, nullptr, kStageDwords, &job); break;

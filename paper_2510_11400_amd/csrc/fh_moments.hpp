@@ -118,11 +118,14 @@ __device__ __forceinline__ double local_tree(const double (&v)[N])
     return w[0];
 }
 
-// The counters and the mask of a tensor, by one workgroup of the first pass.
+// The counters and the mask of a tensor, by the workgroups of the first pass: THREADS channels each, the first ones.  (All of
+// them by one made the pass wait for that one: 26 bf16 tensors of 1 Mi elements with 16384 channels 40.0 us, this way 34.1.)
 template <int THREADS>
-__device__ __forceinline__ void clear_counters(const Cleared& c)
+__device__ __forceinline__ void clear_counters(const Cleared& c, uint32_t block, uint32_t blocks)
 {
-    for (int i = threadIdx.x; i < c.channels; i += THREADS) { c.counts[i] = 0u; c.mask[i] = 0; }
+    const uint32_t parts = ((uint32_t)c.channels + THREADS - 1u) / THREADS, step = (blocks < parts ? blocks : parts) * THREADS;
+    if (block >= parts) return;                               // workgroup-uniform
+    for (uint32_t i = block * THREADS + threadIdx.x; i < (uint32_t)c.channels; i += step) { c.counts[i] = 0u; c.mask[i] = 0; }
 }
 
 // ---- value ranges ------------------------------------------------------------------------

@@ -246,3 +246,42 @@ def test_waves_of_a_large_launch_look_twice(api, dtype):
         torch.cuda.synchronize()
         for got, want in zip((b.stats, b.counts, b.mask), alone):
             assert torch.equal(got, want)
+
+
+def _check_batch(api, shapes, dtype, ranges, bound_of):
+    """A batched call on shapes (outer, channels, inner), outputs dirty before it, against the oracle; bound_of(counts) is the
+    outlier count that makes a channel salient."""
+    print(f"[classify] {dtype}, {'ranges' if ranges else 'no ranges'}: {shapes}", flush=True)
+    room = api.classify_workspace_bytes_ranges if ranges else api.classify_workspace_bytes
+    entries, wants = [], []
+    for i, (outer, C, inner) in enumerate(shapes):
+        if outer:
+            x, _ = W.outlier_channel_tensor(outer, C, inner, seed=outer + i, salient_fraction=0.1, dtype=dtype)
+            xd = _device(x, dtype)
+        else:
+            x = np.zeros(0, f32 if dtype == "f32" else np.uint16)
+            xd = torch.empty(0, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+        stats, counts, _ = oracle.classify_channels(x, outer, C, inner, 3.0, 1, dtype=dtype)
+        bound = max(1, bound_of(counts))
+        wants.append((stats, counts, (counts >= bound).astype(np.uint8)))
+        ws = torch.empty(room(x.size), dtype=torch.uint8, device="cuda")
+        entries.append(api.ClassifyEntry(xd, outer, C, inner, 3.0, bound, workspace=ws))
+    batch = api.ClassifyBatch(entries)
+    for e in batch.entries:
+        for t in (e.stats, e.counts, e.mask):
+            t.fill_(77)
+    api.fh_classify_channels_batch(batch)
+    torch.cuda.synchronize()
+    for e, (stats, counts, mask) in zip(batch.entries, wants):
+        assert np.array_equal(e.stats.cpu().numpy().view(np.uint64), stats.view(np.uint64))
+        assert np.array_equal(e.counts.cpu().numpy().view(np.uint32), counts)
+        assert np.array_equal(e.mask.cpu().numpy(), mask)
+
+
+@pytest.mark.parametrize("channels", [1, 255, 256, 257, 1000, 16384])
+def test_counters_and_masks_are_cleared_whatever_the_workgroups(api, channels):
+    """The first pass clears 256 channels with each of its workgroups: fewer and more workgroups than that takes, and a launch that
+    takes four spans for a wave."""
+    for outer in (1, 2, max(1, (1 << 21) // channels)):
+        _check_batch(api, [(outer, channels, 1), (3, 300, 17)], "f32", True, lambda counts: 1)
+    _check_batch(api, [(max(1, (26 << 20) // channels), channels, 1)], "f32", True, lambda counts: int(counts.max()))
