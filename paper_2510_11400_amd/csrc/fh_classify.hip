@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kThreads) void no_elements_kernel(const EmptyBatch 
 // The first wave of every workgroup of the count pass does this for itself, the first workgroup of a tensor writes it down: as
 // a launch between the passes it was 4.7 us and the gap before it, here the other waves clear the histogram and the ranges are on
 // their way meanwhile.  One tensor of 12 MB 16.9 -> 15.8 us, of 50 MB 29.7 -> 28.4, three of 50 MB 50.7 -> 48.4; on large sets the pass
-// takes longer by as much as the launch took.
+// takes longer by as much as the launch took, and where its workgroups are short by more: there the launch is left (limits_apart, fh_rules.hpp).
 struct LastLevel {
     const f64x2* in;                                          // the partial sums
     int32_t      count;
@@ -234,6 +234,15 @@ __device__ __forceinline__ Limits limits_of(const LastLevel& it, int64_t numel, 
         it.stats[3] = n;
     }
     return Limits{mean, threshold};
+}
+
+// The same as a launch of its own, a wave for each tensor.
+struct LimitsItem { LastLevel last; int64_t numel; };
+struct LimitsBatch { LimitsItem item[kBatch]; };
+__global__ __launch_bounds__(kWave) void limits_kernel(const LimitsBatch args)
+{
+    const LimitsItem& it = args.item[blockIdx.x];
+    limits_of(it.last, it.numel, threadIdx.x, true);
 }
 
 // ---- pass 2: outliers per channel ----------------------------------------------------------
@@ -284,9 +293,9 @@ __device__ __forceinline__ double uniform(double v)            // the same in al
                                           (uint32_t)__builtin_amdgcn_readfirstlane((int)low));
 }
 
-// AHEAD: a launch in which some wave walks more than one span.
+// AHEAD: a launch in which some wave walks more than one span.  APART: the limits are there (limits_apart, fh_rules.hpp).
 constexpr int kAhead = 3;                         // spans requested before the one that is looked at
-template <typename InT, bool AHEAD, typename Args>
+template <typename InT, bool AHEAD, bool APART, typename Args>
 __global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Args batch)
 {
     constexpr int ROWS = Span<InT>::ROWS, EPL = Span<InT>::EPL, ROW = kWave * EPL;
@@ -297,13 +306,13 @@ __global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Args bat
     const uint32_t C = args.channels.d;
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (wave == 0) {
+    if (!APART && wave == 0) {
         const Limits found = limits_of(args.last, args.numel, lane, block == 0);
         if (lane == 0) limits = found;
     }
     for (uint32_t c = threadIdx.x; c < C; c += kThreads) hist[c] = 0u;
     __syncthreads();
-    const double mean = uniform(limits.mean), threshold = uniform(limits.threshold);
+    const double mean = APART ? args.last.stats[0] : uniform(limits.mean), threshold = APART ? args.last.stats[2] : uniform(limits.threshold);
     const InT* x = static_cast<const InT*>(args.x);
     const int64_t numel = args.numel;
     // this wave's spans: first_span, first_span + 1, ...
@@ -412,7 +421,7 @@ __global__ __launch_bounds__(kThreads) void count_outliers_kernel(const Args bat
 // waves as the rules of fh_rules.hpp give the launch: 23 us for 100 MB of fp32 with 3072 channels, the kernel above 25.
 constexpr int kLook = 8;                          // spans whose ranges a wave looks at together: 64 pieces
 constexpr int kRounds = 2;                        // rounds of eight pieces requested together
-template <typename InT, int WAVES, typename Args>
+template <typename InT, int WAVES, bool APART, typename Args>
 __global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Args batch)
 {
     constexpr int kThreads = WAVES * kWave;
@@ -430,13 +439,13 @@ __global__ __launch_bounds__(WAVES * kWave) void count_marked_kernel(const Args 
     const int64_t stop = first + args.spans_per_wave < all_spans ? first + args.spans_per_wave : all_spans;
     const auto range_of = [&](int64_t span) { return span + (lane >> 3) < stop ? args.ranges[span * kPieces + lane] : 0u; };
     uint32_t range = range_of(first);                         // in flight while the counters are cleared
-    if (wave == 0) {
+    if (!APART && wave == 0) {
         const Limits found = limits_of(args.last, numel, lane, block == 0);
         if (lane == 0) limits = found;
     }
     for (uint32_t c = threadIdx.x; c < C; c += kThreads) hist[c] = 0u;
     __syncthreads();
-    const double mean = uniform(limits.mean), threshold = uniform(limits.threshold);
+    const double mean = APART ? args.last.stats[0] : uniform(limits.mean), threshold = APART ? args.last.stats[2] : uniform(limits.threshold);
     for (int64_t span0 = first; span0 < stop; span0 += kLook) {          // wave-uniform
         const bool mark = span0 + (lane >> 3) < stop && may_hold_outliers(range, mean, threshold);
         const uint64_t marks = __ballot(mark);
@@ -593,7 +602,8 @@ fh_status check_item(const fh_classify_item& it, int64_t* numel_out)
     return FH_OK;
 }
 
-// One run of up to kBatch tensors of one dtype: two or three launches, each covering all of them.  The tensors either all have a place for their ranges or all have none.
+// One run of up to kBatch tensors of one dtype: two to five launches, each covering all of them.  The tensors either all
+// have a place for their ranges or all have none.
 fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, const int64_t* numels, int n, bool masks,
                        bool first_pass_done, hipStream_t s)
 {
@@ -662,6 +672,7 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
     Batch<MaskItem> kb;
     reset(cb);
     reset(kb);
+    int of_item[kBatch];                                      // the count pass's tensors among `items`
     int64_t widest = 0;
     for (int i = 0; i < n; ++i)
         if (numels[i] > 0 && items[i].channels > widest) widest = items[i].channels;
@@ -685,36 +696,77 @@ fh_status run_classify(const fh_classify_item* items, uint32_t* const* ranges, c
                                   : (int32_t)(ch <= 512 ? 1 : ch / 128 < 16 ? ch / 128 : 16);
         a.ranges = ranges[i];
         if (marked) a.spans_per_wave *= marked_looks_per_wave(spans, ch);
-        // (counters of channels with 2^32 elements and more may wrap: the masks are then what they end at)
-        const bool here = mask_with_the_counts(ch) && items[i].outer * items[i].inner <= (int64_t)UINT32_MAX;
-        a.mask = masks && here ? static_cast<uint8_t*>(items[i].mask) : nullptr;
+        a.mask = nullptr;
         a.min_outliers = items[i].min_outliers;
         const int64_t per_block = (int64_t)a.spans_per_wave * waves * kSpan;
+        of_item[cb.count] = i;
         if (!push(cb, a, ceil_div(numels[i], per_block))) return FH_ERR_BAD_NUMEL;
-        if (masks && !here)
-            push(kb, MaskItem{a.counts, static_cast<uint8_t*>(items[i].mask), items[i].min_outliers, (int32_t)ch},
-                 ceil_div(ch, kThreads));
     }
     if (cb.count > 0) {
         seal(cb);
-        seal(kb);
         const dim3 grid(cb.block_start[cb.count]);
+        uint32_t of_one_span = 0;
+        bool crowded = false;
+        for (int k = 0; k < cb.count; ++k)
+            if (cb.item[k].spans_per_wave == 1) {
+                const uint32_t workgroups = cb.block_start[k + 1] - cb.block_start[k];
+                of_one_span += workgroups;
+                crowded = crowded || counters_are_crowded(workgroups, cb.item[k].channels.d);
+            }
+        const bool apart = limits_apart(marked, cb.count, grid.x, of_one_span, crowded);
+        if (apart) {
+            LimitsBatch lb;
+            for (int k = 0; k < kBatch; ++k) {
+                const CountArgs& a = cb.item[k < cb.count ? k : 0];
+                lb.item[k] = LimitsItem{a.last, a.numel};
+            }
+            hipLaunchKernelGGL(limits_kernel, dim3(cb.count), dim3(kWave), 0, s, lb);
+        }
+        for (int k = 0; k < cb.count && masks; ++k) {
+            const fh_classify_item& it = items[of_item[k]];
+            // (counters of channels with 2^32 elements and more may wrap: the masks are then what they end at)
+            const bool here = apart    ? mask_with_the_counts_apart(it.channels, marked, cb.count)
+                              : marked ? mask_with_the_counts(it.channels)
+                                       : mask_with_the_counts_unranged(it.channels, ceil_div(cb.item[k].numel, kSpan));
+            if (here && it.outer * it.inner <= (int64_t)UINT32_MAX)
+                cb.item[k].mask = static_cast<uint8_t*>(it.mask);
+            else
+                push(kb, MaskItem{cb.item[k].counts, static_cast<uint8_t*>(it.mask), it.min_outliers, (int32_t)it.channels},
+                     ceil_div(it.channels, kThreads));
+        }
+        seal(kb);
         bool ahead = false;
         for (int k = 0; k < cb.count; ++k) ahead = ahead || cb.item[k].spans_per_wave > 1;
         const dim3 threads(marked ? waves * kWave : kThreads);
-        with_arguments(cb, [&](const auto& args) {
-            if (marked && dtype == FH_F32) {
-                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<float, 4, FH_ARGS>), grid, threads, lds, s, args);
-                else hipLaunchKernelGGL((count_marked_kernel<float, 8, FH_ARGS>), grid, threads, lds, s, args);
-            } else if (marked) {
-                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<uint16_t, 4, FH_ARGS>), grid, threads, lds, s, args);
-                else hipLaunchKernelGGL((count_marked_kernel<uint16_t, 8, FH_ARGS>), grid, threads, lds, s, args);
-            } else if (dtype == FH_F32) {
-                if (ahead) hipLaunchKernelGGL((count_outliers_kernel<float, true, FH_ARGS>), grid, threads, lds, s, args);
-                else hipLaunchKernelGGL((count_outliers_kernel<float, false, FH_ARGS>), grid, threads, lds, s, args);
+        if (apart && marked) {
+            if (dtype == FH_F32) {
+                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<float, 4, true, Batch<CountArgs>>), grid, threads, lds, s, cb);
+                else hipLaunchKernelGGL((count_marked_kernel<float, 8, true, Batch<CountArgs>>), grid, threads, lds, s, cb);
             } else {
-                if (ahead) hipLaunchKernelGGL((count_outliers_kernel<uint16_t, true, FH_ARGS>), grid, threads, lds, s, args);
-                else hipLaunchKernelGGL((count_outliers_kernel<uint16_t, false, FH_ARGS>), grid, threads, lds, s, args);
+                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<uint16_t, 4, true, Batch<CountArgs>>), grid, threads, lds, s, cb);
+                else hipLaunchKernelGGL((count_marked_kernel<uint16_t, 8, true, Batch<CountArgs>>), grid, threads, lds, s, cb);
+            }
+        } else if (apart) {
+            if (dtype == FH_F32) {
+                if (ahead) hipLaunchKernelGGL((count_outliers_kernel<float, true, true, Batch<CountArgs>>), grid, threads, lds, s, cb);
+                else hipLaunchKernelGGL((count_outliers_kernel<float, false, true, Batch<CountArgs>>), grid, threads, lds, s, cb);
+            } else {
+                if (ahead) hipLaunchKernelGGL((count_outliers_kernel<uint16_t, true, true, Batch<CountArgs>>), grid, threads, lds, s, cb);
+                else hipLaunchKernelGGL((count_outliers_kernel<uint16_t, false, true, Batch<CountArgs>>), grid, threads, lds, s, cb);
+            }
+        } else with_arguments(cb, [&](const auto& args) {
+            if (marked && dtype == FH_F32) {
+                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<float, 4, false, FH_ARGS>), grid, threads, lds, s, args);
+                else hipLaunchKernelGGL((count_marked_kernel<float, 8, false, FH_ARGS>), grid, threads, lds, s, args);
+            } else if (marked) {
+                if (waves == 4) hipLaunchKernelGGL((count_marked_kernel<uint16_t, 4, false, FH_ARGS>), grid, threads, lds, s, args);
+                else hipLaunchKernelGGL((count_marked_kernel<uint16_t, 8, false, FH_ARGS>), grid, threads, lds, s, args);
+            } else if (dtype == FH_F32) {
+                if (ahead) hipLaunchKernelGGL((count_outliers_kernel<float, true, false, FH_ARGS>), grid, threads, lds, s, args);
+                else hipLaunchKernelGGL((count_outliers_kernel<float, false, false, FH_ARGS>), grid, threads, lds, s, args);
+            } else {
+                if (ahead) hipLaunchKernelGGL((count_outliers_kernel<uint16_t, true, false, FH_ARGS>), grid, threads, lds, s, args);
+                else hipLaunchKernelGGL((count_outliers_kernel<uint16_t, false, false, FH_ARGS>), grid, threads, lds, s, args);
             }
         });
         if (kb.count > 0) {

@@ -50,10 +50,43 @@ inline bool one_by_itself(int32_t tensors, uint32_t tiles) { return tensors == 1
 // channels 154 -> 134; with 768 channels, whose histograms are short, 76 -> 77, feature maps 16 -> 20: these keep one.
 inline int32_t marked_looks_per_wave(int64_t launch_spans, int64_t channels) { return channels > 1024 && launch_spans > 65536 ? 2 : 1; }
 
-// Whether the count pass sets the mask as it adds to the counters, or a launch behind it does.  The additions are then waited for, and
+// Whether the count pass sets a tensor's mask as it adds to the counters, or a launch behind it does.  The additions are then waited for, and
 // a wide tensor's workgroup has many: 3 tensors of 3072 channels 52 us with the launch and 56 without, 3 of 16384 128 and
 // 154, 24 of 768 78 and 76, 18 of 1024 131 and 126, one of 768 17.9 and 16.9.
 inline bool mask_with_the_counts(int64_t channels) { return channels <= 1024; }
+// The same without value ranges, where more of a large tensor's workgroups add to a counter at a time.  768 channels: one fp32 tensor of
+// 24 Mi elements 49.3 us with the launch and 54.1 without, two of 12 Mi 49.2 and 51.5, eight of 64 Mi (bf16) 445 and 464, 26 of 4 Mi 149 and
+// 151, 26 of 1 Mi 49.3 and 48.2; 1024 channels, eight of 4 Mi (bf16) 36.7 and 34.6, one of 64 Mi 71.9 and 77.8.
+inline bool mask_with_the_counts_unranged(int64_t channels, int64_t tensor_spans)
+{
+    return mask_with_the_counts(channels) && (channels <= 512 || tensor_spans <= 4096);
+}
+// The same where the limits are apart (limits_apart): waiting is then most of what a short workgroup does (eight bf16 tensors of
+// 16 Mi elements without ranges 122 us with the launch and 137 without, of 128 Mi 949 and 1020; with ranges, one of 768 Mi with 256 channels
+// 364 and 393).  Only a tensor alone, without ranges, is bound by the additions themselves, and the launch would come on top: 64 Mi
+// 110.5 and 107.5, 1000 Mi 1575 and 1535 (64 channels), 64 Mi with 512 channels 55.9 and 54.3, 512 Mi 367 and 371.
+inline bool mask_with_the_counts_apart(int64_t channels, bool ranges, int32_t tensors) { return !ranges && tensors == 1 && channels <= 512; }
+
+// Whether a launch before the count pass finishes the moments, or the first wave of each of its workgroups does.  The launch: so many
+// tensors and workgroups, `of_one_span` of these of tensors that have a span for each wave (without value ranges, up to 512 channels), one
+// of which is `crowded` (its workgroups' additions meet on few counters).  The launches apart, this one and the one for the
+// masks behind, take 3 us each; in the pass, the limits and the masks make every workgroup take longer.  Both in the pass and both apart, us:
+//   with ranges: 16 tensors of 16 Mi elements (8192 workgroups) bf16 136 and 135, one of 256 Mi, 256 channels, 134 and 127, eight of 64 Mi (16384), 32
+//   channels, 309 and 279, fp32 492 and 461, three of 256 Mi 537 and 480, 799 and 732; eight of 16 Mi (4096) 69 and 70, 114 and 116;
+//   several without, fp32: two of 4 Mi (2048), 1 channel, 30.7 and 30.7, 64 channels 21.5 and 26.8; three of 4 Mi (3072), 3 channels, 41.9 and 35.1, 64
+//   channels 25.6 and 29.9; 12 of 1 Mi (3072), 3 channels, 23.2 and 26.5; two of 8 Mi (4096), 16, 64 and 128 channels, 64.2 and 57.4, 40.6 and 37.7, 31.5
+//   and 34.1; four of 4 Mi, 32 and 64 channels, 36.5 and 36.5, 31.2 and 34.1; 20 of 1 Mi (5120), 64 channels, 33.1 and 32.0, 26 of 1 Mi 43.5 and 41.0, eight
+//   of 16 Mi bf16 141 and 122, of 128 Mi 1130 and 949;
+//   one without: 20 Mi (5120), 64 channels, 44.1 and 47.0, bf16 38.9 and 41.7, 64 Mi, 512 channels, 89.5 and 94.7, bf16 60.1 and 55.7, 512 Mi bf16 459
+//   and 367;
+//   wide ones without: 16 of 16 Mi, 3072 channels, bf16 188 and 187, fp32 345 and 348, two of 12 Mi 33.5 and 36.8, 43.5 and 44.9.
+inline bool limits_apart(bool ranges, int32_t tensors, uint32_t workgroups, uint32_t of_one_span, bool crowded)
+{
+    if (ranges) return workgroups >= 8192;
+    if (tensors == 1) return of_one_span > 5120;
+    return of_one_span >= 5120 || (of_one_span > 2048 && crowded);
+}
+inline bool counters_are_crowded(uint32_t workgroups, uint32_t channels) { return workgroups >= 1024 && workgroups / 32 >= channels; }
 
 // The Huffman encoder's group sums in a launch of `groups` altogether: scanned by a kernel between the count and the write
 // pass, or every workgroup of the write pass adds up those before its own.  Adding up saves that launch and makes every

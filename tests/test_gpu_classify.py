@@ -278,6 +278,57 @@ def _check_batch(api, shapes, dtype, ranges, bound_of):
         assert np.array_equal(e.mask.cpu().numpy(), mask)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("over", [0, 1])
+def test_moments_finished_in_or_before_the_count_pass_without_ranges(api, over, dtype):
+    """Either side of where the moments of a launch without value ranges are finished by a launch of their own: one tensor, several,
+    several of which one's counters are crowded, each with a ragged end; a wide tensor and one without elements beside them."""
+    top = lambda counts: int(counts.max())
+    _check_batch(api, [(1, 64, (5120 + over) * 64)], dtype, False, top)
+    _check_batch(api, [(1, 256, (5119 + over - 2) * 16), (853, 3072, 1), (3, 37, 63), (0, 5, 7)], dtype, False, top)
+    _check_batch(api, [(1, 32, (2048 + over - 2) * 128), (853, 3072, 1), (3, 7, 331), (0, 5, 7)], dtype, False, top)
+
+
+@pytest.mark.parametrize("channels, inner", [(768, 1), (1024, 1), (513, 3)])
+@pytest.mark.parametrize("spans", [4096, 4097])
+def test_masks_of_wide_tensors_without_ranges(api, spans, channels, inner):
+    """Either side of where a wide tensor's masks leave the count pass."""
+    outer = (spans * 1024) // (channels * inner)
+    _check_batch(api, [(outer, channels, inner), (7, 33, 19)], "bf16", False, lambda counts: int(np.median(counts)))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_moments_finished_before_the_count_pass_with_ranges(api, dtype):
+    """From 8192 workgroups of four waves, eight spans for each, the moments are finished by a launch of their own: narrow tensors,
+    and in workgroups of eight waves beside a wide one.  One of the tensors against the oracle, all against themselves one by one."""
+    for wide in (False, True):
+        spans = 8192 * 32 * (2 if wide else 1)
+        one = (spans // 2 * 1024) // (64 * 4096)
+        shapes = [(one, 64, 4096), (one, 64, 4096), (3000, 1032, 1) if wide else (5, 7, 331)]
+        print(f"[classify] moments apart with ranges, {dtype}: {shapes}", flush=True)
+        entries = []
+        for i, (outer, C, inner) in enumerate(shapes):
+            g = torch.Generator(device="cuda").manual_seed(i)
+            x = torch.empty(outer * C * inner, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+            for at in range(0, x.numel(), 1 << 26):
+                x[at:at + (1 << 26)] = torch.randn(min(1 << 26, x.numel() - at), generator=g, device="cuda").to(x.dtype)
+            entries.append((x, outer, C, inner, 3.0, outer * inner // 400))
+        batch = api.ClassifyBatch([api.ClassifyEntry(*e) for e in entries])
+        api.fh_classify_channels_batch(batch)
+        for e, b in zip(entries, batch.entries):
+            ws = torch.empty(api.classify_workspace_bytes(e[0].numel()), dtype=torch.uint8, device="cuda")
+            alone = api.fh_classify_channels(*e, workspace=ws)            # without ranges: another pass over the tensor
+            torch.cuda.synchronize()
+            for got, want in zip((b.stats, b.counts, b.mask), alone):
+                assert torch.equal(got, want)
+        x, outer, C, inner, k, bound = entries[2]
+        host = x.view(torch.int16).cpu().numpy().view(np.uint16) if dtype == "bf16" else x.cpu().numpy()
+        stats, counts, mask = oracle.classify_channels(host, outer, C, inner, k, bound, dtype=dtype)
+        b = batch.entries[2]
+        assert np.array_equal(b.stats.cpu().numpy().view(np.uint64), stats.view(np.uint64))
+        assert np.array_equal(b.counts.cpu().numpy().view(np.uint32), counts) and np.array_equal(b.mask.cpu().numpy(), mask)
+
+
 @pytest.mark.parametrize("channels", [1, 255, 256, 257, 1000, 16384])
 def test_counters_and_masks_are_cleared_whatever_the_workgroups(api, channels):
     """The first pass clears 256 channels with each of its workgroups: fewer and more workgroups than that takes, and a launch that

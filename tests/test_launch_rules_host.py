@@ -30,6 +30,10 @@ int main(int, char** argv)
         if (!std::strcmp(argv[1], "marked_spans_per_wave")) std::printf("%lld\\n", (long long)fh::marked_spans_per_wave(a, b, c, d));
         else if (!std::strcmp(argv[1], "marked_looks_per_wave")) std::printf("%d\\n", (int)fh::marked_looks_per_wave(a, b));
         else if (!std::strcmp(argv[1], "mask_with_the_counts")) std::printf("%d\\n", (int)fh::mask_with_the_counts(a));
+        else if (!std::strcmp(argv[1], "mask_with_the_counts_unranged")) std::printf("%d\\n", (int)fh::mask_with_the_counts_unranged(a, b));
+        else if (!std::strcmp(argv[1], "mask_with_the_counts_apart")) std::printf("%d\\n", (int)fh::mask_with_the_counts_apart(a, b != 0, (int)c));
+        else if (!std::strcmp(argv[1], "limits_apart")) std::printf("%d\\n", (int)(a < 0 ? fh::limits_apart(true, 1, (unsigned)b, (unsigned)c, d != 0) : fh::limits_apart(false, (int)a, (unsigned)b, (unsigned)c, d != 0)));
+        else if (!std::strcmp(argv[1], "counters_are_crowded")) std::printf("%d\\n", (int)fh::counters_are_crowded((unsigned)a, (unsigned)b));
         else if (!std::strcmp(argv[1], "compress_in_runs")) std::printf("%d\\n", (int)fh::compress_in_runs((unsigned)a));
         else if (!std::strcmp(argv[1], "restore_in_runs")) std::printf("%d\\n", (int)fh::restore_in_runs((unsigned)a));
         else if (!std::strcmp(argv[1], "one_by_itself")) std::printf("%d\\n", (int)fh::one_by_itself((int)a, (unsigned)b));
@@ -93,6 +97,22 @@ def test_looks_and_masks_of_the_count_pass(rules):
     """Two looks for wide tensors of launches with a round of waves; masks with the counts for narrow ones."""
     assert rules("marked_looks_per_wave", [(n, c, 0, 0) for n in (1, 65536, 65537, 1 << 22) for c in (1, 1024, 1025, 16384)]) == [1] * 8 + [1, 1, 2, 2] * 2
     assert rules("mask_with_the_counts", [(c, 0, 0, 0) for c in (1, 1024, 1025, 16384)]) == [1, 1, 0, 0]
+
+
+def test_moments_and_masks_leave_the_count_pass_in_large_launches(rules):
+    """With value ranges from 8192 workgroups; without, by those that have a span for each wave: beyond 5120 of a lone tensor, from 5120
+    of several, beyond 2048 where many of a tensor's meet on few counters.  The masks then come from a launch behind, except a
+    lone narrow tensor's without ranges."""
+    assert rules("limits_apart", [(-1, n, s, 0) for n in (1, 8191, 8192, 1 << 31) for s in (0, n)]) == [0, 0, 0, 0, 1, 1, 1, 1]
+    spans = (0, 2048, 2049, 5119, 5120, 5121, 1 << 20)
+    for tensors, crowded, want in ((1, 0, [0] * 5 + [1, 1]), (1, 1, [0] * 5 + [1, 1]), (2, 0, [0] * 4 + [1] * 3), (26, 1, [0, 0] + [1] * 5)):
+        assert rules("limits_apart", [(tensors, 1 << 20, s, crowded) for s in spans]) == want
+    rows = [(1023, 1, 0, 0), (1024, 1, 0, 0), (1024, 32, 0, 0), (1024, 33, 0, 0), (2048, 64, 0, 0), (2047, 64, 0, 0), (1 << 30, 512, 0, 0)]
+    assert rules("counters_are_crowded", rows) == [0, 1, 1, 0, 1, 0, 1]
+    rows = [(c, ranges, tensors, 0) for c in (1, 512, 513) for ranges in (0, 1) for tensors in (1, 2, 26)]
+    assert rules("mask_with_the_counts_apart", rows) == [1, 0, 0, 0, 0, 0] * 2 + [0] * 6
+    rows = [(c, spans, 0, 0) for c in (1, 512, 513, 1024, 1025) for spans in (1, 4096, 4097, 1 << 30)]
+    assert rules("mask_with_the_counts_unranged", rows) == [1] * 8 + [1, 1, 0, 0] * 2 + [0] * 4
 
 
 def test_short_arguments_for_one_tensor_that_the_device_holds_at_once(rules):
