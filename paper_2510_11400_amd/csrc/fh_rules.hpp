@@ -95,6 +95,23 @@ inline bool counters_are_crowded(uint32_t workgroups, uint32_t channels) { retur
 // 599 and 609; 24 streams of 335 groups 394.5 and 395.7, 24 of 1024 1108 and 1124, six of 4096 1122 and 1151.
 inline bool group_sums_are_scanned(int64_t groups) { return groups > 4096; }
 
+// Is there a scan of the sums of a set's `groups` of tiles between the sparse stage's passes, in a launch of `of_launch` groups?  Without one each
+// group adds up those before it, eight bytes for a group.  Encode | decode, scanned and not, us:
+//   window 2, one set: 2100 groups 17.6 and 13.4 | 17.4 and 13.3, 4000 21.1 and 17.9 | 20.4 and 16.4, 6000 26.6 and 25.5 | 25.0 and 22.7, 8000 33.0
+//   and 34.9 | 29.8 and 30.9; three of 2100 25.5 and 24.0 | 23.8 and 21.3, two of 4000 30.0 and 30.5 | 26.8 and 26.1, five of 2048 35.4 and 36.7 | 30.8
+//   and 31.1, five of 4000 57.8 and 66.4 | 51.1 and 58.3;
+//   window 4: 2100 25.8 and 22.8 | 21.8 and 17.7, 4000 39.1 and 37.1 | 28.2 and 25.8, 6000 51.0 and 50.0 | 38.5 and 37.1, 8000 63.4 and 64.6 | 47.7
+//   and 48.7; two of 4000 60.2 and 60.9 | 44.4 and 44.6 (without a bound 60.1 and 59.0 | 51.9 and 44.9), five of 2048 76.8 and 80.4 | 51.8 and
+//   52.5, five of 4000 138.9 and 152.8 | 90.4 and 99.5;
+//   window 8, whose groups do the most: 2048 55.1 and 53.5 | 40.2 and 38.9, 2500 63.5 and 62.5 | 47.7 and 46.7 (without a bound 52.5 and 54.5 | 46.2
+//   and 41.4), 3500 80.2 and 81.5 | 60.2 and 61.3, 4000 86.8 and 88.1 | 66.3 and 68.5, 6000 130 and 144 | 92 and 100.
+// (Several small sets are added up in any launch: 24 of 1000, window 4, lose 8 of 167 and 7 of 106 us by it.)
+constexpr uint32_t kMostAddedUp = 4096;
+inline bool sparse_sums_are_scanned(uint32_t groups, uint32_t of_launch, int window)
+{
+    return groups > (window < 8 && of_launch <= 8192 ? kMostAddedUp : 2048u);
+}
+
 // The Huffman decoder's stores, in a call of `symbols`: whether half a cache line waits for its other half.
 // Where the memory-side cache holds the output, half lines meet there, and storing early is better: the last stores of a
 // pass are fewer (51 MB 41.4 us, 42.8 in whole lines; 268 MB of two bits a symbol 168 and 175).  Beyond, half lines reach

@@ -40,6 +40,7 @@
 
 #include "fh_batch.hpp"
 #include "fh_channels.hpp"
+#include "fh_rules.hpp"
 #include "fh_scan.hpp"
 #include "fh_stages.hpp"
 
@@ -53,16 +54,6 @@ template <int N> struct Group {
 };
 constexpr int kScanThreads = 512;
 constexpr uint64_t kStreamedFrom = (uint64_t)128 << 20;    // bytes of maps in a launch from which the first pass streams
-// Is there a scan of a set's workgroups' sums between the passes?  Without one each workgroup adds up those before it, eight bytes
-// for a group.  Encode and decode of one set, window 4, scanned and not: 2300 workgroups 28.7 and 26.0, 22.9 and 20.0 us, 3000 33.2 and
-// 31.4, 26.5 and 23.5, 4000 39.2 and 38.4, 31.3 and 29.1.  Several large sets in a launch lose: five of 4000 136.8 and 147.7, 102.3 and
-// 109.2, so beyond 8192 workgroups together sets of more than 2048 are scanned, as other windows' always are (window 8, whose
-// workgroups do the most, 2048: 55.9 and 56.9, 58.4 and 58.4, with 24 bytes for a group).
-constexpr uint32_t kMostAddedUp = 4096;
-inline bool sums_are_scanned(uint32_t groups, uint32_t of_launch, int window)
-{
-    return groups > (window == 4 && of_launch <= 8192 ? kMostAddedUp : 2048u);
-}
 
 struct Sums {                                      // what a run of tiles writes
     uint64_t values, index_bytes, sparse_tiles;
@@ -1185,7 +1176,7 @@ void settle_scans(Run& run, int n)
     for (Batch<Job>* b : {&run.tiled, &run.grouped, &run.all})
         for (int k = 0; k < b->count; ++k) {
             Job& job = b->item[k];
-            job.scanned = job.shape.tiles == 0 || sums_are_scanned(job.wg_count, all, n) ? 1u : 0u;
+            job.scanned = job.shape.tiles == 0 || sparse_sums_are_scanned(job.wg_count, all, n) ? 1u : 0u;
             run.any_scan = run.any_scan || job.scanned;
         }
 }

@@ -96,8 +96,8 @@ def test_all_zero_and_all_dense_maps(api):
 
 
 def test_more_groups_than_the_write_pass_adds_up_itself(api):
-    # beyond 2048 groups of 256 tiles the scan kernel runs between the passes
-    maps, h, w, n = 9000, 16, 16, 2                         # 576000 tiles -> 2250 groups
+    # beyond 4096 groups of 256 tiles the scan kernel runs between the passes
+    maps, h, w, n = 17000, 16, 16, 2                        # 1088000 tiles -> 4250 groups
     x = W.salient_feature_maps(maps, h, w, seed=77)
     _check(api, x, maps, h, w, n, 0.5, name="scan kernel")
 
@@ -110,6 +110,40 @@ def test_groups_on_both_sides_of_the_scan(api, groups):
         maps -= 3                                           # a ragged last group
     x = W.salient_feature_maps(maps, h, w, seed=groups)
     _check(api, x, maps, h, w, 4, 0.5, name="scan or none", eps=0.02)
+
+
+@pytest.mark.parametrize("n, groups", [(2, 2049), (2, 4096), (2, 4097), (8, 2048), (8, 2049)])
+def test_groups_on_both_sides_of_the_scan_in_other_windows(api, n, groups):
+    tiles = groups * (128 if n == 8 else 256) - 3           # a ragged last group
+    x = W.salient_feature_maps(tiles, n, n, seed=groups)
+    _check(api, x, tiles, n, n, n, 0.5, name="scan or none", eps=0.02)
+
+
+@pytest.mark.parametrize("n", [2, 4])
+@pytest.mark.parametrize("groups", [(2048, 2049, 4095), (2048, 2049, 4096), (2000, 4097, 3, 2095), (2000, 2500, 4500)])
+def test_sets_with_and_without_a_scan_share_a_launch(api, n, groups):
+    """Up to 8192 groups in the launch, where sets of up to 4096 are added up, and beyond, where those of up to 2048 are: all,
+    some or one of the sets scanned, beside an empty one."""
+    entries, host = [], []
+    for i, g in enumerate(groups + (0,)):
+        maps = max(0, 16 * g - 1)                           # sixteen tiles to a map: a ragged last group
+        x = W.salient_feature_maps(max(maps, 1), 4 * n, 4 * n, seed=g)[: maps * 16 * n * n]
+        host.append((x, maps))
+        xd = _device(x, "f32") if maps else torch.empty(0, device="cuda")
+        entries.append(api.SparseEntry(maps, 4 * n, 4 * n, n, 0.5, 0.02, x=xd, out=torch.empty(x.size, device="cuda")))
+    batch = api.SparseBatch(entries)
+    print(f"[sparse] window {n}, sets of {groups} groups in a launch", flush=True)
+    api.fh_sparse_encode_batch(batch)
+    api.fh_sparse_decode_batch(batch)
+    torch.cuda.synchronize()
+    for (x, maps), e in zip(host, entries):
+        info, v, idx, totals = oracle.sparse_encode(x, maps, 4 * n, 4 * n, n, 0.5, dtype="f32", eps=0.02)
+        assert np.array_equal(e.buffers.totals.cpu().numpy().view(np.uint64), totals)
+        assert np.array_equal(e.buffers.info.cpu().numpy()[:info.size], info)
+        assert np.array_equal(_bits(_host(e.buffers.values, "f32")[:v.size]), _bits(v))
+        assert np.array_equal(e.buffers.indices.cpu().numpy()[:idx.size], idx)
+        want = oracle.sparse_decode(info, v, idx, maps, 4 * n, 4 * n, n, dtype="f32", eps=0.02)
+        assert np.array_equal(_bits(_host(e.out, "f32")), _bits(want))
 
 
 def test_many_rows_of_the_scan_kernel(api):
@@ -363,7 +397,7 @@ def test_batched_calls_match_the_oracle_for_every_set(api, per_launch):
     """More sets than one launch holds, both dtypes and all windows (several runs), an empty set,
     a set large enough for the scan kernel, with and without an error bound."""
     specs = [(3, 28, 28, 4, "f32", 0.0), (5, 14, 14, 4, "f32", 0.02), (0, 9, 9, 4, "f32", 0.0), (2, 56, 56, 8, "f32", 0.05),
-             (4, 13, 29, 2, "bf16", 0.0), (9000, 16, 16, 2, "f32", 0.0), (7, 7, 7, 8, "bf16", 0.1)]
+             (4, 13, 29, 2, "bf16", 0.0), (17000, 16, 16, 2, "f32", 0.0), (7, 7, 7, 8, "bf16", 0.1)]
     specs += [(2 + i % 14, 10 + i % 14, 12 + 2 * (i % 14), 4, "f32", 0.01 * (i % 3)) for i in range(2 * per_launch + 1)]
     entries, host = [], []
     for i, (maps, h, w, n, dtype, eps) in enumerate(specs):

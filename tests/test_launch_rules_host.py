@@ -39,6 +39,7 @@ int main(int, char** argv)
         else if (!std::strcmp(argv[1], "one_by_itself")) std::printf("%d\\n", (int)fh::one_by_itself((int)a, (unsigned)b));
         else if (!std::strcmp(argv[1], "maps_stay_in_cache")) std::printf("%d\\n", (int)fh::maps_stay_in_cache(a));
         else if (!std::strcmp(argv[1], "group_sums_are_scanned")) std::printf("%d\\n", (int)fh::group_sums_are_scanned(a));
+        else if (!std::strcmp(argv[1], "sparse_sums_are_scanned")) std::printf("%d\\n", (int)fh::sparse_sums_are_scanned((unsigned)a, (unsigned)b, (int)c));
         else if (!std::strcmp(argv[1], "decode_in_whole_lines")) std::printf("%d\\n", (int)fh::decode_in_whole_lines(a));
 }
 ''')
@@ -84,6 +85,15 @@ def test_the_chains_maps_pass_the_caches_by_where_these_do_not_hold_them(rules):
 def test_group_sums_are_scanned_in_launches_of_many_groups(rules):
     """Up to 4096 groups in a launch, however many streams they belong to, there is no scan."""
     assert rules("group_sums_are_scanned", [(n, 0, 0, 0) for n in (0, 1, 335, 4096, 4097, 24 * 335, 1 << 31)]) == [0, 0, 0, 0, 1, 1, 1]
+
+
+def test_sparse_sums_are_scanned_in_large_sets(rules):
+    """Sets of more than 2048 groups; windows of 2 and 4 of more than 4096 while the launch has 8192 at most."""
+    groups = (0, 2048, 2049, 4096, 4097, 1 << 22)
+    for window in (2, 4):
+        assert rules("sparse_sums_are_scanned", [(g, 8192, window, 0) for g in groups]) == [0, 0, 0, 0, 1, 1]
+        assert rules("sparse_sums_are_scanned", [(g, 8193, window, 0) for g in groups]) == [0, 0, 1, 1, 1, 1]
+    assert rules("sparse_sums_are_scanned", [(g, g, 8, 0) for g in groups]) == [0, 0, 1, 1, 1, 1]
 
 
 def test_tiles_go_to_the_xcds_in_runs_in_large_launches_of_fp32(rules):
