@@ -333,6 +333,30 @@ def test_maps_beyond_the_caches_share_restore_as_each_tensor_does_alone(api, dty
         assert torch.equal(e.out.view(torch.int32), single.view(torch.int32)), f"tensor {k}"
 
 
+@pytest.mark.parametrize("window", [2, 4, 8])
+def test_unused_rows_of_maps_that_no_cache_holds(api, window):
+    """147 MiB of maps in a call, of whose rows two thirds are unused: the sparse encoder's passes read past the caches and leave the
+    unused maps out."""
+    outer, C, hw = 64, 24, 112
+    case = (outer, C, hw * hw, (hw, hw), C, 128, 4, "nearest", window, 0.5, 0.02, 0, "f32", 1)
+    assert 2 * outer * C * hw * hw * 4 >= 128 << 20
+    rng = np.random.default_rng(window)
+    xs = []
+    for k in range(2):
+        x = np.clip(rng.standard_normal((outer, C, hw * hw), dtype=np.float32), 0, 6)
+        x[:, k::3] *= np.where(rng.random((outer, C // 3, hw * hw), dtype=np.float32) < 0.05, np.float32(81), np.float32(1))
+        xs.append(x.reshape(-1))
+    batch = api.MixBatch([_entry(api, _device(x, "f32"), case, "f32") for x in xs])
+    for e in batch.entries:
+        e.workspace.random_(0, 256)
+    print(f"[chain] unused rows past the caches, window {window}", flush=True)
+    api.fh_mix_compress_batch(batch)
+    api.fh_mix_decompress_batch(batch)
+    torch.cuda.synchronize()
+    for i, x in enumerate(xs):
+        assert _compare(api, batch, i, x, case, "f32").used == C // 3
+
+
 def test_chain_rejects_bad_arguments_before_any_launch(api):
     print("[chain] argument checks", flush=True)
     import ctypes
