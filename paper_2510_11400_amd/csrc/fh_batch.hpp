@@ -55,10 +55,15 @@ template <typename Item> inline void seal(Batch<Item>& b)
 template <typename Item> inline void reset(Batch<Item>& b) { b.count = 0; b.block_start[0] = 0; }
 
 // A launch of one tensor carries its descriptor alone.  Up to 112 bytes of arguments a launch is enqueued in 2.8 us, with 120 in 3.7,
-// with 1000 to 4000 in 4.1 to 4.3 (launches of an empty kernel in a row); hidden arguments, the grid's size for one, count.  One tensor
-// of 1 MiB, quantised and restored: 18.4 us with the batch's arguments, 16.8 with these.  (Launches with tiles in runs take 40 us and
-// more: they keep the batch's.)  Classification of one tensor of 1.6 MB 15.5 -> 14.7 us, of 26 MB 19.3 -> 17.9; the whole chain on them
-// 93.5 -> 90.3 and 119.7 -> 116.7.  The routed quantiser's descriptor is shortened (fh_kernels.hpp); the sparse stage's is longer and keeps the batch's.
+// with 1000 to 4000 in 4.1 to 4.3 (launches of an empty kernel in a row); hidden arguments, the grid's size for one, count.  What
+// that is worth where calls follow one another, with the batch's arguments and with these, us: one fp32 tensor of 1 MiB quantised and restored
+// 9.4 and 6.6, of 16 MiB 12.2 and 9.7, of 64 MiB 28.9 and 28.4; routed, 0.8 MB, 10.6 and 7.0, 3.2 MB 10.9 and 7.7; classified, 1 MB 10.6 and
+// 6.4, 19 MB 19.2 and 15.2, 77 MB 27.2 and 24.4 (the first pass 0.4 of it, the level between 0.3, the count pass 0.5, of wide tensors the masks 1.5);
+// Huffman-coded, 1 Mi symbols, 32.1 and 31.1 (histogram 0.6, codes 0.2, count and write 0.9), 32 Mi 65.6 and 65.0; decoded 26.7 and
+// 26.4, 35.0 and 34.7; the whole chain, 0.3 MB 95.6 and 81.6, 77 MB 146 and 141 (preparing 1.1, quantiser with first pass 0.7).  Under a caller
+// that takes longer to make its calls than a launch to be enqueued it is worth nothing.  Left out where nothing is gained: launches with tiles in runs
+// (40 us and more), with limits apart, the Huffman scan and the write pass behind it (315 M symbols 329 and 329), decoding in whole lines; the sparse
+// stage's descriptor is longer; the routed quantiser's is shortened (fh_kernels.hpp).
 constexpr size_t kOneLaunchArgs = 112;
 template <typename Item> struct One {
     Item item;

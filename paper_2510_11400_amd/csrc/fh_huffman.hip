@@ -599,10 +599,9 @@ __device__ __forceinline__ void leave_size(const Layout& lay, uint32_t words)
     const StoredForm& f = lay.stored;
     if (f.header) f.header[6] = f.fixed_bytes + f.header[0] * f.value_size + bytes;
 }
-template <typename Args>
-__global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Args batch)
+__global__ __launch_bounds__(kThreads) void huffman_scan_kernel(const Batch<Stream> batch)
 {
-    const Layout lay = resolved(item_of(batch, blockIdx.x));
+    const Layout lay = resolved(batch.item[blockIdx.x]);
     __shared__ uint32_t lds[4];
     uint32_t carry = 0;
     for (uint32_t base = 0; base < lay.groups; base += kThreads) {         // workgroup-uniform trip count
@@ -1329,8 +1328,8 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
             if (!scanned) hipLaunchKernelGGL((huffman_write_kernel<false, FH_ARGS>), groups, dim3(kGroupThreads), 0, s, args);
         });
         if (scanned) {
-            with_arguments(each, [&](const auto& args) { hipLaunchKernelGGL((huffman_scan_kernel<FH_ARGS>), streams, dim3(kThreads), 0, s, args); });
-            with_arguments(grouped, [&](const auto& args) { hipLaunchKernelGGL((huffman_write_kernel<true, FH_ARGS>), groups, dim3(kGroupThreads), 0, s, args); });
+            hipLaunchKernelGGL(huffman_scan_kernel, streams, dim3(kThreads), 0, s, each);
+            hipLaunchKernelGGL((huffman_write_kernel<true, Batch<Stream>>), groups, dim3(kGroupThreads), 0, s, grouped);
         }
     }
     if (count == 0) return FH_OK;
@@ -1421,9 +1420,10 @@ fh_status fh_huffman_decode_batch(const fh_huffman_decode_item* items, int32_t c
         seal(b);
         if (b.count > 0) {
             const dim3 grid(b.block_start[b.count]);
-            with_arguments(b, [&](const auto& args) {
+            if (!small && decode_in_whole_lines(symbols))
+                hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, true, Batch<DecodeJob>>), grid, dim3(kDecodeThreads), 0, s, b);
+            else with_arguments(b, [&](const auto& args) {
                 if (small) hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreadsSmall, false, FH_ARGS>), grid, dim3(kDecodeThreadsSmall), 0, s, args);
-                else if (decode_in_whole_lines(symbols)) hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, true, FH_ARGS>), grid, dim3(kDecodeThreads), 0, s, args);
                 else hipLaunchKernelGGL((huffman_decode_kernel<kDecodeThreads, false, FH_ARGS>), grid, dim3(kDecodeThreads), 0, s, args);
             });
             launched = true;

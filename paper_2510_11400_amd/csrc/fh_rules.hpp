@@ -36,8 +36,8 @@ inline int32_t marked_spans_per_wave(int64_t launch_spans, int64_t tensor_spans,
 inline bool compress_in_runs(uint32_t tiles) { return tiles >= 12288; }
 inline bool restore_in_runs(uint32_t tiles) { return tiles >= 8192; }
 
-// Whether the routed quantiser or its restore takes one tensor's descriptor in a short argument segment (fh_batch.hpp).  One tensor of
-// 1.6 MB, both ways, 10.0 us with the batch's arguments and 8.5 with these, the whole chain on it 90.3 and 88.9.  Putting the
+// Whether the routed quantiser or its restore takes one tensor's descriptor in a short argument segment (fh_batch.hpp).  One fp32 tensor,
+// both ways, with the batch's arguments and with these, us: 0.8 MB 10.6 and 7.0, 3.2 MB 10.9 and 7.7, 19 MB 14.7 and 14.0.  Putting the
 // descriptor together again costs scalar registers, and with them the 65th vector register of the bf16 form, so that seven
 // waves fit a SIMD: launches that the device holds at once in workgroups of four such waves, and whose kernel is over before
 // a longer one is enqueued.

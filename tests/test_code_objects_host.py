@@ -81,7 +81,11 @@ def test_launches_of_one_tensor_have_short_arguments(code_objects):
     """Up to 112 bytes of arguments a launch is enqueued a microsecond sooner; a hidden argument (the grid's size, for
     one) would make the segment some 300 bytes long."""
     kernels = {name: r for name, r in _resources(code_objects).items() if "_one_kernel" in name or "3OneI" in name}
-    assert len(kernels) == 64
+    families = {re.search(r"\d([a-z_]+_kernel)", name).group(1) for name in kernels}
+    assert families == {"compress_one_kernel", "decompress_one_kernel", "compress_mixed_one_kernel", "decompress_mixed_one_kernel",
+                        "moments_one_kernel", "reduce_partials_kernel", "count_outliers_kernel", "count_marked_kernel", "mask_kernel",
+                        "compress_first_kernel", "chain_prepare_kernel", "huffman_histogram_kernel", "huffman_code_kernel",
+                        "huffman_count_kernel", "huffman_write_kernel", "huffman_decode_kernel"}
     for name, r in kernels.items():
         assert r["kernarg_segment_size"] <= 112, f"{name}: {r['kernarg_segment_size']}"
 
