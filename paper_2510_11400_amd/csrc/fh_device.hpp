@@ -143,20 +143,6 @@ __device__ __forceinline__ float from_pair_lane(float v)
         __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
 }
 
-// ---- tiles in runs -------------------------------------------------------------------
-// Workgroups are dealt to the eight XCDs one by one.  Here a window of 8 * RUN of them takes as many tiles so that each XCD has RUN
-// consecutive ones, the windows following one another: what a launch has touched at any time is still one stretch of
-// memory, so that the codes written last are the ones that the restore begins with finds in the memory-side cache.
-// (With one window, an eighth of the launch to each XCD, the quantiser gained and the restore lost as much.)  The last workgroups,
-// short of a window, stay where they are.
-constexpr uint32_t kXcds = 8;
-template <uint32_t RUN> __device__ __forceinline__ uint32_t tile_in_run(uint32_t block, uint32_t blocks)
-{
-    constexpr uint32_t kWindow = kXcds * RUN;
-    const uint32_t first = block / kWindow * kWindow, at = block - first;
-    return first + kWindow <= blocks ? first + at % kXcds * RUN + at / kXcds : block;
-}
-
 // ---- Philox4x32-10 ---------------------------------------------------------------
 // Salmon, Moraes, Dror, Shaw, "Parallel random numbers: as easy as 1, 2, 3" (SC'11),
 // Section 3.3: ten rounds of

@@ -27,11 +27,26 @@ inline int32_t marked_spans_per_wave(int64_t launch_spans, int64_t tensor_spans,
     return (int32_t)(spans < 1 ? 1 : spans > 8 ? 8 : spans);
 }
 
+// Tiles in runs.  Workgroups are dealt to the eight XCDs one by one.  Here a window of 8 * RUN of them takes as many tiles so that each XCD has RUN
+// consecutive ones, the windows following one another: what a launch has touched at any time is still one stretch of
+// memory, so that the codes written last are the ones that the restore begins with finds in the memory-side cache.
+// (With one window, an eighth of the launch to each XCD, the quantiser gained and the restore lost as much.)  The last workgroups,
+// short of a window, stay where they are.  (Host and device: a constexpr function is both.)
+constexpr uint32_t kXcds = 8;
+template <uint32_t RUN> constexpr uint32_t tile_in_run(uint32_t block, uint32_t blocks)
+{
+    constexpr uint32_t kWindow = kXcds * RUN;
+    const uint32_t first = block / kWindow * kWindow, at = block - first;
+    return first + kWindow <= blocks ? first + at % kXcds * RUN + at / kXcds : block;
+}
 // Whether the tiles of the plain quantiser of fp32 and of the restore to fp32 go to the XCDs in runs (fh_device.hpp), in a launch of `tiles`: 16 KiB of input
 // each, respectively 8 KiB of fp32 output.  The quantiser gains in fp32 from some 200 MB on: with runs of 128 a plan's 2 GiB both
 // ways 868 -> 819 us, 1 GiB 398 -> 390, 240 MB of feature maps 89.5 -> 88.4; 278 MB 103.4 and 103.0, 60 MB 26.5 and 27.0; bf16 loses
 // (encoder set 398 -> 407).  The restore of fp32 with runs of 64: encoder set 398 -> 379 us, 126 MB of it 41.0 -> 39.1, the plan
-// 868 -> 854, MobileNetV2-style set 201 -> 197, 60 MB 26.5 and 26.3; runs of 32 gain a half of that, of 128 as much.  Restoring bf16 gains
+// 868 -> 854, MobileNetV2-style set 201 -> 197, 60 MB 26.5 and 26.3; runs of 32 gain a half of that, of 128 as much.  Between 64 and 130 MB,
+// both ways: 2 bits 84 MB 31.4 -> 30.7, 134 MB 50.0 -> 48.0, 4 bits 33.7 -> 32.5 and 50.5 -> 49.6, 8 bits 67 MB 30.7 -> 28.9, 84 MB 34.8 and 35.3, 134 MB
+// 53.2 and 53.4; a restore again and again from 8-bit codes that the cache holds loses, 67 MB 11.1 and 13.5, 84 MB 13.8 and 15.9, 101 MB 16.6
+// and 18.2, 117 MB 21.3 and 20.7, from codes that it does not hold it does not (67 MB 20.1 and 19.8, 101 MB 27.3 and 27.2).  Restoring bf16 gains
 // nothing (280 to 286 us), nor do the routed forms.  (A kernel of its own each: the test in the others cost a set of 60 MB 0.3 us of 25.6.)
 inline bool compress_in_runs(uint32_t tiles) { return tiles >= 12288; }
 inline bool restore_in_runs(uint32_t tiles) { return tiles >= 8192; }

@@ -246,6 +246,14 @@ def test_waves_of_a_large_launch_look_twice(api, dtype):
         torch.cuda.synchronize()
         for got, want in zip((b.stats, b.counts, b.mask), alone):
             assert torch.equal(got, want)
+    for k in (0, 2):                                          # looked at twice; both with the oracle as well
+        x, outer, C, inner, sigma, bound = entries[k]
+        host = x.view(torch.int16).cpu().numpy().view(np.uint16) if dtype == "bf16" else x.cpu().numpy()
+        stats, counts, mask = oracle.classify_channels(host, outer, C, inner, sigma, bound, dtype=dtype)
+        b = batch.entries[k]
+        assert np.array_equal(b.stats.cpu().numpy().view(np.uint64), stats.view(np.uint64))
+        assert np.array_equal(b.counts.cpu().numpy().view(np.uint32), counts)
+        assert np.array_equal(b.mask.cpu().numpy(), mask)
 
 
 def _check_batch(api, shapes, dtype, ranges, bound_of):

@@ -375,3 +375,17 @@ def test_a_tensor_by_itself_gives_what_it_gives_in_a_batch(api, dtype, bits, rou
             if kept:
                 rows = [r.reshape(outer, cap, inner)[:, :int(mask.sum())] for r in (raw, two[0].raw)]
                 assert torch.equal(rows[0].view(bits_of), rows[1].view(bits_of)), what
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("group", [64, 128, 256])
+def test_a_tensor_by_itself_against_the_oracle(api, group, dtype):
+    """The kernels of one tensor in every group size: channels as rows of elements and one channel per element, in two forms (rows
+    of the raw store listed or not), with a kept channel, all kept and none, ragged ends."""
+    shapes = [(3, 10, 7), (1, 1, 1), (8, 64, 64), (5, 33, 49), (64, 48, 1), (333, 769, 1), (4, 4096, 1), (2, 4100, 3), (7, 3, 5000)]
+    for i, (outer, C, inner) in enumerate(shapes):
+        x, _ = W.outlier_channel_tensor(outer, C, inner, seed=i, dtype=dtype)
+        for kept in (0.0, 0.1, 1.0):
+            mask = _mask(C, kept, i)
+            bits, rounding = ((2, "stochastic"), (4, "nearest"), (8, "stochastic"), (4, "stochastic"), (2, "nearest"), (8, "nearest"))[(i + int(kept * 10)) % 6]
+            _roundtrip(api, x, outer, C, inner, mask, max(1, int(mask.sum())), group, bits, rounding, dtype=dtype, name="alone")

@@ -275,6 +275,26 @@ def test_full_configuration_bit_exact(api, idx):
     _full_config_check(api, idx)
 
 
+@pytest.mark.parametrize("group", [64, 128, 256])
+def test_tiles_in_runs_with_a_ragged_last_window(api, group):
+    """A launch of fp32 large enough for tiles in runs in both directions, of one tensor and of three, whose tiles end inside a
+    window; the last workgroups take their own."""
+    from types import SimpleNamespace
+
+    tiles = 12288 + 1024 + 333                                # of 4096 elements; windows of 1024, to restore 512 of 2048
+    for sizes in ([tiles * 4096 - 1001], [7 * 4096, 5000 * 4096 + 3, (tiles - 5008) * 4096 - 77]):
+        specs, arrays = [], []
+        for i, n in enumerate(sizes):
+            bits, rounding = ((4, "nearest"), (2, "stochastic"), (8, "nearest"))[(i + group // 128) % 3]
+            specs.append(SimpleNamespace(group_size=group, bits=bits, rounding=rounding, seed=5, tensor_id=i, dtype="f32"))
+            arrays.append(np.random.default_rng(n).standard_normal(n, dtype=f32))
+        _say(f"[parity] tiles in runs, G{group}, {sizes}")
+        entries = _batch_roundtrip(api, None, specs, arrays)
+        for sp, x, e in zip(specs, arrays, entries):
+            p, m, o = _oracle_roundtrip(x, sp)
+            _assert_same(f"G{group} B{sp.bits} n={x.size}", group, _host(e.packed), _host(e.meta), _host(e.out), p, m, o)
+
+
 def test_restored_values_of_every_bf16_neighbourhood_round_as_the_oracle_does(api):
     """Restoring bf16 rounds with the hardware's conversion.  A group whose codes and scale are 0 restores its zero
     point: every upper half of a binary32 with the lower halves around the ties and the ends, subnormals, infinities and

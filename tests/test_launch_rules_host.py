@@ -39,6 +39,7 @@ int main(int, char** argv)
         else if (!std::strcmp(argv[1], "one_by_itself")) std::printf("%d\\n", (int)fh::one_by_itself((int)a, (unsigned)b));
         else if (!std::strcmp(argv[1], "maps_stay_in_cache")) std::printf("%d\\n", (int)fh::maps_stay_in_cache(a));
         else if (!std::strcmp(argv[1], "group_sums_are_scanned")) std::printf("%d\\n", (int)fh::group_sums_are_scanned(a));
+        else if (!std::strcmp(argv[1], "tile_in_run")) std::printf("%u\\n", a == 64 ? fh::tile_in_run<64>((unsigned)b, (unsigned)c) : fh::tile_in_run<128>((unsigned)b, (unsigned)c));
         else if (!std::strcmp(argv[1], "sparse_sums_are_scanned")) std::printf("%d\\n", (int)fh::sparse_sums_are_scanned((unsigned)a, (unsigned)b, (int)c));
         else if (!std::strcmp(argv[1], "decode_in_whole_lines")) std::printf("%d\\n", (int)fh::decode_in_whole_lines(a));
 }
@@ -101,6 +102,22 @@ def test_tiles_go_to_the_xcds_in_runs_in_large_launches_of_fp32(rules):
     rows = [(n, 0, 0, 0) for n in tiles]
     assert rules("compress_in_runs", rows) == [0, 0, 0, 0, 1, 1]
     assert rules("restore_in_runs", rows) == [0, 0, 1, 1, 1, 1]
+
+
+@pytest.mark.parametrize("run", [64, 128])
+@pytest.mark.parametrize("windows, over", [(0, 1), (0, -1), (1, -1), (1, 0), (1, 1), (3, -1), (3, 0), (3, 1), (16, 77), (24, 5)])
+def test_tiles_in_runs_are_all_tiles(rules, run, windows, over):
+    """Every tile once; inside a whole window every eighth workgroup has the next tile of a run, behind the last window a
+    workgroup's own."""
+    window = 8 * run
+    blocks = windows * window + over if windows or over > 0 else window - 1
+    tiles = rules("tile_in_run", [(run, b, blocks, 0) for b in range(blocks)])
+    assert sorted(tiles) == list(range(blocks))
+    whole = blocks // window * window
+    assert tiles[whole:] == list(range(whole, blocks))
+    for first in range(0, whole, window):
+        for xcd in range(8):
+            assert tiles[first + xcd:first + window:8] == list(range(first + xcd * run, first + (xcd + 1) * run))
 
 
 def test_looks_and_masks_of_the_count_pass(rules):
