@@ -11,8 +11,8 @@
 // Every stage is the library's own batched call; this file only lays the caller's two buffers
 // out, strings the calls together on one stream, and adds two small kernels: one that takes the
 // masks from the outlier counts, numbers the salient channels of every tensor of the call, clears
-// the rows of the raw stores that no channel uses (they read as zero) and the headers, and one that adds up what a
-// tensor's stored form occupies where the entropy stage does not do that.  Sizes that depend on the data (stream lengths) never visit the host:
+// the headers and, where the sparse stage does not, the rows of the raw stores that no channel uses (they read as zero), and one
+// that adds up what a tensor's stored form occupies where the entropy stage does not do that.  Sizes that depend on the data (stream lengths) never visit the host:
 // the sparse stage's totals feed the Huffman stage through device memory.
 #include "../../include/fedhybrid.h"
 
@@ -38,7 +38,7 @@ struct PrepItem {
     uint64_t*       header;                        // 8 words, cleared; [7] = slots in use
     uint8_t*        raw;                           // the raw store: [outer][raw_channels][row_bytes]
     uint64_t        row_bytes;
-    uint32_t        outer;
+    uint32_t        outer;                         // samples whose unused rows are to be cleared
     int32_t         channels, raw_channels;
     uint32_t        blocks;                        // workgroups of this item
 };
@@ -222,9 +222,9 @@ fh_status check_item(const fh_mix_item& it, bool forward, fh_mix_regions* r, int
 
 uint8_t* at(void* base, size_t off) { return static_cast<uint8_t*>(base) + off; }
 
-// Which maps of an item's raw store hold anything.  Where a map is a row of the store, the sparse encoder is told and does not
-// read the others; where it is not ([tokens][hidden] tensors), or an empty tile would not be a sparse one, it reads
-// the zeros they are.
+// Which maps of an item's raw store hold anything.  Where a map is a row of the store, the sparse encoder is told, and does not read the
+// others but sets them to zero; where it is not ([tokens][hidden] tensors), or an empty tile would not be a sparse one, those
+// rows are cleared before it reads them.
 MapsInUse rows_in_use(const fh_mix_item& it, const fh_mix_regions& reg)
 {
     const bool by_rows = it.h * it.w == it.inner && it.tau >= 0.0f;
@@ -323,11 +323,11 @@ fh_status fh_mix_compress_batch(const fh_mix_item* items, int32_t count, void* s
             p.header = reinterpret_cast<uint64_t*>(at(it.store, reg[i].header));
             p.raw = at(it.workspace, reg[i].raw);
             p.row_bytes = (uint64_t)it.inner * elem_size(it.x_dtype);
-            p.outer = reg[i].raw_bytes ? (uint32_t)it.outer : 0u;
+            p.outer = reg[i].raw_bytes && !rows_in_use(it, reg[i]).count ? (uint32_t)it.outer : 0u;
             p.channels = (int32_t)it.channels;
             p.raw_channels = (int32_t)it.raw_channels;
             // every workgroup counts the salient channels first: 16 KiB of rows for each of its waves at least
-            const uint64_t want = reg[i].raw_bytes / ((kPrepThreads / 64) * kClearUnit) + 1u;
+            const uint64_t want = p.outer ? reg[i].raw_bytes / ((kPrepThreads / 64) * kClearUnit) + 1u : 1u;
             p.blocks = (uint32_t)(want < 512u ? want : 512u);
             push(b, p, p.blocks);
         }

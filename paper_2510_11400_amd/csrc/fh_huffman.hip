@@ -45,15 +45,14 @@ constexpr int kChunkWordsMax = kChunk * kMaxLen / 32;
 constexpr int kHistCopies = 32;                     // one per LDS bank
 constexpr int kHistThreads = 1024;
 constexpr int kHistBlocksMax = 512;                // histogram workgroups per stream: two per compute unit
-// decode: 16-byte output vectors held back and stored together; 51 MB of index streams one at a time 61.4 us, 2 52.3, 4 52.0,
-// with 8 the code no longer fits the instruction cache and takes 55.6 (the rings likewise: half of 51 MB noise 102 and 89)
+// decode: 16-byte output vectors held back and stored together; 51 MB of index streams one at a time 54.5 us, 2 44.5, 4 44.4,
+// with 8 the code no longer fits the instruction cache and takes 58.2
 constexpr int kBurst = 4;
 // decode: threads per workgroup, one workgroup per compute unit.  The payload slice in LDS is what limits the chunks in
 // flight on a unit.  With 1024 threads the stage holds 768 chunks at 46 words (5.75 bits per symbol) and 1024 at 34.5: a
 // stream whose chunks come to slightly more than 768 per unit (51 MB of index streams: 788) takes one pass and not two;
-// four waves per SIMD then keep the LDS busy (53.9 us before four symbols shared a window of the stream, 51.5 now).
-// A launch of fewer chunks has 512 threads, half as many waves to a SIMD, and a stage of 61 words for each: 25 MB of index
-// streams 46.8 us as two workgroups of 256, 35.5 as one of 512.
+// four waves per SIMD then keep the LDS busy (44.4 us).  A launch of fewer chunks has 512 threads, half as many waves to a SIMD, and
+// a stage of 61 words for each: 13 MB of index streams 28.7 us, with 1024 threads 31.5, 26 MB 32.4 and 32.8.
 constexpr int kDecodeThreads = 1024;
 constexpr int kDecodeThreadsSmall = 512;
 // LDS for the payload slice, in words: what fits beside the tables

@@ -120,9 +120,10 @@ struct Job {
 };
 
 // Is the map one of those that hold nothing?  (False where the maps are not the rows of a raw store.)  The encoder does not read
-// them: a room of a sixteenth of the channels where 4 % are kept leaves 36 % of the maps unused.  `scale` is
+// them, and its first pass sets them to zero: a room of a sixteenth of the channels where 4 % are kept leaves 36 % of the maps unused.  `scale` is
 // floor(2^32 / rows), so that the quotient is the right one or one less.
-// On the MobileNetV2-style set the count pass then takes 8.6 us in place of 10.9, the write pass 14.3 in place of 16.4.
+// On the MobileNetV2-style set the write pass then takes 14.3 us in place of 16.4, the count pass 10.6 in place of 10.9 (8.6 without the zeros), and
+// the chain's preparing kernel, which cleared those maps before, 5.0 in place of 8.2: both ways 376 -> 370.
 // (The decoder writes all maps: which of them are zeros is for the stream to say, not for a word of a header beside it.)
 __device__ __forceinline__ bool map_unused(const MapsInUse& use, uint32_t map)
 {
@@ -641,6 +642,12 @@ __global__ __launch_bounds__(Group<N>::kTiles) void sparse_count_kernel(const Ba
     bool look = b < s.tiles;
     if (look) t = tile_pos<N>(s, b);
     if (ROWS && look && map_unused(job.use, t.map)) {         // zeros, and sparse
+        Bits none[N][N];
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+#pragma unroll
+            for (int c = 0; c < N; ++c) none[r][c] = (Bits)0;
+        store_tile<Bits, N, false>(static_cast<Bits*>(const_cast<void*>(s.x)) + t.origin, t, s.w, s.rows_are_vectors != 0u, none);
         info[b] = (uint8_t)0;
         mine = tile_packed(0u, t, s.step.two_eps > 0.0f);
         sparse = true;

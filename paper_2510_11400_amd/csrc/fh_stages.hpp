@@ -38,7 +38,7 @@ fh_status compress_kept(const fh_mixed_item* items, int32_t count, hipStream_t s
 constexpr int64_t kFirstSpan = 2048;               // elements of such a span at most
 
 // Maps that are the rows of a raw store, `rows` to a sample, of which the first *count (device) are in use: the others are
-// zeros and are not read.  scale: floor(2^32 / rows), all ones for a single row.  count null: all maps are in use.
+// not read, count as zeros and are set to zero.  scale: floor(2^32 / rows), all ones for a single row.  count null: all maps are in use.
 struct MapsInUse { const uint64_t* count; uint32_t rows, scale; };
 inline MapsInUse maps_in_use(const uint64_t* count, uint32_t rows)
 {
