@@ -256,13 +256,14 @@ struct CountArgs {
     SmallDiv inner, channels;
     int32_t spans_per_wave;                                   // consecutive spans one wave walks
     const uint32_t* ranges;                                   // of the tensor's pieces (count_marked_kernel)
-    uint8_t* mask;                                            // cleared; null: the caller takes it from the counts
+    uint8_t* mask;                                            // cleared; null: it is taken from the counts behind the pass
     int64_t min_outliers;
 };
 
 // A workgroup's histogram to the tensor's counters.  The additions to a counter follow one another, so just one of them takes it
 // over the bound, and that one sets the mask: no launch behind the pass that reads the counters again (557 MiB set 108.5 -> 106.5
-// us).  An addition whose result is waited for costs more than one that is not, so that is for tensors of few channels (fh_rules.hpp).
+// us).  An addition whose result is waited for costs more than one that is not, so that is for tensors of few channels and
+// launches that are not too large (fh_rules.hpp).
 template <int THREADS>
 __device__ __forceinline__ void add_outliers(const CountArgs& args, const uint32_t* hist)
 {
