@@ -313,7 +313,7 @@ fh_status fh_sparse_decode(const void *info, const void *values, size_t values_b
 
 /* The same for several tensors, as a plan classifies every compressible activation of a model:
  * each kind of kernel is launched once per run of up to fh_classify_batch_capacity() items (a launch
- * may take more) of one dtype, so small tensors do not each pay five launches.  All items are checked before the
+ * may take more) of one dtype, so small tensors do not each pay for all of them.  All items are checked before the
  * first launch; results are identical to calling fh_classify_channels item by item.  The
  * items' outputs and workspaces must not overlap. */
 typedef struct fh_classify_item {

@@ -39,7 +39,7 @@ template <uint32_t RUN> constexpr uint32_t tile_in_run(uint32_t block, uint32_t 
     const uint32_t first = block / kWindow * kWindow, at = block - first;
     return first + kWindow <= blocks ? first + at % kXcds * RUN + at / kXcds : block;
 }
-// Whether the tiles of the plain quantiser of fp32 and of the restore to fp32 go to the XCDs in runs (fh_device.hpp), in a launch of `tiles`: 16 KiB of input
+// Whether the tiles of the plain quantiser of fp32 and of the restore to fp32 go to the XCDs in runs, in a launch of `tiles`: 16 KiB of input
 // each, respectively 8 KiB of fp32 output.  The quantiser gains in fp32 from some 200 MB on: with runs of 128 a plan's 2 GiB both
 // ways 868 -> 819 us, 1 GiB 398 -> 390, 240 MB of feature maps 89.5 -> 88.4; 278 MB 103.4 and 103.0, 60 MB 26.5 and 27.0; bf16 loses
 // (encoder set 398 -> 407).  The restore of fp32 with runs of 64: encoder set 398 -> 379 us, 126 MB of it 41.0 -> 39.1, the plan
