@@ -414,8 +414,13 @@ hipError_t launch_decompress(const DecompressBatch& b, int out_dtype, int group_
     const uint32_t tiles = b.tile_start[b.count];
     if (tiles == 0) return hipSuccess;
     const dim3 grid(tiles), block(kDBlock);
+    uint64_t elements = 0, code_bits = 0;
+    for (int k = 0; k < b.count; ++k) {
+        elements += (uint64_t)b.item[k].numel;
+        code_bits += (uint64_t)b.item[k].numel * (uint64_t)b.item[k].bits;
+    }
 #define FH_LAUNCH(T, GS, RUNS) hipLaunchKernelGGL((decompress_kernel<T, GS, RUNS>), grid, block, 0, s, b)
-    if (out_dtype == 0 && restore_in_runs(tiles)) {
+    if (out_dtype == 0 && restore_in_runs(tiles, elements, code_bits)) {
         if (group_size == 64) FH_LAUNCH(float, 64, true);
         else if (group_size == 128) FH_LAUNCH(float, 128, true);
         else FH_LAUNCH(float, 256, true);

@@ -43,13 +43,21 @@ template <uint32_t RUN> constexpr uint32_t tile_in_run(uint32_t block, uint32_t 
 // each, respectively 8 KiB of fp32 output.  The quantiser gains in fp32 from some 200 MB on: with runs of 128 a plan's 2 GiB both
 // ways 868 -> 819 us, 1 GiB 398 -> 390, 240 MB of feature maps 89.5 -> 88.4; 278 MB 103.4 and 103.0, 60 MB 26.5 and 27.0; bf16 loses
 // (encoder set 398 -> 407).  The restore of fp32 with runs of 64: encoder set 398 -> 379 us, 126 MB of it 41.0 -> 39.1, the plan
-// 868 -> 854, MobileNetV2-style set 201 -> 197, 60 MB 26.5 and 26.3; runs of 32 gain a half of that, of 128 as much.  Between 64 and 130 MB,
-// both ways: 2 bits 84 MB 31.4 -> 30.7, 134 MB 50.0 -> 48.0, 4 bits 33.7 -> 32.5 and 50.5 -> 49.6, 8 bits 67 MB 30.7 -> 28.9, 84 MB 34.8 and 35.3, 134 MB
-// 53.2 and 53.4; a restore again and again from 8-bit codes that the cache holds loses, 67 MB 11.1 and 13.5, 84 MB 13.8 and 15.9, 101 MB 16.6
-// and 18.2, 117 MB 21.3 and 20.7, from codes that it does not hold it does not (67 MB 20.1 and 19.8, 101 MB 27.3 and 27.2).  Restoring bf16 gains
-// nothing (280 to 286 us), nor do the routed forms.  (A kernel of its own each: the test in the others cost a set of 60 MB 0.3 us of 25.6.)
+// 868 -> 854, MobileNetV2-style set 201 -> 197, 60 MB 26.5 and 26.3; runs of 32 gain a half of that, of 128 as much.  By the codes'
+// width, restore in order and in runs, codes and output in the cache | from sets in turn, 1.6 GB of them:
+//   2 bits 67 MB 11.2 and 11.3 | 11.3 and 11.6, 101 MB 16.8 and 16.8 | 16.9 and 16.6, 168 MB 28.3 and 27.3 | 28.3 and 26.2, 557 MB 97 and 87 | 97 and 87;
+//   4 bits 67 MB 11.4 and 11.5 | 11.8 and 12.2, 101 MB 17.0 and 16.8 | 17.0 and 17.5, 168 MB 28.1 and 27.0 | 27.5 and 27.6, 557 MB 92 and 86 | 92 and 87;
+//   8 bits 67 MB 11.1 and 13.5 | 15.2 and 15.8, 101 MB 16.4 and 17.7 | 20.8 and 22.3, 168 MB 30.2 and 30.6 | 32.0 and 33.2, 268 MB 47.2 and 47.4 | 53.4 and
+//   53.2, 335 MB 58.9 and 58.9 | 65.6 and 65.8, 400 MB 70.0 and 70.2 | 80.0 and 78.4, 800 MB 139 and 138 | 159 and 155;
+//   a third of each 84 MB 14.9 and 14.4 | 17.4 and 17.6, 134 MB 23.3 and 22.1 | 26.1 and 24.8, 268 MB 44.4 and 43.1 | 44.6 and 43.5.
+// Both ways on sets in turn, 2 and 4 bits lose 0.4 us of 25 at 67 MB, 2 bits gain from 92 MB on, 4 bits from 200 MB on with nothing either way before;
+// 8 bits 67 MB 28.5 and 29.0, 101 MB 40.4 and 41.2, 335 MB 128 and 128, 800 MB 314 and 306 (on one tensor again and again 67 MB 30.4 and 28.3,
+// 84 MB 34.8 and 35.2).  So sets of mostly 8 bits wait for 335 MB.  Restoring bf16 gains nothing (280 to 286 us), nor do the routed forms.  (A kernel of its own each: the test in the others cost a set of 60 MB 0.3 us of 25.6.)
 inline bool compress_in_runs(uint32_t tiles) { return tiles >= 12288; }
-inline bool restore_in_runs(uint32_t tiles) { return tiles >= 8192; }
+inline bool restore_in_runs(uint32_t tiles, uint64_t elements, uint64_t code_bits)
+{
+    return tiles >= (code_bits > 6u * elements ? 40960u : 8192u);
+}
 
 // Whether the routed quantiser or its restore takes one tensor's descriptor in a short argument segment (fh_batch.hpp).  One fp32 tensor,
 // both ways, with the batch's arguments and with these, us: 0.8 MB 10.6 and 7.0, 3.2 MB 10.9 and 7.7, 19 MB 14.7 and 14.0.  Putting the

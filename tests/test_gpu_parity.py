@@ -295,6 +295,19 @@ def test_tiles_in_runs_with_a_ragged_last_window(api, group):
             _assert_same(f"G{group} B{sp.bits} n={x.size}", group, _host(e.packed), _host(e.meta), _host(e.out), p, m, o)
 
 
+@pytest.mark.parametrize("tiles", [40959, 40960])
+def test_codes_of_eight_bits_on_both_sides_of_the_runs(api, tiles):
+    """The restore of a tensor of 8-bit codes in order and in runs, its last tile a ragged one."""
+    from types import SimpleNamespace
+
+    sp = SimpleNamespace(group_size=128, bits=8, rounding="nearest", seed=5, tensor_id=0, dtype="f32")
+    x = np.random.default_rng(tiles).standard_normal(tiles * 2048 - 1003, dtype=f32)
+    _say(f"[parity] 8 bits, {tiles} tiles to restore")
+    e = _batch_roundtrip(api, None, [sp], [x])[0]
+    p, m, o = _oracle_roundtrip(x, sp)
+    _assert_same(f"8 bits, {tiles} tiles", 128, _host(e.packed), _host(e.meta), _host(e.out), p, m, o)
+
+
 def test_restored_values_of_every_bf16_neighbourhood_round_as_the_oracle_does(api):
     """Restoring bf16 rounds with the hardware's conversion.  A group whose codes and scale are 0 restores its zero
     point: every upper half of a binary32 with the lower halves around the ties and the ends, subnormals, infinities and

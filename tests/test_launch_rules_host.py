@@ -35,7 +35,7 @@ int main(int, char** argv)
         else if (!std::strcmp(argv[1], "limits_apart")) std::printf("%d\\n", (int)(a < 0 ? fh::limits_apart(true, 1, (unsigned)b, (unsigned)c, d != 0) : fh::limits_apart(false, (int)a, (unsigned)b, (unsigned)c, d != 0)));
         else if (!std::strcmp(argv[1], "counters_are_crowded")) std::printf("%d\\n", (int)fh::counters_are_crowded((unsigned)a, (unsigned)b));
         else if (!std::strcmp(argv[1], "compress_in_runs")) std::printf("%d\\n", (int)fh::compress_in_runs((unsigned)a));
-        else if (!std::strcmp(argv[1], "restore_in_runs")) std::printf("%d\\n", (int)fh::restore_in_runs((unsigned)a));
+        else if (!std::strcmp(argv[1], "restore_in_runs")) std::printf("%d\\n", (int)fh::restore_in_runs((unsigned)a, (unsigned long long)b, (unsigned long long)c));
         else if (!std::strcmp(argv[1], "one_by_itself")) std::printf("%d\\n", (int)fh::one_by_itself((int)a, (unsigned)b));
         else if (!std::strcmp(argv[1], "maps_stay_in_cache")) std::printf("%d\\n", (int)fh::maps_stay_in_cache(a));
         else if (!std::strcmp(argv[1], "group_sums_are_scanned")) std::printf("%d\\n", (int)fh::group_sums_are_scanned(a));
@@ -102,6 +102,14 @@ def test_tiles_go_to_the_xcds_in_runs_in_large_launches_of_fp32(rules):
     rows = [(n, 0, 0, 0) for n in tiles]
     assert rules("compress_in_runs", rows) == [0, 0, 0, 0, 1, 1]
     assert rules("restore_in_runs", rows) == [0, 0, 1, 1, 1, 1]
+
+
+def test_tiles_of_wide_codes_go_in_runs_in_the_largest_restores(rules):
+    """Codes of 8 bits, alone or with few others, from 335 MB of fp32 on; sets of a third 8 bits, and of narrower codes, as any."""
+    tiles = (8191, 8192, 40959, 40960)
+    for elements, code_bits, want in ((300, 2400, [0, 0, 0, 1]), (300, 1801, [0, 0, 0, 1]), (300, 1800, [0, 1, 1, 1]), (300, 1400, [0, 1, 1, 1]),
+                                      (1 << 31, 2 << 31, [0, 1, 1, 1]), (48 << 31, 8 * 48 << 31, [0, 0, 0, 1])):
+        assert rules("restore_in_runs", [(n, elements, code_bits, 0) for n in tiles]) == want
 
 
 @pytest.mark.parametrize("run", [64, 128])
