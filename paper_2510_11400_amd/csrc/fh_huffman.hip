@@ -44,7 +44,7 @@ constexpr int kMaxLen = 24;
 constexpr int kChunkWordsMax = kChunk * kMaxLen / 32;
 constexpr int kHistCopies = 32;                     // one per LDS bank
 constexpr int kHistThreads = 1024;
-constexpr int kHistBlocksMax = 512;                // histogram workgroups per stream: two per compute unit
+static_assert(kHistThreads * 16 == kHistRound, "a vector of sixteen symbols for each thread (fh_rules.hpp)");
 // decode: 16-byte output vectors held back and stored together; 51 MB of index streams one at a time 54.5 us, 2 44.5, 4 44.4,
 // with 8 the code no longer fits the instruction cache and takes 58.2
 constexpr int kBurst = 4;
@@ -98,16 +98,6 @@ struct Layout {                                    // where things are in the st
 
 __device__ __forceinline__ uint64_t chunks_for(uint64_t n) { return (n + 255u) >> 8; }
 
-// Histogram workgroups of a stream: four vectors per thread up to 4 Mi symbols, eight of what lies beyond, more in long streams,
-// since a workgroup clears and adds up 32 KiB of counters whatever it counts.  (Eight throughout, the five streams of 8 MB
-// of the whole chain take 7.5 us, this way 5.5.)
-__host__ __device__ __forceinline__ uint32_t hist_blocks_for(uint64_t n)
-{
-    constexpr uint64_t each = (uint64_t)kHistThreads * 16u * 4u, few = 64;
-    const uint64_t want = n == 0 ? 0 : n <= few * each ? n / each + 1u : few + (n - few * each) / (2u * each) + 1u;
-    return (uint32_t)(want < (uint64_t)kHistBlocksMax ? want : (uint64_t)kHistBlocksMax);
-}
-
 // The layout a kernel works with.  When the symbol count lives in device memory (it is the
 // output of an earlier call on the same stream), the host has sized buffers and grids for an
 // upper bound; the count itself, and what follows from it -- chunks, groups, where the payload
@@ -127,7 +117,7 @@ __device__ __forceinline__ Layout resolved(const Stream& given)
         lay.n = there < given.n ? there : given.n;
         lay.chunks = (uint32_t)chunks_for(lay.n);
         lay.groups = (lay.chunks + 255u) >> 8;
-        lay.hist_blocks = hist_blocks_for(lay.n);
+        lay.hist_blocks = histogram_workgroups(lay.n);
     }
     lay.len = given.out;
     lay.offsets = reinterpret_cast<uint32_t*>(given.out + 256);
@@ -1306,7 +1296,7 @@ fh_status encode_all(const fh_huffman_encode_item* items, const StoredForm* stor
             lay.n = it.n;
             lay.n_dev = static_cast<const uint64_t*>(it.n_device);
             lay.stored = stored ? stored[i] : StoredForm{nullptr, 0, 0};
-            lay.hist_blocks = hist_blocks_for(it.n);
+            lay.hist_blocks = histogram_workgroups(it.n);
             if ((uint64_t)grouped.block_start[grouped.count] + lay.groups > (uint64_t)INT_MAX) {
                 if (each.count == 0) return FH_ERR_BAD_NUMEL;
                 break;

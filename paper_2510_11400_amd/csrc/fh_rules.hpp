@@ -111,6 +111,20 @@ inline bool limits_apart(bool ranges, int32_t tensors, uint32_t workgroups, uint
 }
 inline bool counters_are_crowded(uint32_t workgroups, uint32_t channels) { return workgroups >= 1024 && workgroups / 32 >= channels; }
 
+// Histogram workgroups of a stream of n symbols: four vectors per thread up to 4 Mi symbols, eight of what lies beyond, more in long
+// streams, since a workgroup clears and adds up 32 KiB of counters whatever it counts.  (Eight throughout, the five streams of 8 MB
+// of the whole chain take 7.5 us, this way 5.5.)  Where that is a few more than one for each compute unit, one for each: of 281 workgroups a
+// tenth of the units has two, and all wait for these.  Encoding 31 MB of three symbols, index bytes, noise 40.4, 64.5, 52.0 us with the few more and
+// 37.2, 61.1, 48.7 without, 33 MB 41.2, 52.6, 52.5 and 37.9, 49.2, 49.2; 36 MB (275, or 307) 47.7, 59.4, 59.8 and 48.1, 59.8, 59.9, 50 MB and more the same.
+constexpr uint64_t kHistRound = 1024 * 16;                    // symbols that a workgroup takes at a time
+constexpr uint32_t histogram_workgroups(uint64_t n)
+{
+    constexpr uint64_t four = 4u * kHistRound, eight = 8u * kHistRound, few = 64, units = 256, most = 2u * units;
+    const uint64_t want = n == 0 ? 0 : n <= few * four ? n / four + 1u : few + (n - few * four) / eight + 1u;
+    const uint64_t held = want <= units ? want : n / eight + 1u > units ? n / eight + 1u : units;
+    return (uint32_t)(held < most ? held : most);
+}
+
 // The Huffman encoder's group sums in a launch of `groups` altogether: scanned by a kernel between the count and the write
 // pass, or every workgroup of the write pass adds up those before its own.  Adding up saves that launch and makes every
 // workgroup of the write pass take longer, so what counts is how many of those there are.  Encoding, scanned and not: one

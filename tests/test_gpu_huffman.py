@@ -51,6 +51,12 @@ def test_sizes_around_vectors_chunks_and_groups(api, n):
     _check(api, data, "normal around 128")
 
 
+@pytest.mark.parametrize("n", [224 * 131072 - 1, 224 * 131072 + 16, 256 * 131072 - 1, 256 * 131072, 257 * 131072 + 5])
+def test_sizes_around_a_histogram_workgroup_for_each_unit(api, n):
+    rng = np.random.default_rng(n)
+    _check(api, (rng.standard_normal(n, dtype=np.float32) * np.float32(9.5) + np.float32(128)).clip(0, 255).astype(np.uint8), "histogram workgroups")
+
+
 @pytest.mark.parametrize("spread", [2.5, 14.0, 20.0, -1.0, 0.0])
 def test_streams_long_enough_that_a_workgroup_decodes_several_groups(api, spread):
     # Beyond 256 * 488 chunks the decoder has a workgroup of 1024 threads per compute unit and deals the chunks out evenly: 1026

@@ -38,6 +38,7 @@ int main(int, char** argv)
         else if (!std::strcmp(argv[1], "restore_in_runs")) std::printf("%d\\n", (int)fh::restore_in_runs((unsigned)a, (unsigned long long)b, (unsigned long long)c));
         else if (!std::strcmp(argv[1], "one_by_itself")) std::printf("%d\\n", (int)fh::one_by_itself((int)a, (unsigned)b));
         else if (!std::strcmp(argv[1], "maps_stay_in_cache")) std::printf("%d\\n", (int)fh::maps_stay_in_cache(a));
+        else if (!std::strcmp(argv[1], "histogram_workgroups")) std::printf("%u\\n", fh::histogram_workgroups((unsigned long long)a));
         else if (!std::strcmp(argv[1], "group_sums_are_scanned")) std::printf("%d\\n", (int)fh::group_sums_are_scanned(a));
         else if (!std::strcmp(argv[1], "tile_in_run")) std::printf("%u\\n", a == 64 ? fh::tile_in_run<64>((unsigned)b, (unsigned)c) : fh::tile_in_run<128>((unsigned)b, (unsigned)c));
         else if (!std::strcmp(argv[1], "sparse_sums_are_scanned")) std::printf("%d\\n", (int)fh::sparse_sums_are_scanned((unsigned)a, (unsigned)b, (int)c));
@@ -86,6 +87,20 @@ def test_the_chains_maps_pass_the_caches_by_where_these_do_not_hold_them(rules):
 def test_group_sums_are_scanned_in_launches_of_many_groups(rules):
     """Up to 4096 groups in a launch, however many streams they belong to, there is no scan."""
     assert rules("group_sums_are_scanned", [(n, 0, 0, 0) for n in (0, 1, 335, 4096, 4097, 24 * 335, 1 << 31)]) == [0, 0, 0, 0, 1, 1, 1]
+
+
+def test_histogram_workgroups_of_a_stream(rules):
+    """More for more symbols (a launch is sized for a bound of the count, the kernels go by the count), one for each of 256 units
+    while fewer than nine vectors for a thread would take a few more, 512 at most, and their counts fit the payload's place."""
+    unit = 8 * 16384
+    sizes = sorted({n + d for n in (1, 65536, 1 << 22, 224 * unit, 225 * unit, 255 * unit, 256 * unit, 257 * unit, 511 * unit, 1 << 32)
+                    for d in (-1, 0, 1)} | {31000000, 33000000})
+    got = rules("histogram_workgroups", [(n, 0, 0, 0) for n in sizes])
+    assert got == sorted(got) and got[0] == 0 and got[1] == 1 and got[-1] == 512
+    of = dict(zip(sizes, got))
+    assert [of[n] for n in (224 * unit - 1, 224 * unit, 31000000, 33000000, 256 * unit - 1, 256 * unit, 257 * unit)] == [256, 256, 256, 256, 256, 257, 258]
+    assert [of[n] for n in (65535, 65536, 1 << 22, 511 * unit - 1, 511 * unit)] == [1, 2, 65, 511, 512]
+    assert all(blocks == 1 or 1024 * blocks + 16 <= n // 8 for n, blocks in of.items() if n)
 
 
 def test_sparse_sums_are_scanned_in_large_sets(rules):
